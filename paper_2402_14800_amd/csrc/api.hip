@@ -258,6 +258,34 @@ static int expert_outputs(const void* x, const void* Wgate, const void* W1, cons
   hipStream_t s = (hipStream_t)hip_stream;
   const size_t es = dtype_size(dt);
 
+  if (dt == MOEP_BF16 && T <= FEW_MAX_AVERAGE) {
+    // Few rows: every expert's weights are read where they lie, and that read bounds the call.
+    const int eb = experts_per_launch(T, E, F);
+    if (int st = launch_router(x, Wgate, T, E, H, dt, logits, s)) return st;
+    const size_t gu_bytes = packed ? packed_b_bytes(F, H, true) : (size_t)F * H * es;
+    const size_t dn_bytes = packed ? packed_b_bytes(H, F, false) : (size_t)H * F * es;
+    const char* w_up = (const char*)(packed ? packed : W1);
+    const char* w_dn = packed ? (const char*)packed + (size_t)E * gu_bytes : (const char*)W2;
+    for (int e0 = 0; e0 < E; e0 += eb) {
+      const int ne = E - e0 < eb ? E - e0 : eb;
+      FewGemmArgs up;                             // h[e] = silu(x W1[e]^T) * (x W3[e]^T), row-major
+      up.X = x; up.ldx = H;
+      up.W0 = w_up + (size_t)e0 * gu_bytes; up.packed = packed != nullptr;
+      up.W1 = packed ? nullptr : (const char*)W3 + (size_t)e0 * gu_bytes;
+      up.C = ws; up.ldc = F; up.c_expert_rows = T;
+      up.N = F; up.K = H; up.epilogue = EPI_SWIGLU;
+      up.max_rows = T; up.experts = ne;
+      if (int st = launch_gemm_few(up, s, "gemm_gate_up_swiglu_few")) return st;
+      FewGemmArgs down;                           // Y[e] = h[e] W2[e]^T
+      down.X = ws; down.ldx = F; down.x_expert_rows = T;
+      down.W0 = w_dn + (size_t)e0 * dn_bytes; down.packed = up.packed;
+      down.C = (char*)Y + (size_t)e0 * T * H * es; down.ldc = H; down.c_expert_rows = T;
+      down.N = H; down.K = F; down.epilogue = EPI_STORE;
+      down.max_rows = T; down.experts = ne;
+      if (int st = launch_gemm_few(down, s, "gemm_down_few")) return st;
+    }
+    return MOEP_OK;
+  }
   if (dt == MOEP_BF16) {
     // Operands are packed once per call into the blocked layout of the packed GEMM (x; every expert's
     // weights, unless the caller has done that already); h stays in that layout between the two projections
@@ -431,6 +459,35 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
                           const void* W2, moep_dtype dt, char* w, hipStream_t s, void* plain_out = nullptr,
                           const void* packed = nullptr, void* direct_out = nullptr) {
   const int H = p.H, F = p.F;
+  if (p.few) {
+    // Few rows per expert: the weights are read where they lie (row-major, or packed by moe_pack_weights) and h is row-major.
+    FewGemmArgs up;
+    up.X = x; up.ldx = H; up.row_of = (const int32_t*)(w + p.off_slot_token);
+    up.W0 = packed ? packed : W1; up.W1 = packed ? nullptr : W3; up.packed = packed != nullptr;
+    up.C = w + p.off_h; up.ldc = F;
+    up.N = F; up.K = H; up.epilogue = EPI_SWIGLU;
+    up.split_k = plain_out == nullptr;
+    up.max_rows = p.T;
+    up.busy_tiles = p.E < p.max_slots ? p.E : p.max_slots;
+    up.tile_expert = (const int32_t*)(w + p.off_tile_expert);
+    up.tile_row0 = (const int32_t*)(w + p.off_tile_row0);
+    up.seg_end = (const int32_t*)(w + p.off_seg_end);
+    up.tiles_in_use = up.tile_expert + p.max_tiles;
+    up.max_tiles = p.max_tiles;
+    if (int st = launch_gemm_few(up, s, "gemm_gate_up_swiglu_few")) return st;
+    FewGemmArgs down = up;
+    down.X = w + p.off_h; down.ldx = F; down.row_of = nullptr;
+    down.W0 = packed ? (const char*)packed + (size_t)p.E * packed_b_bytes(F, H, true) : W2; down.W1 = nullptr;
+    down.C = plain_out ? plain_out : w + p.off_slot_out; down.ldc = H;
+    down.N = H; down.K = F;
+    down.epilogue = plain_out ? EPI_STORE : EPI_ROWSCALE_F32;
+    down.row_scale = plain_out ? nullptr : (const float*)(w + p.off_slot_scale);
+    if (!plain_out && direct_out) {
+      down.row_dest = (const int32_t*)(w + p.off_slot_dest);
+      down.direct_out = direct_out;
+    }
+    return launch_gemm_few(down, s, "gemm_down_few");
+  }
   if (dt == MOEP_BF16) {
     // Packed-operand path: the routed rows of x are gathered into one 256-row block per tile, every
     // expert's weights are re-laid out, and h stays in the packed layout between the two projections.
@@ -499,7 +556,7 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
 size_t moe_forward_skip_workspace(int64_t T, int E, int H, int F, moep_dtype dt) {
   if (!valid_shape(T, E, H, F, dt, "moe_forward_skip_workspace")) return 0;
   SkipPlan p;
-  if (plan_skip(T, E, H, F, dt, 2, &p)) return 0;
+  if (plan_skip(T, E, H, F, dt, 2, E, &p)) return 0;
   return p.total;
 }
 
@@ -531,7 +588,7 @@ static int forward_pruned_skip(const void* x, const void* Wgate, const void* W1,
   if (T == 0) return MOEP_OK;
   if (!x || !out || !skip_mask) return fail(MOEP_EINVAL, "%s: NULL x, out or skip_mask", who);
   SkipPlan p;
-  if (int st = plan_skip(T, E, H, F, dt, 2, &p)) return st;
+  if (int st = plan_skip(T, E, H, F, dt, 2, __builtin_popcount(kept_mask), &p)) return st;
   if (int st = check_ws(ws, ws_bytes, p.total, who)) return st;
   hipStream_t s = (hipStream_t)hip_stream;
   char* w = (char*)ws;
@@ -592,7 +649,7 @@ size_t moe_forward_skip_topk_workspace(int64_t T, int E, int H, int F, moep_dtyp
   if (!valid_shape(T, E, H, F, dt, "moe_forward_skip_topk_workspace")) return 0;
   if (k < 1 || k > 16) return 0;
   SkipPlan p;
-  if (plan_skip(T, E, H, F, dt, k, &p)) return 0;
+  if (plan_skip(T, E, H, F, dt, k, E, &p)) return 0;
   return p.total;
 }
 
@@ -613,7 +670,7 @@ int moe_forward_skip_topk(const void* x, const void* Wgate, const void* W1, cons
   if (T == 0) return MOEP_OK;
   if (!x || !out || !n_used) return fail(MOEP_EINVAL, "%s: NULL x, out or n_used", who);
   SkipPlan p;
-  if (int st = plan_skip(T, E, H, F, dt, k, &p)) return st;
+  if (int st = plan_skip(T, E, H, F, dt, k, __builtin_popcount(kept_mask), &p)) return st;
   if (int st = check_ws(ws, ws_bytes, p.total, who)) return st;
   hipStream_t s = (hipStream_t)hip_stream;
   char* w = (char*)ws;
@@ -663,7 +720,7 @@ size_t moe_expert_outputs_ranked_workspace(int64_t T, int E, int H, int F, moep_
   if (!valid_shape(T, E, H, F, dt, "moe_expert_outputs_ranked_workspace")) return 0;
   if (n_rank < 1 || n_rank > 16 || n_rank > E) return 0;
   SkipPlan p;
-  if (plan_skip(T, E, H, F, dt, n_rank, &p, false)) return 0;
+  if (plan_skip(T, E, H, F, dt, n_rank, E, &p, false)) return 0;
   return p.total;
 }
 
@@ -681,7 +738,7 @@ int moe_expert_outputs_ranked(const void* x, const void* Wgate, const void* W1, 
   if (!x || !logits || !ranked_experts || !slot_of || !Yr)
     return fail(MOEP_EINVAL, "%s: NULL x, logits, ranked_experts, slot_of or Yr", who);
   SkipPlan p;
-  if (int st = plan_skip(T, E, H, F, dt, n_rank, &p, false)) return st;
+  if (int st = plan_skip(T, E, H, F, dt, n_rank, E, &p, false)) return st;
   if (int st = check_ws(ws, ws_bytes, p.total, who)) return st;
   hipStream_t s = (hipStream_t)hip_stream;
   char* w = (char*)ws;

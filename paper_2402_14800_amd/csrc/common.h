@@ -116,6 +116,43 @@ int launch_pack_b_bf16(const void* W0, const void* W1, int N, int K, int experts
                        const char* name);
 int launch_gemm_bf16_packed(const PackedGemmArgs& g, hipStream_t s, const char* name);
 
+// ---- bf16 GEMM for few rows per expert (gemm_few.hip) -----------------------------------
+constexpr int FEW_ROWS = 64;     // rows per tile of its grouped map
+// Up to this many rows per expert the read of the weights bounds the layer and gemm_few.hip is the faster path; beyond
+// it its 64-row tiles read them from the caches too often.  Dense calls: exactly; routed calls: on average, a token's k
+// slots spread over the kept experts and none skipped.  Few-rows path against 256-row tiles, packed weights, us per call:
+// Mixtral shape (E 8, H 4096, F 14336), top-2, T = 128 / 192 (32 / 48 rows): 586 / 766 against 733 / 741, and with six
+// experts kept, T = 160 (53 rows): 778 against 629; layer of E 16, H 2048, F 5632, dense, T = 16 / 48: 382 / 573 against
+// 531 / 560.
+constexpr int64_t FEW_MAX_AVERAGE = 32;
+struct FewGemmArgs {
+  const void* X = nullptr;       // row-major rows of A, leading dimension ldx
+  int64_t ldx = 0;
+  const int32_t* row_of = nullptr;   // grouped, optional: row r of the launch is row row_of[r] of X
+  int64_t x_expert_rows = 0;     // dense: rows between consecutive experts of X (0: every expert reads the same rows)
+  const void* W0 = nullptr;      // packed: blocked copy of every expert's weights; else [experts, N, K] row-major
+  const void* W1 = nullptr;      // row-major EPI_SWIGLU: the linear branch
+  bool packed = false;
+  void* C = nullptr;             // EPI_STORE, EPI_SWIGLU: bf16 rows; EPI_ROWSCALE_F32: fp32 rows; leading dimension ldc
+  int64_t ldc = 0, c_expert_rows = 0;
+  int N = 0, K = 0;
+  int epilogue = EPI_STORE;
+  bool split_k = false;          // several wavefronts may share a column group (another order of summation)
+  int64_t max_rows = 0;          // dense: rows; grouped: most rows an expert can have
+  int64_t busy_tiles = 1;        // tiles that are expected to hold rows (sizes the split)
+  int experts = 1;               // dense
+  // grouped: the tile map of GemmArgs with FEW_ROWS rows per tile
+  const int32_t* tile_expert = nullptr;
+  const int32_t* tile_row0 = nullptr;
+  const int32_t* seg_end = nullptr;
+  const int32_t* tiles_in_use = nullptr;
+  int64_t max_tiles = 0;
+  const float* row_scale = nullptr;
+  const int32_t* row_dest = nullptr;   // as in PackedGemmArgs
+  void* direct_out = nullptr;
+};
+int launch_gemm_few(const FewGemmArgs& g, hipStream_t s, const char* name);
+
 // ---- router -------------------------------------------------------------------
 int launch_router(const void* x, const void* Wgate, int64_t T, int E, int H, moep_dtype dt,
                   float* logits, hipStream_t s);
@@ -176,12 +213,15 @@ struct SkipPlan {
   int64_t T; int E, H, F;
   int ks;                // slots per token (2 for the top-2 rule, k for the generalised rule)
   int64_t max_slots;     // ks T
+  bool few;              // bf16, few rows per expert: gemm_few.hip, no operand is re-laid out
+  int tile_rows;         // rows per tile of the map
   int64_t max_tiles;     // upper bound on M tiles over all experts
   size_t off_logits, off_slot_token, off_slot_scale, off_slot_dest, off_pos, off_counts, off_seg_end,
          off_tile_expert, off_tile_row0, off_order_up, off_order_down, off_h, off_xp, off_w13, off_w2, off_slot_out, total;
   bool packed;           // bf16: packed-operand GEMMs (tile order tables are built)
 };
-int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, SkipPlan* p, bool with_slot_out = true);
+// kept_experts: experts that tokens can be routed to (decides the path, not the size of the workspace)
+int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_experts, SkipPlan* p, bool with_slot_out = true);
 int launch_skip_routing(const SkipPlan& p, const float* logits, uint32_t kept_mask, float beta, uint8_t* skip_mask,
                         int32_t* top2_out, char* ws, hipStream_t s);
 // `singles_done`: tokens routed to a single expert already have their output (written by the down projection)

@@ -1,0 +1,290 @@
+// bf16 expert GEMMs for FEW rows per expert (token generation, small batches): C = epilogue(A B^T), fp32 accumulate.
+//
+// With a few dozen rows per expert the work is a read of the weights: 2 flop per weight byte and row, so the launch
+// is bound by the memory from one row to about a hundred.  The 256-row tiles of gemm_bf16_packed.hip cannot reach that
+// bound: one token leaves most compute units without a tile (the down projection of 4096 x 14336 has 16 tiles per
+// expert, each a serial walk over 448 slices: 251 us for one token), and the padding rows are multiplied all the same.
+//
+// Here a weight element goes from memory straight into the register of the one wavefront that multiplies it; nothing is
+// staged in LDS and nothing is shared, so there is no barrier in the loop.  A wavefront takes 32 output columns (gate/up:
+// 32 gate and the 32 up rows of the same columns) x up to 64 rows and walks every KS-th pair of 32-deep slices; the KS
+// wavefronts that share the columns add their partial sums in LDS, in a fixed order, at the end.  KS is chosen so that about 2048
+// wavefronts are in flight (8 per compute unit, each with 4 to 24 KB of loads outstanding).
+// Rows of A (x through a token list, or h) are read as MFMA fragments from L1/L2: they are a few hundred KB, shared by all.
+//
+// Weights come either as the caller stores them (row-major [N, K]) or in the blocked layout of moe_pack_weights;
+// the same 16-row fragments, the same slices in the same order, so both give the same bits.  A packed fragment is 1 KB of
+// consecutive bytes, a row-major pair of slices is one whole 128-byte line of each of 16 rows.
+// (weights row-major: 4.3 TB/s, whose loads ask for 64 bytes of 16 rows at a time; with the non-temporal hint, which the
+// packed weights are read with, 3.8).
+// Measured, skipping forward of the Mixtral shape (E 8, H 4096, F 14336) on packed weights, before and after: one token
+// 359 -> 88 us, 16 tokens (all 2.8 GB of weights) 720 -> 447 us = 6.3 TB/s; row-major weights, which needed a packing pass
+// over all of them per call: 1842 -> 646 us for 16 tokens, 1486 -> 133 us for one.
+// With KS = 1 the products are also summed in the order of gemm_packed_kernel (one v_mfma_f32_16x16x32_bf16 per slice,
+// slices ascending), bit for bit: the entry points that store every expert output rely on that and always use KS = 1.
+#include "common.h"
+
+namespace moep {
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+
+constexpr int SLICE = 256 * 64;     // bytes of one packed block (256 rows x 32 k), see gemm_bf16_packed.hip
+constexpr int MAX_WAVES = 8;
+constexpr int WANT_WAVES = 2048;    // wavefronts a launch is split into, about
+
+struct FewArgs {
+  const char* W0; const char* W1;     // row-major: W0 [N,K] (gate), W1 (up); packed: W0 = blocked copy
+  int64_t w_expert_bytes;
+  const char* X; int64_t x_row_bytes; // rows of A
+  const int32_t* row_of;              // grouped gate/up: row r of the launch is row row_of[r] of X; NULL: r itself
+  int64_t x_expert_rows;              // dense: rows between consecutive experts in X (0: shared)
+  void* C; int64_t ldc;               // elements
+  int64_t c_expert_rows;              // dense
+  int N, nsl;                         // output columns; K / 32
+  int ks;                             // wavefronts per group of 32 columns
+  // grouped: tile t = rows tile_row0[t] .. seg_end[tile_expert[t]] - 1, at most FEW_ROWS of them
+  const int32_t* tile_expert; const int32_t* tile_row0; const int32_t* seg_end; const int32_t* tiles_in_use;
+  // dense: tile t = rows (t % row_tiles) * FEW_ROWS .. of expert t / row_tiles
+  int row_tiles; int64_t rows;
+  const float* row_scale;
+  const int32_t* row_dest; uint16_t* direct_out;
+};
+
+// One tile, M groups of 16 rows (M >= the groups in use; rows beyond row_end repeat the last one and are not stored).
+template <int EPI, bool PACKED, int M>
+__device__ __forceinline__ void few_tile(const FewArgs& p, int expert, int64_t row0, int64_t row_end, float* lds) {
+  constexpr int NF = EPI == EPI_SWIGLU ? 4 : 2;      // weight fragments of 16 rows: (gate, up) x 2 or 2
+  // pairs of slices held in registers (all but the one being multiplied are in flight)
+  constexpr int D = EPI == EPI_SWIGLU ? (M >= 4 ? 2 : 3) : 4;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ks = p.ks;
+  const int kpart = wave % ks;
+  const int unit = blockIdx.x * ((int)(blockDim.x >> 6) / ks) + wave / ks;
+  const int n0 = unit * 32;
+  const bool in_range = n0 < p.N;
+  const int lrow = lane & 15, kg = lane >> 4;
+  // Weight fragments.  Row f of fragment b of a group of 32 columns is column 8 (f >> 2) + 4 b + (f & 3), so that a lane
+  // of the (transposed) result tiles holds 8 consecutive columns; the blocked layout stores the rows in that order.
+  const char* wp[NF];
+  int64_t wstep;                                     // bytes from a slice to the next
+  if (PACKED) {
+    const int c = in_range ? n0 : 0;
+    const int tile = EPI == EPI_SWIGLU ? c >> 7 : c >> 8;
+    const int r0 = EPI == EPI_SWIGLU ? c & 127 : c & 255;
+    const char* base = p.W0 + (int64_t)expert * p.w_expert_bytes + (int64_t)tile * p.nsl * SLICE;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const int row = r0 + (f & 1) * 16 + lrow + (EPI == EPI_SWIGLU && f >= 2 ? 128 : 0);
+      wp[f] = base + row * 64 + ((kg ^ ((row >> 2) & 3)) << 4);
+    }
+    wstep = SLICE;
+  } else {
+    const int c = (in_range ? n0 : 0) + 8 * (lrow >> 2) + (lrow & 3);
+    const int64_t pitch = (int64_t)p.nsl * 64;
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+      wp[f] = (EPI == EPI_SWIGLU && f >= 2 ? p.W1 : p.W0) + (int64_t)expert * p.w_expert_bytes + (c + 4 * (f & 1)) * pitch +
+              kg * 16;
+    wstep = 64;
+  }
+  const char* xp[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    int64_t r = row0 + m * 16 + lrow;
+    if (r >= row_end) r = row_end - 1;
+    r = p.row_of ? (int64_t)p.row_of[r] : r + (int64_t)expert * p.x_expert_rows;
+    xp[m] = p.X + r * p.x_row_bytes + kg * 16;
+  }
+  f32x4 acc[NF][M];
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[f][m][v] = 0.f;
+
+  const int pairs = p.nsl >> 1;                      // K is a multiple of 64
+  const int n = kpart < pairs ? (pairs - kpart + ks - 1) / ks : 0;    // pairs of this wavefront: kpart, kpart + ks, ...
+  bf16x8 w[D][2][NF], xv[D][2][M];
+  // (past its last pair a wavefront re-reads that one: in bounds, and the number of loads in flight is always the same)
+  auto fetch = [&](int slot, int i) {
+    const int s = 2 * (kpart + ks * (i < n ? i : n - 1));
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) w[slot][u][f] = PACKED ? __builtin_nontemporal_load((const bf16x8*)(wp[f] + (s + u) * wstep))
+                                                                         : *(const bf16x8*)(wp[f] + (s + u) * wstep);
+#pragma unroll
+      for (int m = 0; m < M; ++m) xv[slot][u][m] = *(const bf16x8*)(xp[m] + (int64_t)(s + u) * 64);
+    }
+  };
+  if (in_range && n > 0) {
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d) fetch(d, d);
+    for (int i0 = 0; i0 < n; i0 += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        fetch((d + D - 1) % D, i0 + d + D - 1);
+        if (i0 + d < n) {
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+              for (int m = 0; m < M; ++m)
+                acc[f][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[d][u][f], xv[d][u][m], acc[f][m], 0, 0, 0);
+        }
+      }
+    }
+  }
+  // Sum over the ks wavefronts of a column group, halving: the upper half hands its sums to the lower half.
+  for (int half = ks >> 1; half >= 1; half >>= 1) {
+    float* const mine = lds + ((wave / ks) * half + (kpart % half)) * (NF * M * 256) + lane * 4;
+    if (kpart >= half && kpart < 2 * half) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int m = 0; m < M; ++m) *(f32x4*)(mine + (f * M + m) * 256) = acc[f][m];
+    }
+    __syncthreads();
+    if (kpart < half) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int m = 0; m < M; ++m) acc[f][m] += *(const f32x4*)(mine + (f * M + m) * 256);
+    }
+    __syncthreads();
+  }
+  if (kpart != 0 || !in_range) return;
+  // Register v of lane l of tile (f, m): column n0 + 8 (l / 16) + 4 (f & 1) + v, row 16 m + l % 16.
+  const int col = n0 + 8 * kg;
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const int64_t r = row0 + m * 16 + lrow;
+    if (r >= row_end) continue;
+    const int64_t cr = r + (int64_t)expert * p.c_expert_rows;
+    bf16x2 o[4];
+    if (EPI == EPI_SWIGLU) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        f32x2 h;
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+          const int b = c >> 1, v = 2 * (c & 1) + d;
+          const float g = acc[b][m][v], u = acc[(NF >> 1) + b][m][v];
+          h[d] = g * u * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
+        }
+        o[c] = __builtin_convertvector(h, bf16x2);
+      }
+      *(u32x4*)((uint16_t*)p.C + cr * p.ldc + col) = __builtin_bit_cast(u32x4, o);
+    } else {
+      int64_t dest = -1;
+      if (EPI == EPI_ROWSCALE_F32 && p.row_dest) dest = p.row_dest[r];
+      if (EPI == EPI_STORE || dest >= 0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const f32x2 h = {acc[c >> 1][m][2 * (c & 1)], acc[c >> 1][m][2 * (c & 1) + 1]};
+          o[c] = __builtin_convertvector(h, bf16x2);
+        }
+        uint16_t* const row = EPI == EPI_STORE ? (uint16_t*)p.C + cr * p.ldc : p.direct_out + dest * p.ldc;
+        *(u32x4*)(row + col) = __builtin_bit_cast(u32x4, o);
+      } else {
+        const float sc = p.row_scale[r];
+        float* dst = (float*)p.C + cr * p.ldc + col;
+        *(f32x4*)dst = sc * acc[0][m];
+        *(f32x4*)(dst + 4) = sc * acc[1][m];
+      }
+    }
+  }
+}
+
+// MMAX: groups of 16 rows that any tile of the launch can hold; a tile takes the smallest body that fits it.
+template <int EPI, bool PACKED, int MMAX>
+__global__ __launch_bounds__(64 * MAX_WAVES) void gemm_few_kernel(FewArgs p) {
+  extern __shared__ __attribute__((aligned(16))) float few_lds[];
+  const int t = blockIdx.y;
+  int expert;
+  int64_t row0, row_end;
+  if (p.tile_expert) {
+    if (t >= *p.tiles_in_use) return;
+    expert = p.tile_expert[t];
+    row0 = p.tile_row0[t];
+    row_end = p.seg_end[expert];
+  } else {
+    expert = t / p.row_tiles;
+    row0 = (int64_t)(t - expert * p.row_tiles) * FEW_ROWS;
+    row_end = p.rows;
+  }
+  if (row_end > row0 + FEW_ROWS) row_end = row0 + FEW_ROWS;
+  const int rows = (int)(row_end - row0);
+  if (MMAX == 1 || rows <= 16) few_tile<EPI, PACKED, 1>(p, expert, row0, row_end, few_lds);
+  else if (MMAX == 2 || rows <= 32) few_tile<EPI, PACKED, 2>(p, expert, row0, row_end, few_lds);
+  else few_tile<EPI, PACKED, 4>(p, expert, row0, row_end, few_lds);
+}
+
+template <int EPI, bool PACKED>
+void launch(const FewArgs& a, int mmax, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  if (mmax == 1) hipLaunchKernelGGL((gemm_few_kernel<EPI, PACKED, 1>), grid, dim3(threads), lds, s, a);
+  else if (mmax == 2) hipLaunchKernelGGL((gemm_few_kernel<EPI, PACKED, 2>), grid, dim3(threads), lds, s, a);
+  else hipLaunchKernelGGL((gemm_few_kernel<EPI, PACKED, 4>), grid, dim3(threads), lds, s, a);
+}
+
+}  // namespace
+
+int launch_gemm_few(const FewGemmArgs& g, hipStream_t s, const char* name) {
+  if (g.K <= 0 || g.K % 64 || g.N <= 0 || g.N % 32) return fail(MOEP_EUNSUPPORTED, "%s: K=%d, N=%d must be multiples of 64 and 32", name, g.K, g.N);
+  if (((uintptr_t)g.X | (uintptr_t)g.W0 | (uintptr_t)g.W1 | (uintptr_t)g.C | (uintptr_t)g.direct_out) & 15)
+    return fail(MOEP_EUNSUPPORTED, "%s: operands must be 16-byte aligned", name);
+  if (g.ldx % 8 || g.ldc % 8 || g.ldc < g.N) return fail(MOEP_EINVAL, "%s: bad leading dimension", name);
+  const bool grouped = g.tile_expert != nullptr;
+  if (grouped && (!g.tile_row0 || !g.seg_end || !g.tiles_in_use)) return fail(MOEP_EINVAL, "%s: incomplete tile map", name);
+  if (g.epilogue == EPI_ROWSCALE_F32 && !g.row_scale) return fail(MOEP_EINVAL, "%s: row_scale is NULL", name);
+  if (g.max_rows <= 0) return MOEP_OK;
+  FewArgs a = {};
+  a.W0 = (const char*)g.W0; a.W1 = (const char*)g.W1;
+  a.w_expert_bytes = g.packed ? (int64_t)packed_b_bytes(g.N, g.K, g.epilogue == EPI_SWIGLU) : (int64_t)g.N * g.K * 2;
+  a.X = (const char*)g.X; a.x_row_bytes = g.ldx * 2; a.row_of = g.row_of; a.x_expert_rows = g.x_expert_rows;
+  a.C = g.C; a.ldc = g.ldc; a.c_expert_rows = g.c_expert_rows;
+  a.N = g.N; a.nsl = g.K / 32;
+  a.tile_expert = g.tile_expert; a.tile_row0 = g.tile_row0; a.seg_end = g.seg_end; a.tiles_in_use = g.tiles_in_use;
+  a.row_tiles = (int)ceil_div(g.max_rows, FEW_ROWS); a.rows = g.max_rows;
+  a.row_scale = g.row_scale; a.row_dest = g.row_dest; a.direct_out = (uint16_t*)g.direct_out;
+  const int64_t tiles = grouped ? g.max_tiles : (int64_t)a.row_tiles * g.experts;
+  if (tiles > 65535) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
+  const int units = g.N / 32;
+  const int rows = (int)(g.max_rows < FEW_ROWS ? g.max_rows : FEW_ROWS);
+  const int mmax = rows <= 16 ? 1 : rows <= 32 ? 2 : 4;
+  // Wavefronts per column group: a power of two that brings the launch to about 2048 wavefronts, with 4 pairs of slices
+  // each at least.  Stored expert outputs (EPI_STORE, and the gate/up pass before it) keep one: see the head of the file.
+  int ks = 1;
+  if (g.split_k)
+    while (ks < MAX_WAVES && (int64_t)units * g.busy_tiles * ks < WANT_WAVES && g.K / 64 >= 8 * ks) ks *= 2;
+  a.ks = ks;
+  const int waves = ks > 4 ? ks : 4;
+  const dim3 grid((unsigned)ceil_div(units, waves / ks), (unsigned)tiles);
+  const size_t lds = ks > 1 ? (size_t)(waves / ks) * (ks / 2) * (g.epilogue == EPI_SWIGLU ? 4 : 2) * mmax * 1024 : 0;
+  Timed t(name, s);
+  if (g.packed) {
+    switch (g.epilogue) {
+      case EPI_STORE: launch<EPI_STORE, true>(a, mmax, grid, waves * 64, lds, s); break;
+      case EPI_SWIGLU: launch<EPI_SWIGLU, true>(a, mmax, grid, waves * 64, lds, s); break;
+      default: launch<EPI_ROWSCALE_F32, true>(a, mmax, grid, waves * 64, lds, s); break;
+    }
+  } else {
+    switch (g.epilogue) {
+      case EPI_STORE: launch<EPI_STORE, false>(a, mmax, grid, waves * 64, lds, s); break;
+      case EPI_SWIGLU: launch<EPI_SWIGLU, false>(a, mmax, grid, waves * 64, lds, s); break;
+      default: launch<EPI_ROWSCALE_F32, false>(a, mmax, grid, waves * 64, lds, s); break;
+    }
+  }
+  MOEP_HIP(hipGetLastError());
+  return MOEP_OK;
+}
+
+}  // namespace moep

@@ -1,13 +1,14 @@
 // Dynamic skipping, top-2 (Sec. 3.3; output per App. A.2): routing, dispatch and combine.
-// The expert FFNs themselves are the grouped GEMMs (see gemm_bf16_packed.hip / gemm_f32.hip).
+// The expert FFNs themselves are the grouped GEMMs (see gemm_bf16_packed.hip / gemm_few.hip / gemm_f32.hip).
 //
 //   route    per token: top-2 experts by logit among the kept experts (ties -> lower index), delta = l_e1 - l_e0 in fp32,
 //            skip iff delta < theta = fp32(ln beta) (theta = -inf for beta = 0), weights
 //            a0 = 1 / (1 + rho), a1 = rho / (1 + rho), rho = exp(delta); a0 = 1 when skipped.
 //            Also counts, per block of 256 tokens, the rows each expert receives.
 //   scan     turns the counts into each (block, expert)'s first slot, each expert's segment end,
-//            and the map from 256-row M tiles to (expert, first row) that the grouped GEMMs walk
+//            and the map from M tiles (256 rows, or 64) to (expert, first row) that the grouped GEMMs walk
 //            (entry [max_tiles] of the expert list holds the number of tiles in use).
+//            (a batch of up to 512 tokens goes through route, scan and scatter in ONE workgroup, dispatch_one)
 //   scatter  writes slot -> token and slot -> weight lists and token -> slot positions.  Within an
 //            expert's segment the rows are in ascending token order, so the result is reproducible.
 //   combine  out[t] = slot_out[pos0] (+ slot_out[pos1] unless skipped); the down projection has
@@ -25,6 +26,27 @@ namespace moep {
 namespace {
 
 constexpr int RB = 256;     // tokens per routing block
+// Most tokens that the one-workgroup dispatch takes: one thread each; up to here it is shorter than the three kernels
+// it replaces (their counts and lists would go through memory twice for nothing).
+constexpr int DISPATCH_ONE_MAX = 512;
+
+struct Top2 { int e0, e1; float a0, a1; bool skip; };
+
+// The top-2 rule on one row of logits.
+__device__ __forceinline__ Top2 route_top2(const float* l, int E, uint32_t kept, float theta) {
+  int e0 = -1, e1 = -1;
+  float l0 = -INFINITY, l1 = -INFINITY;
+  for (int e = 0; e < E; ++e) {          // strict comparisons: the lower index wins a tie
+    if (!((kept >> e) & 1u)) continue;   // a removed expert and its routing weight are gone
+    const float v = l[e];
+    if (e0 < 0 || v > l0) { l1 = l0; e1 = e0; l0 = v; e0 = e; }
+    else if (e1 < 0 || v > l1) { l1 = v; e1 = e; }
+  }
+  const float delta = l1 - l0;
+  const bool skip = delta < theta;
+  const float rho = expf(delta);
+  return {e0, e1, skip ? 1.0f : 1.0f / (1.0f + rho), skip ? 0.0f : rho / (1.0f + rho), skip};
+}
 
 __global__ __launch_bounds__(RB) void route_kernel(const float* __restrict__ logits, int64_t T,
                                                    int E, uint32_t kept, float theta, uint8_t* __restrict__ skip_mask,
@@ -35,27 +57,14 @@ __global__ __launch_bounds__(RB) void route_kernel(const float* __restrict__ log
   __syncthreads();
   const int64_t t = (int64_t)blockIdx.x * RB + threadIdx.x;
   if (t < T) {
-    const float* l = logits + t * E;
-    int e0 = -1, e1 = -1;
-    float l0 = -INFINITY, l1 = -INFINITY;
-    for (int e = 0; e < E; ++e) {          // strict comparisons: the lower index wins a tie
-      if (!((kept >> e) & 1u)) continue;   // a removed expert and its routing weight are gone
-      const float v = l[e];
-      if (e0 < 0 || v > l0) { l1 = l0; e1 = e0; l0 = v; e0 = e; }
-      else if (e1 < 0 || v > l1) { l1 = v; e1 = e; }
-    }
-    const float delta = l1 - l0;
-    const bool skip = delta < theta;
-    const float rho = expf(delta);
-    const float a0 = skip ? 1.0f : 1.0f / (1.0f + rho);
-    const float a1 = skip ? 0.0f : rho / (1.0f + rho);
-    skip_mask[t] = skip ? 1 : 0;
-    top2[2 * t] = e0;
-    top2[2 * t + 1] = e1;
-    tw[2 * t] = a0;
-    tw[2 * t + 1] = a1;
-    atomicAdd(&cnt[e0], 1);
-    if (!skip) atomicAdd(&cnt[e1], 1);
+    const Top2 r = route_top2(logits + t * E, E, kept, theta);
+    skip_mask[t] = r.skip ? 1 : 0;
+    top2[2 * t] = r.e0;
+    top2[2 * t + 1] = r.e1;
+    tw[2 * t] = r.a0;
+    tw[2 * t + 1] = r.a1;
+    atomicAdd(&cnt[r.e0], 1);
+    if (!r.skip) atomicAdd(&cnt[r.e1], 1);
   }
   __syncthreads();
   if ((int)threadIdx.x < E) counts[(int64_t)blockIdx.x * E + threadIdx.x] = cnt[threadIdx.x];
@@ -66,7 +75,7 @@ __global__ __launch_bounds__(RB) void route_kernel(const float* __restrict__ log
 __global__ __launch_bounds__(256) void scan_kernel(int32_t* __restrict__ counts, int64_t n_blocks,
                                                    int E, int32_t* __restrict__ seg_end,
                                                    int32_t* __restrict__ tile_expert,
-                                                   int32_t* __restrict__ tile_row0, int max_tiles) {
+                                                   int32_t* __restrict__ tile_row0, int max_tiles, int tile_rows) {
   __shared__ int total[32], begin[33];
   __shared__ int n_tiles;
   const int e = threadIdx.x;
@@ -83,7 +92,7 @@ __global__ __launch_bounds__(256) void scan_kernel(int32_t* __restrict__ counts,
     int idx = 0;
     for (int i = 0; i < E; ++i) {
       seg_end[E + i] = idx;
-      for (int row = begin[i]; row < begin[i + 1] && idx < max_tiles; row += GEMM_BM) {
+      for (int row = begin[i]; row < begin[i + 1] && idx < max_tiles; row += tile_rows) {
         tile_expert[idx] = i;
         tile_row0[idx] = row;
         ++idx;
@@ -210,6 +219,46 @@ __global__ __launch_bounds__(256) void combine_kernel(const float4* __restrict__
 
 
 // ---- generalised top-k skipping -----------------------------------------------------------
+// The generalised rule on one row of logits: the top-K experts es, best first, the number istar that stays, and
+// the renormalised weights of those (0 for the others).
+template <int K>
+__device__ __forceinline__ int route_topk(const float* l, int E, uint32_t kept, double beta, int (&es)[K], float (&w)[K]) {
+  uint32_t avail = kept;
+  double ex[K];
+  float l_first = 0.f;
+#pragma unroll
+  for (int m = 0; m < K; ++m) {            // m-th largest kept logit; strict >: lower index wins a tie
+    int best = -1;
+    float bv = 0.f;
+    for (int e = 0; e < E; ++e) {
+      if (!((avail >> e) & 1u)) continue;
+      const float v = l[e];
+      if (best < 0 || v > bv) { best = e; bv = v; }
+    }
+    avail &= ~(1u << best);
+    es[m] = best;
+    if (m == 0) l_first = bv;
+    ex[m] = exp((double)bv - (double)l_first);
+  }
+  double tail[K + 1];                      // tail[i] = sum_{m > i} w_m (m counted from 1)
+  tail[K] = 0.0;
+#pragma unroll
+  for (int i = K - 1; i >= 0; --i) tail[i] = tail[i + 1] + ex[i];
+  const double budget = beta * tail[0];
+  int istar = K;
+#pragma unroll
+  for (int i = K - 1; i >= 1; --i)
+    if (!(tail[i] > budget)) istar = i;    // ends at the smallest i that passes; tail[K] = 0 always passes
+  // tails shrink with i, so "passes" is monotone and the smallest passing i is the answer
+  double den = 0.0;
+#pragma unroll
+  for (int m = 0; m < K; ++m)
+    if (m < istar) den += ex[m];
+#pragma unroll
+  for (int m = 0; m < K; ++m) w[m] = m < istar ? (float)(ex[m] / den) : 0.0f;
+  return istar;
+}
+
 template <int K>
 __global__ __launch_bounds__(RB) void route_topk_kernel(const float* __restrict__ logits, int64_t T,
                                                         int E, uint32_t kept, double beta,
@@ -222,44 +271,14 @@ __global__ __launch_bounds__(RB) void route_topk_kernel(const float* __restrict_
   __syncthreads();
   const int64_t t = (int64_t)blockIdx.x * RB + threadIdx.x;
   if (t < T) {
-    const float* l = logits + t * E;
-    uint32_t avail = kept;
     int es[K];
-    double ex[K];
-    float l_first = 0.f;
-#pragma unroll
-    for (int m = 0; m < K; ++m) {            // m-th largest kept logit; strict >: lower index wins a tie
-      int best = -1;
-      float bv = 0.f;
-      for (int e = 0; e < E; ++e) {
-        if (!((avail >> e) & 1u)) continue;
-        const float v = l[e];
-        if (best < 0 || v > bv) { best = e; bv = v; }
-      }
-      avail &= ~(1u << best);
-      es[m] = best;
-      if (m == 0) l_first = bv;
-      ex[m] = exp((double)bv - (double)l_first);
-    }
-    double tail[K + 1];                      // tail[i] = sum_{m > i} w_m (m counted from 1)
-    tail[K] = 0.0;
-#pragma unroll
-    for (int i = K - 1; i >= 0; --i) tail[i] = tail[i + 1] + ex[i];
-    const double budget = beta * tail[0];
-    int istar = K;
-#pragma unroll
-    for (int i = K - 1; i >= 1; --i)
-      if (!(tail[i] > budget)) istar = i;    // ends at the smallest i that passes; tail[K] = 0 always passes
-    // tails shrink with i, so "passes" is monotone and the smallest passing i is the answer
-    double den = 0.0;
-#pragma unroll
-    for (int m = 0; m < K; ++m)
-      if (m < istar) den += ex[m];
+    float w[K];
+    const int istar = route_topk<K>(logits + t * E, E, kept, beta, es, w);
     n_used[t] = istar;
 #pragma unroll
     for (int m = 0; m < K; ++m) {
       topk[t * K + m] = es[m];
-      tw[t * K + m] = m < istar ? (float)(ex[m] / den) : 0.0f;
+      tw[t * K + m] = w[m];
       if (m < istar) atomicAdd(&cnt[es[m]], 1);
     }
   }
@@ -339,13 +358,117 @@ __global__ __launch_bounds__(256) void combine_topk_kernel(const float4* __restr
   }
 }
 
+// ---- the whole dispatch in one workgroup ----------------------------------------------------
+// route, scan and scatter for a batch that fits one workgroup (a thread per token): three launches of 4 to 5 us each,
+// all of it latency, become one.  Same outputs as the three, entry for entry.  TOP2: the top-2 rule with its skip
+// mask; else the generalised rule with its counts.  tw is not written: the weights go straight to the slots.
+template <int K, bool TOP2>
+__global__ __launch_bounds__(DISPATCH_ONE_MAX) void dispatch_one_kernel(
+    const float* __restrict__ logits, int T, int E, uint32_t kept, float theta, double beta, uint8_t* __restrict__ skip_mask,
+    int32_t* __restrict__ n_used, int32_t* __restrict__ experts, int32_t* __restrict__ slot_token,
+    float* __restrict__ slot_scale, int32_t* __restrict__ slot_dest, int32_t* __restrict__ pos, int32_t* __restrict__ seg_end,
+    int32_t* __restrict__ tile_expert, int32_t* __restrict__ tile_row0, int max_tiles, int tile_rows) {
+  constexpr int WAVES = DISPATCH_ONE_MAX / 64;
+  __shared__ int wave_base[WAVES][32];     // counts, then first slots, of (wavefront, expert)
+  __shared__ int begin[33], first_tile[33];
+  const int t = threadIdx.x;
+  const int lane = t & 63, wave = t >> 6;
+  const bool live = t < T;
+  int es[K], rank[K], used = 0;
+  float w[K];
+#pragma unroll
+  for (int m = 0; m < K; ++m) { es[m] = -1; rank[m] = 0; w[m] = 0.f; }
+  if (live) {
+    if constexpr (TOP2) {
+      const Top2 r = route_top2(logits + (int64_t)t * E, E, kept, theta);
+      es[0] = r.e0; w[0] = r.a0;
+      es[1] = r.e1; w[1] = r.a1;
+      used = r.skip ? 1 : 2;
+      skip_mask[t] = r.skip ? 1 : 0;
+    } else {
+      used = route_topk<K>(logits + (int64_t)t * E, E, kept, beta, es, w);
+      n_used[t] = used;
+    }
+#pragma unroll
+    for (int m = 0; m < K; ++m) {
+      experts[t * K + m] = es[m];
+      if (m >= used) es[m] = -1;
+    }
+  }
+  const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  for (int e = 0; e < E; ++e) {             // a token routes to an expert at most once
+    bool has = false;
+#pragma unroll
+    for (int m = 0; m < K; ++m) has |= es[m] == e;
+    const unsigned long long b = __ballot(has);
+    const int before = __popcll(b & below);
+#pragma unroll
+    for (int m = 0; m < K; ++m)
+      if (es[m] == e) rank[m] = before;
+    if (lane == 0) wave_base[wave][e] = __popcll(b);
+  }
+  __syncthreads();
+  const int waves = blockDim.x >> 6;
+  if (t < E) {                              // slots before (wavefront, expert t) within the expert's segment
+    int run = 0;
+    for (int v = 0; v < waves; ++v) {
+      const int c = wave_base[v][t];
+      wave_base[v][t] = run;
+      run += c;
+    }
+    begin[t + 1] = run;                     // for now: the expert's rows
+  }
+  __syncthreads();
+  if (t == 0) {
+    int run = 0, tiles = 0;
+    begin[0] = 0;
+    for (int e = 0; e < E; ++e) {
+      const int c = begin[e + 1];
+      first_tile[e] = tiles;
+      seg_end[E + e] = tiles;
+      tiles += (c + tile_rows - 1) / tile_rows;
+      run += c;
+      begin[e + 1] = run;
+      seg_end[e] = run;
+    }
+    first_tile[E] = tiles;
+    seg_end[2 * E] = tiles;
+    tile_expert[max_tiles] = tiles;         // number of tiles in use, read by the grouped GEMMs
+  }
+  __syncthreads();
+  if (t < E)
+    for (int i = first_tile[t]; i < first_tile[t + 1]; ++i) {
+      tile_expert[i] = t;
+      tile_row0[i] = begin[t] + (i - first_tile[t]) * tile_rows;
+    }
+  for (int i = first_tile[E] + t; i < max_tiles; i += blockDim.x) {
+    tile_expert[i] = -1;
+    tile_row0[i] = 0;
+  }
+  if (!live) return;
+#pragma unroll
+  for (int m = 0; m < K; ++m) {
+    int p = -1;
+    if (m < used) {
+      p = begin[es[m]] + wave_base[wave][es[m]] + rank[m];
+      slot_token[p] = t;
+      slot_scale[p] = w[m];
+      slot_dest[p] = used == 1 ? t : -1;    // a token's only slot (weight 1) is the token's output
+    }
+    pos[t * K + m] = p;
+  }
+}
+
 }  // namespace
 
-int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, SkipPlan* p, bool with_slot_out) {
+int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_experts, SkipPlan* p, bool with_slot_out) {
   if ((int64_t)ks * T >= ((int64_t)1 << 31)) return fail(MOEP_EUNSUPPORTED, "moe_forward_skip: T too large");
   p->T = T; p->E = E; p->H = H; p->F = F; p->ks = ks;
   p->max_slots = (int64_t)ks * T;
-  p->max_tiles = ceil_div((int64_t)ks * T, GEMM_BM) + E;
+  p->few = dt == MOEP_BF16 && p->max_slots <= FEW_MAX_AVERAGE * kept_experts;
+  p->tile_rows = p->few ? FEW_ROWS : GEMM_BM;
+  p->max_tiles = ceil_div((int64_t)ks * T, p->tile_rows) + E;
+  const int64_t map_tiles = ceil_div((int64_t)ks * T, dt == MOEP_BF16 ? FEW_ROWS : GEMM_BM) + E;   // either path's map fits
   const int64_t n_blocks = ceil_div(T, RB);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
@@ -356,19 +479,20 @@ int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, SkipPlan* p
   p->off_pos = take((size_t)T * ks * 4 * 3);           // pos, experts, weights: [T,ks] each
   p->off_counts = take((size_t)n_blocks * E * 4);
   p->off_seg_end = take((size_t)(2 * E + 1) * 4);          // segment ends, then each expert's first tile
-  p->off_tile_expert = take((size_t)(p->max_tiles + 1) * 4);   // + the count of tiles in use
-  p->off_tile_row0 = take((size_t)p->max_tiles * 4);
+  p->off_tile_expert = take((size_t)(map_tiles + 1) * 4);   // + the count of tiles in use
+  p->off_tile_row0 = take((size_t)map_tiles * 4);
   p->packed = dt == MOEP_BF16;
   p->off_order_up = p->off_order_down = 0;
   if (dt == MOEP_BF16) {
-    if (ceil_div(F, GEMM_BN_SWIGLU) > 4096 || ceil_div(H, GEMM_BN_STORE) > 4096 || p->max_tiles >= (1 << 20))
+    const int64_t gemm_tiles = ceil_div((int64_t)ks * T, GEMM_BM) + E;
+    if (ceil_div(F, GEMM_BN_SWIGLU) > 4096 || ceil_div(H, GEMM_BN_STORE) > 4096 || gemm_tiles >= (1 << 20))
       return fail(MOEP_EUNSUPPORTED, "moe_forward_skip: too many tiles for the tile order tables");
-    p->off_order_up = take((size_t)p->max_tiles * ceil_div(F, GEMM_BN_SWIGLU) * 4);
-    p->off_order_down = take((size_t)p->max_tiles * ceil_div(H, GEMM_BN_STORE) * 4);
+    p->off_order_up = take((size_t)gemm_tiles * ceil_div(F, GEMM_BN_SWIGLU) * 4);
+    p->off_order_down = take((size_t)gemm_tiles * ceil_div(H, GEMM_BN_STORE) * 4);
     // packed-operand GEMMs: h and the gathered x hold one 256-row block per tile; every expert's weights
     // are re-laid out once per call
-    p->off_h = take(packed_a_bytes(p->max_tiles * GEMM_BM, F));
-    p->off_xp = take(packed_a_bytes(p->max_tiles * GEMM_BM, H));
+    p->off_h = take(packed_a_bytes(gemm_tiles * GEMM_BM, F));
+    p->off_xp = take(packed_a_bytes(gemm_tiles * GEMM_BM, H));
     p->off_w13 = take((size_t)E * packed_b_bytes(F, H, true));
     p->off_w2 = take((size_t)E * packed_b_bytes(H, F, false));
   } else {
@@ -382,7 +506,7 @@ int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, SkipPlan* p
 
 // Tile order tables of the two grouped projections (bf16 path), from the tile map scan_kernel has just written.
 static void launch_order_tables(const SkipPlan& p, char* ws, hipStream_t s) {
-  if (!p.packed) return;
+  if (!p.packed || p.few) return;
   const int32_t* expert_first = (const int32_t*)(ws + p.off_seg_end) + p.E;
   const int n_up = (int)ceil_div(p.F, GEMM_BN_SWIGLU), n_down = (int)ceil_div(p.H, GEMM_BN_STORE);
   hipLaunchKernelGGL(order_kernel, dim3((unsigned)ceil_div(p.max_tiles * n_up, 256)), dim3(256), 0, s, expert_first, p.E,
@@ -401,11 +525,21 @@ int launch_skip_routing(const SkipPlan& p, const float* logits, uint32_t kept_ma
   const int64_t n_blocks = ceil_div(T, RB);
   const float theta = beta > 0.0f ? (float)std::log((double)beta) : -INFINITY;
   Timed t("skip_route_dispatch", s);
+  if (T <= DISPATCH_ONE_MAX) {
+    hipLaunchKernelGGL((dispatch_one_kernel<2, true>), dim3(1), dim3((unsigned)ceil_div(T, 64) * 64), 0, s, logits, (int)T,
+                       p.E, kept_mask, theta, 0.0, skip_mask, (int32_t*)nullptr, top2, (int32_t*)(ws + p.off_slot_token),
+                       (float*)(ws + p.off_slot_scale), (int32_t*)(ws + p.off_slot_dest), pos,
+                       (int32_t*)(ws + p.off_seg_end), (int32_t*)(ws + p.off_tile_expert),
+                       (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows);
+    launch_order_tables(p, ws, s);
+    MOEP_HIP(hipGetLastError());
+    return MOEP_OK;
+  }
   hipLaunchKernelGGL(route_kernel, dim3((unsigned)n_blocks), dim3(RB), 0, s, logits, T, p.E, kept_mask, theta,
                      skip_mask, top2, tw, counts);
   hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(256), 0, s, counts, n_blocks, p.E,
                      (int32_t*)(ws + p.off_seg_end), (int32_t*)(ws + p.off_tile_expert),
-                     (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles);
+                     (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows);
   launch_order_tables(p, ws, s);
   hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)n_blocks), dim3(RB), 0, s, top2, tw, skip_mask,
                      counts, T, p.E, (int32_t*)(ws + p.off_slot_token),
@@ -446,6 +580,26 @@ int launch_skip_topk_routing(const SkipPlan& p, const float* logits, uint32_t ke
   float* slot_scale = (float*)(ws + p.off_slot_scale);
   int32_t* slot_dest = (int32_t*)(ws + p.off_slot_dest);
   Timed t("skip_route_dispatch", s);
+  if (T <= DISPATCH_ONE_MAX) {
+#define MOEP_ONE_CASE(KK)                                                                                               \
+  case KK:                                                                                                              \
+    hipLaunchKernelGGL((dispatch_one_kernel<KK, false>), dim3(1), dim3((unsigned)ceil_div(T, 64) * 64), 0, s, logits,   \
+                       (int)T, p.E, kept_mask, 0.0f, (double)beta, (uint8_t*)nullptr, n_used, topk, slot_token,         \
+                       slot_scale, slot_dest, pos, (int32_t*)(ws + p.off_seg_end), (int32_t*)(ws + p.off_tile_expert),  \
+                       (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows);                                \
+    break;
+    switch (K) {
+      MOEP_ONE_CASE(1) MOEP_ONE_CASE(2) MOEP_ONE_CASE(3) MOEP_ONE_CASE(4)
+      MOEP_ONE_CASE(5) MOEP_ONE_CASE(6) MOEP_ONE_CASE(7) MOEP_ONE_CASE(8)
+      MOEP_ONE_CASE(9) MOEP_ONE_CASE(10) MOEP_ONE_CASE(11) MOEP_ONE_CASE(12)
+      MOEP_ONE_CASE(13) MOEP_ONE_CASE(14) MOEP_ONE_CASE(15) MOEP_ONE_CASE(16)
+      default: return fail(MOEP_EUNSUPPORTED, "top-k routing: k=%d (1..16)", K);
+    }
+#undef MOEP_ONE_CASE
+    launch_order_tables(p, ws, s);
+    MOEP_HIP(hipGetLastError());
+    return MOEP_OK;
+  }
 #define MOEP_ROUTE_CASE(KK)                                                                    \
   case KK:                                                                                    \
     hipLaunchKernelGGL(route_topk_kernel<KK>, dim3((unsigned)n_blocks), dim3(RB), 0, s, logits, T, p.E, \
@@ -461,7 +615,7 @@ int launch_skip_topk_routing(const SkipPlan& p, const float* logits, uint32_t ke
 #undef MOEP_ROUTE_CASE
   hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(256), 0, s, counts, n_blocks, p.E,
                      (int32_t*)(ws + p.off_seg_end), (int32_t*)(ws + p.off_tile_expert),
-                     (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles);
+                     (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows);
   launch_order_tables(p, ws, s);
 #define MOEP_SCATTER_CASE(KK)                                                                  \
   case KK:                                                                                    \

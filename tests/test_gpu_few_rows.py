@@ -1,0 +1,85 @@
+"""GPU parity of the few-rows expert GEMMs and the one-workgroup dispatch, through the C ABI: the sizes at which their
+tiles, splits and hand-overs end.  Tolerances are those of test_gpu_parity (each of h and the output is rounded to bf16
+once); where two paths sum the same products in the same order the results are the same bits."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2402_14800_amd as pkg
+from paper_2402_14800_amd import workloads as wl
+from tests.test_gpu_parity import check_outputs, small_layer, to_dev
+
+pytestmark = pytest.mark.gpu
+NAMES = ("x", "Wgate", "W1", "W3", "W2")
+
+
+def bits(t):
+    return t.view(torch.int16)
+
+
+@pytest.mark.parametrize("E,H,F,T,kept", [
+    (8, 128, 192, 1, 0xff),            # one token; columns end inside a packed tile
+    (8, 128, 192, 16, 0xff),
+    (8, 576, 1024, 17, 0xff),          # a second group of 16 rows, an odd number of slice pairs
+    (4, 4096, 64, 33, 0xf),            # eight wavefronts share a column group in one projection only
+    (8, 64, 2112, 63, 0xff),           # one slice pair: no split
+    (8, 256, 512, 32, 0b10000010),     # 32 rows for each of two experts
+    (8, 128, 256, 128, 0xff),          # the last batch of the few-rows path, and the first beyond it
+    (8, 128, 256, 129, 0xff),
+    (32, 64, 128, 511, 0xffffffff),    # around the largest batch of the one-workgroup dispatch
+    (32, 64, 128, 513, 0xffffffff),
+])
+def test_forward_with_few_rows_matches_oracle(E, H, F, T, kept):
+    _, layer = small_layer("bf16", E, 2, H, F, T, index=21)
+    if T == 128:                       # all tokens alike: two experts get 128 rows each, three tiles of 64 rows and less
+        layer["x"][:] = layer["x"][0] * (1 + torch.arange(T)[:, None] % 3).to(layer["x"].dtype)
+    d = to_dev(layer)
+    beta = 0.6
+    out, skip, lg, top2 = pkg.moe_forward_pruned_skip(*[d[n] for n in NAMES], kept, beta)
+    packed = pkg.moe_pack_weights(d["W1"], d["W3"], d["W2"])
+    out_p, skip_p, lg_p, top2_p = pkg.moe_forward_pruned_skip_packed(d["x"], d["Wgate"], packed, F, beta, kept_mask=kept)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(out), bits(out_p)) and torch.equal(skip, skip_p)
+    assert torch.equal(lg, lg_p) and torch.equal(top2, top2_p)
+    kept_set = [e for e in range(E) if kept >> e & 1]
+    ref, ref_skip, e0, e1 = oracle.forward_skip(*[wl.to_f64(layer[n]) for n in NAMES], float(np.float32(beta)),
+                                                logits=lg.cpu().numpy(), kept=kept_set)
+    assert np.array_equal(skip.cpu().numpy().astype(bool), ref_skip)
+    assert np.array_equal(top2.cpu().numpy(), np.stack([e0, e1], axis=1))
+    check_outputs(wl.to_f64(out), ref, "out")
+
+
+@pytest.mark.parametrize("E,H,F,T,k", [(16, 128, 192, 9, 4), (16, 192, 128, 512, 1), (16, 64, 128, 140, 16)])
+def test_topk_forward_with_few_rows_matches_oracle(E, H, F, T, k):
+    _, layer = small_layer("bf16", E, k, H, F, T, index=22)
+    d = to_dev(layer)
+    out, used, lg, experts = pkg.moe_forward_skip_topk(*[d[n] for n in NAMES], k, 0.1)
+    torch.cuda.synchronize()
+    ref, i_star, ids = oracle.forward_skip_topk(*[wl.to_f64(layer[n]) for n in NAMES], k, float(np.float32(0.1)),
+                                                logits=lg.cpu().numpy())
+    assert np.array_equal(used.cpu().numpy(), i_star) and np.array_equal(experts.cpu().numpy(), ids)
+    check_outputs(wl.to_f64(out), ref, "out")
+
+
+@pytest.mark.parametrize("E,H,F,T", [(8, 128, 192, 1), (3, 576, 320, 17), (8, 64, 64, 31), (20, 128, 64, 32), (5, 256, 512, 33)])
+def test_expert_outputs_of_few_rows_are_those_of_many(E, H, F, T):
+    """A token's expert outputs do not depend on the size of the batch, on who packed the weights, or on whether the
+    rank-limited pass computed them: the products are summed in the same order everywhere."""
+    _, layer = small_layer("bf16", E, 2, H, F, 300, index=23)
+    d = to_dev(layer)
+    many_lg, many = pkg.moe_expert_outputs(*[d[n] for n in NAMES])
+    x = d["x"][:T].contiguous()
+    lg, Y = pkg.moe_expert_outputs(x, *[d[n] for n in NAMES[1:]])
+    packed = pkg.moe_pack_weights(d["W1"], d["W3"], d["W2"])
+    lg_p, Y_p = pkg.moe_expert_outputs_packed(x, d["Wgate"], packed, F)
+    n = min(3, E)
+    lg_r, experts, slot, Yr = pkg.moe_expert_outputs_ranked(x, *[d[n_] for n_ in NAMES[1:]], n)
+    torch.cuda.synchronize()
+    assert torch.equal(lg, many_lg[:T]) and torch.equal(lg_p, lg) and torch.equal(lg_r, lg)
+    assert torch.equal(bits(Y), bits(many[:, :T].contiguous())) and torch.equal(bits(Y_p), bits(Y))
+    t = torch.arange(T, device=Y.device)
+    for j in range(n):
+        assert torch.equal(bits(Yr[slot[:, j].long()]), bits(Y[experts[:, j].long(), t]))
+    _, ref = oracle.expert_outputs(*[wl.to_f64(v) for v in (x, *[layer[n_] for n_ in NAMES[1:]])])
+    check_outputs(wl.to_f64(Y), ref, "Y")
