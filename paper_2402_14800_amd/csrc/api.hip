@@ -222,6 +222,15 @@ static int experts_per_launch(int64_t T, int E, int F) {
   return fit < 1 ? 1 : (fit > (size_t)E ? E : (int)fit);
 }
 
+// Whether the GEMMs read row-major expert weights where they lie or from a blocked copy made first.  Making the copy
+// costs a read and a write of all weights whatever the batch (1.1 ms at 2.8 GB); without it the GEMMs run a few percent
+// longer (64-byte instead of 1 KB pieces).  Both grow with the weights, so the line is a number of rows per expert
+// (routed calls: nominal, with no token skipped).  In place against packed first, us per call:
+// Mixtral shape, skipping forward, T = 777 (194 rows) 925 / 1903, 16384 (4096) 7137 / 7680, 32768 (8192) 13852 / 13930;
+// E 8, H 1024, F 3584: ranked, 3001 rows 694 / 737, 12288 rows 2136 / 2107; dense, 16384 rows 2477 / 2412;
+// E 16, H 2048, F 5632: dense, 1024 rows 1098 / 1465, 8192 rows 6883 / 6826.
+static constexpr int64_t IN_PLACE_MAX_ROWS = 6144;
+
 static size_t expert_outputs_workspace_bf16(int64_t T, int E, int H, int F, bool weights_prepacked) {
   size_t need = align256((size_t)experts_per_launch(T, E, F) * packed_a_bytes(T, F)) + align256(packed_a_bytes(T, H));
   if (!weights_prepacked)
@@ -287,8 +296,8 @@ static int expert_outputs(const void* x, const void* Wgate, const void* W1, cons
     return MOEP_OK;
   }
   if (dt == MOEP_BF16) {
-    // Operands are packed once per call into the blocked layout of the packed GEMM (x; every expert's
-    // weights, unless the caller has done that already); h stays in that layout between the two projections
+    // Operands are packed once per call into the blocked layout of the packed GEMM (x; many rows: every expert's
+    // weights, unless the caller has done that already; fewer rows read them in place); h stays in that layout between the two projections
     // and never exists row-major.  Each projection is ONE launch over a batch of experts.
     const int eb = experts_per_launch(T, E, F);
     const size_t h_bytes = packed_a_bytes(T, F);
@@ -303,7 +312,13 @@ static int expert_outputs(const void* x, const void* Wgate, const void* W1, cons
       st_x = launch_pack_a_bf16(x, H, T, H, xp, s, "pack_x");
     }
     if (st_x) return st_x;
-    if (packed) {                     // all W1/W3 pairs, then all W2
+    const bool in_place = !packed && T <= IN_PLACE_MAX_ROWS;
+    const size_t gu_bytes = in_place ? (size_t)F * H * es : packed_b_bytes(F, H, true);
+    const size_t dn_bytes = in_place ? (size_t)H * F * es : packed_b_bytes(H, F, false);
+    if (in_place) {
+      wgu = (const char*)W1;
+      wdn = (const char*)W2;
+    } else if (packed) {              // all W1/W3 pairs, then all W2
       wgu = (const char*)packed;
       wdn = wgu + (size_t)E * packed_b_bytes(F, H, true);
     } else {
@@ -313,12 +328,13 @@ static int expert_outputs(const void* x, const void* Wgate, const void* W1, cons
     for (int e0 = 0; e0 < E; e0 += eb) {
       const int ne = E - e0 < eb ? E - e0 : eb;
       PackedGemmArgs up;                          // h[e] = silu(x W1[e]^T) * (x W3[e]^T)
-      up.A = xp; up.B = wgu + (size_t)e0 * packed_b_bytes(F, H, true); up.C = hp;
+      up.A = xp; up.B = wgu + (size_t)e0 * gu_bytes; up.C = hp;
+      up.b_row_major = in_place; up.B1 = in_place ? (const char*)W3 + (size_t)e0 * gu_bytes : nullptr;
       up.M = T; up.N = F; up.K = H; up.epilogue = EPI_SWIGLU;
       up.experts = ne; up.a_expert_bytes = 0; up.c_expert_bytes = (int64_t)h_bytes;
       if (int st = launch_gemm_bf16_packed(up, s, "gemm_gate_up_swiglu")) return st;
       PackedGemmArgs down;                        // Y[e] = h[e] W2[e]^T
-      down.A = hp; down.B = wdn + (size_t)e0 * packed_b_bytes(H, F, false);
+      down.A = hp; down.B = wdn + (size_t)e0 * dn_bytes; down.b_row_major = in_place;
       down.C = (char*)Y + (size_t)e0 * T * H * es; down.ldc = H;
       down.M = T; down.N = H; down.K = F; down.epilogue = EPI_STORE;
       down.experts = ne; down.a_expert_bytes = (int64_t)h_bytes; down.c_expert_bytes = (int64_t)((size_t)T * H * es);
@@ -490,7 +506,7 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
   }
   if (dt == MOEP_BF16) {
     // Packed-operand path: the routed rows of x are gathered into one 256-row block per tile, every
-    // expert's weights are re-laid out, and h stays in the packed layout between the two projections.
+    // expert's weights are re-laid out (many rows) or read in place, and h stays in the packed layout between the two projections.
     const int32_t* slot_token = (const int32_t*)(w + p.off_slot_token);
     const int32_t* tile_expert = (const int32_t*)(w + p.off_tile_expert);
     const int32_t* tile_row0 = (const int32_t*)(w + p.off_tile_row0);
@@ -500,7 +516,11 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
                                              p.max_tiles, H, w + p.off_xp, s, "pack_x_routed")) return st;
     const char* w13 = w + p.off_w13;
     const char* w2 = w + p.off_w2;
-    if (packed) {                     // packed once by moe_pack_weights: all W1/W3 pairs, then all W2
+    const bool in_place = !packed && p.max_slots <= IN_PLACE_MAX_ROWS * p.E;
+    if (in_place) {
+      w13 = (const char*)W1;
+      w2 = (const char*)W2;
+    } else if (packed) {              // packed once by moe_pack_weights: all W1/W3 pairs, then all W2
       w13 = (const char*)packed;
       w2 = w13 + (size_t)p.E * packed_b_bytes(F, H, true);
     } else {
@@ -509,6 +529,7 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
     }
     PackedGemmArgs up;
     up.A = w + p.off_xp; up.B = w13; up.C = w + p.off_h;
+    up.b_row_major = in_place; up.B1 = in_place ? W3 : nullptr;
     up.M = p.max_slots; up.N = F; up.K = H; up.epilogue = EPI_SWIGLU;
     up.tile_expert = tile_expert; up.tile_row0 = tile_row0; up.seg_end = seg_end; up.tiles_in_use = tiles_in_use;
     up.max_m_tiles = p.max_tiles;
@@ -516,7 +537,7 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
     if (int st = launch_gemm_bf16_packed(up, s, "gemm_gate_up_swiglu_routed")) return st;
     PackedGemmArgs down = up;
     down.tile_order = (const uint32_t*)(w + p.off_order_down);
-    down.A = w + p.off_h; down.B = w2;
+    down.A = w + p.off_h; down.B = w2; down.B1 = nullptr;
     down.C = plain_out ? plain_out : w + p.off_slot_out; down.ldc = H;
     down.N = H; down.K = F;
     down.epilogue = plain_out ? EPI_STORE : EPI_ROWSCALE_F32;

@@ -78,6 +78,8 @@ int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name);
 struct PackedGemmArgs {
   const void* A = nullptr;       // packed A operand, indexed by M tile
   const void* B = nullptr;       // packed_b_bytes(N, K, epilogue == EPI_SWIGLU) per expert
+  bool b_row_major = false;      // B (and B1, the linear branch of EPI_SWIGLU) as the caller stores them: [N, K] per expert
+  const void* B1 = nullptr;
   void* C = nullptr;             // EPI_STORE / EPI_ROWSCALE_F32: row-major [rows, ldc]; EPI_SWIGLU: packed A operand, K = N
   int64_t ldc = 0;
   int64_t M = 0;                 // rows (dense mode)

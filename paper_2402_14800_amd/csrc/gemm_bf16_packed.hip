@@ -15,6 +15,10 @@
 // reordered so that the transposed accumulator tiles give each lane 8 consecutive output columns, and
 // for the gate/up projection a block holds 128 rows of W1 followed by the same 128 rows of W3.
 //
+// BROW: the weight operand is read as the caller stores it, row-major, and the same LDS image is made by the loads' lane
+// addresses (each brings 16 rows x 64 bytes; both permutations above are in the address).  The same products in the same
+// order, hence the same bits, 2 to 8 % slower than on packed weights, without the packing pass.
+//
 // Kernel.  One workgroup of 256 threads (4 wavefronts, 2 along M x 2 along N, one per SIMD) owns a
 // 256 x 256 tile of the accumulator (256 x 128 outputs in SwiGLU mode); a wavefront owns 128 x 128 =
 // 8 x 8 MFMA tiles, whose 256 accumulator registers sit in the AGPR half of the wavefront's 512 registers.
@@ -139,7 +143,8 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
 // ---- GEMM --------------------------------------------------------------------------------------
 struct KArgs {
   const char* A;          // packed, tile-major
-  const char* B;          // packed weight blocks
+  const char* B;          // packed weight blocks; BROW: the weights as the caller stores them, row-major [N, K]
+  const char* B1;         // BROW, gate/up: the linear branch
   void* C;                // EPI_STORE: row-major bf16 [M, ldc]; EPI_SWIGLU: packed A operand with K = N
   int64_t M, ldc;
   int N;                  // output columns
@@ -167,7 +172,7 @@ struct KArgs {
 // that ever not so, the line-ups would group the wrong workgroups and cost time, never a result.
 __device__ unsigned long long g_round_count[8 * 8];
 
-template <int EPI, bool GROUPED>
+template <int EPI, bool GROUPED, bool BROW>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_packed_kernel(KArgs p) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -186,12 +191,21 @@ void gemm_packed_kernel(KArgs p) {
   // Logical tile id -> (tm, tn).  Ids i, i + 8, ... belong to XCD i % 8 (the grid is a multiple of 8 or
   // a single round); every XCD gets a contiguous run of tiles, GROUP_M M-tiles deep.
   constexpr uint32_t GROUP_M = EPI == EPI_SWIGLU ? GEMM_GROUP_M_SWIGLU : GEMM_GROUP_M_STORE;
-  // weight blocks of the tile's expert
+  // weight blocks of the tile's expert (BROW: the first of this wavefront's 64 weight rows; rows come in whole groups of
+  // 64, a group beyond the last one re-reads that, its products are never stored)
+  const int64_t pitch = (int64_t)nsl * 64;
   auto b_tile = [&](int tm_, int tn_, int e_) {
-    const char* b = p.B + ((size_t)tn_ * nsl) * SLICE + wave_u * 4096;
+    const char* b;
+    if (BROW) {
+      const int row = EPI == EPI_SWIGLU ? tn_ * 128 + (wave_u & 1) * 64 : tn_ * 256 + wave_u * 64;
+      b = (EPI == EPI_SWIGLU && wave_u >= 2 ? p.B1 : p.B) + (int64_t)min(row, p.N - 64) * pitch;
+    } else {
+      b = p.B + ((size_t)tn_ * nsl) * SLICE + wave_u * 4096;
+    }
     b += (int64_t)(GROUPED ? p.tile_expert[tm_] : e_) * p.b_expert_bytes;
     return b;
   };
+  constexpr int B_STEP = BROW ? 64 : SLICE;       // bytes from a slice of the weights to the next
   // Dense: e = the GEMM of a batched launch the tile belongs to; each of them is dealt to the XCDs exactly as a
   // launch of its own would be when its tile count is a multiple of 8, else the batch is one flat run of tiles.
   auto decode = [&](uint32_t L, int& tm, int& tn, int& e) {
@@ -247,8 +261,13 @@ void gemm_packed_kernel(KArgs p) {
   // step that issues the loads has no address arithmetic to do first)
   const char* ga = a_ld + lane_off;
   const char* gb = b_ld + lane_off;
+  // BROW: 1 KB of a block holds 16 rows of 64 bytes; lane l brings row 4 (l / 16) + (l / 4) % 4 of them, i.e. weight row
+  // 8 (l / 16) + (l / 4) % 4 (+ 4 for odd KBs, + 32 from one pair of KBs to the next), chunk (l % 4) ^ (l / 16).
+  // (the instruction's offset moves both addresses: what it adds to the global one is taken off the uniform base)
+  const uint32_t brow_off = (uint32_t)((8 * (lane >> 4) + ((lane >> 2) & 3)) * (int)pitch + (((lane & 3) ^ (lane >> 4)) << 4));
 #define MOEP_LOAD1(q)                                                                           \
-  __builtin_amdgcn_global_load_lds((gptr_t)((q) < 4 ? ga : gb),                                   \
+  __builtin_amdgcn_global_load_lds((gptr_t)((q) < 4 ? ga : !BROW ? gb :                           \
+      b_ld + ((((q) & 2) ? 32 : 0) * pitch + (((q) & 1) ? 4 : 0) * pitch - ((q) & 3) * 1024) + brow_off), \
       (__attribute__((address_space(3))) void*)(lds3 + st_ld + ((q) < 4 ? 0 : SLICE) + wave_u * 4096), 16, ((q) & 3) * 1024, 0);
   // After a slice has been issued: next slice, next stage (branch-free, so that it can be scheduled into
   // the shadow of the MFMAs).  Past the end of the workgroup's stream the loader stays on its last slice:
@@ -256,8 +275,7 @@ void gemm_packed_kernel(KArgs p) {
   // the wait counts below hold to the end.
 #define MOEP_ADVANCE_LOADER()                                                                   \
   {                                                                                             \
-    const int adv_ = ld_ok ? SLICE : 0;                                                         \
-    a_ld += adv_; b_ld += adv_;                                                                 \
+    a_ld += ld_ok ? SLICE : 0; b_ld += ld_ok ? B_STEP : 0;                                      \
     s_ld += ld_ok ? 1 : 0;                                                                      \
     st_ld = st_ld + STAGE == LDS_BYTES ? 0 : st_ld + STAGE;                                     \
     ga = a_ld + lane_off; gb = b_ld + lane_off;                                                 \
@@ -320,7 +338,7 @@ void gemm_packed_kernel(KArgs p) {
       b_ld = b_tile(tm_ld, tn_ld, e_ld);                                                        \
     } else {                                                                                    \
       ld_ok = false;                                                                            \
-      a_ld -= SLICE; b_ld -= SLICE;                                                             \
+      a_ld -= SLICE; b_ld -= B_STEP;                                                            \
     }                                                                                           \
     ga = a_ld + lane_off; gb = b_ld + lane_off;                                                 \
   }
@@ -531,12 +549,12 @@ void gemm_packed_kernel(KArgs p) {
 constexpr int kMaxDevices = 64;
 struct DeviceState {
   int compute_units = 0;
-  bool attr_set[3][2] = {};
+  bool attr_set[3][2][2] = {};
 };
 std::mutex g_dev_mu;
 DeviceState g_dev[kMaxDevices];
 
-template <int EPI, bool GROUPED>
+template <int EPI, bool GROUPED, bool BROW>
 int launch(const KArgs& k, hipStream_t s) {
   int dev = 0, cus = 0;
   MOEP_HIP(hipGetDevice(&dev));
@@ -549,10 +567,10 @@ int launch(const KArgs& k, hipStream_t s) {
       MOEP_HIP(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
       d.compute_units = v > 0 ? v : 256;
     }
-    if (!d.attr_set[EPI][GROUPED]) {   // raising the dynamic LDS limit is per function and device, once
-      MOEP_HIP(hipFuncSetAttribute((const void*)gemm_packed_kernel<EPI, GROUPED>,
+    if (!d.attr_set[EPI][GROUPED][BROW]) {   // raising the dynamic LDS limit is per function and device, once
+      MOEP_HIP(hipFuncSetAttribute((const void*)gemm_packed_kernel<EPI, GROUPED, BROW>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES));
-      d.attr_set[EPI][GROUPED] = true;
+      d.attr_set[EPI][GROUPED][BROW] = true;
     }
     cus = d.compute_units;
   }
@@ -560,7 +578,7 @@ int launch(const KArgs& k, hipStream_t s) {
   int grid = cus & ~7;                        // one persistent workgroup per compute unit, a multiple of 8
   if (grid < 8) grid = 8;
   if (nblk < grid) grid = (int)nblk;          // a single round: any size
-  hipLaunchKernelGGL((gemm_packed_kernel<EPI, GROUPED>), dim3(grid), dim3(THREADS), LDS_BYTES, s, k);
+  hipLaunchKernelGGL((gemm_packed_kernel<EPI, GROUPED, BROW>), dim3(grid), dim3(THREADS), LDS_BYTES, s, k);
   MOEP_HIP(hipGetLastError());
   return MOEP_OK;
 }
@@ -631,7 +649,14 @@ int launch_gemm_bf16_packed(const PackedGemmArgs& g, hipStream_t s, const char* 
   k.A = (const char*)g.A; k.B = (const char*)g.B; k.C = g.C;
   k.M = g.M; k.ldc = g.ldc; k.N = g.N; k.nsl = g.K / 32;
   k.tile_expert = g.tile_expert; k.tile_row0 = g.tile_row0; k.seg_end = g.seg_end; k.tiles_in_use = g.tiles_in_use;
-  k.b_expert_bytes = (int64_t)packed_b_bytes(g.N, g.K, g.epilogue == EPI_SWIGLU);
+  if (g.b_row_major) {
+    if (g.N % 64 || ((uintptr_t)g.B1 & 15) || (g.epilogue == EPI_SWIGLU && !g.B1))
+      return fail(MOEP_EUNSUPPORTED, "%s: row-major weights need N=%d to be a multiple of 64 and 16-byte alignment", name, g.N);
+    k.B1 = (const char*)g.B1;
+    k.b_expert_bytes = (int64_t)g.N * g.K * 2;
+  } else {
+    k.b_expert_bytes = (int64_t)packed_b_bytes(g.N, g.K, g.epilogue == EPI_SWIGLU);
+  }
   k.row_scale = g.row_scale;
   if (g.experts < 1 || (grouped && g.experts != 1)) return fail(MOEP_EINVAL, "%s: bad batch count %d", name, g.experts);
   k.experts = g.experts; k.a_expert_bytes = g.a_expert_bytes; k.c_expert_bytes = g.c_expert_bytes;
@@ -645,18 +670,21 @@ int launch_gemm_bf16_packed(const PackedGemmArgs& g, hipStream_t s, const char* 
   if (m_tiles * n_tiles * g.experts >= ((int64_t)1 << 31)) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
   k.m_tiles = (int)m_tiles; k.n_tiles = (int)n_tiles;
   Timed t(name, s);
+#define MOEP_GEMM_CASE(EPI, GROUPED) \
+  return g.b_row_major ? launch<EPI, GROUPED, true>(k, s) : launch<EPI, GROUPED, false>(k, s)
   if (grouped) {
     switch (g.epilogue) {
-      case EPI_STORE: return launch<EPI_STORE, true>(k, s);
-      case EPI_SWIGLU: return launch<EPI_SWIGLU, true>(k, s);
-      case EPI_ROWSCALE_F32: return launch<EPI_ROWSCALE_F32, true>(k, s);
+      case EPI_STORE: MOEP_GEMM_CASE(EPI_STORE, true);
+      case EPI_SWIGLU: MOEP_GEMM_CASE(EPI_SWIGLU, true);
+      case EPI_ROWSCALE_F32: MOEP_GEMM_CASE(EPI_ROWSCALE_F32, true);
     }
   } else {
     switch (g.epilogue) {
-      case EPI_STORE: return launch<EPI_STORE, false>(k, s);
-      case EPI_SWIGLU: return launch<EPI_SWIGLU, false>(k, s);
+      case EPI_STORE: MOEP_GEMM_CASE(EPI_STORE, false);
+      case EPI_SWIGLU: MOEP_GEMM_CASE(EPI_SWIGLU, false);
     }
   }
+#undef MOEP_GEMM_CASE
   return fail(MOEP_EINVAL, "%s: unsupported epilogue %d", name, g.epilogue);
 }
 

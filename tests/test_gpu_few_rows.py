@@ -83,3 +83,24 @@ def test_expert_outputs_of_few_rows_are_those_of_many(E, H, F, T):
         assert torch.equal(bits(Yr[slot[:, j].long()]), bits(Y[experts[:, j].long(), t]))
     _, ref = oracle.expert_outputs(*[wl.to_f64(v) for v in (x, *[layer[n_] for n_ in NAMES[1:]])])
     check_outputs(wl.to_f64(Y), ref, "Y")
+
+
+@pytest.mark.parametrize("E,H,F,T,n", [(2, 64, 64, 6144, 1), (2, 64, 64, 6145, 1), (3, 192, 448, 300, 2), (4, 320, 1088, 257, 4)])
+def test_weights_in_place_give_the_bits_of_packed_weights(E, H, F, T, n):
+    """Around the row count up to which the GEMMs read row-major weights where they lie, and at column counts that end
+    inside a tile (64, 192 and 320 of 256 columns, 448 and 1088 of 128)."""
+    _, layer = small_layer("bf16", E, 2, H, F, T, index=24)
+    d = to_dev(layer)
+    ws = [d[n_] for n_ in NAMES]
+    packed = pkg.moe_pack_weights(d["W1"], d["W3"], d["W2"])
+    lg, Y = pkg.moe_expert_outputs(*ws)
+    lg_p, Y_p = pkg.moe_expert_outputs_packed(d["x"], d["Wgate"], packed, F)
+    out, skip, _, _ = pkg.moe_forward_skip(*ws, 0.5)
+    out_p, skip_p, _, _ = pkg.moe_forward_pruned_skip_packed(d["x"], d["Wgate"], packed, F, 0.5)
+    _, experts, slot, Yr = pkg.moe_expert_outputs_ranked(*ws, n)
+    torch.cuda.synchronize()
+    assert torch.equal(lg, lg_p) and torch.equal(bits(Y), bits(Y_p))
+    assert torch.equal(bits(out), bits(out_p)) and torch.equal(skip, skip_p)
+    t = torch.arange(T, device=Y.device)
+    for j in range(n):
+        assert torch.equal(bits(Yr[slot[:, j].long()]), bits(Y[experts[:, j].long(), t]))
