@@ -343,21 +343,33 @@ static int expert_outputs(const void* x, const void* Wgate, const void* W1, cons
     return MOEP_OK;
   }
   if (int st = launch_router(x, Wgate, T, E, H, dt, logits, s)) return st;
-  for (int e = 0; e < E; ++e) {
-    GemmArgs up;                                  // h = silu(x W1[e]^T) * (x W3[e]^T)
+  // Several experts go into a launch (a small layer's expert has too few tiles for the chip): the h of a batch's first
+  // expert in the workspace, those of the others in the part of Y that belongs to experts still to come.
+  const int64_t h_elems = T * F, y_elems = T * H;
+  for (int e0 = 0, ne; e0 < E; e0 += ne) {
+    // the largest ne with (ne - 1) h within the outputs of the experts beyond the batch
+    ne = (int)((h_elems + (E - e0) * y_elems) / (h_elems + y_elems));
+    if (ne < 1) ne = 1;
+    float* const later = (float*)Y + (e0 + ne) * y_elems;
+    GemmArgs up;                                  // h[e] = silu(x W1[e]^T) * (x W3[e]^T)
     up.A = x; up.lda = H;
-    up.B0 = (const char*)W1 + (size_t)e * F * H * es;
-    up.B1 = (const char*)W3 + (size_t)e * F * H * es;
+    up.B0 = (const char*)W1 + (size_t)e0 * F * H * es;
+    up.B1 = (const char*)W3 + (size_t)e0 * F * H * es;
+    up.b_expert_stride = (int64_t)F * H;
     up.C = ws; up.ldc = F;
     up.M = T; up.N = F; up.K = H;
     up.epilogue = EPI_SWIGLU;
+    up.experts = ne; up.C_rest = later; up.c_expert_stride = h_elems;
     if (int st = launch_gemm_f32(up, s, "gemm_gate_up_swiglu")) return st;
-    GemmArgs down;                                // Y[e] = h W2[e]^T
+    GemmArgs down;                                // Y[e] = h[e] W2[e]^T
     down.A = ws; down.lda = F;
-    down.B0 = (const char*)W2 + (size_t)e * H * F * es;
-    down.C = (char*)Y + (size_t)e * T * H * es; down.ldc = H;
+    down.B0 = (const char*)W2 + (size_t)e0 * H * F * es;
+    down.b_expert_stride = (int64_t)H * F;
+    down.C = (float*)Y + e0 * y_elems; down.ldc = H;
     down.M = T; down.N = H; down.K = F;
     down.epilogue = EPI_STORE;
+    down.experts = ne; down.A_rest = later; down.a_expert_stride = h_elems;
+    down.C_rest = (float*)Y + (e0 + 1) * y_elems; down.c_expert_stride = y_elems;
     if (int st = launch_gemm_f32(down, s, "gemm_down")) return st;
   }
   return MOEP_OK;

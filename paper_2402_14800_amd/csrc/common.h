@@ -60,6 +60,12 @@ struct GemmArgs {
   const int32_t* tile_row0 = nullptr;
   const int32_t* seg_end = nullptr;     // [E] end row (exclusive) of each expert's segment
   int64_t b_expert_stride = 0;          // elements between consecutive experts' weights
+  // Dense batched mode: `experts` GEMMs of the same shape in one launch.  Expert 0 reads A and writes C; expert e > 0
+  // reads A_rest + (e - 1) a_expert_stride (A_rest NULL: A as well) and writes C_rest + (e - 1) c_expert_stride (elements).
+  int experts = 1;
+  const void* A_rest = nullptr;
+  void* C_rest = nullptr;
+  int64_t a_expert_stride = 0, c_expert_stride = 0;
   int64_t max_m_tiles = 0;              // grouped: number of entries in tile_expert/tile_row0
   const int32_t* tiles_in_use = nullptr; // grouped, optional: device count of leading entries that hold work
 };

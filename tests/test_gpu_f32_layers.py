@@ -1,0 +1,46 @@
+"""GPU parity of the fp32 expert GEMMs at the edges of their tiles: rows of 32 and 64, columns of 64 and 128, slabs of 32
+k-values, and batches of experts whose intermediate sits in the outputs of experts still to come.  Bound: a sum of K
+fp32 products carries at most K 2^-24 of the sum of their magnitudes; 1e-5 of the largest output covers K <= 576."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2402_14800_amd as pkg
+from paper_2402_14800_amd import workloads as wl
+from tests.test_gpu_parity import small_layer, to_dev
+
+pytestmark = pytest.mark.gpu
+NAMES = ("x", "Wgate", "W1", "W3", "W2")
+
+
+@pytest.mark.parametrize("E,H,F,T", [
+    (8, 36, 68, 1),         # one row; K = 36 and 68: a partly filled slab
+    (3, 64, 60, 33),        # F < H: two experts' h in the outputs of the third
+    (7, 128, 132, 65),      # F just above H, a second tile of one row
+    (5, 576, 64, 97),       # h much smaller than the outputs: four experts in a launch
+    (2, 4, 260, 130),       # the narrowest H, F = 65 H: a launch per expert
+    (1, 64, 128, 4500),     # enough tiles for 64-row tiles in one projection
+    (8, 192, 128, 1400),    # 64-row tiles in both
+])
+def test_fp32_expert_outputs_at_tile_edges(E, H, F, T):
+    _, layer = small_layer("f32", E, 2, H, F, T, index=25)
+    d = to_dev(layer)
+    ws = [d[n] for n in NAMES]
+    lg, Y = pkg.moe_expert_outputs(*ws)
+    n = min(2, E)
+    lg_r, experts, slot, Yr = pkg.moe_expert_outputs_ranked(*ws, n)
+    torch.cuda.synchronize()
+    args = [wl.to_f64(layer[n_]) for n_ in NAMES]
+    _, ref = oracle.expert_outputs(*args)
+    assert np.abs(wl.to_f64(Y) - ref).max() <= 1e-5 * np.abs(ref).max()
+    t = torch.arange(T, device=Y.device)
+    assert torch.equal(lg, lg_r)
+    for j in range(n):
+        assert torch.equal(Yr[slot[:, j].long()], Y[experts[:, j].long(), t])
+    if E >= 2:
+        out, skip, lg_f, _ = pkg.moe_forward_skip(*ws, 0.5)
+        torch.cuda.synchronize()
+        ref_out, ref_skip, _, _ = oracle.forward_skip(*args, 0.5, logits=lg_f.cpu().numpy())
+        assert np.array_equal(skip.cpu().numpy().astype(bool), ref_skip)
+        assert np.abs(wl.to_f64(out) - ref_out).max() <= 1e-5 * np.abs(ref_out).max()
