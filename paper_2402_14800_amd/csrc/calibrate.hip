@@ -5,12 +5,18 @@
 // exactly by a most-significant-digit radix select on the order-preserving integer image of the
 // floats, and beta = (exp(delta_lo) + exp(delta_hi)) / 2 is formed in fp64 at the very end.
 //
-//   keys     one thread per token: top-2 (ties -> lower index), delta, key; block 0 also clears
-//            the histograms (a kernel rather than a memset so that the call can be graph-captured)
-//   hist     4 passes of 8 bits: count the keys that match the digits chosen so far, separately
-//            for the lower and the upper median rank (integer atomics only: order-independent)
-//   choose   one block: find the digit whose bucket holds the wanted rank, narrow the rank
-//   finish   turn the two keys back into floats and write beta
+//   select_one  few tokens: everything in one workgroup, the keys in LDS.
+//   keys        more tokens: one thread per token: top-2 (ties -> lower index), delta, key; block 0 also clears
+//               the histograms (a kernel rather than a memset so that the call can be graph-captured)
+//   hist        3 passes of 11, 11 and 10 bits: every workgroup first finds, from the finished histogram of the pass
+//               before, the digit that holds each wanted rank (the same integers in all of them; block 0 notes them
+//               for the pass after), then counts the keys that match the digits chosen so far (integer atomics only:
+//               order-independent)
+//   finish      the last digit, the two keys turned back into floats, beta
+//
+// Nothing here is bound by bytes (a million tokens are 32 MB of logits): it is launches and the serial walk over a
+// histogram.  4 passes of 8 bits with a one-thread walk between them took 9 launches and 45 to 90 us at any size.
+// Measured (E 8), before and after: 2048 tokens 65 -> 12 us, 16384 56 -> 19 us, 262144 70 -> 30 us.
 #include <cmath>
 
 #include "common.h"
@@ -18,7 +24,11 @@
 namespace moep {
 namespace {
 
-constexpr int CB = 256;
+constexpr int CB = 256;            // threads of the multi-workgroup kernels
+// select_one: at most 8192 tokens (8 per thread, their keys 32 KB of LDS) and 16384 logits, which one compute unit reads
+// as fast as the other form launches its kernels (E 8: 2048 tokens 14 us against 18, 4096 tokens 21 against 18).
+constexpr int ONE_MAX = 8192, ONE_LOGITS = 16384;
+constexpr int BITS = 11, BINS = 1 << BITS, PASSES = 3;
 
 struct SelectState {          // per wanted rank q in {0, 1}
   uint32_t prefix[2];         // digits chosen so far, in place
@@ -34,98 +44,188 @@ __device__ __forceinline__ float key_to_float(uint32_t k) {
   return __builtin_bit_cast(float, u);
 }
 
-__global__ __launch_bounds__(CB) void keys_kernel(const float* __restrict__ logits, int64_t T, int E,
-                                                  uint32_t kept, uint32_t* __restrict__ keys,
-                                                  uint32_t* __restrict__ hist, SelectState* state) {
-  if (blockIdx.x == 0) {
-    for (int i = threadIdx.x; i < 4 * 2 * 256; i += CB) hist[i] = 0;
-    if (threadIdx.x == 0) {
-      state->prefix[0] = state->prefix[1] = 0;
-      state->rem[0] = (uint32_t)((T - 1) / 2);
-      state->rem[1] = (uint32_t)(T / 2);
-    }
-  }
-  const int64_t t = (int64_t)blockIdx.x * CB + threadIdx.x;
-  if (t >= T) return;
-  const float* l = logits + t * E;
-  int e0 = -1, e1 = -1;
-  float l0 = 0.f, l1 = 0.f;
-  for (int e = 0; e < E; ++e) {
-    if (!((kept >> e) & 1u)) continue;
-    const float v = l[e];
-    if (e0 < 0 || v > l0) { l1 = l0; e1 = e0; l0 = v; e0 = e; }
-    else if (e1 < 0 || v > l1) { l1 = v; e1 = e; }
-  }
-  keys[t] = float_to_key(l1 - l0);
+template <int EMAX>
+__device__ __forceinline__ uint32_t token_key(const float* logits, int64_t t, int E, bool vec, uint32_t kept) {
+  float v[EMAX];
+  load_logits<EMAX>(logits, t, E, vec, v);
+  const TopTwo t2 = top_two<EMAX>(v, E, kept);
+  return float_to_key(t2.l1 - t2.l0);
 }
 
-__global__ __launch_bounds__(CB) void hist_kernel(const uint32_t* __restrict__ keys, int64_t T, int pass,
-                                                  const SelectState* __restrict__ state,
-                                                  uint32_t* __restrict__ hist) {
-  __shared__ uint32_t h[2][256];
-  h[0][threadIdx.x] = 0;
-  h[1][threadIdx.x] = 0;
-  __syncthreads();
-  const int shift = 24 - 8 * pass;
-  const uint32_t high = pass == 0 ? 0u : (0xffffffffu << (shift + 8));   // digits already chosen
-  const uint32_t p0 = state->prefix[0], p1 = state->prefix[1];
-  for (int64_t i = (int64_t)blockIdx.x * CB + threadIdx.x; i < T; i += (int64_t)gridDim.x * CB) {
-    const uint32_t k = keys[i];
-    const uint32_t d = (k >> shift) & 255u;
-    if ((k & high) == p0) atomicAdd(&h[0][d], 1u);
-    if ((k & high) == p1) atomicAdd(&h[1][d], 1u);
+// Digit p covers bits [shift(p), shift(p) + width): 11, 11 and 10 bits from the top.
+__device__ __forceinline__ int digit_shift(int p) { return p == 0 ? 21 : p == 1 ? 10 : 0; }
+__device__ __forceinline__ uint32_t digit_bins(int p) { return p == 2 ? 1u << 10 : 1u << BITS; }
+__device__ __forceinline__ uint32_t chosen_bits(int p) { return p == 0 ? 0u : p == 1 ? 0xffe00000u : 0xfffffc00u; }
+
+// The bucket of a histogram of BINS counts that holds rank `rem`, and the rank inside it, found by the first BINS / 8
+// threads of the workgroup (a multiple of 64 of them); result[0], result[1] for all.  The last bucket takes a rank beyond
+// the total.  Ends with a barrier.
+__device__ void find_bucket(const uint32_t* h, uint32_t rem, uint32_t* scratch /* BINS / 512 */, uint32_t* result) {
+  constexpr int W = BINS / 8 / 64;                // wavefronts
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t c[8], sum = 0, upto = 0;
+  if (tid < BINS / 8) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { c[i] = h[tid * 8 + i]; sum += c[i]; }
+    upto = sum;                                   // inclusive sum over the wavefront
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t v = __shfl_up(upto, off, 64);
+      if (lane >= off) upto += v;
+    }
+    if (lane == 63) scratch[wave] = upto;
   }
   __syncthreads();
-  uint32_t* g = hist + (size_t)pass * 512;
-  if (h[0][threadIdx.x]) atomicAdd(&g[threadIdx.x], h[0][threadIdx.x]);
-  if (h[1][threadIdx.x]) atomicAdd(&g[256 + threadIdx.x], h[1][threadIdx.x]);
+  if (tid < BINS / 8) {
+    uint32_t before = upto - sum;
+    for (int w = 0; w < W; ++w)
+      if (w < wave) before += scratch[w];
+    const bool last = tid == BINS / 8 - 1;
+    if (rem >= before && (rem < before + sum || last)) {
+      int d = 0;
+      for (; d < 7; ++d) {
+        if (before + c[d] > rem) break;
+        before += c[d];
+      }
+      result[0] = (uint32_t)(tid * 8 + d);
+      result[1] = rem - before;
+    }
+  }
+  __syncthreads();
 }
 
-__global__ __launch_bounds__(64) void choose_kernel(const uint32_t* __restrict__ hist, int pass,
-                                                    SelectState* state, float* __restrict__ beta_out) {
-  const int q = threadIdx.x;
-  if (q < 2) {
-    const uint32_t* g = hist + (size_t)pass * 512 + q * 256;
-    uint32_t rem = state->rem[q], run = 0;
-    int d = 0;
-    for (; d < 255; ++d) {              // the wanted key is in the first bucket whose running count exceeds rem
-      const uint32_t c = g[d];
-      if (run + c > rem) break;
-      run += c;
-    }
-    state->prefix[q] |= (uint32_t)d << (24 - 8 * pass);
-    state->rem[q] = rem - run;
-  }
-  if (pass == 3) {
+__device__ __forceinline__ float beta_of(uint32_t key_lo, uint32_t key_hi) {
+  const double lo = exp((double)key_to_float(key_lo));
+  const double hi = exp((double)key_to_float(key_hi));
+  return (float)(0.5 * (lo + hi));
+}
+
+template <int EMAX>
+__global__ __launch_bounds__(1024) void select_one_kernel(const float* __restrict__ logits, int T, int E, bool vec, uint32_t kept,
+                                                          float* __restrict__ beta_out) {
+  __shared__ uint32_t keys[ONE_MAX];
+  __shared__ uint32_t h[2][BINS];
+  __shared__ uint32_t scratch[BINS / 512], found[2][2];
+  for (int i = threadIdx.x; i < T; i += 1024) keys[i] = token_key<EMAX>(logits, i, E, vec, kept);
+  uint32_t prefix[2] = {0u, 0u}, rem[2] = {(uint32_t)((T - 1) / 2), (uint32_t)(T / 2)};
+  for (int p = 0; p < PASSES; ++p) {
+    for (int i = threadIdx.x; i < 2 * BINS; i += 1024) (&h[0][0])[i] = 0;
     __syncthreads();
-    if (threadIdx.x == 0) {
-      const double lo = exp((double)key_to_float(state->prefix[0]));
-      const double hi = exp((double)key_to_float(state->prefix[1]));
-      *beta_out = (float)(0.5 * (lo + hi));
+    const bool same = prefix[0] == prefix[1];     // one histogram serves both ranks until they part
+    const uint32_t mask = chosen_bits(p);
+    const int shift = digit_shift(p);
+    for (int i = threadIdx.x; i < T; i += 1024) {
+      const uint32_t k = keys[i], d = (k >> shift) & (digit_bins(p) - 1);
+      if ((k & mask) == prefix[0]) atomicAdd(&h[0][d], 1u);
+      if (!same && (k & mask) == prefix[1]) atomicAdd(&h[1][d], 1u);
     }
+    __syncthreads();
+    for (int q = 0; q < 2; ++q) find_bucket(h[same ? 0 : q], rem[q], scratch, found[q]);
+    for (int q = 0; q < 2; ++q) {
+      prefix[q] |= found[q][0] << shift;
+      rem[q] = found[q][1];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *beta_out = beta_of(prefix[0], prefix[1]);
+}
+
+template <int EMAX>
+__global__ __launch_bounds__(CB) void keys_kernel(const float* __restrict__ logits, int64_t T, int E, bool vec,
+                                                  uint32_t kept, uint32_t* __restrict__ keys,
+                                                  uint32_t* __restrict__ hist) {
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < PASSES * 2 * BINS; i += CB) hist[i] = 0;
+  const int64_t t = (int64_t)blockIdx.x * CB + threadIdx.x;
+  if (t < T) keys[t] = token_key<EMAX>(logits, t, E, vec, kept);
+}
+
+// The state before pass p, from the one before pass p - 1 and that pass's histogram.
+__device__ void state_before(int p, int64_t T, const SelectState* __restrict__ states, const uint32_t* __restrict__ hist,
+                             uint32_t* scratch, uint32_t (*found)[2], SelectState* out) {
+  if (p == 0) {
+    out->prefix[0] = out->prefix[1] = 0;
+    out->rem[0] = (uint32_t)((T - 1) / 2);
+    out->rem[1] = (uint32_t)(T / 2);
+    return;
+  }
+  for (int q = 0; q < 2; ++q) find_bucket(hist + (size_t)((p - 1) * 2 + q) * BINS, states[p - 1].rem[q], scratch, found[q]);
+  for (int q = 0; q < 2; ++q) {
+    out->prefix[q] = states[p - 1].prefix[q] | (found[q][0] << digit_shift(p - 1));
+    out->rem[q] = found[q][1];
   }
 }
+
+__global__ __launch_bounds__(CB) void hist_kernel(const uint32_t* __restrict__ keys, int64_t T, int p,
+                                                  SelectState* __restrict__ states, uint32_t* __restrict__ hist) {
+  __shared__ uint32_t h[2][BINS];
+  __shared__ uint32_t scratch[BINS / 512], found[2][2];
+  SelectState st;
+  state_before(p, T, states, hist, scratch, found, &st);
+  if (blockIdx.x == 0 && threadIdx.x == 0) states[p] = st;
+  for (int i = threadIdx.x; i < 2 * BINS; i += CB) (&h[0][0])[i] = 0;
+  __syncthreads();
+  const bool same = st.prefix[0] == st.prefix[1];
+  const uint32_t mask = chosen_bits(p);
+  const int shift = digit_shift(p);
+  for (int64_t i = (int64_t)blockIdx.x * CB + threadIdx.x; i < T; i += (int64_t)gridDim.x * CB) {
+    const uint32_t k = keys[i], d = (k >> shift) & (digit_bins(p) - 1);
+    if ((k & mask) == st.prefix[0]) atomicAdd(&h[0][d], 1u);
+    if (!same && (k & mask) == st.prefix[1]) atomicAdd(&h[1][d], 1u);
+  }
+  __syncthreads();
+  uint32_t* g = hist + (size_t)p * 2 * BINS;
+  for (int i = threadIdx.x; i < BINS; i += CB) {
+    const uint32_t lo = h[0][i], hi = same ? lo : h[1][i];
+    if (lo) atomicAdd(&g[i], lo);
+    if (hi) atomicAdd(&g[BINS + i], hi);
+  }
+}
+
+__global__ __launch_bounds__(CB) void finish_kernel(int64_t T, const SelectState* __restrict__ states,
+                                                    const uint32_t* __restrict__ hist, float* __restrict__ beta_out) {
+  __shared__ uint32_t scratch[BINS / 512], found[2][2];
+  SelectState st;
+  state_before(PASSES, T, states, hist, scratch, found, &st);
+  if (threadIdx.x == 0) *beta_out = beta_of(st.prefix[0], st.prefix[1]);
+}
+
+static_assert(BINS / 8 <= CB, "find_bucket needs a thread per 8 buckets");
 
 }  // namespace
 
 size_t calibrate_workspace_bytes(int64_t T) {
-  return align256((size_t)T * 4) + align256(4 * 2 * 256 * 4) + align256(sizeof(SelectState));
+  return align256((size_t)T * 4) + align256(PASSES * 2 * BINS * 4) + align256(PASSES * sizeof(SelectState));
 }
 
 int launch_calibrate_beta(const float* logits, int64_t T, int E, uint32_t kept_mask, float* beta_out,
                           char* ws, hipStream_t s) {
+  Timed t("skip_calibrate_beta", s);
+  const bool vec = logits_vec(logits, E);
+  if (T <= ONE_MAX && T * E <= ONE_LOGITS) {
+#define MOEP_ONE(EMAX) \
+  hipLaunchKernelGGL(select_one_kernel<EMAX>, dim3(1), dim3(1024), 0, s, logits, (int)T, E, vec, kept_mask, beta_out)
+    if (E <= 8) MOEP_ONE(8);
+    else if (E <= 16) MOEP_ONE(16);
+    else MOEP_ONE(32);
+#undef MOEP_ONE
+    MOEP_HIP(hipGetLastError());
+    return MOEP_OK;
+  }
   uint32_t* keys = (uint32_t*)ws;
   uint32_t* hist = (uint32_t*)(ws + align256((size_t)T * 4));
-  SelectState* state = (SelectState*)((char*)hist + align256(4 * 2 * 256 * 4));
+  SelectState* states = (SelectState*)((char*)hist + align256(PASSES * 2 * BINS * 4));
   const int64_t n_blocks = ceil_div(T, CB);
-  const unsigned hist_blocks = (unsigned)(n_blocks < 1024 ? n_blocks : 1024);
-  Timed t("skip_calibrate_beta", s);
-  hipLaunchKernelGGL(keys_kernel, dim3((unsigned)n_blocks), dim3(CB), 0, s, logits, T, E, kept_mask, keys,
-                     hist, state);
-  for (int pass = 0; pass < 4; ++pass) {
-    hipLaunchKernelGGL(hist_kernel, dim3(hist_blocks), dim3(CB), 0, s, keys, T, pass, state, hist);
-    hipLaunchKernelGGL(choose_kernel, dim3(1), dim3(64), 0, s, hist, pass, state, beta_out);
-  }
+  const unsigned hist_blocks = (unsigned)(n_blocks < 512 ? n_blocks : 512);
+#define MOEP_KEYS(EMAX) \
+  hipLaunchKernelGGL(keys_kernel<EMAX>, dim3((unsigned)n_blocks), dim3(CB), 0, s, logits, T, E, vec, kept_mask, keys, hist)
+  if (E <= 8) MOEP_KEYS(8);
+  else if (E <= 16) MOEP_KEYS(16);
+  else MOEP_KEYS(32);
+#undef MOEP_KEYS
+  for (int p = 0; p < PASSES; ++p)
+    hipLaunchKernelGGL(hist_kernel, dim3(hist_blocks), dim3(CB), 0, s, keys, T, p, states, hist);
+  hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(CB), 0, s, T, states, hist, beta_out);
   MOEP_HIP(hipGetLastError());
   return MOEP_OK;
 }

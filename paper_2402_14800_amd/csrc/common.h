@@ -34,6 +34,45 @@ static inline size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline size_t dtype_size(moep_dtype dt) { return dt == MOEP_BF16 ? 2 : 4; }
 
+// ---- one token's logits -------------------------------------------------------
+// Row t of logits [T,E] in registers, EMAX >= E (entries beyond E are 0), all loads in flight together; 16 bytes each when
+// `vec` says that every row is 16-byte aligned.  A loop that loads and compares expert by expert waits for each load.
+template <int EMAX>
+__device__ __forceinline__ void load_logits(const float* __restrict__ logits, int64_t t, int E, bool vec, float (&v)[EMAX]) {
+  const float* l = logits + t * E;
+  if (vec) {
+#pragma unroll
+    for (int q = 0; q < EMAX / 4; ++q) {
+      float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (4 * q < E) f = *(const float4*)(l + 4 * q);
+      v[4 * q] = f.x; v[4 * q + 1] = f.y; v[4 * q + 2] = f.z; v[4 * q + 3] = f.w;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < EMAX; ++e) v[e] = e < E ? l[e] : 0.f;
+  }
+}
+static inline bool logits_vec(const float* logits, int E) { return E % 4 == 0 && ((uintptr_t)logits & 15) == 0; }
+
+// The two largest logits among the kept experts (at least two); strict comparisons: the lower index wins a tie.
+struct TopTwo { int e0, e1; float l0, l1; };
+template <int EMAX>
+__device__ __forceinline__ TopTwo top_two(const float (&v)[EMAX], int E, uint32_t kept) {
+  int e0 = -1, e1 = -1;
+  float l0 = 0.f, l1 = 0.f;
+#pragma unroll
+  for (int e = 0; e < EMAX; ++e) {
+    const bool there = e < E && ((kept >> e) & 1u);   // a removed expert and its routing weight are gone
+    const bool first = there && (e0 < 0 || v[e] > l0);
+    const bool second = there && !first && (e1 < 0 || v[e] > l1);
+    l1 = first ? l0 : second ? v[e] : l1;
+    e1 = first ? e0 : second ? e : e1;
+    l0 = first ? v[e] : l0;
+    e0 = first ? e : e0;
+  }
+  return {e0, e1, l0, l1};
+}
+
 // ---- fp32 GEMM: C = epilogue(A B^T), A [M,K] and B [N,K] both K-contiguous, row-major operands -----
 enum GemmEpilogue {
   EPI_STORE = 0,      // C[m,n] = acc                       (C in dt, N columns)

@@ -32,32 +32,29 @@ constexpr int DISPATCH_ONE_MAX = 512;
 
 struct Top2 { int e0, e1; float a0, a1; bool skip; };
 
-// The top-2 rule on one row of logits.
-__device__ __forceinline__ Top2 route_top2(const float* l, int E, uint32_t kept, float theta) {
-  int e0 = -1, e1 = -1;
-  float l0 = -INFINITY, l1 = -INFINITY;
-  for (int e = 0; e < E; ++e) {          // strict comparisons: the lower index wins a tie
-    if (!((kept >> e) & 1u)) continue;   // a removed expert and its routing weight are gone
-    const float v = l[e];
-    if (e0 < 0 || v > l0) { l1 = l0; e1 = e0; l0 = v; e0 = e; }
-    else if (e1 < 0 || v > l1) { l1 = v; e1 = e; }
-  }
-  const float delta = l1 - l0;
+// The top-2 rule on row t of the logits.
+template <int EMAX>
+__device__ __forceinline__ Top2 route_top2(const float* logits, int64_t t, int E, bool vec, uint32_t kept, float theta) {
+  float v[EMAX];
+  load_logits<EMAX>(logits, t, E, vec, v);
+  const TopTwo t2 = top_two<EMAX>(v, E, kept);
+  const float delta = t2.l1 - t2.l0;
   const bool skip = delta < theta;
   const float rho = expf(delta);
-  return {e0, e1, skip ? 1.0f : 1.0f / (1.0f + rho), skip ? 0.0f : rho / (1.0f + rho), skip};
+  return {t2.e0, t2.e1, skip ? 1.0f : 1.0f / (1.0f + rho), skip ? 0.0f : rho / (1.0f + rho), skip};
 }
 
+template <int EMAX>
 __global__ __launch_bounds__(RB) void route_kernel(const float* __restrict__ logits, int64_t T,
-                                                   int E, uint32_t kept, float theta, uint8_t* __restrict__ skip_mask,
-                                                   int32_t* __restrict__ top2,
+                                                   int E, bool vec, uint32_t kept, float theta,
+                                                   uint8_t* __restrict__ skip_mask, int32_t* __restrict__ top2,
                                                    float* __restrict__ tw, int32_t* __restrict__ counts) {
   __shared__ int cnt[32];
   if (threadIdx.x < 32) cnt[threadIdx.x] = 0;
   __syncthreads();
   const int64_t t = (int64_t)blockIdx.x * RB + threadIdx.x;
   if (t < T) {
-    const Top2 r = route_top2(logits + t * E, E, kept, theta);
+    const Top2 r = route_top2<EMAX>(logits, t, E, vec, kept, theta);
     skip_mask[t] = r.skip ? 1 : 0;
     top2[2 * t] = r.e0;
     top2[2 * t + 1] = r.e1;
@@ -221,8 +218,11 @@ __global__ __launch_bounds__(256) void combine_kernel(const float4* __restrict__
 // ---- generalised top-k skipping -----------------------------------------------------------
 // The generalised rule on one row of logits: the top-K experts es, best first, the number istar that stays, and
 // the renormalised weights of those (0 for the others).
-template <int K>
-__device__ __forceinline__ int route_topk(const float* l, int E, uint32_t kept, double beta, int (&es)[K], float (&w)[K]) {
+template <int K, int EMAX>
+__device__ __forceinline__ int route_topk(const float* logits, int64_t t, int E, bool vec, uint32_t kept, double beta,
+                                          int (&es)[K], float (&w)[K]) {
+  float l[EMAX];
+  load_logits<EMAX>(logits, t, E, vec, l);
   uint32_t avail = kept;
   double ex[K];
   float l_first = 0.f;
@@ -230,11 +230,9 @@ __device__ __forceinline__ int route_topk(const float* l, int E, uint32_t kept, 
   for (int m = 0; m < K; ++m) {            // m-th largest kept logit; strict >: lower index wins a tie
     int best = -1;
     float bv = 0.f;
-    for (int e = 0; e < E; ++e) {
-      if (!((avail >> e) & 1u)) continue;
-      const float v = l[e];
-      if (best < 0 || v > bv) { best = e; bv = v; }
-    }
+#pragma unroll
+    for (int e = 0; e < EMAX; ++e)
+      if (((avail >> e) & 1u) && (best < 0 || l[e] > bv)) { best = e; bv = l[e]; }
     avail &= ~(1u << best);
     es[m] = best;
     if (m == 0) l_first = bv;
@@ -259,9 +257,9 @@ __device__ __forceinline__ int route_topk(const float* l, int E, uint32_t kept, 
   return istar;
 }
 
-template <int K>
+template <int K, int EMAX>
 __global__ __launch_bounds__(RB) void route_topk_kernel(const float* __restrict__ logits, int64_t T,
-                                                        int E, uint32_t kept, double beta,
+                                                        int E, bool vec, uint32_t kept, double beta,
                                                         int32_t* __restrict__ n_used,
                                                         int32_t* __restrict__ topk,
                                                         float* __restrict__ tw,
@@ -273,7 +271,7 @@ __global__ __launch_bounds__(RB) void route_topk_kernel(const float* __restrict_
   if (t < T) {
     int es[K];
     float w[K];
-    const int istar = route_topk<K>(logits + t * E, E, kept, beta, es, w);
+    const int istar = route_topk<K, EMAX>(logits, t, E, vec, kept, beta, es, w);
     n_used[t] = istar;
 #pragma unroll
     for (int m = 0; m < K; ++m) {
@@ -362,9 +360,9 @@ __global__ __launch_bounds__(256) void combine_topk_kernel(const float4* __restr
 // route, scan and scatter for a batch that fits one workgroup (a thread per token): three launches of 4 to 5 us each,
 // all of it latency, become one.  Same outputs as the three, entry for entry.  TOP2: the top-2 rule with its skip
 // mask; else the generalised rule with its counts.  tw is not written: the weights go straight to the slots.
-template <int K, bool TOP2>
+template <int K, bool TOP2, int EMAX>
 __global__ __launch_bounds__(DISPATCH_ONE_MAX) void dispatch_one_kernel(
-    const float* __restrict__ logits, int T, int E, uint32_t kept, float theta, double beta, uint8_t* __restrict__ skip_mask,
+    const float* __restrict__ logits, int T, int E, bool vec, uint32_t kept, float theta, double beta, uint8_t* __restrict__ skip_mask,
     int32_t* __restrict__ n_used, int32_t* __restrict__ experts, int32_t* __restrict__ slot_token,
     float* __restrict__ slot_scale, int32_t* __restrict__ slot_dest, int32_t* __restrict__ pos, int32_t* __restrict__ seg_end,
     int32_t* __restrict__ tile_expert, int32_t* __restrict__ tile_row0, int max_tiles, int tile_rows) {
@@ -380,13 +378,13 @@ __global__ __launch_bounds__(DISPATCH_ONE_MAX) void dispatch_one_kernel(
   for (int m = 0; m < K; ++m) { es[m] = -1; rank[m] = 0; w[m] = 0.f; }
   if (live) {
     if constexpr (TOP2) {
-      const Top2 r = route_top2(logits + (int64_t)t * E, E, kept, theta);
+      const Top2 r = route_top2<EMAX>(logits, t, E, vec, kept, theta);
       es[0] = r.e0; w[0] = r.a0;
       es[1] = r.e1; w[1] = r.a1;
       used = r.skip ? 1 : 2;
       skip_mask[t] = r.skip ? 1 : 0;
     } else {
-      used = route_topk<K>(logits + (int64_t)t * E, E, kept, beta, es, w);
+      used = route_topk<K, EMAX>(logits, t, E, vec, kept, beta, es, w);
       n_used[t] = used;
     }
 #pragma unroll
@@ -525,18 +523,29 @@ int launch_skip_routing(const SkipPlan& p, const float* logits, uint32_t kept_ma
   const int64_t n_blocks = ceil_div(T, RB);
   const float theta = beta > 0.0f ? (float)std::log((double)beta) : -INFINITY;
   Timed t("skip_route_dispatch", s);
+  const bool vec = logits_vec(logits, p.E);
   if (T <= DISPATCH_ONE_MAX) {
-    hipLaunchKernelGGL((dispatch_one_kernel<2, true>), dim3(1), dim3((unsigned)ceil_div(T, 64) * 64), 0, s, logits, (int)T,
-                       p.E, kept_mask, theta, 0.0, skip_mask, (int32_t*)nullptr, top2, (int32_t*)(ws + p.off_slot_token),
-                       (float*)(ws + p.off_slot_scale), (int32_t*)(ws + p.off_slot_dest), pos,
-                       (int32_t*)(ws + p.off_seg_end), (int32_t*)(ws + p.off_tile_expert),
-                       (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows);
+#define MOEP_ONE(EMAX)                                                                                                   \
+  hipLaunchKernelGGL((dispatch_one_kernel<2, true, EMAX>), dim3(1), dim3((unsigned)ceil_div(T, 64) * 64), 0, s, logits,  \
+                     (int)T, p.E, vec, kept_mask, theta, 0.0, skip_mask, (int32_t*)nullptr, top2,                        \
+                     (int32_t*)(ws + p.off_slot_token), (float*)(ws + p.off_slot_scale),                                 \
+                     (int32_t*)(ws + p.off_slot_dest), pos, (int32_t*)(ws + p.off_seg_end),                              \
+                     (int32_t*)(ws + p.off_tile_expert), (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows)
+    if (p.E <= 8) MOEP_ONE(8);
+    else if (p.E <= 16) MOEP_ONE(16);
+    else MOEP_ONE(32);
+#undef MOEP_ONE
     launch_order_tables(p, ws, s);
     MOEP_HIP(hipGetLastError());
     return MOEP_OK;
   }
-  hipLaunchKernelGGL(route_kernel, dim3((unsigned)n_blocks), dim3(RB), 0, s, logits, T, p.E, kept_mask, theta,
-                     skip_mask, top2, tw, counts);
+#define MOEP_ROUTE(EMAX)                                                                                                \
+  hipLaunchKernelGGL(route_kernel<EMAX>, dim3((unsigned)n_blocks), dim3(RB), 0, s, logits, T, p.E, vec, kept_mask, theta, \
+                     skip_mask, top2, tw, counts)
+  if (p.E <= 8) MOEP_ROUTE(8);
+  else if (p.E <= 16) MOEP_ROUTE(16);
+  else MOEP_ROUTE(32);
+#undef MOEP_ROUTE
   hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(256), 0, s, counts, n_blocks, p.E,
                      (int32_t*)(ws + p.off_seg_end), (int32_t*)(ws + p.off_tile_expert),
                      (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows);
@@ -580,13 +589,17 @@ int launch_skip_topk_routing(const SkipPlan& p, const float* logits, uint32_t ke
   float* slot_scale = (float*)(ws + p.off_slot_scale);
   int32_t* slot_dest = (int32_t*)(ws + p.off_slot_dest);
   Timed t("skip_route_dispatch", s);
+  const bool vec = logits_vec(logits, p.E);
   if (T <= DISPATCH_ONE_MAX) {
-#define MOEP_ONE_CASE(KK)                                                                                               \
-  case KK:                                                                                                              \
-    hipLaunchKernelGGL((dispatch_one_kernel<KK, false>), dim3(1), dim3((unsigned)ceil_div(T, 64) * 64), 0, s, logits,   \
-                       (int)T, p.E, kept_mask, 0.0f, (double)beta, (uint8_t*)nullptr, n_used, topk, slot_token,         \
-                       slot_scale, slot_dest, pos, (int32_t*)(ws + p.off_seg_end), (int32_t*)(ws + p.off_tile_expert),  \
-                       (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows);                                \
+#define MOEP_ONE(KK, EMAX)                                                                                             \
+  hipLaunchKernelGGL((dispatch_one_kernel<KK, false, EMAX>), dim3(1), dim3((unsigned)ceil_div(T, 64) * 64), 0, s,      \
+                     logits, (int)T, p.E, vec, kept_mask, 0.0f, (double)beta, (uint8_t*)nullptr, n_used, topk,         \
+                     slot_token, slot_scale, slot_dest, pos, (int32_t*)(ws + p.off_seg_end),                           \
+                     (int32_t*)(ws + p.off_tile_expert), (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows)
+#define MOEP_ONE_CASE(KK)                                                                                              \
+  case KK:                                                                                                             \
+    if (p.E <= 16) MOEP_ONE(KK, 16);                                                                                   \
+    else MOEP_ONE(KK, 32);                                                                                             \
     break;
     switch (K) {
       MOEP_ONE_CASE(1) MOEP_ONE_CASE(2) MOEP_ONE_CASE(3) MOEP_ONE_CASE(4)
@@ -596,14 +609,18 @@ int launch_skip_topk_routing(const SkipPlan& p, const float* logits, uint32_t ke
       default: return fail(MOEP_EUNSUPPORTED, "top-k routing: k=%d (1..16)", K);
     }
 #undef MOEP_ONE_CASE
+#undef MOEP_ONE
     launch_order_tables(p, ws, s);
     MOEP_HIP(hipGetLastError());
     return MOEP_OK;
   }
-#define MOEP_ROUTE_CASE(KK)                                                                    \
-  case KK:                                                                                    \
-    hipLaunchKernelGGL(route_topk_kernel<KK>, dim3((unsigned)n_blocks), dim3(RB), 0, s, logits, T, p.E, \
-                       kept_mask, (double)beta, n_used, topk, tw, counts);                    \
+#define MOEP_ROUTE(KK, EMAX)                                                                                           \
+  hipLaunchKernelGGL((route_topk_kernel<KK, EMAX>), dim3((unsigned)n_blocks), dim3(RB), 0, s, logits, T, p.E, vec,       \
+                     kept_mask, (double)beta, n_used, topk, tw, counts)
+#define MOEP_ROUTE_CASE(KK)                                                                                            \
+  case KK:                                                                                                             \
+    if (p.E <= 16) MOEP_ROUTE(KK, 16);                                                                                 \
+    else MOEP_ROUTE(KK, 32);                                                                                           \
     break;
   switch (K) {
     MOEP_ROUTE_CASE(1) MOEP_ROUTE_CASE(2) MOEP_ROUTE_CASE(3) MOEP_ROUTE_CASE(4)
@@ -613,6 +630,7 @@ int launch_skip_topk_routing(const SkipPlan& p, const float* logits, uint32_t ke
     default: return fail(MOEP_EUNSUPPORTED, "top-k routing: k=%d (1..16)", K);
   }
 #undef MOEP_ROUTE_CASE
+#undef MOEP_ROUTE
   hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(256), 0, s, counts, n_blocks, p.E,
                      (int32_t*)(ws + p.off_seg_end), (int32_t*)(ws + p.off_tile_expert),
                      (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows);

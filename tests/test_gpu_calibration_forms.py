@@ -1,0 +1,47 @@
+"""The calibration of beta and the selection statistics at the sizes where they change form (one workgroup, several), at
+odd expert counts, and on logits whose rows are not 16-byte aligned.  Counts are exact; beta within 2e-6 (fp32 result of
+an fp64 exponential)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2402_14800_amd as pkg
+
+pytestmark = pytest.mark.gpu
+
+
+def logits_on_gpu(T, E, seed, offset=0, rounding=None):
+    lg = np.random.Generator(np.random.PCG64(seed)).standard_normal((T, E)).astype(np.float32)
+    if rounding:
+        lg = (np.round(lg * rounding) / rounding).astype(np.float32)      # many ties
+    buf = torch.empty(T * E + offset, dtype=torch.float32, device="cuda:0")
+    view = buf[offset:].view(T, E)
+    view.copy_(torch.from_numpy(lg))
+    return lg, view
+
+
+@pytest.mark.parametrize("T,E,offset,rounding", [
+    (1, 2, 0, None), (2048, 8, 0, None), (2049, 8, 0, None), (512, 32, 0, None), (513, 32, 1, None),
+    (8192, 2, 0, None), (8193, 2, 0, None), (3277, 5, 0, None), (3276, 5, 0, None), (4097, 16, 2, None),
+    (2000, 8, 0, 4.0), (30001, 8, 0, 4.0), (140001, 4, 0, 2.0),
+])
+def test_beta_at_every_form(T, E, offset, rounding):
+    lg, dev = logits_on_gpu(T, E, 31 + T, offset, rounding)
+    got = float(pkg.skip_calibrate_beta(dev).item())
+    ref = oracle.median_skip_ratio(lg)
+    assert abs(got - ref) <= 2e-6 * ref
+
+
+@pytest.mark.parametrize("T,E,k,offset,rounding", [
+    (1, 1, 1, 0, None), (1023, 8, 2, 0, 4.0), (1024, 8, 2, 0, None), (1025, 8, 2, 0, None), (1024, 32, 2, 0, None),
+    (1025, 31, 31, 0, 2.0), (777, 9, 4, 0, None), (5000, 16, 4, 3, None), (300, 17, 17, 0, None),
+])
+def test_selection_statistics_at_every_form(T, E, k, offset, rounding):
+    lg, dev = logits_on_gpu(T, E, 57 + T, offset, rounding)
+    r = max(1, E // 2)
+    count, co, mask = pkg.expert_selection_stats(dev, k, r)
+    ref_count, ref_co = oracle.expert_selection_stats(lg, k)
+    assert np.array_equal(count.cpu().numpy(), ref_count) and np.array_equal(co.cpu().numpy(), ref_co)
+    order = sorted(range(E), key=lambda e: (-int(ref_count[e]), e))
+    assert (int(mask.item()) & 0xFFFFFFFF) == sum(1 << e for e in order[:r])
