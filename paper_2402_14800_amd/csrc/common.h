@@ -236,9 +236,9 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
                      char* ws, hipStream_t s, const RankedSource* ranked = nullptr, bool reuse_gram = false);
 
 // fp64 sum of n_tiles partial sums per subset (partial[tile * n_sub + subset]) in a fixed order -> loss; sum of the
-// partial counts -> *unaffected (may be NULL); lowest-index argmin and its kept mask
+// partial counts -> *unaffected (may be NULL; `cleared`: already 0); lowest-index argmin and its kept mask
 int launch_reduce_argmin(const float* partial, const uint32_t* partial_cnt, int64_t n_tiles, int64_t n_sub, int E,
-                         int r, float* loss, int32_t* argmin, uint32_t* argmin_mask, int64_t* unaffected,
+                         int r, float* loss, int32_t* argmin, uint32_t* argmin_mask, int64_t* unaffected, bool cleared,
                          hipStream_t s);
 // masks[i] = kept mask of subset i
 int launch_subset_masks(int E, int r, int64_t n_sub, uint32_t* masks, hipStream_t s);

@@ -259,18 +259,24 @@ __host__ __device__ constexpr int rec_size(int cap) {
 // One thread per token.  STAGED: the thread builds its record in LDS (rec_floats + 1 words apart: no bank conflicts)
 // and the workgroup then writes its tokens' records, which are consecutive in memory, in 16-byte pieces; otherwise
 // (records too large for the LDS) every thread writes its own record word by word.
-template <int EMAX, bool STAGED>
+// CAP = the record's capacity at compile time: the order then sits in registers and every Gram entry is fetched before the
+// first is used (a run-time capacity made the gathers one long chain: 12 us per launch however few the tokens, now 8);
+// 0 = run time, for the capacities whose unrolled form would not fit the registers.
+// unaffected (may be NULL) is cleared for the counting that follows.
+template <int EMAX, int CAP, bool STAGED>
 __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ logits,
                                                    const float* __restrict__ G,
-                                                   float* __restrict__ rec, int64_t T, int E,
-                                                   int k, int n_act, int cap, int rec_floats) {
+                                                   float* __restrict__ rec, int64_t T, int E, bool vec,
+                                                   int k, int n_act, int cap_rt, int rec_floats,
+                                                   unsigned long long* __restrict__ unaffected) {
   extern __shared__ float stage[];
+  const int cap = CAP ? CAP : cap_rt;
   const int64_t t0 = (int64_t)blockIdx.x * blockDim.x;
   const int64_t t = t0 + threadIdx.x;
+  if (unaffected && blockIdx.x == 0 && threadIdx.x == 0) *unaffected = 0ull;
   if (t < T) {
   float l[EMAX];
-#pragma unroll
-  for (int e = 0; e < EMAX; ++e) l[e] = e < E ? logits[t * E + e] : 0.f;
+  load_logits<EMAX>(logits, t, E, vec, l);
   // rank of expert e = number of experts that precede it: larger logit, or equal and lower index
   int rank[EMAX];
 #pragma unroll
@@ -282,8 +288,52 @@ __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ log
     rank[e] = e < E ? c : 255;
   }
   float* R = STAGED ? stage + threadIdx.x * (rec_floats + 1) : rec + t * rec_floats;
-  for (int i = 0; i < rec_floats; ++i) R[i] = 0.f;
   uint32_t* Rord = (uint32_t*)(R + rec_order_off(cap));
+  if constexpr (CAP > 0) {
+    int ord[CAP];
+    float lv[CAP], ex[CAP], g[rec_tri(CAP)];
+#pragma unroll
+    for (int j = 0; j < CAP; ++j) {
+      ord[j] = 0;
+      lv[j] = 0.f;
+#pragma unroll
+      for (int e = 0; e < EMAX; ++e)
+        if (j < n_act && rank[e] == j) { ord[j] = e; lv[j] = l[e]; }
+    }
+    const float* Gt = G + t * E * E;
+    int idx = 0;
+#pragma unroll
+    for (int i = 0; i < CAP; ++i)
+#pragma unroll
+      for (int j = i; j < CAP; ++j, ++idx) g[idx] = j < n_act ? Gt[ord[i] * E + ord[j]] : 0.f;
+    float den = 0.f;
+#pragma unroll
+    for (int j = 0; j < CAP; ++j) {
+      ex[j] = j < n_act ? expf(lv[j] - lv[0]) : 0.f;
+      if (j < k) den += ex[j];               // (k <= n_act: every rank below k can be selected, or r < k and E = n_act)
+    }
+#pragma unroll
+    for (int j = 0; j < CAP; ++j) {
+      R[j] = ex[j];
+      R[CAP + j] = lv[j];
+      R[2 * CAP + j] = j < k ? ex[j] / den : 0.f;
+    }
+    idx = 0;
+#pragma unroll
+    for (int i = 0; i < CAP; ++i)
+#pragma unroll
+      for (int j = i; j < CAP; ++j, ++idx) R[3 * CAP + idx] = i == j ? g[idx] : 2.0f * g[idx];
+#pragma unroll
+    for (int w = 0; w < (CAP + 3) / 4; ++w) {
+      uint32_t packed = 0;
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        if (4 * w + b < CAP) packed |= (uint32_t)ord[4 * w + b] << (8 * b);
+      Rord[w] = packed;
+    }
+    for (int i = rec_order_off(CAP) + (CAP + 3) / 4; i < rec_size(CAP); ++i) R[i] = 0.f;
+  } else {
+  for (int i = 0; i < rec_floats; ++i) R[i] = 0.f;
   int ord[EMAX];
   float l0 = 0.f;
   for (int j = 0; j < n_act; ++j) {
@@ -316,6 +366,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ log
     Rord[w] = packed;
   }
   }
+  }
   if (STAGED) {
     __syncthreads();
     const int64_t left = T - t0;
@@ -331,8 +382,12 @@ __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ log
 // ------------------------------------------------------------------ scoring
 // EXACT: every one of the CAP rank positions is in use (n_act == CAP), which removes the
 // per-position guards from the token loop.
+// A token costs a lane a wait for its record (scalar loads) and a short dependent chain, so a tile is dealt to SCORE_STRANDS
+// strands of wavefronts (threadIdx.y), whose sums are added in LDS in strand order (28 and 70 subsets, E 8: 2048
+// tokens 46 -> 18 us for both, 262144 tokens 232 -> 131 us).
+constexpr int SCORE_STRANDS = 8;
 template <int CAP, bool EXACT>
-__global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ rec, int64_t T,
+__global__ __launch_bounds__(1024) void score_kernel(const float* __restrict__ rec, int64_t T,
                                                     int tok_tile, int E, int r, int kk, int kfull,
                                                     int n_act_rt, uint32_t n_sub,
                                                     float* __restrict__ partial,
@@ -348,9 +403,11 @@ __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ re
   const int64_t t_begin = (int64_t)blockIdx.y * tok_tile;
   const int64_t t_end = t_begin + tok_tile < T ? t_begin + tok_tile : T;
 
+  const int strand = __builtin_amdgcn_readfirstlane((int)threadIdx.y), strands = blockDim.y;
+
   float total = 0.f;
   uint32_t same_cnt = 0;
-  for (int64_t t = t_begin; t < t_end; ++t) {
+  for (int64_t t = t_begin + strand; t < t_end; t += strands) {
     const float* R = rec + t * RS;                       // wave-uniform
     const uint32_t* Rord = (const uint32_t*)(R + OFF_O);
     // Everything the selection needs is fetched up front, unconditionally (wave-uniform scalar
@@ -409,7 +466,17 @@ __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ re
     same_cnt += (same && live) ? 1u : 0u;
     total += same ? 0.f : q;
   }
-  if (live) {
+  __shared__ float s_total[1024];
+  __shared__ uint32_t s_same[1024];
+  const int at = threadIdx.y * blockDim.x + threadIdx.x;
+  s_total[at] = total;
+  s_same[at] = same_cnt;
+  __syncthreads();
+  if (strand == 0 && live) {
+    for (int w = 1; w < strands; ++w) {
+      total += s_total[w * blockDim.x + threadIdx.x];
+      same_cnt += s_same[w * blockDim.x + threadIdx.x];
+    }
     partial[(int64_t)blockIdx.y * n_sub + sub] = total;
     partial_cnt[(int64_t)blockIdx.y * n_sub + sub] = same_cnt;
   }
@@ -655,6 +722,69 @@ __global__ __launch_bounds__(1024) void argmin_kernel(const float* __restrict__ 
   }
 }
 
+// reduce and argmin in one workgroup, for few partial sums: thread (strand, j) adds tiles strand, strand + strands, ... of
+// subsets j, j + S, ... in fp64 (S = the power of two from n_sub up, at most 1024), a tree over the strands, then the
+// workgroup's argmin.  Also writes the count of unaffected pairs, so that nothing has to be cleared first.
+__global__ __launch_bounds__(1024) void reduce_one_kernel(const float* __restrict__ partial,
+                                                          const uint32_t* __restrict__ partial_cnt, int n_tiles,
+                                                          uint32_t n_sub, int S, int E, int r, float* __restrict__ loss,
+                                                          unsigned long long* __restrict__ unaffected,
+                                                          int32_t* __restrict__ argmin, uint32_t* __restrict__ argmin_mask) {
+  __shared__ double ss[1024];
+  __shared__ unsigned long long sc[1024];
+  __shared__ float sv[1024];
+  __shared__ uint32_t si[1024];
+  const int j = threadIdx.x & (S - 1), strand = threadIdx.x / S, strands = 1024 / S;
+  unsigned long long c = 0;
+  float best = INFINITY;
+  uint32_t bi = 0xffffffffu;
+  for (uint32_t s0 = 0; s0 < n_sub; s0 += S) {
+    const uint32_t sub = s0 + j;
+    double s = 0.0;
+    if (sub < n_sub)
+#pragma unroll 4
+      for (int i = strand; i < n_tiles; i += strands) {
+        s += (double)partial[(int64_t)i * n_sub + sub];
+        c += partial_cnt[(int64_t)i * n_sub + sub];
+      }
+    ss[threadIdx.x] = s;
+    __syncthreads();
+    for (int off = strands >> 1; off >= 1; off >>= 1) {
+      if (strand < off) ss[threadIdx.x] += ss[threadIdx.x + off * S];
+      __syncthreads();
+    }
+    if (strand == 0 && sub < n_sub) {
+      const float v = (float)ss[threadIdx.x];
+      loss[sub] = v;
+      if (v < best || bi == 0xffffffffu) { best = v; bi = sub; }   // ascending: first minimum wins
+    }
+  }
+  sc[threadIdx.x] = c;
+  sv[threadIdx.x] = best;
+  si[threadIdx.x] = bi;
+  __syncthreads();
+  for (int off = 512; off >= 1; off >>= 1) {
+    if ((int)threadIdx.x < off) {
+      sc[threadIdx.x] += sc[threadIdx.x + off];
+      const float v = sv[threadIdx.x + off];
+      const uint32_t i = si[threadIdx.x + off];
+      const float mv = sv[threadIdx.x];
+      const uint32_t mi = si[threadIdx.x];
+      if (i != 0xffffffffu && (mi == 0xffffffffu || v < mv || (v == mv && i < mi))) {
+        sv[threadIdx.x] = v;
+        si[threadIdx.x] = i;
+      }
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    if (unaffected) *unaffected = sc[0];
+    const uint32_t i = si[0] == 0xffffffffu ? 0u : si[0];
+    *argmin = (int32_t)i;
+    *argmin_mask = unrank_device(E, r, i);
+  }
+}
+
 // Lanes per scoring workgroup: one lane per subset, whole wavefronts, at most four of them.
 int score_threads(int64_t n_sub) {
   return n_sub >= 256 ? 256 : (int)((n_sub + 63) / 64) * 64;
@@ -736,11 +866,15 @@ static void launch_score(const EnumPlan& p, const float* rec, float* partial, ui
                          hipStream_t s) {
   const int threads = score_threads(p.n_sub);
   dim3 grid((unsigned)ceil_div(p.n_sub, threads), (unsigned)p.n_tok_tiles);
+  // 256 subsets and more: strands only where there are too few workgroups without (1820 subsets of 16 ranks, 5000 tokens:
+  // 126 us without, 150 with; 2024 subsets of 23 ranks, 3000 tokens: 391 without, 329 with).
+  const int most = threads == 256 && (int64_t)grid.x * grid.y >= 1024 ? 1 : SCORE_STRANDS;
+  const int strands = 1024 / threads < most ? 1024 / threads : most;
   if (p.n_act == CAP)
-    hipLaunchKernelGGL((score_kernel<CAP, true>), grid, dim3(threads), 0, s, rec, p.T, p.tok_tile, p.E, p.r,
+    hipLaunchKernelGGL((score_kernel<CAP, true>), grid, dim3(threads, strands), 0, s, rec, p.T, p.tok_tile, p.E, p.r,
                        p.kk, p.k, p.n_act, (uint32_t)p.n_sub, partial, pcnt);
   else
-    hipLaunchKernelGGL((score_kernel<CAP, false>), grid, dim3(threads), 0, s, rec, p.T, p.tok_tile, p.E, p.r,
+    hipLaunchKernelGGL((score_kernel<CAP, false>), grid, dim3(threads, strands), 0, s, rec, p.T, p.tok_tile, p.E, p.r,
                        p.kk, p.k, p.n_act, (uint32_t)p.n_sub, partial, pcnt);
 }
 
@@ -805,18 +939,30 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
       const bool staged = lds <= 64 * 1024;
       if (!staged) tpb = 256;
       const dim3 grid((unsigned)ceil_div(p.T, tpb));
-#define MOEP_PREP_LAUNCH(EMAX)                                                                                      \
+      const bool vec = logits_vec(logits, p.E);
+      unsigned long long* const clear = (unsigned long long*)unaffected;
+#define MOEP_PREP_LAUNCH(EMAX, CAP)                                                                                 \
   do {                                                                                                              \
     if (staged)                                                                                                     \
-      hipLaunchKernelGGL((prep_kernel<EMAX, true>), grid, dim3(tpb), lds, s, logits, G, rec, p.T, p.E, p.k, p.n_act, \
-                         cap, p.rec_floats);                                                                        \
+      hipLaunchKernelGGL((prep_kernel<EMAX, CAP, true>), grid, dim3(tpb), lds, s, logits, G, rec, p.T, p.E, vec,    \
+                         p.k, p.n_act, cap, p.rec_floats, clear);                                                   \
     else                                                                                                            \
-      hipLaunchKernelGGL((prep_kernel<EMAX, false>), grid, dim3(tpb), 0, s, logits, G, rec, p.T, p.E, p.k, p.n_act,  \
-                         cap, p.rec_floats);                                                                        \
+      hipLaunchKernelGGL((prep_kernel<EMAX, CAP, false>), grid, dim3(tpb), 0, s, logits, G, rec, p.T, p.E, vec,     \
+                         p.k, p.n_act, cap, p.rec_floats, clear);                                                   \
   } while (0)
-      if (p.E <= 8) MOEP_PREP_LAUNCH(8);
-      else if (p.E <= 16) MOEP_PREP_LAUNCH(16);
-      else MOEP_PREP_LAUNCH(32);
+#define MOEP_PREP_CAPS(EMAX)                                                                                        \
+  switch (cap) {                                                                                                    \
+    case 2: MOEP_PREP_LAUNCH(EMAX, 2); break;                                                                       \
+    case 4: MOEP_PREP_LAUNCH(EMAX, 4); break;                                                                       \
+    case 6: MOEP_PREP_LAUNCH(EMAX, 6); break;                                                                       \
+    case 8: MOEP_PREP_LAUNCH(EMAX, 8); break;                                                                       \
+    case 12: MOEP_PREP_LAUNCH(EMAX, 12); break;                                                                     \
+    default: MOEP_PREP_LAUNCH(EMAX, 0); break;                                                                      \
+  }
+      if (p.E <= 8) { MOEP_PREP_CAPS(8) }
+      else if (p.E <= 16) { MOEP_PREP_CAPS(16) }
+      else { MOEP_PREP_CAPS(32) }
+#undef MOEP_PREP_CAPS
 #undef MOEP_PREP_LAUNCH
       MOEP_HIP(hipGetLastError());
     }
@@ -880,13 +1026,26 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
     }
   }
   return launch_reduce_argmin(partial, pcnt, p.T > 0 ? p.n_tok_tiles : 0, p.n_sub, p.E, p.r, loss, argmin, argmin_mask,
-                              unaffected, s);
+                              unaffected, p.T > 0, s);
 }
 
+// Partial sums that one workgroup reduces as fast as three launches follow each other (28 + 70 subsets, 2048 tokens: 15 us
+// for both against 26).
+constexpr int64_t REDUCE_ONE_MAX = 32768;
+
 int launch_reduce_argmin(const float* partial, const uint32_t* pcnt, int64_t n_tiles, int64_t n_sub, int E, int r,
-                         float* loss, int32_t* argmin, uint32_t* argmin_mask, int64_t* unaffected, hipStream_t s) {
+                         float* loss, int32_t* argmin, uint32_t* argmin_mask, int64_t* unaffected, bool cleared,
+                         hipStream_t s) {
   Timed t("loss_reduce_argmin", s);
-  if (unaffected) hipLaunchKernelGGL(zero_i64_kernel, dim3(1), dim3(1), 0, s, (unsigned long long*)unaffected);
+  if (n_tiles * n_sub <= REDUCE_ONE_MAX && n_sub <= REDUCE_ONE_MAX) {
+    int S = 1;
+    while (S < n_sub && S < 1024) S <<= 1;
+    hipLaunchKernelGGL(reduce_one_kernel, dim3(1), dim3(1024), 0, s, partial, pcnt, (int)n_tiles, (uint32_t)n_sub, S, E, r,
+                       loss, (unsigned long long*)unaffected, argmin, argmin_mask);
+    MOEP_HIP(hipGetLastError());
+    return MOEP_OK;
+  }
+  if (unaffected && !cleared) hipLaunchKernelGGL(zero_i64_kernel, dim3(1), dim3(1), 0, s, (unsigned long long*)unaffected);
   if (n_sub >= 1024)
     hipLaunchKernelGGL(reduce_kernel<32>, dim3((unsigned)ceil_div(n_sub, 32)), dim3(256), 0, s, partial, pcnt,
                        n_tiles, (uint32_t)n_sub, loss, (unsigned long long*)unaffected);

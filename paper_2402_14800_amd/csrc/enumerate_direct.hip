@@ -283,7 +283,7 @@ int launch_enumerate_direct(const DirectPlan& p, const float* logits, const void
     if (st) return st;
   }
   return launch_reduce_argmin(partial, pcnt, p.T > 0 ? p.blocks : 0, p.n_sub, p.E, p.r, loss, argmin, argmin_mask,
-                              unaffected, s);
+                              unaffected, false, s);
 }
 
 }  // namespace moep

@@ -1,0 +1,36 @@
+"""The enumeration's reduction on both sides of its one-workgroup form, scoring tiles dealt to strands of wavefronts, and
+the record capacities of the routing prep, against the fp64 oracle (losses: fp32 sums within a tile of 32 tokens and up to
+a few hundred fp32 operations per term, 1e-5 relative covers both)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2402_14800_amd as pkg
+from paper_2402_14800_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("E,k,r,T,H,dtype", [
+    (8, 2, 4, 14976, 64, "bf16"),      # 468 tiles x 70 subsets: the last size of the one-workgroup reduction
+    (8, 2, 4, 14977, 64, "bf16"),      # one token more: reduced by a workgroup per subset
+    (8, 2, 4, 33, 64, "bf16"),         # a tile of one token: strands without work
+    (4, 2, 2, 7, 64, "f32"),           # fewer tokens than strands
+    (1, 1, 1, 40, 64, "bf16"),         # one expert, one subset
+    (10, 3, 5, 600, 64, "bf16"),       # 252 subsets: 256 lanes, several tiles
+    (17, 4, 9, 6, 64, "bf16"),         # capacity 12 with more than 16 experts
+    (18, 1, 16, 100, 64, "bf16"),      # capacity 4 with more than 16 experts
+    (13, 2, 7, 50, 64, "bf16"),        # 8 active ranks of 13 experts, 1716 subsets
+])
+def test_enumeration_at_the_edges_of_its_forms(E, k, r, T, H, dtype):
+    logits, Y = wl.make_enumeration_inputs(E, T, H, dtype, seed=77 + E + T)
+    loss, amin, amask, unaff = pkg.prune_enumerate(logits.to("cuda:0"), Y.to("cuda:0"), k, r)
+    torch.cuda.synchronize()
+    ref, ref_amin, masks = oracle.prune_enumerate_gram_form(wl.to_f64(logits), wl.to_f64(Y), k, r)[:3]
+    got = loss.cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * np.abs(ref).max())
+    assert int(amin.item()) == int(np.argmin(got))
+    assert (int(amask.item()) & 0xFFFFFFFF) == int(masks[int(amin.item())])
+    import math
+    assert int(unaff.item()) == (T * math.comb(E - k, r - k) if r >= k else 0)
