@@ -113,7 +113,16 @@ constexpr int GEMM_BM = 256;   // rows per tile of either GEMM implementation's 
 // bf16 packed GEMM: M tiles per group of tiles that an XCD works through together, and output columns per tile,
 // for the gate/up (SwiGLU) and the down projection (measured: the long-K down projection prefers 4 x 8 tiles per XCD)
 constexpr int GEMM_GROUP_M_SWIGLU = 8, GEMM_GROUP_M_STORE = 4;
+// output columns per tile; half-width tiles for launches that would leave compute units without a tile
 constexpr int GEMM_BN_SWIGLU = 128, GEMM_BN_STORE = 256;
+static inline int gemm_tile_columns(bool gate_up, bool half) { return (gate_up ? GEMM_BN_SWIGLU : GEMM_BN_STORE) >> (half ? 1 : 0); }
+// Whether a launch of `tiles` full-width tiles is shorter with twice as many of half the width, on 256 compute units: while
+// they still fit one round.  Forward of 777 tokens at the Mixtral shape (128 tiles in its down projection) 764 -> 716 us,
+// dense pass of 64 tokens 798 -> 739 us; with 896 gate/up tiles taken as 7 half rounds for 4 the former was 790 us, and 160
+// tiles as two half rounds for one cost 445 -> 507 us (E 16, H 2048, F 5632, top-4, 1001 tokens).
+__host__ __device__ static inline bool half_width_pays(int64_t tiles) { return tiles <= 128; }
+// A tile order starts with a header: word TILE_ORDER_HALF says whether its entries are half-width tiles.
+constexpr int TILE_ORDER_HEADER = 4, TILE_ORDER_HALF = 0;
 
 int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name);
 
@@ -137,8 +146,8 @@ struct PackedGemmArgs {
   const int32_t* seg_end = nullptr;
   const int32_t* tiles_in_use = nullptr;
   int64_t max_m_tiles = 0;
-  // Grouped mode, optional: the order in which the launch walks its tiles, entry i = (M tile << 12) | N tile,
-  // tiles_in_use x n_tiles entries (see order_kernel in skip.hip); without it groups of M tiles may straddle experts.
+  // Grouped mode: the order in which the launch walks its tiles: TILE_ORDER_HEADER words, then entry i = (M tile << 12) |
+  // N tile, tiles_in_use x n_tiles entries (see order_kernel in skip.hip).
   const uint32_t* tile_order = nullptr;
   // Dense batched mode: `experts` GEMMs of the same shape in one launch; expert e reads A + e a_expert_bytes
   // (0: every expert reads the same A), B + e packed_b_bytes(..), and writes C + e c_expert_bytes.

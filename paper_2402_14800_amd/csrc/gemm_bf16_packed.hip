@@ -149,7 +149,8 @@ struct KArgs {
   int64_t M, ldc;
   int N;                  // output columns
   int nsl;                // K / 32
-  int m_tiles, n_tiles;
+  int m_tiles, n_tiles;   // n_tiles: of the width the launch walks (grouped: of half the width)
+  int n_tiles_full, half_width;
   // grouped mode (rows partitioned into per-expert segments, tile t = rows tile_row0[t] .. of expert
   // tile_expert[t]; A and a packed C are indexed by TILE, a row-major C by row)
   const int32_t* tile_expert; const int32_t* tile_row0; const int32_t* seg_end; const int32_t* tiles_in_use;
@@ -162,7 +163,7 @@ struct KArgs {
   // EPI_ROWSCALE_F32: rows with row_dest[r] >= 0 go, as bf16 and unscaled, to row row_dest[r] of direct_out
   const int32_t* row_dest;
   uint16_t* direct_out;
-  const uint32_t* tile_order;   // grouped mode, optional: entry bid = (M tile << 12) | N tile
+  const uint32_t* tile_order;   // grouped mode: a header, then entry bid = (M tile << 12) | N tile
 };
 
 // Round counters of the persistent workgroups, one per XCD (64 bytes apart); see round_sync in the kernel.
@@ -172,9 +173,9 @@ struct KArgs {
 // that ever not so, the line-ups would group the wrong workgroups and cost time, never a result.
 __device__ unsigned long long g_round_count[8 * 8];
 
-template <int EPI, bool GROUPED, bool BROW>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void gemm_packed_kernel(KArgs p) {
+// NG: accumulator tiles of a wavefront along N: 8, or 4 for tiles of half the width.
+template <int EPI, bool GROUPED, bool BROW, int NG>
+__device__ __forceinline__ void gemm_body(const KArgs& p) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -184,43 +185,49 @@ void gemm_packed_kernel(KArgs p) {
   const int nsl = p.nsl;
   // Grouped launches are sized for the largest possible tile map; only its leading entries hold work.
   const uint32_t m_tiles = GROUPED ? (uint32_t)*p.tiles_in_use : (uint32_t)p.m_tiles;
-  const uint32_t per_expert = m_tiles * (uint32_t)p.n_tiles;
+  const uint32_t n_tiles = GROUPED && NG == 8 ? (uint32_t)p.n_tiles_full : (uint32_t)p.n_tiles;
+  const uint32_t per_expert = m_tiles * n_tiles;
   const uint32_t nblk = GROUPED ? per_expert : per_expert * (uint32_t)p.experts;
   const uint32_t G = gridDim.x;
 
   // Logical tile id -> (tm, tn).  Ids i, i + 8, ... belong to XCD i % 8 (the grid is a multiple of 8 or
   // a single round); every XCD gets a contiguous run of tiles, GROUP_M M-tiles deep.
-  constexpr uint32_t GROUP_M = EPI == EPI_SWIGLU ? GEMM_GROUP_M_SWIGLU : GEMM_GROUP_M_STORE;
-  // weight blocks of the tile's expert (BROW: the first of this wavefront's 64 weight rows; rows come in whole groups of
+  constexpr uint32_t GROUP_M = (EPI == EPI_SWIGLU ? GEMM_GROUP_M_SWIGLU : GEMM_GROUP_M_STORE) * NG / 8;
+  // weight blocks of the tile's expert (BROW: the first of this wavefront's 64 or 32 weight rows; rows come in whole groups of
   // 64, a group beyond the last one re-reads that, its products are never stored)
   const int64_t pitch = (int64_t)nsl * 64;
   auto b_tile = [&](int tm_, int tn_, int e_) {
     const char* b;
     if (BROW) {
-      const int row = EPI == EPI_SWIGLU ? tn_ * 128 + (wave_u & 1) * 64 : tn_ * 256 + wave_u * 64;
-      b = (EPI == EPI_SWIGLU && wave_u >= 2 ? p.B1 : p.B) + (int64_t)min(row, p.N - 64) * pitch;
-    } else {
+      constexpr int ROWS = 8 * NG;                // weight rows that a wavefront brings per slice
+      const int row = EPI == EPI_SWIGLU ? tn_ * (2 * ROWS) + (wave_u & 1) * ROWS : tn_ * (4 * ROWS) + wave_u * ROWS;
+      b = (EPI == EPI_SWIGLU && wave_u >= 2 ? p.B1 : p.B) + (int64_t)min(row, p.N - ROWS) * pitch;
+    } else if (NG == 8) {
       b = p.B + ((size_t)tn_ * nsl) * SLICE + wave_u * 4096;
+    } else {                                      // half a block: 128 rows, or 64 gate rows and the same 64 up rows
+      b = p.B + ((size_t)(tn_ >> 1) * nsl) * SLICE +
+          (EPI == EPI_SWIGLU ? (tn_ & 1) * 4096 + (wave_u >> 1) * 8192 + (wave_u & 1) * 2048 : (tn_ & 1) * 8192 + wave_u * 2048);
     }
     b += (int64_t)(GROUPED ? p.tile_expert[tm_] : e_) * p.b_expert_bytes;
     return b;
   };
   constexpr int B_STEP = BROW ? 64 : SLICE;       // bytes from a slice of the weights to the next
   // Dense: e = the GEMM of a batched launch the tile belongs to; each of them is dealt to the XCDs exactly as a
-  // launch of its own would be when its tile count is a multiple of 8, else the batch is one flat run of tiles.
+  // launch of its own would be when its tile count is a multiple of 8 and the launch takes several rounds, else the batch
+  // is one flat run of tiles (in a single round that keeps an expert's operands on one XCD).
   auto decode = [&](uint32_t L, int& tm, int& tn, int& e) {
     const uint32_t xcd = L & 7, j = L >> 3;
     if (GROUPED) {
       // the order of the tiles was laid out by the caller (groups of M tiles aligned to experts, see order_kernel);
       // XCD x walks entries x per + min(x, rem) ... of it
       const uint32_t per = nblk >> 3, rem = nblk & 7;
-      const uint32_t v = p.tile_order[xcd * per + (xcd < rem ? xcd : rem) + j];
+      const uint32_t v = p.tile_order[TILE_ORDER_HEADER + xcd * per + (xcd < rem ? xcd : rem) + j];
       e = 0;
       tm = (int)(v >> 12);
       tn = (int)(v & 4095u);
     } else {
       uint32_t bid;
-      if ((per_expert & 7) == 0) {
+      if ((per_expert & 7) == 0 && nblk > G) {
         const uint32_t per8 = per_expert >> 3;
         const uint32_t eu = j / per8;
         e = (int)eu;
@@ -232,7 +239,7 @@ void gemm_packed_kernel(KArgs p) {
         e = (int)eu;
         bid -= eu * per_expert;
       }
-      const uint32_t group_sz = GROUP_M * (uint32_t)p.n_tiles;
+      const uint32_t group_sz = GROUP_M * n_tiles;
       const uint32_t group = bid / group_sz;
       const uint32_t first_m = group * GROUP_M;
       const uint32_t gm = min(m_tiles - first_m, GROUP_M);
@@ -268,7 +275,8 @@ void gemm_packed_kernel(KArgs p) {
 #define MOEP_LOAD1(q)                                                                           \
   __builtin_amdgcn_global_load_lds((gptr_t)((q) < 4 ? ga : !BROW ? gb :                           \
       b_ld + ((((q) & 2) ? 32 : 0) * pitch + (((q) & 1) ? 4 : 0) * pitch - ((q) & 3) * 1024) + brow_off), \
-      (__attribute__((address_space(3))) void*)(lds3 + st_ld + ((q) < 4 ? 0 : SLICE) + wave_u * 4096), 16, ((q) & 3) * 1024, 0);
+      (__attribute__((address_space(3))) void*)(lds3 + st_ld + ((q) < 4 ? wave_u * 4096 : SLICE + wave_u * (NG * 512))), 16, \
+      ((q) & 3) * 1024, 0);
   // After a slice has been issued: next slice, next stage (branch-free, so that it can be scheduled into
   // the shadow of the MFMAs).  Past the end of the workgroup's stream the loader stays on its last slice:
   // the re-reads are in bounds and land in stages nobody reads again, every step issues the same loads and
@@ -350,56 +358,61 @@ void gemm_packed_kernel(KArgs p) {
   const int frow = lane & 15, fk = lane >> 4;
   const int fpos = (fk ^ ((frow >> 2) & 3)) << 4;
   const int a_fb = (wm * 128 + frow) * 64 + fpos;
-  const int b_fb = SLICE + ((EPI == EPI_SWIGLU ? wn * 64 : wn * 128) + frow) * 64 + fpos;
+  const int b_fb = SLICE + ((EPI == EPI_SWIGLU ? wn * (NG * 8) : wn * (NG * 16)) + frow) * 64 + fpos;
   int st_rd = 0;                      // byte offset of the stage the next fragment read takes
   int ra = a_fb, rb = b_fb;           // the same, added to the lane's fragment offsets
 
-  f32x4 acc[8][8];
+  f32x4 acc[8][NG];
 #define MOEP_ZERO_ACC()                                                                         \
   _Pragma("unroll") for (int i = 0; i < 8; ++i)                                                 \
-    _Pragma("unroll") for (int j = 0; j < 8; ++j)                                               \
+    _Pragma("unroll") for (int j = 0; j < NG; ++j)                                              \
       _Pragma("unroll") for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
-  bf16x8 fa[2][8], fb[2][8];
-  // B tile j of a wavefront: SwiGLU: gate tiles 0 .. 3 and up tiles 4 .. 7 (128 rows further) of the same
-  // 64 columns; otherwise eight consecutive 16-row tiles.
+  bf16x8 fa[2][8], fb[2][NG];
+  // B tile j of a wavefront: SwiGLU: gate tiles 0 .. NG/2 - 1 and up tiles (NG 16 rows further) of the same
+  // 8 NG columns; otherwise NG consecutive 16-row tiles.
 #define MOEP_RB(slot, j)                                                                        \
-  fb[slot][j] = *(const bf16x8*)(lds + rb + (EPI == EPI_SWIGLU ? ((j) >> 2) * 8192 + ((j) & 3) * 1024 : (j) * 1024));
+  fb[slot][j] = *(const bf16x8*)(lds + rb + (EPI == EPI_SWIGLU ? ((j) / (NG / 2)) * (NG * 1024) + ((j) % (NG / 2)) * 1024 : (j) * 1024));
 #define MOEP_RA(slot, i) fa[slot][i] = *(const bf16x8*)(lds + ra + (i) * 1024);
   // (B fragments visited back and forth, so that only one operand changes from one MFMA to the next: 0.6 % faster)
 #define MOEP_MFMA(slot)                                                                         \
   _Pragma("unroll") for (int i = 0; i < 8; ++i)                                                 \
-    _Pragma("unroll") for (int jj = 0; jj < 8; ++jj) {                                          \
-      const int j = (i & 1) ? 7 - jj : jj;                                                      \
+    _Pragma("unroll") for (int jj = 0; jj < NG; ++jj) {                                         \
+      const int j = (i & 1) ? NG - 1 - jj : jj;                                                 \
       acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[slot][j], fa[slot][i], acc[i][j], 0, 0, 0); }
   // Source order = wanted issue order (a direct load writes LDS, so the compiler keeps it ordered with
   // the fragment reads around it): two fragment reads, one direct load, eight times over, spread over
   // the first 48 of the step's 64 MFMAs by the scheduling groups below.
 #define MOEP_READS_LOADS(slot)                                                                  \
-  MOEP_RB(slot, 0) MOEP_RB(slot, 1) MOEP_LOAD1(0) MOEP_RB(slot, 2) MOEP_RB(slot, 3) MOEP_LOAD1(1) \
-  MOEP_RB(slot, 4) MOEP_RB(slot, 5) MOEP_LOAD1(2) MOEP_RB(slot, 6) MOEP_RB(slot, 7) MOEP_LOAD1(3) \
-  MOEP_RA(slot, 0) MOEP_RA(slot, 1) MOEP_LOAD1(4) MOEP_RA(slot, 2) MOEP_RA(slot, 3) MOEP_LOAD1(5) \
-  MOEP_RA(slot, 4) MOEP_RA(slot, 5) MOEP_LOAD1(6) MOEP_RA(slot, 6) MOEP_RA(slot, 7) MOEP_LOAD1(7)
+  if constexpr (NG == 8) {                                                                      \
+    MOEP_RB(slot, 0) MOEP_RB(slot, 1) MOEP_LOAD1(0) MOEP_RB(slot, 2) MOEP_RB(slot, 3) MOEP_LOAD1(1) \
+    MOEP_RB(slot, 4) MOEP_RB(slot, 5) MOEP_LOAD1(2) MOEP_RB(slot, 6) MOEP_RB(slot, 7) MOEP_LOAD1(3) \
+    MOEP_RA(slot, 0) MOEP_RA(slot, 1) MOEP_LOAD1(4) MOEP_RA(slot, 2) MOEP_RA(slot, 3) MOEP_LOAD1(5) \
+    MOEP_RA(slot, 4) MOEP_RA(slot, 5) MOEP_LOAD1(6) MOEP_RA(slot, 6) MOEP_RA(slot, 7) MOEP_LOAD1(7) \
+  } else {                                                                                      \
+    MOEP_RB(slot, 0) MOEP_RB(slot, 1) MOEP_LOAD1(0) MOEP_RB(slot, 2) MOEP_RB(slot, 3) MOEP_LOAD1(1) \
+    MOEP_RA(slot, 0) MOEP_RA(slot, 1) MOEP_LOAD1(2) MOEP_RA(slot, 2) MOEP_RA(slot, 3) MOEP_LOAD1(3) \
+    MOEP_RA(slot, 4) MOEP_RA(slot, 5) MOEP_LOAD1(4) MOEP_RA(slot, 6) MOEP_RA(slot, 7) MOEP_LOAD1(5) \
+  }
 #define MOEP_READS(slot)                                                                        \
-  MOEP_RB(slot, 0) MOEP_RB(slot, 1) MOEP_RB(slot, 2) MOEP_RB(slot, 3)                           \
-  MOEP_RB(slot, 4) MOEP_RB(slot, 5) MOEP_RB(slot, 6) MOEP_RB(slot, 7)                           \
-  MOEP_RA(slot, 0) MOEP_RA(slot, 1) MOEP_RA(slot, 2) MOEP_RA(slot, 3)                           \
-  MOEP_RA(slot, 4) MOEP_RA(slot, 5) MOEP_RA(slot, 6) MOEP_RA(slot, 7)
+  _Pragma("unroll") for (int j_ = 0; j_ < NG; ++j_) { MOEP_RB(slot, j_) }                       \
+  _Pragma("unroll") for (int i_ = 0; i_ < 8; ++i_) { MOEP_RA(slot, i_) }
   // Two MFMAs, a fragment read, two MFMAs, a fragment read, two MFMAs, a direct load: never more than one
-  // memory instruction between two MFMAs (1 % faster than 3 + read + 3 + read + load).
+  // memory instruction between two MFMAs (1 % faster than 3 + read + 3 + read + load).  Half-width tiles: one MFMA
+  // before the load.
 #define MOEP_SCHED(LOADS)                                                                       \
-  _Pragma("unroll") for (int q_ = 0; q_ < 8; ++q_) {                                            \
+  _Pragma("unroll") for (int q_ = 0; q_ < (NG == 8 ? 8 : 6); ++q_) {                            \
     __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                          \
     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                          \
     __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                          \
     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                          \
-    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                          \
+    __builtin_amdgcn_sched_group_barrier(0x008, NG == 8 ? 2 : 1, 0);                            \
     if (LOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                               \
   }
   // s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, lgkmcnt in bits 11:8 (0 here), expcnt 6:4 left at 7.
-  // Loads complete in issue order, so "at most 8 outstanding" means that everything but the slice issued in
+  // Loads complete in issue order, so "at most 8 (half-width tiles: 6) outstanding" means that everything but the slice issued in
   // this step has landed, in particular the two slices whose fragments are read before the next barrier
   // (stores of an epilogue only add to the count).
-  constexpr int VM_MAIN = 8;
+  constexpr int VM_MAIN = 4 + NG / 2;
   constexpr int W_MAIN = 0x0070 | (VM_MAIN & 15) | ((VM_MAIN >> 4) << 14);
   // One step: multiply the slice whose fragments are in `slot`; meanwhile fetch the slice NS - 1 ahead and
   // read the next slice's fragments into the other slot.  The barrier at the end of every second step tells
@@ -424,7 +437,8 @@ void gemm_packed_kernel(KArgs p) {
   // ---- prologue: the first NS - 1 slices of this workgroup's stream -----------------------------------
 #pragma unroll 1
   for (int n = 0; n < NS - 1; ++n) {
-    MOEP_LOAD1(0) MOEP_LOAD1(1) MOEP_LOAD1(2) MOEP_LOAD1(3) MOEP_LOAD1(4) MOEP_LOAD1(5) MOEP_LOAD1(6) MOEP_LOAD1(7)
+    MOEP_LOAD1(0) MOEP_LOAD1(1) MOEP_LOAD1(2) MOEP_LOAD1(3) MOEP_LOAD1(4) MOEP_LOAD1(5)
+    if constexpr (NG == 8) { MOEP_LOAD1(6) MOEP_LOAD1(7) }
     MOEP_ADVANCE_LOADER()
     MOEP_NEXT_LOAD_TILE()
   }
@@ -479,8 +493,8 @@ void gemm_packed_kernel(KArgs p) {
       if (r >= row_end) continue;
       if (EPI == EPI_SWIGLU) {
 #pragma unroll
-        for (int P = 0; P < 2; ++P) {
-        const int n = tn * 128 + wn * 64 + 32 * P + q8;
+        for (int P = 0; P < NG / 4; ++P) {
+        const int n = tn * (NG * 16) + wn * (NG * 8) + 32 * P + q8;
         if (n < p.N) {
           bf16x2 o[4];
 #pragma unroll
@@ -489,7 +503,7 @@ void gemm_packed_kernel(KArgs p) {
 #pragma unroll
             for (int d = 0; d < 2; ++d) {
               const int b = 2 * P + (c >> 1), v = 2 * (c & 1) + d;
-              const float g = acc[i][b][v], u = acc[i][4 + b][v];
+              const float g = acc[i][b][v], u = acc[i][NG / 2 + b][v];
               h[d] = g * u * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
             }
             o[c] = __builtin_convertvector(h, bf16x2);
@@ -504,8 +518,8 @@ void gemm_packed_kernel(KArgs p) {
         int64_t dest = -1;                                       // EPI_ROWSCALE_F32: >= 0: this row is a token's only slot
         if (EPI == EPI_ROWSCALE_F32 && p.row_dest) dest = p.row_dest[r];
 #pragma unroll
-        for (int P = 0; P < 4; ++P) {
-          const int n = tn * 256 + wn * 128 + 32 * P + q8;
+        for (int P = 0; P < NG / 2; ++P) {
+          const int n = tn * (NG * 32) + wn * (NG * 16) + 32 * P + q8;
           if (n >= p.N) continue;
           if (EPI == EPI_STORE || (EPI == EPI_ROWSCALE_F32 && dest >= 0)) {
             bf16x2 o[4];
@@ -542,6 +556,18 @@ void gemm_packed_kernel(KArgs p) {
 #undef MOEP_READS
 #undef MOEP_SCHED
 #undef MOEP_STEP
+}
+
+// A launch with so few tiles that compute units would stand idle walks tiles of half the width instead, 256 x 128
+// accumulator columns (64 outputs in SwiGLU mode), bits unchanged.  Half-width tiles cost well over half the time of full
+// ones (the same rows of A per step), so they only pay while they still fit one round (half_width_pays).  Grouped launches
+// learn from the tile order's header which it is: only the device knows how many tiles the routing made.
+// Down projection 4096 x 14336, 8 experts of about 150 rows: 128 tiles 360 us, 256 of half the width 281 us.
+template <int EPI, bool GROUPED, bool BROW>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void gemm_packed_kernel(KArgs p) {
+  if (GROUPED ? p.tile_order[TILE_ORDER_HALF] != 0 : p.half_width != 0) gemm_body<EPI, GROUPED, BROW, 4>(p);
+  else gemm_body<EPI, GROUPED, BROW, 8>(p);
 }
 
 // Per-device launch state, filled on a device's first launch under a mutex (first calls from several host
@@ -666,9 +692,13 @@ int launch_gemm_bf16_packed(const PackedGemmArgs& g, hipStream_t s, const char* 
   k.tile_order = grouped ? g.tile_order : nullptr;
   if ((g.a_expert_bytes | g.c_expert_bytes) & 15) return fail(MOEP_EUNSUPPORTED, "%s: per-expert strides must be multiples of 16 bytes", name);
   const int64_t m_tiles = grouped ? g.max_m_tiles : ceil_div(g.M, 256);
-  const int64_t n_tiles = ceil_div(g.N, g.epilogue == EPI_SWIGLU ? 128 : 256);
+  // (grouped: tiles for the larger possible grid; the order's header tells the kernel which width to walk)
+  const int64_t n_full = ceil_div(g.N, gemm_tile_columns(g.epilogue == EPI_SWIGLU, false));
+  const int64_t n_half = ceil_div(g.N, gemm_tile_columns(g.epilogue == EPI_SWIGLU, true));
+  const bool half = !grouped && half_width_pays(m_tiles * n_full * g.experts);
+  const int64_t n_tiles = grouped || half ? n_half : n_full;
   if (m_tiles * n_tiles * g.experts >= ((int64_t)1 << 31)) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
-  k.m_tiles = (int)m_tiles; k.n_tiles = (int)n_tiles;
+  k.m_tiles = (int)m_tiles; k.n_tiles = (int)n_tiles; k.n_tiles_full = (int)n_full; k.half_width = half ? 1 : 0;
   Timed t(name, s);
 #define MOEP_GEMM_CASE(EPI, GROUPED) \
   return g.b_row_major ? launch<EPI, GROUPED, true>(k, s) : launch<EPI, GROUPED, false>(k, s)

@@ -120,24 +120,32 @@ __global__ __launch_bounds__(256) void scan_kernel(int32_t* __restrict__ counts,
 // Entries are grouped per EXPERT: group_m consecutive M tiles of one expert, walked along N (all group_m tiles of
 // one N tile, then the next N tile), so that the tiles in flight share the same few weight panels; an expert's last
 // group may be smaller.  Entry = (M tile << 12) | N tile.
-__global__ __launch_bounds__(256) void order_kernel(const int32_t* __restrict__ expert_first, int E, int n_tiles,
-                                                    int group_m, uint32_t* __restrict__ order) {
+// blockIdx.y: 0 the gate/up projection's table, 1 the down projection's.  The width of the tiles is decided here, from the
+// number of tiles the routing made, and noted in the table's header.
+struct OrderArgs { uint32_t* order; int n_full, n_half, group_m; };
+__global__ __launch_bounds__(256) void order_kernel(const int32_t* __restrict__ expert_first, int E, OrderArgs up,
+                                                    OrderArgs down) {
+  const OrderArgs a = blockIdx.y ? down : up;
   __shared__ int first[33];
   if ((int)threadIdx.x <= E) first[threadIdx.x] = expert_first[threadIdx.x];
   __syncthreads();
+  const bool half = half_width_pays((int64_t)first[E] * a.n_full);
+  const int n_tiles = half ? a.n_half : a.n_full;
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.order[TILE_ORDER_HALF] = half ? 1u : 0u;
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (q >= (int64_t)first[E] * n_tiles) return;
   int e = 0;
   while (e + 1 < E && (int64_t)first[e + 1] * n_tiles <= q) ++e;
   const int64_t qe = q - (int64_t)first[e] * n_tiles;
   const int c = first[e + 1] - first[e];
+  const int group_m = half ? a.group_m / 2 : a.group_m;
   const int64_t gsz = (int64_t)group_m * n_tiles;
   const int g = (int)(qe / gsz);
   const int first_m = g * group_m;
   const int gm = c - first_m < group_m ? c - first_m : group_m;
   const int in_group = (int)(qe - g * gsz);
   const int tn = in_group / gm, m = first_m + in_group % gm;
-  order[q] = ((uint32_t)(first[e] + m) << 12) | (uint32_t)tn;
+  a.order[TILE_ORDER_HEADER + q] = ((uint32_t)(first[e] + m) << 12) | (uint32_t)tn;
 }
 
 __global__ __launch_bounds__(RB) void scatter_kernel(const int32_t* __restrict__ top2,
@@ -483,10 +491,11 @@ int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_ex
   p->off_order_up = p->off_order_down = 0;
   if (dt == MOEP_BF16) {
     const int64_t gemm_tiles = ceil_div((int64_t)ks * T, GEMM_BM) + E;
-    if (ceil_div(F, GEMM_BN_SWIGLU) > 4096 || ceil_div(H, GEMM_BN_STORE) > 4096 || gemm_tiles >= (1 << 20))
+    const int64_t n_up = ceil_div(F, gemm_tile_columns(true, true)), n_down = ceil_div(H, gemm_tile_columns(false, true));
+    if (n_up > 4096 || n_down > 4096 || gemm_tiles >= (1 << 20))
       return fail(MOEP_EUNSUPPORTED, "moe_forward_skip: too many tiles for the tile order tables");
-    p->off_order_up = take((size_t)gemm_tiles * ceil_div(F, GEMM_BN_SWIGLU) * 4);
-    p->off_order_down = take((size_t)gemm_tiles * ceil_div(H, GEMM_BN_STORE) * 4);
+    p->off_order_up = take((size_t)(TILE_ORDER_HEADER + gemm_tiles * n_up) * 4);
+    p->off_order_down = take((size_t)(TILE_ORDER_HEADER + gemm_tiles * n_down) * 4);
     // packed-operand GEMMs: h and the gathered x hold one 256-row block per tile; every expert's weights
     // are re-laid out once per call
     p->off_h = take(packed_a_bytes(gemm_tiles * GEMM_BM, F));
@@ -506,11 +515,14 @@ int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_ex
 static void launch_order_tables(const SkipPlan& p, char* ws, hipStream_t s) {
   if (!p.packed || p.few) return;
   const int32_t* expert_first = (const int32_t*)(ws + p.off_seg_end) + p.E;
-  const int n_up = (int)ceil_div(p.F, GEMM_BN_SWIGLU), n_down = (int)ceil_div(p.H, GEMM_BN_STORE);
-  hipLaunchKernelGGL(order_kernel, dim3((unsigned)ceil_div(p.max_tiles * n_up, 256)), dim3(256), 0, s, expert_first, p.E,
-                     n_up, GEMM_GROUP_M_SWIGLU, (uint32_t*)(ws + p.off_order_up));
-  hipLaunchKernelGGL(order_kernel, dim3((unsigned)ceil_div(p.max_tiles * n_down, 256)), dim3(256), 0, s, expert_first, p.E,
-                     n_down, GEMM_GROUP_M_STORE, (uint32_t*)(ws + p.off_order_down));
+  const OrderArgs up = {(uint32_t*)(ws + p.off_order_up), (int)ceil_div(p.F, gemm_tile_columns(true, false)),
+                        (int)ceil_div(p.F, gemm_tile_columns(true, true)), GEMM_GROUP_M_SWIGLU};
+  const OrderArgs down = {(uint32_t*)(ws + p.off_order_down), (int)ceil_div(p.H, gemm_tile_columns(false, false)),
+                          (int)ceil_div(p.H, gemm_tile_columns(false, true)), GEMM_GROUP_M_STORE};
+  // entries of the larger table: p.max_tiles full-width tiles, or the few half-width ones that half_width_pays allows
+  const int64_t n = p.max_tiles * (up.n_full > down.n_full ? up.n_full : down.n_full);
+  hipLaunchKernelGGL(order_kernel, dim3((unsigned)ceil_div(n > 512 ? n : 512, 256), 2), dim3(256), 0, s, expert_first, p.E,
+                     up, down);
 }
 
 int launch_skip_routing(const SkipPlan& p, const float* logits, uint32_t kept_mask, float beta, uint8_t* skip_mask,

@@ -104,3 +104,25 @@ def test_weights_in_place_give_the_bits_of_packed_weights(E, H, F, T, n):
     t = torch.arange(T, device=Y.device)
     for j in range(n):
         assert torch.equal(bits(Yr[slot[:, j].long()]), bits(Y[experts[:, j].long(), t]))
+
+
+@pytest.mark.parametrize("E,H,F,T", [(1, 64, 64, 32769), (2, 320, 192, 8193), (8, 192, 320, 1025)])
+def test_half_width_tiles_give_the_bits_of_full_width_tiles(E, H, F, T):
+    """One token more makes 129 tiles of 128 (or the launch of twice as many rows leaves one round), and the GEMMs walk tiles
+    of another width: the rows both batches hold are the same bits, dense and through the tile order of the routed pass."""
+    _, layer = small_layer("bf16", E, 2, H, F, T, index=26)
+    d = to_dev(layer)
+    rest = [d[n] for n in NAMES[1:]]
+    _, many = pkg.moe_expert_outputs(d["x"], *rest)
+    _, experts, slot, Yr = pkg.moe_expert_outputs_ranked(d["x"], *rest, 1)
+    torch.cuda.synchronize()
+    for rows in (T - 1, T // 2, 100):
+        x = d["x"][:rows].contiguous()
+        _, Y = pkg.moe_expert_outputs(x, *rest)
+        _, experts_s, slot_s, Yr_s = pkg.moe_expert_outputs_ranked(x, *rest, 1)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(Y), bits(many[:, :rows].contiguous()))
+        assert torch.equal(experts_s, experts[:rows])
+        assert torch.equal(bits(Yr_s[slot_s[:, 0].long()]), bits(Yr[slot[:rows, 0].long()]))
+        t = torch.arange(rows, device=Y.device)
+        assert torch.equal(bits(Yr_s[slot_s[:, 0].long()]), bits(Y[experts_s[:, 0].long(), t]))
