@@ -89,8 +89,11 @@ __device__ __forceinline__ uint4 load_streaming(const uint4* p) {
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-template <int EPAD, bool RANKED, bool STREAM>
-__global__ __launch_bounds__(256) void gram_bf16_kernel(const uint4* __restrict__ Y,
+// F32: rows of floats, four v_mfma_f32_16x16x4_f32 per 16-byte chunk and 16 rows (the same register as both operands again;
+// fp32 products and sums); E 8, H 512, 1501 tokens 47 -> 9 us against a wavefront per token with a shuffle tree per
+// pair of experts, which re-read every row E times.
+template <bool F32, int EPAD, bool RANKED, bool STREAM>
+__global__ __launch_bounds__(256) void gram_kernel(const uint4* __restrict__ Y,
                                                         const int32_t* __restrict__ slot_of,
                                                         const int32_t* __restrict__ experts,
                                                         float* __restrict__ G, int64_t T, int E, int n,
@@ -103,8 +106,8 @@ __global__ __launch_bounds__(256) void gram_bf16_kernel(const uint4* __restrict_
   const int64_t t0 = tile * TPT;
   if (t0 >= T) return;
   uint4* st = stage[wave];
-  const int chunks = H / 8;                             // 16-byte chunks per row
-  const int nkb = (chunks + 63) / 64;                   // blocks of 512 hidden units
+  const int chunks = H / (F32 ? 4 : 8);                 // 16-byte chunks per row
+  const int nkb = (chunks + 63) / 64;                   // blocks of 1 KB of every row
   // row j of the tile: expert (rank position) j % EPAD of token t0 + j / EPAD; rows without data read as zeros
   const uint4* rowp[16];
   bool rvalid[16];
@@ -133,10 +136,19 @@ __global__ __launch_bounds__(256) void gram_bf16_kernel(const uint4* __restrict_
     // every row agrees, here chunk 4 s + (l >> 4) of the block
 #pragma unroll
     for (int s = 0; s < 16; s += 2) {
-      const bf16x8 a0 = __builtin_bit_cast(bf16x8, st[row * 64 + ((4 * s + kg) ^ row)]);
-      const bf16x8 a1 = __builtin_bit_cast(bf16x8, st[row * 64 + ((4 * (s + 1) + kg) ^ row)]);
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, a0, acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, a1, acc1, 0, 0, 0);
+      const uint4 c0 = st[row * 64 + ((4 * s + kg) ^ row)], c1 = st[row * 64 + ((4 * (s + 1) + kg) ^ row)];
+      if constexpr (F32) {
+        const f32x4 a0 = __builtin_bit_cast(f32x4, c0), a1 = __builtin_bit_cast(f32x4, c1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[i], a0[i], acc0, 0, 0, 0);
+          acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[i], a1[i], acc1, 0, 0, 0);
+        }
+      } else {
+        const bf16x8 a0 = __builtin_bit_cast(bf16x8, c0), a1 = __builtin_bit_cast(bf16x8, c1);
+        acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, a0, acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, a1, acc1, 0, 0, 0);
+      }
     }
   }
 #undef MOEP_GRAM_FETCH
@@ -190,7 +202,52 @@ __global__ __launch_bounds__(256) void gram_bf16_32_kernel(const uint4* __restri
   }
 }
 
-// ------------------------------------------------------------------ Gram, fp32 storage
+// fp32, E in 17..32: one token per 32x32 tile, rows fetched and staged as above (32 KB of LDS per wavefront, two of them
+// per workgroup): E 32, H 512, 300 tokens 580 -> 16 us against a shuffle tree per pair of experts.  (The same staging in
+// bf16 was slower than the kernel above: E 20, H 1024, 2000 tokens 21 against 17 us.)
+__global__ __launch_bounds__(128) void gram_f32_32_kernel(const uint4* __restrict__ Y, float* __restrict__ G, int64_t T, int E,
+                                                      int H) {
+  __shared__ uint4 stage[2][32 * 64];
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int64_t t = (int64_t)blockIdx.x * 2 + wave;
+  if (t >= T) return;
+  uint4* st = stage[wave];
+  const int chunks = H / 4;
+  const int nkb = (chunks + 63) / 64;
+  const uint4* const src = Y + t * chunks + lane;         // row e: e T rows further
+  const int64_t row_step = T * chunks;
+  const int row = lane & 31, kg = lane >> 5;
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  uint4 v[32];
+#define MOEP_GRAM_FETCH(kb)                                                                                  \
+  _Pragma("unroll") for (int j = 0; j < 32; ++j)                                                             \
+    v[j] = j < E && (kb) * 64 + lane < chunks ? src[j * row_step + (kb) * 64] : make_uint4(0, 0, 0, 0);
+  MOEP_GRAM_FETCH(0)
+  for (int kb = 0; kb < nkb; ++kb) {
+#pragma unroll
+    for (int j = 0; j < 32; ++j) st[j * 64 + (lane ^ j)] = v[j];
+    if (kb + 1 < nkb) { MOEP_GRAM_FETCH(kb + 1) }
+    // MFMA 32x32: lane l supplies row l % 32; chunk 2 s + (l / 32) of the block
+#pragma unroll 8
+    for (int s = 0; s < 32; ++s) {
+      const f32x4 a = __builtin_bit_cast(f32x4, st[row * 64 + ((2 * s + kg) ^ row)]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], a[i], acc, 0, 0, 0);
+    }
+  }
+#undef MOEP_GRAM_FETCH
+  const int col = lane & 31;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int r = 8 * (w >> 2) + 4 * (lane >> 5) + (w & 3);
+    if (r < E && col < E) G[(t * E + r) * E + col] = acc[w];
+  }
+}
+
+// ------------------------------------------------------------------ Gram, fp32 storage, rows of any length and alignment
 __global__ __launch_bounds__(256) void gram_f32_kernel(const float* __restrict__ Y,
                                                        float* __restrict__ G, int64_t T, int E,
                                                        int H) {
@@ -894,19 +951,25 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
       const unsigned per_tok_blocks = (unsigned)ceil_div(p.T, 4);
       // streaming loads for a Y beyond half a GB
       const bool stream = (double)p.T * (ranked ? ranked->n_rank : p.E) * p.H * 2.0 >= 512.0 * 1024 * 1024;
-#define MOEP_GRAM_LAUNCH(EPAD, RANKED, GRID, ...)                                                              \
-  do {                                                                                                         \
-    if (stream)                                                                                                \
-      hipLaunchKernelGGL((gram_bf16_kernel<EPAD, RANKED, true>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__);    \
-    else                                                                                                       \
-      hipLaunchKernelGGL((gram_bf16_kernel<EPAD, RANKED, false>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__);   \
+#define MOEP_GRAM_LAUNCH(EPAD, RANKED, GRID, ...)                                                                  \
+  do {                                                                                                             \
+    if (dt != MOEP_BF16)                                                                                           \
+      hipLaunchKernelGGL((gram_kernel<true, EPAD, RANKED, false>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__);      \
+    else if (stream)                                                                                               \
+      hipLaunchKernelGGL((gram_kernel<false, EPAD, RANKED, true>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__);      \
+    else                                                                                                           \
+      hipLaunchKernelGGL((gram_kernel<false, EPAD, RANKED, false>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__);     \
   } while (0)
-      if (ranked) {
+      // fp32 rows that are not whole 16-byte chunks go through the kernels that read word by word
+      const bool by_word = dt != MOEP_BF16 && (p.H % 4 || ((uintptr_t)Y & 15));
+      if (by_word && ranked)
+        hipLaunchKernelGGL(gram_ranked_f32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const float*)Y, ranked->slot_of,
+                           ranked->experts, G, p.T, p.E, ranked->n_rank, p.H);
+      else if (by_word)
+        hipLaunchKernelGGL(gram_f32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const float*)Y, G, p.T, p.E, p.H);
+      else if (ranked) {
         const int n = ranked->n_rank;
-        if (dt != MOEP_BF16)
-          hipLaunchKernelGGL(gram_ranked_f32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const float*)Y,
-                             ranked->slot_of, ranked->experts, G, p.T, p.E, n, p.H);
-        else if (n <= 4)
+        if (n <= 4)
           MOEP_GRAM_LAUNCH(4, true, (unsigned)ceil_div(p.T, 16), (const uint4*)Y, ranked->slot_of, ranked->experts, G,
                            p.T, p.E, n, p.H);
         else if (n <= 8)
@@ -915,19 +978,18 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
         else
           MOEP_GRAM_LAUNCH(16, true, per_tok_blocks, (const uint4*)Y, ranked->slot_of, ranked->experts, G, p.T, p.E, n,
                            p.H);
+      } else if (p.E <= 4) {
+        MOEP_GRAM_LAUNCH(4, false, (unsigned)ceil_div(p.T, 16), (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
+      } else if (p.E <= 8) {
+        MOEP_GRAM_LAUNCH(8, false, (unsigned)ceil_div(p.T, 8), (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
+      } else if (p.E <= 16) {
+        MOEP_GRAM_LAUNCH(16, false, per_tok_blocks, (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
       } else if (dt == MOEP_BF16) {
-        if (p.E <= 4)
-          MOEP_GRAM_LAUNCH(4, false, (unsigned)ceil_div(p.T, 16), (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
-        else if (p.E <= 8)
-          MOEP_GRAM_LAUNCH(8, false, (unsigned)ceil_div(p.T, 8), (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
-        else if (p.E <= 16)
-          MOEP_GRAM_LAUNCH(16, false, per_tok_blocks, (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
-        else
-          hipLaunchKernelGGL(gram_bf16_32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const uint4*)Y, G, p.T, p.E, p.H);
-#undef MOEP_GRAM_LAUNCH
+        hipLaunchKernelGGL(gram_bf16_32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const uint4*)Y, G, p.T, p.E, p.H);
       } else {
-        hipLaunchKernelGGL(gram_f32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const float*)Y, G, p.T, p.E, p.H);
+        hipLaunchKernelGGL(gram_f32_32_kernel, dim3((unsigned)ceil_div(p.T, 2)), dim3(128), 0, s, (const uint4*)Y, G, p.T, p.E, p.H);
       }
+#undef MOEP_GRAM_LAUNCH
       MOEP_HIP(hipGetLastError());
     }
     {

@@ -34,3 +34,22 @@ def test_enumeration_at_the_edges_of_its_forms(E, k, r, T, H, dtype):
     assert (int(amask.item()) & 0xFFFFFFFF) == int(masks[int(amin.item())])
     import math
     assert int(unaff.item()) == (T * math.comb(E - k, r - k) if r >= k else 0)
+
+
+@pytest.mark.parametrize("E,H,T", [(4, 4, 3), (8, 256, 17), (8, 260, 9), (16, 516, 5), (17, 36, 4), (32, 300, 3), (6, 37, 11), (20, 33, 2)])
+def test_fp32_gram_at_row_lengths_and_alignments(E, H, T):
+    """fp32 outputs: rows of whole and of partly filled 1 KB blocks, of lengths that are no multiple of 16 bytes, and a Y that
+    is only 4-byte aligned."""
+    logits, Y = wl.make_enumeration_inputs(E, T, H, "f32", seed=5 * E + H)
+    k, r = 2, E - 1
+    lg = logits.to("cuda:0")
+    buf = torch.empty(E * T * H + 1, dtype=torch.float32, device="cuda:0")
+    shifted = buf[1:].view(E, T, H)
+    shifted.copy_(Y)
+    ref, _, _ = oracle.prune_enumerate_gram_form(wl.to_f64(logits), wl.to_f64(Y), k, r)
+    for Yd in (Y.to("cuda:0"), shifted):
+        loss, amin, _, _ = pkg.prune_enumerate(lg, Yd, k, r)
+        torch.cuda.synchronize()
+        got = loss.cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * np.abs(ref).max())
+        assert int(amin.item()) == int(np.argmin(got))
