@@ -157,11 +157,96 @@ __global__ __launch_bounds__(256) void router_mfma_kernel(const uint4* __restric
   }
 }
 
+// The same for few tokens, where a wavefront's serial walk over H is all there is (11 us for one token of H = 4096, 27 for
+// 777, however many there are): two wavefronts share the 16 tokens, one takes the even slices (acc0 above), the other the odd ones (acc1), each with
+// 32 slices' loads in flight, and their sums are added at the end -- the sums of the kernel above, bit for bit.
+template <bool PACK, bool WIDE>
+__global__ __launch_bounds__(256) void router_few_kernel(const uint4* __restrict__ x, const uint4* __restrict__ Wgate,
+                                                         float* __restrict__ logits, int64_t T, int E, int H,
+                                                         uint4* __restrict__ xpacked) {
+  constexpr int B = WIDE ? 8 : 16;                        // slices per batch, two batches in registers
+  __shared__ r_f32x4 odd[2][WIDE ? 2 : 1][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int pair = wave >> 1, parity = wave & 1;
+  const int64_t t0 = ((int64_t)blockIdx.x * 2 + pair) * 16;
+  const bool active = t0 < (PACK ? (T + 255) / 256 * 256 : T);
+  const int row = lane & 15, kg = lane >> 4;
+  const int chunks = H / 8;
+  const int64_t t = t0 + row < T ? t0 + row : T - 1;
+  const uint4* xp = x + t * chunks + kg + parity * 4;
+  const int p_row = (int)((t0 + row) & 255);
+  uint4* const dst = PACK ? xpacked + ((t0 >> 8) * (int64_t)(H / 32) + parity) * 1024 + p_row * 4 + (kg ^ ((p_row >> 2) & 3)) : nullptr;
+  const bool w_valid = row < E, w2_valid = WIDE && 16 + row < E;
+  const uint4* wp = Wgate + (int64_t)(w_valid ? row : 0) * chunks + kg + parity * 4;
+  const uint4* wp2 = Wgate + (int64_t)(w2_valid ? 16 + row : 0) * chunks + kg + parity * 4;
+  const int n = (H / 32 - parity + 1) / 2;                // slices of this parity: parity, parity + 2, ...
+  r_f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc2 = acc0;
+  uint4 xv[2][B], wv[2][B], wv2[2][WIDE ? B : 1];
+  auto fetch = [&](int set, int i0) {
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      const bool in = i0 + i < n;
+      xv[set][i] = in ? xp[(int64_t)(i0 + i) * 8] : make_uint4(0, 0, 0, 0);
+      wv[set][i] = (in && w_valid) ? wp[(int64_t)(i0 + i) * 8] : make_uint4(0, 0, 0, 0);
+      if (WIDE) wv2[set][i] = (in && w2_valid) ? wp2[(int64_t)(i0 + i) * 8] : make_uint4(0, 0, 0, 0);
+    }
+  };
+  auto use = [&](int set, int i0) {
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      if (PACK && i0 + i < n) dst[(int64_t)(i0 + i) * 2048] = xv[set][i];
+      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[set][i]),
+                                                     __builtin_bit_cast(r_bf16x8, wv[set][i]), acc0, 0, 0, 0);
+      if (WIDE)
+        acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[set][i]),
+                                                       __builtin_bit_cast(r_bf16x8, wv2[set][i]), acc2, 0, 0, 0);
+    }
+  };
+  if (active) {
+    fetch(0, 0);
+    for (int i0 = 0; i0 < n; i0 += 2 * B) {
+      fetch(1, i0 + B);
+      use(0, i0);
+      fetch(0, i0 + 2 * B);
+      use(1, i0 + B);
+    }
+  }
+  if (parity == 1) {
+    odd[pair][0][lane] = acc0;
+    if (WIDE) odd[pair][WIDE ? 1 : 0][lane] = acc2;
+  }
+  __syncthreads();
+  if (parity == 1 || !active) return;
+  const r_f32x4 o0 = odd[pair][0][lane], o2 = odd[pair][WIDE ? 1 : 0][lane];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int64_t tt = t0 + 4 * kg + v;
+    if (tt < T && row < E) logits[tt * E + row] = acc0[v] + o0[v];
+    if (WIDE && tt < T && 16 + row < E) logits[tt * E + 16 + row] = acc2[v] + o2[v];
+  }
+}
+
+// Up to this many tokens the two-wavefront form is the faster one; beyond it there are wavefronts enough to hide the loads.
+// E 8, H 4096, us: 48 tokens 21 -> 16, 4096 27 -> 17, 8192 27 -> 24, 16384 38 -> 43; with the packed copy of x: 2048 tokens
+// 44 -> 22, 16384 99 -> 93 (H 1024: 25 -> 21), 32768 155 -> 140 (H 1024: 40 -> 42).
+constexpr int64_t ROUTER_FEW_MAX = 8192, ROUTER_FEW_MAX_PACK = 16384;
+
 bool mfma_router_applies(int E, int H) { return E <= 32 && H % 32 == 0; }
 
 template <bool PACK>
 void launch_mfma(const void* x, const void* Wgate, int64_t T, int E, int H, float* logits, void* xpacked,
                  int64_t blocks, hipStream_t s) {
+  if (T <= (PACK ? ROUTER_FEW_MAX_PACK : ROUTER_FEW_MAX)) {
+    const dim3 grid((unsigned)(2 * blocks));              // 32 tokens per workgroup instead of 64
+    if (E > 16)
+      hipLaunchKernelGGL((router_few_kernel<PACK, true>), grid, dim3(256), 0, s, (const uint4*)x, (const uint4*)Wgate,
+                         logits, T, E, H, (uint4*)xpacked);
+    else
+      hipLaunchKernelGGL((router_few_kernel<PACK, false>), grid, dim3(256), 0, s, (const uint4*)x, (const uint4*)Wgate,
+                         logits, T, E, H, (uint4*)xpacked);
+    return;
+  }
   if (E > 16)
     hipLaunchKernelGGL((router_mfma_kernel<PACK, true>), dim3((unsigned)blocks), dim3(256), 0, s, (const uint4*)x,
                        (const uint4*)Wgate, logits, T, E, H, (uint4*)xpacked);
