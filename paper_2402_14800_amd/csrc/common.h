@@ -175,12 +175,12 @@ int launch_gemm_bf16_packed(const PackedGemmArgs& g, hipStream_t s, const char* 
 // ---- bf16 GEMM for few rows per expert (gemm_few.hip) -----------------------------------
 constexpr int FEW_ROWS = 64;     // rows per tile of its grouped map
 // Up to this many rows per expert the read of the weights bounds the layer and gemm_few.hip is the faster path; beyond
-// it its 64-row tiles read them from the caches too often.  Dense calls: exactly; routed calls: on average, a token's k
-// slots spread over the kept experts and none skipped.  Few-rows path against 256-row tiles, packed weights, us per call:
-// Mixtral shape (E 8, H 4096, F 14336), top-2, T = 128 / 192 (32 / 48 rows): 586 / 766 against 733 / 741, and with six
-// experts kept, T = 160 (53 rows): 778 against 629; layer of E 16, H 2048, F 5632, dense, T = 16 / 48: 382 / 573 against
-// 531 / 560.
-constexpr int64_t FEW_MAX_AVERAGE = 32;
+// it its 64-row tiles read A and the weights from the caches too often.  Dense calls: exactly; routed calls: on average, a
+// token's k slots spread over the kept experts and none skipped.  Few-rows path against 256-row tiles, us per call:
+// Mixtral shape (E 8, H 4096, F 14336), top-2, packed, T = 200 / 256 (50 / 64 rows): 639 / 691 against 679 / 676, row-major
+// 710 / 762 against 817 / 816; dense, row-major, 48 rows 764 against 904, packed, 64 rows 782 against 695;
+// layer of E 16, H 2048, F 5632, dense, packed, 32 / 64 rows: 309 / 414 against 376 / 381.
+constexpr int64_t FEW_MAX_AVERAGE = 48;
 struct FewGemmArgs {
   const void* X = nullptr;       // row-major rows of A, leading dimension ldx
   int64_t ldx = 0;

@@ -5,23 +5,25 @@
 // bound: one token leaves most compute units without a tile (the down projection of 4096 x 14336 has 16 tiles per
 // expert, each a serial walk over 448 slices: 251 us for one token), and the padding rows are multiplied all the same.
 //
-// Here a weight element goes from memory straight into the register of the one wavefront that multiplies it; nothing is
-// staged in LDS and nothing is shared, so there is no barrier in the loop.  A wavefront takes 32 output columns (gate/up:
+// Here a weight element goes from memory through a wavefront's own LDS ring into the register of the one wavefront that
+// multiplies it; nothing is shared, so there is no barrier in the loop.  A wavefront takes 32 output columns (gate/up:
 // 32 gate and the 32 up rows of the same columns) x up to 64 rows and walks every KS-th pair of 32-deep slices; the KS
-// wavefronts that share the columns add their partial sums in LDS, in a fixed order, at the end.  KS is chosen so that about 2048
-// wavefronts are in flight (8 per compute unit, each with 4 to 24 KB of loads outstanding).
-// Rows of A (x through a token list, or h) are read as MFMA fragments from L1/L2: they are a few hundred KB, shared by all.
+// wavefronts that share the columns add their partial sums in LDS, in a fixed order, at the end.  KS is chosen so that
+// about 2048 wavefronts are launched (8192 measured slower); 8 of them fit a compute unit with their rings, 64 to 128 KB
+// of loads in flight.  Rows of A (x through a token list, or h) are read as MFMA fragments from L1/L2: a few hundred KB.
 //
-// Weights come either as the caller stores them (row-major [N, K]) or in the blocked layout of moe_pack_weights;
-// the same 16-row fragments, the same slices in the same order, so both give the same bits.  A packed fragment is 1 KB of
-// consecutive bytes, a row-major pair of slices is one whole 128-byte line of each of 16 rows.
-// (weights row-major: 4.3 TB/s, whose loads ask for 64 bytes of 16 rows at a time; with the non-temporal hint, which the
-// packed weights are read with, 3.8).
-// Measured, skipping forward of the Mixtral shape (E 8, H 4096, F 14336) on packed weights, before and after: one token
-// 359 -> 88 us, 16 tokens (all 2.8 GB of weights) 720 -> 447 us = 6.3 TB/s; row-major weights, which needed a packing pass
-// over all of them per call: 1842 -> 646 us for 16 tokens, 1486 -> 133 us for one.
+// Weights come either as the caller stores them (row-major [N, K]) or in the blocked layout of moe_pack_weights; the same
+// 16-row fragments, the same slices in the same order, so both give the same bits.  Every load is 1 KB straight into LDS:
+// packed, a fragment's consecutive bytes; row-major, whole 128-byte lines of 8 rows.  (Fragment-shaped loads into registers
+// ask for 64 bytes of 16 rows: row-major weights then came at 4.3 TB/s instead of 5.4; and from 64 rows on, the registers
+// that the ring saves are worth 10 % on packed weights too.)
+// Measured, skipping forward of the Mixtral shape (E 8, H 4096, F 14336) against the 256-row tiles: packed weights, one
+// token 359 -> 82 us, 16 tokens (all 2.8 GB of weights) 720 -> 440 us = 6.4 TB/s, 128 tokens 733 -> 518 us; row-major
+// weights, which needed a packing pass over all of them per call: 1486 -> 92 us, 1842 -> 526 us, 1860 -> 587 us.
 // With KS = 1 the products are also summed in the order of gemm_packed_kernel (one v_mfma_f32_16x16x32_bf16 per slice,
 // slices ascending), bit for bit: the entry points that store every expert output rely on that and always use KS = 1.
+#include <atomic>
+
 #include "common.h"
 
 namespace moep {
@@ -35,6 +37,8 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 constexpr int SLICE = 256 * 64;     // bytes of one packed block (256 rows x 32 k), see gemm_bf16_packed.hip
 constexpr int MAX_WAVES = 8;
+constexpr int RING_BYTES = 16384;   // LDS of a wavefront's load ring
+constexpr double STREAM_BYTES = 192e6;   // weights of a launch from which they are streamed
 constexpr int WANT_WAVES = 2048;    // wavefronts a launch is split into, about
 
 struct FewArgs {
@@ -47,6 +51,7 @@ struct FewArgs {
   int64_t c_expert_rows;              // dense
   int N, nsl;                         // output columns; K / 32
   int ks;                             // wavefronts per group of 32 columns
+  bool stream;                        // non-temporal weight loads
   // grouped: tile t = rows tile_row0[t] .. seg_end[tile_expert[t]] - 1, at most FEW_ROWS of them
   const int32_t* tile_expert; const int32_t* tile_row0; const int32_t* seg_end; const int32_t* tiles_in_use;
   // dense: tile t = rows (t % row_tiles) * FEW_ROWS .. of expert t / row_tiles
@@ -56,11 +61,10 @@ struct FewArgs {
 };
 
 // One tile, M groups of 16 rows (M >= the groups in use; rows beyond row_end repeat the last one and are not stored).
-template <int EPI, bool PACKED, int M>
+template <int EPI, bool PACKED, int M, bool STREAM>
 __device__ __forceinline__ void few_tile(const FewArgs& p, int expert, int64_t row0, int64_t row_end, float* lds) {
   constexpr int NF = EPI == EPI_SWIGLU ? 4 : 2;      // weight fragments of 16 rows: (gate, up) x 2 or 2
-  // pairs of slices held in registers (all but the one being multiplied are in flight)
-  constexpr int D = EPI == EPI_SWIGLU ? (M >= 4 ? 2 : 3) : 4;
+  constexpr int D = RING_BYTES / (NF * 2048);        // pairs of slices in the ring (all but the one being multiplied are in flight)
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int ks = p.ks;
@@ -72,7 +76,6 @@ __device__ __forceinline__ void few_tile(const FewArgs& p, int expert, int64_t r
   // Weight fragments.  Row f of fragment b of a group of 32 columns is column 8 (f >> 2) + 4 b + (f & 3), so that a lane
   // of the (transposed) result tiles holds 8 consecutive columns; the blocked layout stores the rows in that order.
   const char* wp[NF];
-  int64_t wstep;                                     // bytes from a slice to the next
   if (PACKED) {
     const int c = in_range ? n0 : 0;
     const int tile = EPI == EPI_SWIGLU ? c >> 7 : c >> 8;
@@ -80,18 +83,16 @@ __device__ __forceinline__ void few_tile(const FewArgs& p, int expert, int64_t r
     const char* base = p.W0 + (int64_t)expert * p.w_expert_bytes + (int64_t)tile * p.nsl * SLICE;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
-      const int row = r0 + (f & 1) * 16 + lrow + (EPI == EPI_SWIGLU && f >= 2 ? 128 : 0);
-      wp[f] = base + row * 64 + ((kg ^ ((row >> 2) & 3)) << 4);
+      wp[f] = base + (r0 + (f & 1) * 16 + (EPI == EPI_SWIGLU && f >= 2 ? 128 : 0)) * 64 + lane * 16;
     }
-    wstep = SLICE;
   } else {
-    const int c = (in_range ? n0 : 0) + 8 * (lrow >> 2) + (lrow & 3);
-    const int64_t pitch = (int64_t)p.nsl * 64;
+    // Loads bring whole 128-byte lines (a pair of slices) of 8 rows each: lane l the chunk (l % 8) ^ (l / 8) of fragment row
+    // l / 8 (and, 16 columns further, of row 8 + l / 8).  In LDS a fragment row is 128 bytes, chunk c at position c ^ (row % 8).
+    const int c = (in_range ? n0 : 0) + 8 * (lane >> 5) + ((lane >> 3) & 3);
 #pragma unroll
     for (int f = 0; f < NF; ++f)
-      wp[f] = (EPI == EPI_SWIGLU && f >= 2 ? p.W1 : p.W0) + (int64_t)expert * p.w_expert_bytes + (c + 4 * (f & 1)) * pitch +
-              kg * 16;
-    wstep = 64;
+      wp[f] = (EPI == EPI_SWIGLU && f >= 2 ? p.W1 : p.W0) + (int64_t)expert * p.w_expert_bytes +
+              (int64_t)(c + 4 * (f & 1)) * p.nsl * 64 + (((lane & 7) ^ (lane >> 3)) << 4);
   }
   const char* xp[M];
 #pragma unroll
@@ -111,38 +112,63 @@ __device__ __forceinline__ void few_tile(const FewArgs& p, int expert, int64_t r
 
   const int pairs = p.nsl >> 1;                      // K is a multiple of 64
   const int n = kpart < pairs ? (pairs - kpart + ks - 1) / ks : 0;    // pairs of this wavefront: kpart, kpart + ks, ...
-  bf16x8 w[D][2][NF], xv[D][2][M];
+  bf16x8 w[2][NF], xv[D][2][M];
+  typedef __attribute__((address_space(3))) char lds_char;
+  typedef const __attribute__((address_space(1))) void* gptr_t;
+  lds_char* const ring3 = (lds_char*)lds + wave * RING_BYTES;
+  const char* const ring = (const char*)lds + wave * RING_BYTES;
   // (past its last pair a wavefront re-reads that one: in bounds, and the number of loads in flight is always the same)
   auto fetch = [&](int slot, int i) {
     const int s = 2 * (kpart + ks * (i < n ? i : n - 1));
+    // 1 KB per load: packed, a fragment of slice s + j; row-major, both slices of 8 rows of a fragment
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int f = 0; f < NF; ++f)
 #pragma unroll
-      for (int f = 0; f < NF; ++f) w[slot][u][f] = PACKED ? __builtin_nontemporal_load((const bf16x8*)(wp[f] + (s + u) * wstep))
-                                                                         : *(const bf16x8*)(wp[f] + (s + u) * wstep);
+      for (int j = 0; j < 2; ++j)
+        __builtin_amdgcn_global_load_lds(
+            (gptr_t)(wp[f] + (PACKED ? (int64_t)(s + j) * SLICE : (int64_t)s * 64 + (int64_t)j * 16 * p.nsl * 64)),
+            (__attribute__((address_space(3))) void*)(ring3 + slot * (NF * 2048) + f * 2048 + j * 1024), 16, 0, STREAM ? 2 : 0);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int m = 0; m < M; ++m) xv[slot][u][m] = *(const bf16x8*)(xp[m] + (int64_t)(s + u) * 64);
-    }
   };
+  // where a lane's 16 bytes of slice u of a fragment lie in the ring
+  const int frag_at[2] = {PACKED ? lrow * 64 + ((kg ^ ((lrow >> 2) & 3)) << 4) : lrow * 128 + ((kg ^ (lrow & 7)) << 4),
+                          PACKED ? 1024 + lrow * 64 + ((kg ^ ((lrow >> 2) & 3)) << 4) : lrow * 128 + (((4 + kg) ^ (lrow & 7)) << 4)};
+  // s_waitcnt vmcnt: all but the loads of the D - 1 newest fetches have landed (they complete in issue order)
+  constexpr int VM = (D - 1) * (2 * NF + 2 * M);
+  static_assert(VM < 64, "more loads in flight than the counter holds");
+  constexpr int W_VM = 0x0f70 | (VM & 15) | ((VM >> 4) << 14);
   if (in_range && n > 0) {
 #pragma unroll
     for (int d = 0; d < D - 1; ++d) fetch(d, d);
     for (int i0 = 0; i0 < n; i0 += D) {
 #pragma unroll
       for (int d = 0; d < D; ++d) {
+        __builtin_amdgcn_sched_barrier(0);   // (the slot's last fragments have been read)
         fetch((d + D - 1) % D, i0 + d + D - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(W_VM);
+        __builtin_amdgcn_sched_barrier(0);
         if (i0 + d < n) {
 #pragma unroll
-          for (int u = 0; u < 2; ++u)
+          for (int u = 0; u < 2; ++u) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+              w[u][f] = *(const bf16x8*)(ring + d * (NF * 2048) + f * 2048 + frag_at[u]);
 #pragma unroll
             for (int f = 0; f < NF; ++f)
 #pragma unroll
               for (int m = 0; m < M; ++m)
-                acc[f][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[d][u][f], xv[d][u][m], acc[f][m], 0, 0, 0);
+                acc[f][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][f], xv[d][u][m], acc[f][m], 0, 0, 0);
+          }
         }
       }
     }
   }
+  __builtin_amdgcn_s_waitcnt(0x0070);    // the re-reads still in flight target this workgroup's LDS, which the sums below reuse
+  if (ks > 1) __syncthreads();
   // Sum over the ks wavefronts of a column group, halving: the upper half hands its sums to the lower half.
   for (int half = ks >> 1; half >= 1; half >>= 1) {
     float* const mine = lds + ((wave / ks) * half + (kpart % half)) * (NF * M * 256) + lane * 4;
@@ -223,16 +249,42 @@ __global__ __launch_bounds__(64 * MAX_WAVES) void gemm_few_kernel(FewArgs p) {
   }
   if (row_end > row0 + FEW_ROWS) row_end = row0 + FEW_ROWS;
   const int rows = (int)(row_end - row0);
-  if (MMAX == 1 || rows <= 16) few_tile<EPI, PACKED, 1>(p, expert, row0, row_end, few_lds);
-  else if (MMAX == 2 || rows <= 32) few_tile<EPI, PACKED, 2>(p, expert, row0, row_end, few_lds);
-  else few_tile<EPI, PACKED, 4>(p, expert, row0, row_end, few_lds);
+#define MOEP_FEW_TILE(M)                                                        \
+  do {                                                                          \
+    if (p.stream) few_tile<EPI, PACKED, M, true>(p, expert, row0, row_end, few_lds);  \
+    else few_tile<EPI, PACKED, M, false>(p, expert, row0, row_end, few_lds);          \
+  } while (0)
+  if (MMAX == 1 || rows <= 16) MOEP_FEW_TILE(1);
+  else if (MMAX == 2 || rows <= 32) MOEP_FEW_TILE(MMAX < 2 ? 1 : 2);
+  else MOEP_FEW_TILE(MMAX < 4 ? 1 : 4);
+#undef MOEP_FEW_TILE
+}
+
+// Dynamic LDS beyond 64 KB has to be allowed per kernel and device, once (bit d: done on device d; a second thread that
+// does it as well does no harm).
+template <int EPI, bool PACKED, int MMAX>
+int launch_m(const FewArgs& a, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  static std::atomic<uint64_t> allowed{0};
+  if (lds > 64 * 1024) {
+    int dev = 0;
+    MOEP_HIP(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 64) return fail(MOEP_EUNSUPPORTED, "device ordinal %d beyond 63", dev);
+    if (!(allowed.load() >> dev & 1)) {
+      MOEP_HIP(hipFuncSetAttribute((const void*)gemm_few_kernel<EPI, PACKED, MMAX>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, MAX_WAVES * RING_BYTES));
+      allowed.fetch_or((uint64_t)1 << dev);
+    }
+  }
+  hipLaunchKernelGGL((gemm_few_kernel<EPI, PACKED, MMAX>), grid, dim3(threads), lds, s, a);
+  MOEP_HIP(hipGetLastError());
+  return MOEP_OK;
 }
 
 template <int EPI, bool PACKED>
-void launch(const FewArgs& a, int mmax, dim3 grid, int threads, size_t lds, hipStream_t s) {
-  if (mmax == 1) hipLaunchKernelGGL((gemm_few_kernel<EPI, PACKED, 1>), grid, dim3(threads), lds, s, a);
-  else if (mmax == 2) hipLaunchKernelGGL((gemm_few_kernel<EPI, PACKED, 2>), grid, dim3(threads), lds, s, a);
-  else hipLaunchKernelGGL((gemm_few_kernel<EPI, PACKED, 4>), grid, dim3(threads), lds, s, a);
+int launch(const FewArgs& a, int mmax, dim3 grid, int threads, size_t lds, hipStream_t s) {
+  if (mmax == 1) return launch_m<EPI, PACKED, 1>(a, grid, threads, lds, s);
+  if (mmax == 2) return launch_m<EPI, PACKED, 2>(a, grid, threads, lds, s);
+  return launch_m<EPI, PACKED, 4>(a, grid, threads, lds, s);
 }
 
 }  // namespace
@@ -266,25 +318,28 @@ int launch_gemm_few(const FewGemmArgs& g, hipStream_t s, const char* name) {
   if (g.split_k)
     while (ks < MAX_WAVES && (int64_t)units * g.busy_tiles * ks < WANT_WAVES && g.K / 64 >= 8 * ks) ks *= 2;
   a.ks = ks;
+  // Weights far beyond the caches are read with the non-temporal hint, a layer that may still be cached is not.
+  // Non-temporal against plain, forward: Mixtral shape, 16 tokens, packed 440 / 489 us, row-major 526 / 573; E 8, H 1024,
+  // F 3584 (176 MB in all), 16 tokens, called again and again: 52 / 49.
+  a.stream = (double)g.N * g.K * 2.0 * (g.epilogue == EPI_SWIGLU ? 2.0 : 1.0) * (grouped ? (double)g.busy_tiles : (double)g.experts) > STREAM_BYTES;
   const int waves = ks > 4 ? ks : 4;
   const dim3 grid((unsigned)ceil_div(units, waves / ks), (unsigned)tiles);
-  const size_t lds = ks > 1 ? (size_t)(waves / ks) * (ks / 2) * (g.epilogue == EPI_SWIGLU ? 4 : 2) * mmax * 1024 : 0;
+  const size_t sums = ks > 1 ? (size_t)(waves / ks) * (ks / 2) * (g.epilogue == EPI_SWIGLU ? 4 : 2) * mmax * 1024 : 0;
+  const size_t ring = (size_t)waves * RING_BYTES;
+  const size_t lds = sums > ring ? sums : ring;
   Timed t(name, s);
   if (g.packed) {
     switch (g.epilogue) {
-      case EPI_STORE: launch<EPI_STORE, true>(a, mmax, grid, waves * 64, lds, s); break;
-      case EPI_SWIGLU: launch<EPI_SWIGLU, true>(a, mmax, grid, waves * 64, lds, s); break;
-      default: launch<EPI_ROWSCALE_F32, true>(a, mmax, grid, waves * 64, lds, s); break;
-    }
-  } else {
-    switch (g.epilogue) {
-      case EPI_STORE: launch<EPI_STORE, false>(a, mmax, grid, waves * 64, lds, s); break;
-      case EPI_SWIGLU: launch<EPI_SWIGLU, false>(a, mmax, grid, waves * 64, lds, s); break;
-      default: launch<EPI_ROWSCALE_F32, false>(a, mmax, grid, waves * 64, lds, s); break;
+      case EPI_STORE: return launch<EPI_STORE, true>(a, mmax, grid, waves * 64, lds, s);
+      case EPI_SWIGLU: return launch<EPI_SWIGLU, true>(a, mmax, grid, waves * 64, lds, s);
+      default: return launch<EPI_ROWSCALE_F32, true>(a, mmax, grid, waves * 64, lds, s);
     }
   }
-  MOEP_HIP(hipGetLastError());
-  return MOEP_OK;
+  switch (g.epilogue) {
+    case EPI_STORE: return launch<EPI_STORE, false>(a, mmax, grid, waves * 64, lds, s);
+    case EPI_SWIGLU: return launch<EPI_SWIGLU, false>(a, mmax, grid, waves * 64, lds, s);
+    default: return launch<EPI_ROWSCALE_F32, false>(a, mmax, grid, waves * 64, lds, s);
+  }
 }
 
 }  // namespace moep

@@ -24,15 +24,15 @@ def bits(t):
     (8, 576, 1024, 17, 0xff),          # a second group of 16 rows, an odd number of slice pairs
     (4, 4096, 64, 33, 0xf),            # eight wavefronts share a column group in one projection only
     (8, 64, 2112, 63, 0xff),           # one slice pair: no split
-    (8, 256, 512, 32, 0b10000010),     # 32 rows for each of two experts
-    (8, 128, 256, 128, 0xff),          # the last batch of the few-rows path, and the first beyond it
-    (8, 128, 256, 129, 0xff),
+    (8, 256, 512, 47, 0b10000010),     # 47 rows for each of two experts
+    (8, 128, 256, 192, 0xff),          # the last batch of the few-rows path, and the first beyond it
+    (8, 128, 256, 193, 0xff),
     (32, 64, 128, 511, 0xffffffff),    # around the largest batch of the one-workgroup dispatch
     (32, 64, 128, 513, 0xffffffff),
 ])
 def test_forward_with_few_rows_matches_oracle(E, H, F, T, kept):
     _, layer = small_layer("bf16", E, 2, H, F, T, index=21)
-    if T == 128:                       # all tokens alike: two experts get 128 rows each, three tiles of 64 rows and less
+    if T == 192:                       # all tokens alike: two experts get 192 rows each, three tiles of 64 rows
         layer["x"][:] = layer["x"][0] * (1 + torch.arange(T)[:, None] % 3).to(layer["x"].dtype)
     d = to_dev(layer)
     beta = 0.6
@@ -62,7 +62,7 @@ def test_topk_forward_with_few_rows_matches_oracle(E, H, F, T, k):
     check_outputs(wl.to_f64(out), ref, "out")
 
 
-@pytest.mark.parametrize("E,H,F,T", [(8, 128, 192, 1), (3, 576, 320, 17), (8, 64, 64, 31), (20, 128, 64, 32), (5, 256, 512, 33)])
+@pytest.mark.parametrize("E,H,F,T", [(8, 128, 192, 1), (3, 576, 320, 17), (8, 64, 64, 47), (20, 128, 64, 48), (5, 256, 512, 49), (4, 2048, 6144, 33)])
 def test_expert_outputs_of_few_rows_are_those_of_many(E, H, F, T):
     """A token's expert outputs do not depend on the size of the batch, on who packed the weights, or on whether the
     rank-limited pass computed them: the products are summed in the same order everywhere."""
