@@ -3,15 +3,16 @@
 // (256-row M tiles) are those of the bf16 kernel.
 //
 // Bound by the fp32 matrix rate (157 TFLOP/s nominal; 109 reached at 6000 tokens) where there are tiles for the chip, by the
-// serial walk over K where there are not.  A workgroup of 256 threads owns 64 (few tiles: 32) rows x 128 accumulator columns
-// (gate/up: 64 columns of either branch) and walks K in slabs of 32 through two LDS buffers: the next slab is in flight
-// in registers while the current one is multiplied, one barrier per slab (two slabs in flight: 3 % slower).  The tiles are
-// small because the layers are: a dense pass takes as many experts per launch as its scratch room allows for the same reason.
+// serial walk over K where there are not.  A workgroup of 256 threads owns 64 rows x 128 accumulator columns (gate/up: 64
+// columns of either branch; few tiles: 32 x 128, then 32 x 64) and walks K in slabs of 32 through two LDS buffers: the next
+// slab is in flight in registers while the current one is multiplied, one barrier per slab (two slabs in flight: 3 %
+// slower).  The tiles are small because the layers are: a dense pass takes as many experts per launch as its scratch room
+// allows for the same reason.
 // A row of a slab is 128 bytes in LDS, its 16-byte chunk c at position c ^ (row & 7), so that the fragment reads (16 rows
 // apart 128 bytes) are free of bank conflicts.  A lane reads 4 consecutive k as one 16-byte word; element j of it feeds
 // MFMA j, for both operands alike, so the four MFMAs of 16 k-values sum k = j, 4 + j, 8 + j, 12 + j.
 // Measured, all experts, E 8, H 512, F 1024, against the plain-FMA kernel with 64 x 64 tiles that this replaces: T = 64
-// 1356 -> 241 us, 1501 1369 -> 477, 6000 2284 -> 1383; E 4, H 64, F 128, T = 512: 109 -> 39 us.
+// 1356 -> 164 us, 1501 1369 -> 454, 6000 2284 -> 1376; E 4, H 64, F 128, T = 512: 109 -> 36 us.
 // A row's sum depends on K only, so a token's outputs do not depend on the batch or on the tile.
 #include "common.h"
 
@@ -20,7 +21,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-constexpr int TB = 128, TK = 32, THREADS = 256;            // accumulator columns, k per slab
+constexpr int TK = 32, THREADS = 256;                      // k per slab
 
 struct FArgs {
   const float* A; const float* B0; const float* B1;
@@ -34,9 +35,9 @@ struct FArgs {
   int N, K;
 };
 
-template <int EPI, int TM>    // TM = rows per tile
+template <int EPI, int TM, int TB>    // TM = rows, TB = accumulator columns per tile
 __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
-  constexpr int RT = TM / 32;                              // 16-row tiles of a wavefront = rows staged per thread
+  constexpr int RT = TM / 32, CT = TB / 32;                // 16-row and 16-column tiles of a wavefront = rows staged per thread
   constexpr int SLAB = (TM + TB) * TK;                     // floats of one LDS buffer
   constexpr int TN = EPI == EPI_SWIGLU ? TB / 2 : TB;      // output columns
   __shared__ __attribute__((aligned(16))) float lds[2][SLAB];
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
   // one repeat it (their products are not stored), chunks beyond K are zero
   const int sr = tid >> 3, sc = tid & 7;
   const float* ap[RT];
-  const float* bp[4];
+  const float* bp[CT];
 #pragma unroll
   for (int i = 0; i < RT; ++i) {
     int64_t r = row0 + sr + 32 * i;
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
     ap[i] = A + (p.a_rows ? (int64_t)p.a_rows[r] : r) * p.lda + sc * 4;
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < CT; ++i) {
     const int br = sr + 32 * i;
     const float* base = EPI == EPI_SWIGLU && br >= TN ? B1 : B0;
     int n = n0 + (EPI == EPI_SWIGLU ? br % TN : br);
@@ -83,27 +84,27 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
     bp[i] = base + (int64_t)n * p.K + sc * 4;
   }
   const int spos = sr * TK + ((sc ^ (sr & 7)) << 2);       // (rows 32 apart keep the position)
-  f32x4 ga[RT], gb[4];
+  f32x4 ga[RT], gb[CT];
   auto fetch = [&](int k0) {
     const bool in = k0 + sc * 4 < p.K;                     // K is a multiple of 4
 #pragma unroll
     for (int i = 0; i < RT; ++i) ga[i] = in ? *(const f32x4*)(ap[i] + k0) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) gb[i] = in ? *(const f32x4*)(bp[i] + k0) : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < CT; ++i) gb[i] = in ? *(const f32x4*)(bp[i] + k0) : f32x4{0.f, 0.f, 0.f, 0.f};
   };
   auto put = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < RT; ++i) *(f32x4*)(&lds[buf][spos + 32 * i * TK]) = ga[i];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) *(f32x4*)(&lds[buf][TM * TK + spos + 32 * i * TK]) = gb[i];
+    for (int i = 0; i < CT; ++i) *(f32x4*)(&lds[buf][TM * TK + spos + 32 * i * TK]) = gb[i];
   };
 
   const int frow = lane & 15, fg = lane >> 4;
-  f32x4 acc[RT][4];
+  f32x4 acc[RT][CT];
 #pragma unroll
   for (int i = 0; i < RT; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < CT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int slabs = (p.K + TK - 1) / TK;
   fetch(0);
@@ -115,12 +116,12 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
 #pragma unroll
     for (int h = 0; h < TK / 16; ++h) {
       const int pos = ((4 * h + fg) ^ (frow & 7)) << 2;    // (fragment rows are 16 apart: the same position in all)
-      f32x4 fa[RT], fb[4];
+      f32x4 fa[RT], fb[CT];
 #pragma unroll
       for (int i = 0; i < RT; ++i) fa[i] = *(const f32x4*)(buf + (wm * (TM / 2) + i * 16 + frow) * TK + pos);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = EPI == EPI_SWIGLU ? (j >> 1) * TN + wn * 32 + (j & 1) * 16 : wn * 64 + j * 16;
+      for (int j = 0; j < CT; ++j) {
+        const int r = EPI == EPI_SWIGLU ? (j / (CT / 2)) * TN + wn * (TN / 2) + (j % (CT / 2)) * 16 : wn * (TB / 2) + j * 16;
         fb[j] = *(const f32x4*)(buf + TM * TK + (r + frow) * TK + pos);
       }
 #pragma unroll
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+          for (int j = 0; j < CT; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][e], fa[i][e], acc[i][j], 0, 0, 0);
     }
     if (s + 1 < slabs) put((s + 1) & 1);                   // (that buffer was last read before the previous barrier)
@@ -142,14 +143,14 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
     if (r >= row_end) continue;
     const float scale = EPI == EPI_ROWSCALE_F32 ? p.row_scale[r] : 1.0f;
 #pragma unroll
-    for (int j = 0; j < (EPI == EPI_SWIGLU ? 2 : 4); ++j) {
-      const int n = n0 + (EPI == EPI_SWIGLU ? wn * 32 : wn * 64) + j * 16 + fg * 4;
+    for (int j = 0; j < (EPI == EPI_SWIGLU ? CT / 2 : CT); ++j) {
+      const int n = n0 + wn * (TN / 2) + j * 16 + fg * 4;
       if (n >= p.N) continue;                              // N is a multiple of 4
       f32x4 o;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         float x = acc[i][j][v];
-        if (EPI == EPI_SWIGLU) x = x / (1.0f + expf(-x)) * acc[i][j + 2][v];
+        if (EPI == EPI_SWIGLU) x = x / (1.0f + expf(-x)) * acc[i][CT / 2 + j][v];
         if (EPI == EPI_ROWSCALE_F32) x *= scale;
         o[v] = x;
       }
@@ -158,8 +159,10 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
   }
 }
 
-// (two 64-row tiles per compute unit; T 1501 of the layer above: 477 us with the line at 512 tiles, 551 us without 32-row tiles)
+// (two 64-row tiles per compute unit; T 1501 of the layer above: 470 us with the line at 512 tiles, 551 us without 32-row tiles)
 constexpr int64_t SMALL_TILES_BELOW = 512;
+// (the same line for half the width again: T 64 of that layer 241 -> 164 us, 400 270 -> 227, 1501 470 -> 454; at 256 tiles 464)
+constexpr int64_t NARROW_TILES_BELOW = 512;
 
 }  // namespace
 
@@ -176,16 +179,19 @@ int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name) {
   f.a_expert_stride = g.a_expert_stride; f.c_expert_stride = g.c_expert_stride;
   f.N = g.N; f.K = g.K;
   if (g.experts < 1 || g.experts > 65535 || (g.tile_expert && g.experts != 1)) return fail(MOEP_EINVAL, "%s: bad batch count %d", name, g.experts);
-  const int64_t n_tiles = ceil_div(g.N, g.epilogue == EPI_SWIGLU ? TB / 2 : TB);
   auto m_tiles = [&](int tm) { return g.tile_expert ? g.max_m_tiles * (GEMM_BM / tm) : ceil_div(g.M, tm); };
-  const int tm = m_tiles(64) * n_tiles * g.experts < SMALL_TILES_BELOW ? 32 : 64;
-  if (m_tiles(tm) > 2147483647LL || n_tiles > 65535) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
-  dim3 grid((unsigned)m_tiles(tm), (unsigned)n_tiles, (unsigned)g.experts);
+  auto n_tiles = [&](int tb) { return ceil_div(g.N, g.epilogue == EPI_SWIGLU ? tb / 2 : tb); };
+  // 64 x 128 accumulators per tile, 32 x 128 where those are few, 32 x 64 where these are
+  const int tm = m_tiles(64) * n_tiles(128) * g.experts < SMALL_TILES_BELOW ? 32 : 64;
+  const int tb = tm == 32 && m_tiles(32) * n_tiles(128) * g.experts < NARROW_TILES_BELOW ? 64 : 128;
+  if (m_tiles(tm) > 2147483647LL || n_tiles(tb) > 65535) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
+  dim3 grid((unsigned)m_tiles(tm), (unsigned)n_tiles(tb), (unsigned)g.experts);
   Timed t(name, s);
 #define MOEP_F32_CASE(EPI)                                                                              \
   case EPI:                                                                                             \
-    if (tm == 32) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 32>), grid, dim3(THREADS), 0, s, f);         \
-    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 64>), grid, dim3(THREADS), 0, s, f);                  \
+    if (tb == 64) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 32, 64>), grid, dim3(THREADS), 0, s, f);       \
+    else if (tm == 32) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 32, 128>), grid, dim3(THREADS), 0, s, f); \
+    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 64, 128>), grid, dim3(THREADS), 0, s, f);               \
     break;
   switch (g.epilogue) {
     MOEP_F32_CASE(EPI_STORE) MOEP_F32_CASE(EPI_SWIGLU) MOEP_F32_CASE(EPI_ROWSCALE_F32)

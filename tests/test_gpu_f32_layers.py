@@ -20,8 +20,9 @@ NAMES = ("x", "Wgate", "W1", "W3", "W2")
     (7, 128, 132, 65),      # F just above H, a second tile of one row
     (5, 576, 64, 97),       # h much smaller than the outputs: four experts in a launch
     (2, 4, 260, 130),       # the narrowest H, F = 65 H: a launch per expert
-    (1, 64, 128, 4500),     # enough tiles for 64-row tiles in one projection
-    (8, 192, 128, 1400),    # 64-row tiles in both
+    (8, 192, 128, 1400),    # five experts in a launch, 32 x 64 tiles
+    (8, 192, 128, 3000),    # 32 x 128 tiles
+    (8, 64, 128, 9001),     # 64 x 128 tiles
 ])
 def test_fp32_expert_outputs_at_tile_edges(E, H, F, T):
     _, layer = small_layer("f32", E, 2, H, F, T, index=25)
