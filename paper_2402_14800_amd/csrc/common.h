@@ -208,6 +208,9 @@ struct FewGemmArgs {
   void* direct_out = nullptr;
 };
 int launch_gemm_few(const FewGemmArgs& g, hipStream_t s, const char* name);
+int gemm_few_allow_lds();   // raises the dynamic LDS limit of its kernels on the current device
+// First use of a device by a bf16 expert GEMM: raises the limits of all of them; its compute-unit count.
+int gemm_device_ready(int* compute_units);
 
 // ---- router -------------------------------------------------------------------
 int launch_router(const void* x, const void* Wgate, int64_t T, int E, int H, moep_dtype dt,

@@ -570,36 +570,28 @@ void gemm_packed_kernel(KArgs p) {
   else gemm_body<EPI, GROUPED, BROW, 8>(p);
 }
 
-// Per-device launch state, filled on a device's first launch under a mutex (first calls from several host
-// threads are safe): the compute-unit count, and whether each instantiation's dynamic LDS limit has been raised.
+// Per-device launch state, filled on a device's first launch under a mutex (first calls from several host threads are
+// safe): the compute-unit count, and whether the dynamic LDS limits have been raised.  They are raised for EVERY expert
+// GEMM at once, so that after one call at any size a call at any other only launches (and can be captured).
 constexpr int kMaxDevices = 64;
 struct DeviceState {
   int compute_units = 0;
-  bool attr_set[3][2][2] = {};
+  bool ready = false;
 };
 std::mutex g_dev_mu;
 DeviceState g_dev[kMaxDevices];
 
 template <int EPI, bool GROUPED, bool BROW>
+int allow_lds() {
+  MOEP_HIP(hipFuncSetAttribute((const void*)gemm_packed_kernel<EPI, GROUPED, BROW>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES));
+  return MOEP_OK;
+}
+
+template <int EPI, bool GROUPED, bool BROW>
 int launch(const KArgs& k, hipStream_t s) {
-  int dev = 0, cus = 0;
-  MOEP_HIP(hipGetDevice(&dev));
-  if (dev < 0 || dev >= kMaxDevices) return fail(MOEP_EUNSUPPORTED, "device ordinal %d beyond %d", dev, kMaxDevices - 1);
-  {
-    std::lock_guard<std::mutex> lk(g_dev_mu);
-    DeviceState& d = g_dev[dev];
-    if (!d.compute_units) {
-      int v = 0;
-      MOEP_HIP(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
-      d.compute_units = v > 0 ? v : 256;
-    }
-    if (!d.attr_set[EPI][GROUPED][BROW]) {   // raising the dynamic LDS limit is per function and device, once
-      MOEP_HIP(hipFuncSetAttribute((const void*)gemm_packed_kernel<EPI, GROUPED, BROW>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES));
-      d.attr_set[EPI][GROUPED][BROW] = true;
-    }
-    cus = d.compute_units;
-  }
+  int cus = 0;
+  if (int st = gemm_device_ready(&cus)) return st;
   const int64_t nblk = (int64_t)k.m_tiles * k.n_tiles * k.experts;
   int grid = cus & ~7;                        // one persistent workgroup per compute unit, a multiple of 8
   if (grid < 8) grid = 8;
@@ -623,6 +615,28 @@ int launch_pack(PackArgs p, int64_t tiles, int K, int experts, hipStream_t s, co
 }
 
 }  // namespace
+
+int gemm_device_ready(int* compute_units) {
+  int dev = 0;
+  MOEP_HIP(hipGetDevice(&dev));
+  if (dev < 0 || dev >= kMaxDevices) return fail(MOEP_EUNSUPPORTED, "device ordinal %d beyond %d", dev, kMaxDevices - 1);
+  std::lock_guard<std::mutex> lk(g_dev_mu);
+  DeviceState& d = g_dev[dev];
+  if (!d.ready) {
+    int v = 0;
+    MOEP_HIP(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
+    d.compute_units = v > 0 ? v : 256;
+    for (auto allow : {allow_lds<EPI_STORE, false, false>, allow_lds<EPI_STORE, false, true>, allow_lds<EPI_STORE, true, false>,
+                       allow_lds<EPI_STORE, true, true>, allow_lds<EPI_SWIGLU, false, false>, allow_lds<EPI_SWIGLU, false, true>,
+                       allow_lds<EPI_SWIGLU, true, false>, allow_lds<EPI_SWIGLU, true, true>,
+                       allow_lds<EPI_ROWSCALE_F32, true, false>, allow_lds<EPI_ROWSCALE_F32, true, true>})
+      if (int st = allow()) return st;
+    if (int st = gemm_few_allow_lds()) return st;
+    d.ready = true;
+  }
+  if (compute_units) *compute_units = d.compute_units;
+  return MOEP_OK;
+}
 
 size_t packed_a_bytes(int64_t rows, int K) {
   return (size_t)ceil_div(rows, 256) * 256 * (size_t)K * 2;

@@ -22,8 +22,6 @@
 // weights, which needed a packing pass over all of them per call: 1486 -> 92 us, 1842 -> 526 us, 1860 -> 587 us.
 // With KS = 1 the products are also summed in the order of gemm_packed_kernel (one v_mfma_f32_16x16x32_bf16 per slice,
 // slices ascending), bit for bit: the entry points that store every expert output rely on that and always use KS = 1.
-#include <atomic>
-
 #include "common.h"
 
 namespace moep {
@@ -260,34 +258,36 @@ __global__ __launch_bounds__(64 * MAX_WAVES) void gemm_few_kernel(FewArgs p) {
 #undef MOEP_FEW_TILE
 }
 
-// Dynamic LDS beyond 64 KB has to be allowed per kernel and device, once (bit d: done on device d; a second thread that
-// does it as well does no harm).
 template <int EPI, bool PACKED, int MMAX>
-int launch_m(const FewArgs& a, dim3 grid, int threads, size_t lds, hipStream_t s) {
-  static std::atomic<uint64_t> allowed{0};
-  if (lds > 64 * 1024) {
-    int dev = 0;
-    MOEP_HIP(hipGetDevice(&dev));
-    if (dev < 0 || dev >= 64) return fail(MOEP_EUNSUPPORTED, "device ordinal %d beyond 63", dev);
-    if (!(allowed.load() >> dev & 1)) {
-      MOEP_HIP(hipFuncSetAttribute((const void*)gemm_few_kernel<EPI, PACKED, MMAX>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, MAX_WAVES * RING_BYTES));
-      allowed.fetch_or((uint64_t)1 << dev);
-    }
-  }
-  hipLaunchKernelGGL((gemm_few_kernel<EPI, PACKED, MMAX>), grid, dim3(threads), lds, s, a);
-  MOEP_HIP(hipGetLastError());
+int allow_lds() {
+  MOEP_HIP(hipFuncSetAttribute((const void*)gemm_few_kernel<EPI, PACKED, MMAX>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               MAX_WAVES * RING_BYTES));
+  return MOEP_OK;
+}
+template <int EPI>
+int allow_lds_epilogue() {
+  for (auto allow : {allow_lds<EPI, true, 1>, allow_lds<EPI, true, 2>, allow_lds<EPI, true, 4>, allow_lds<EPI, false, 1>,
+                     allow_lds<EPI, false, 2>, allow_lds<EPI, false, 4>})
+    if (int st = allow()) return st;
   return MOEP_OK;
 }
 
 template <int EPI, bool PACKED>
 int launch(const FewArgs& a, int mmax, dim3 grid, int threads, size_t lds, hipStream_t s) {
-  if (mmax == 1) return launch_m<EPI, PACKED, 1>(a, grid, threads, lds, s);
-  if (mmax == 2) return launch_m<EPI, PACKED, 2>(a, grid, threads, lds, s);
-  return launch_m<EPI, PACKED, 4>(a, grid, threads, lds, s);
+  if (mmax == 1) hipLaunchKernelGGL((gemm_few_kernel<EPI, PACKED, 1>), grid, dim3(threads), lds, s, a);
+  else if (mmax == 2) hipLaunchKernelGGL((gemm_few_kernel<EPI, PACKED, 2>), grid, dim3(threads), lds, s, a);
+  else hipLaunchKernelGGL((gemm_few_kernel<EPI, PACKED, 4>), grid, dim3(threads), lds, s, a);
+  MOEP_HIP(hipGetLastError());
+  return MOEP_OK;
 }
 
 }  // namespace
+
+int gemm_few_allow_lds() {
+  if (int st = allow_lds_epilogue<EPI_STORE>()) return st;
+  if (int st = allow_lds_epilogue<EPI_SWIGLU>()) return st;
+  return allow_lds_epilogue<EPI_ROWSCALE_F32>();
+}
 
 int launch_gemm_few(const FewGemmArgs& g, hipStream_t s, const char* name) {
   if (g.K <= 0 || g.K % 64 || g.N <= 0 || g.N % 32) return fail(MOEP_EUNSUPPORTED, "%s: K=%d, N=%d must be multiples of 64 and 32", name, g.K, g.N);
@@ -298,6 +298,7 @@ int launch_gemm_few(const FewGemmArgs& g, hipStream_t s, const char* name) {
   if (grouped && (!g.tile_row0 || !g.seg_end || !g.tiles_in_use)) return fail(MOEP_EINVAL, "%s: incomplete tile map", name);
   if (g.epilogue == EPI_ROWSCALE_F32 && !g.row_scale) return fail(MOEP_EINVAL, "%s: row_scale is NULL", name);
   if (g.max_rows <= 0) return MOEP_OK;
+  if (int st = gemm_device_ready(nullptr)) return st;
   FewArgs a = {};
   a.W0 = (const char*)g.W0; a.W1 = (const char*)g.W1;
   a.w_expert_bytes = g.packed ? (int64_t)packed_b_bytes(g.N, g.K, g.epilogue == EPI_SWIGLU) : (int64_t)g.N * g.K * 2;
