@@ -25,7 +25,8 @@
  *   - Return value: a moep_status.  Nothing throws or aborts across the ABI.
  *     After a non-zero status moep_last_error() describes it.  Inputs holding
  *     NaN or Inf give unspecified results.
- *   - Same inputs give bitwise identical outputs (no floating-point atomics).
+ *   - Same inputs give bitwise identical outputs (no floating-point atomics).  A token's logits, expert outputs and layer
+ *     output do not depend on the other tokens of the call either: alone, in a batch or in a prompt, they are the same bits.
  *   - State the library keeps.  Host: the calling thread's last error message; per GPU, behind a
  *     mutex, the compute-unit count and which kernels have had their LDS limit raised (so
  *     first calls from several host threads are safe); the event pool of moep_timing_*.  Device:

@@ -494,7 +494,6 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
     up.W0 = packed ? packed : W1; up.W1 = packed ? nullptr : W3; up.packed = packed != nullptr;
     up.C = w + p.off_h; up.ldc = F;
     up.N = F; up.K = H; up.epilogue = EPI_SWIGLU;
-    up.split_k = plain_out == nullptr;
     up.max_rows = p.T;
     up.busy_tiles = p.E < p.max_slots ? p.E : p.max_slots;
     up.tile_expert = (const int32_t*)(w + p.off_tile_expert);

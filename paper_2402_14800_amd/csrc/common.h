@@ -193,9 +193,8 @@ struct FewGemmArgs {
   int64_t ldc = 0, c_expert_rows = 0;
   int N = 0, K = 0;
   int epilogue = EPI_STORE;
-  bool split_k = false;          // several wavefronts may share a column group (another order of summation)
   int64_t max_rows = 0;          // dense: rows; grouped: most rows an expert can have
-  int64_t busy_tiles = 1;        // tiles that are expected to hold rows (sizes the split)
+  int64_t busy_tiles = 1;        // tiles that are expected to hold rows (choose the load ring and the cache policy)
   int experts = 1;               // dense
   // grouped: the tile map of GemmArgs with FEW_ROWS rows per tile
   const int32_t* tile_expert = nullptr;
@@ -208,8 +207,7 @@ struct FewGemmArgs {
   void* direct_out = nullptr;
 };
 int launch_gemm_few(const FewGemmArgs& g, hipStream_t s, const char* name);
-int gemm_few_allow_lds();   // raises the dynamic LDS limit of its kernels on the current device
-// First use of a device by a bf16 expert GEMM: raises the limits of all of them; its compute-unit count.
+// First use of a device by a bf16 expert GEMM: raises the dynamic LDS limits of all of them; its compute-unit count.
 int gemm_device_ready(int* compute_units);
 
 // ---- router -------------------------------------------------------------------

@@ -631,7 +631,6 @@ int gemm_device_ready(int* compute_units) {
                        allow_lds<EPI_SWIGLU, true, false>, allow_lds<EPI_SWIGLU, true, true>,
                        allow_lds<EPI_ROWSCALE_F32, true, false>, allow_lds<EPI_ROWSCALE_F32, true, true>})
       if (int st = allow()) return st;
-    if (int st = gemm_few_allow_lds()) return st;
     d.ready = true;
   }
   if (compute_units) *compute_units = d.compute_units;

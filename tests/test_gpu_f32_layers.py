@@ -45,3 +45,21 @@ def test_fp32_expert_outputs_at_tile_edges(E, H, F, T):
         ref_out, ref_skip, _, _ = oracle.forward_skip(*args, 0.5, logits=lg_f.cpu().numpy())
         assert np.array_equal(skip.cpu().numpy().astype(bool), ref_skip)
         assert np.abs(wl.to_f64(out) - ref_out).max() <= 1e-5 * np.abs(ref_out).max()
+
+
+@pytest.mark.parametrize("E,H,F,T", [(8, 64, 128, 9001), (4, 260, 132, 3000)])
+def test_fp32_outputs_do_not_depend_on_the_batch(E, H, F, T):
+    """A token alone, in small batches and in one that takes the largest tiles: the same bits of its outputs."""
+    _, layer = small_layer("f32", E, 2, H, F, T, index=30)
+    d = to_dev(layer)
+    rest = [d[n] for n in NAMES[1:]]
+    lg, Y = pkg.moe_expert_outputs(d["x"], *rest)
+    out, skip, _, _ = pkg.moe_forward_skip(d["x"], *rest, 0.5)
+    torch.cuda.synchronize()
+    for t0, rows in ((11, 1), (0, 33), (100, 700)):
+        x = d["x"][t0:t0 + rows].contiguous()
+        lg_p, Y_p = pkg.moe_expert_outputs(x, *rest)
+        out_p, skip_p, _, _ = pkg.moe_forward_skip(x, *rest, 0.5)
+        torch.cuda.synchronize()
+        assert torch.equal(lg_p, lg[t0:t0 + rows]) and torch.equal(Y_p, Y[:, t0:t0 + rows].contiguous())
+        assert torch.equal(skip_p, skip[t0:t0 + rows]) and torch.equal(out_p, out[t0:t0 + rows])

@@ -126,3 +126,28 @@ def test_half_width_tiles_give_the_bits_of_full_width_tiles(E, H, F, T):
         assert torch.equal(bits(Yr_s[slot_s[:, 0].long()]), bits(Yr[slot[:rows, 0].long()]))
         t = torch.arange(rows, device=Y.device)
         assert torch.equal(bits(Yr_s[slot_s[:, 0].long()]), bits(Y[experts_s[:, 0].long(), t]))
+
+
+@pytest.mark.parametrize("E,H,F", [(8, 1024, 2048), (4, 2112, 576), (8, 128, 4160)])
+def test_forward_bits_do_not_depend_on_the_batch(E, H, F):
+    """Decoded alone, in a batch or as part of a prompt, a token has the same output: its products are summed over K in one
+    order on every path.  k T of 48 E is the last batch of the few-rows path; the reference batch is beyond it."""
+    T = 24 * E + 100
+    _, layer = small_layer("bf16", E, 2, H, F, T, index=29)
+    d = to_dev(layer)
+    x, rest = d["x"], [d[n] for n in NAMES[1:]]
+    packed = pkg.moe_pack_weights(*rest[1:])
+    beta, k = 0.6, min(3, E)
+    out, skip, _, _ = pkg.moe_forward_skip(x, *rest, beta)
+    out_k, used, _, _ = pkg.moe_forward_skip_topk(x, *rest, k, 0.1)
+    torch.cuda.synchronize()
+    for t0, rows in ((0, 1), (7, 1), (3, 4), (5, 17), (0, 48), (0, 24 * E), (0, 24 * E + 1)):
+        part = x[t0:t0 + rows].contiguous()
+        want, want_k = bits(out[t0:t0 + rows]), bits(out_k[t0:t0 + rows])
+        got, got_skip, _, _ = pkg.moe_forward_skip(part, *rest, beta)
+        got_p, _, _, _ = pkg.moe_forward_pruned_skip_packed(part, rest[0], packed, F, beta)
+        got_k, got_used, _, _ = pkg.moe_forward_skip_topk(part, *rest, k, 0.1)
+        torch.cuda.synchronize()
+        assert torch.equal(got_skip, skip[t0:t0 + rows]) and torch.equal(got_used, used[t0:t0 + rows])
+        assert torch.equal(bits(got), want) and torch.equal(bits(got_p), want)
+        assert torch.equal(bits(got_k), want_k)
