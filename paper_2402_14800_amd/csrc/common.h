@@ -181,6 +181,20 @@ constexpr int FEW_ROWS = 64;     // rows per tile of its grouped map
 // 710 / 762 against 817 / 816; dense, row-major, 48 rows 764 against 904, packed, 64 rows 782 against 695;
 // layer of E 16, H 2048, F 5632, dense, packed, 32 / 64 rows: 309 / 414 against 376 / 381.
 constexpr int64_t FEW_MAX_AVERAGE = 48;
+// Routing need not be even: at worst all T tokens are on the same k experts, and each of those walks its weights once per
+// 64 of them.  Beyond two such tiles the path is therefore kept to a lower average, unless the weights of k experts stay in
+// the caches between the tiles (and T within eight of them).  All tokens on two experts, packed, us, few-rows path against
+// 256-row tiles after packing or gathering x, evenly routed in brackets: Mixtral shape (705 MB for two experts) T = 128: 342
+// against 415 (537 against 738), T = 160: 440 against 420 (608 against 742), T = 192: 533 against 424; E 8, H 1024, F 3584
+// (44 MB) T = 160: 52 against 122 (56 against 117); E 32, H 2048, F 2048 (50 MB) T = 512: 112 against 149 (200 against 273),
+// T = 640: 187 against 151 (221 against 270).
+constexpr int64_t FEW_MAX_AVERAGE_MANY = 32;
+constexpr double FEW_CACHED_BYTES = 128e6;   // (half of the last-level cache)
+// k slots for each of T tokens, expert_bytes of weights per expert
+inline bool few_rows(int64_t T, int k, int kept_experts, double expert_bytes) {
+  if (k * T > FEW_MAX_AVERAGE * kept_experts) return false;
+  return T <= 2 * FEW_ROWS || k * T <= FEW_MAX_AVERAGE_MANY * kept_experts || (T <= 8 * FEW_ROWS && k * expert_bytes <= FEW_CACHED_BYTES);
+}
 struct FewGemmArgs {
   const void* X = nullptr;       // row-major rows of A, leading dimension ldx
   int64_t ldx = 0;

@@ -251,11 +251,14 @@ __global__ __launch_bounds__(64 * waves_of(RING_BYTES)) void gemm_few_kernel(Few
   const int t = blockIdx.y;
   int expert;
   int64_t row0, row_end;
+  bool stream = p.stream;
   if (p.tile_expert) {
     if (t >= *p.tiles_in_use) return;
     expert = p.tile_expert[t];
     row0 = p.tile_row0[t];
     row_end = p.seg_end[expert];
+    // Weights that another tile of the expert reads too are left to the caches (160 tokens on two experts: 509 -> 440 us).
+    if ((t > 0 && p.tile_expert[t - 1] == expert) || row_end > row0 + FEW_ROWS) stream = false;
   } else {
     expert = t / p.row_tiles;
     row0 = (int64_t)(t - expert * p.row_tiles) * FEW_ROWS;
@@ -265,7 +268,7 @@ __global__ __launch_bounds__(64 * waves_of(RING_BYTES)) void gemm_few_kernel(Few
   const int rows = (int)(row_end - row0);
 #define MOEP_FEW_TILE(M)                                                                     \
   do {                                                                                       \
-    if (p.stream) few_tile<EPI, PACKED, M, true, RING_BYTES>(p, n0, expert, row0, row_end, ring);  \
+    if (stream) few_tile<EPI, PACKED, M, true, RING_BYTES>(p, n0, expert, row0, row_end, ring);  \
     else few_tile<EPI, PACKED, M, false, RING_BYTES>(p, n0, expert, row0, row_end, ring);          \
   } while (0)
   if (MMAX == 1 || rows <= 16) MOEP_FEW_TILE(1);

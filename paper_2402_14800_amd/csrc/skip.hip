@@ -486,7 +486,7 @@ int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_ex
   if ((int64_t)ks * T >= ((int64_t)1 << 31)) return fail(MOEP_EUNSUPPORTED, "moe_forward_skip: T too large");
   p->T = T; p->E = E; p->H = H; p->F = F; p->ks = ks;
   p->max_slots = (int64_t)ks * T;
-  p->few = dt == MOEP_BF16 && p->max_slots <= FEW_MAX_AVERAGE * kept_experts;
+  p->few = dt == MOEP_BF16 && few_rows(T, ks, kept_experts, 3.0 * H * F * 2);
   p->tile_rows = p->few ? FEW_ROWS : GEMM_BM;
   p->max_tiles = ceil_div((int64_t)ks * T, p->tile_rows) + E;
   const int64_t map_tiles = ceil_div((int64_t)ks * T, dt == MOEP_BF16 ? FEW_ROWS : GEMM_BM) + E;   // either path's map fits

@@ -27,12 +27,13 @@ def bits(t):
     (8, 256, 512, 47, 0b10000010),     # 47 rows for each of two experts
     (8, 128, 256, 192, 0xff),          # the last batch of the few-rows path, and the first beyond it
     (8, 128, 256, 193, 0xff),
+    (32, 64, 128, 512, 0xffffffff),    # the same with many experts: eight tiles of 64 rows
     (32, 64, 128, 511, 0xffffffff),    # around the largest batch of the one-workgroup dispatch
     (32, 64, 128, 513, 0xffffffff),
 ])
 def test_forward_with_few_rows_matches_oracle(E, H, F, T, kept):
     _, layer = small_layer("bf16", E, 2, H, F, T, index=21)
-    if T == 192:                       # all tokens alike: two experts get 192 rows each, three tiles of 64 rows
+    if T in (192, 512):                # all tokens alike: two experts get T rows each, several tiles of 64 rows
         layer["x"][:] = layer["x"][0] * (1 + torch.arange(T)[:, None] % 3).to(layer["x"].dtype)
     d = to_dev(layer)
     beta = 0.6
@@ -141,7 +142,7 @@ def test_forward_bits_do_not_depend_on_the_batch(E, H, F):
     out, skip, _, _ = pkg.moe_forward_skip(x, *rest, beta)
     out_k, used, _, _ = pkg.moe_forward_skip_topk(x, *rest, k, 0.1)
     torch.cuda.synchronize()
-    for t0, rows in ((0, 1), (7, 1), (3, 4), (5, 17), (0, 48), (0, 24 * E), (0, 24 * E + 1)):
+    for t0, rows in ((0, 1), (7, 1), (3, 4), (5, 17), (0, 48), (0, 16 * E), (0, 16 * E + 1), (0, 24 * E), (0, 24 * E + 1)):
         part = x[t0:t0 + rows].contiguous()
         want, want_k = bits(out[t0:t0 + rows]), bits(out_k[t0:t0 + rows])
         got, got_skip, _, _ = pkg.moe_forward_skip(part, *rest, beta)
@@ -151,3 +152,33 @@ def test_forward_bits_do_not_depend_on_the_batch(E, H, F):
         assert torch.equal(got_skip, skip[t0:t0 + rows]) and torch.equal(got_used, used[t0:t0 + rows])
         assert torch.equal(bits(got), want) and torch.equal(bits(got_p), want)
         assert torch.equal(bits(got_k), want_k)
+
+
+def test_streamed_weights_give_the_bits_of_many_rows():
+    """A layer whose launches read more than 192 MB of weights (402 and 201 MB here): they come past the caches, except where
+    an expert has several tiles.  The reference is the 256-row path on a larger batch."""
+    E, H, F, T = 8, 2048, 6144, 300
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(31)
+
+    def normal(*shape, std):
+        return torch.randn(shape, generator=gen, device="cuda:0").mul_(std).to(torch.bfloat16)
+
+    x = normal(T, H, std=1.0)
+    x[64:128] = x[0]                    # one pair of experts has several tiles
+    rest = [normal(E, H, std=H ** -0.5), normal(E, F, H, std=H ** -0.5), normal(E, F, H, std=H ** -0.5), normal(E, H, F, std=F ** -0.5)]
+    packed = pkg.moe_pack_weights(*rest[1:])
+    out, _, _, _ = pkg.moe_forward_skip(x, *rest, 0.5)
+    _, Y = pkg.moe_expert_outputs(x, *rest)
+    torch.cuda.synchronize()
+    for rows in (5, 48, 128, 129):      # (128: the last batch of the few-rows path for a layer that no cache holds)
+        part = x[:rows].contiguous()
+        got, _, _, _ = pkg.moe_forward_skip(part, *rest, 0.5)
+        got_p, _, _, _ = pkg.moe_forward_pruned_skip_packed(part, rest[0], packed, F, 0.5)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(got), bits(out[:rows])) and torch.equal(bits(got_p), bits(out[:rows]))
+    part = x[:33].contiguous()
+    _, Y_r = pkg.moe_expert_outputs(part, *rest)
+    _, Y_p = pkg.moe_expert_outputs_packed(part, rest[0], packed, F)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(Y_r), bits(Y[:, :33].contiguous())) and torch.equal(bits(Y_p), bits(Y_r))
