@@ -41,7 +41,9 @@
  *     buffers (prune_enumerate_static excepted, see there).
  *   - Shape limits: 1 <= E <= 32; T >= 0 (T = 0 is a valid empty batch);
  *     for MOEP_BF16, H and F must be multiples of 64; for MOEP_F32, multiples of 4.
- *     x, the weights, Y and the other [.,H] arrays must be 16-byte aligned (MOEP_EUNSUPPORTED otherwise).
+ *     x, the weights, Y and the other [.,H] arrays must be 16-byte aligned (MOEP_EUNSUPPORTED otherwise), except the
+ *     MOEP_F32 Y and Yr of the expert passes and of prune_enumerate*, for which 4 bytes suffice (slower; not
+ *     prune_enumerate_direct).
  */
 #ifndef MOEPRUNE_H
 #define MOEPRUNE_H

@@ -344,12 +344,13 @@ static int expert_outputs(const void* x, const void* Wgate, const void* W1, cons
   }
   if (int st = launch_router(x, Wgate, T, E, H, dt, logits, s)) return st;
   // Several experts go into a launch (a small layer's expert has too few tiles for the chip): the h of a batch's first
-  // expert in the workspace, those of the others in the part of Y that belongs to experts still to come.
+  // expert in the workspace, those of the others in the part of Y that belongs to experts still to come (where it is 16-byte
+  // aligned, as the GEMM reads them; a Y that is not is written all the same).
   const int64_t h_elems = T * F, y_elems = T * H;
   for (int e0 = 0, ne; e0 < E; e0 += ne) {
     // the largest ne with (ne - 1) h within the outputs of the experts beyond the batch
     ne = (int)((h_elems + (E - e0) * y_elems) / (h_elems + y_elems));
-    if (ne < 1) ne = 1;
+    if (ne < 1 || ((uintptr_t)Y & 15)) ne = 1;
     float* const later = (float*)Y + (e0 + ne) * y_elems;
     GemmArgs up;                                  // h[e] = silu(x W1[e]^T) * (x W3[e]^T)
     up.A = x; up.lda = H;

@@ -86,7 +86,7 @@ struct GemmArgs {
   const int32_t* a_rows = nullptr;  // optional: logical row m reads A row a_rows[m]
   const void* B0 = nullptr;      // [N, K] (per expert), leading dimension K
   const void* B1 = nullptr;      // second weight for EPI_SWIGLU
-  void* C = nullptr;             // [rows, N], leading dimension ldc (elements)
+  void* C = nullptr;             // [rows, N], leading dimension ldc (elements); 4-byte alignment suffices here and for C_rest
   int64_t ldc = 0;
   int64_t M = 0;                 // logical rows (dense mode) or upper bound on rows (grouped)
   int N = 0, K = 0;

@@ -33,6 +33,7 @@ struct FArgs {
   const float* A_rest; float* C_rest;                      // dense, blockIdx.z = expert: experts 1, 2, ...
   int64_t a_expert_stride, c_expert_stride;
   int N, K;
+  bool c_by_word;                                          // C or C_rest is not 16-byte aligned: stored float by float
 };
 
 template <int EPI, int TM, int TB>    // TM = rows, TB = accumulator columns per tile
@@ -64,7 +65,7 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
 
-  // staging: a thread brings chunk (tid & 7) of rows tid / 8 + 32 i of A (i < TM / 32) and of B (i < 4); rows beyond the last
+  // staging: a thread brings chunk (tid & 7) of rows tid / 8 + 32 i of A (i < TM / 32) and of B (i < TB / 32); rows beyond the last
   // one repeat it (their products are not stored), chunks beyond K are zero
   const int sr = tid >> 3, sc = tid & 7;
   const float* ap[RT];
@@ -154,7 +155,13 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
         if (EPI == EPI_ROWSCALE_F32) x *= scale;
         o[v] = x;
       }
-      *(f32x4*)(C + r * p.ldc + n) = o;
+      float* const dst = C + r * p.ldc + n;
+      if (p.c_by_word) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) dst[v] = o[v];
+      } else {
+        *(f32x4*)dst = o;
+      }
     }
   }
 }
@@ -178,6 +185,9 @@ int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name) {
   f.A_rest = (const float*)g.A_rest; f.C_rest = (float*)g.C_rest;
   f.a_expert_stride = g.a_expert_stride; f.c_expert_stride = g.c_expert_stride;
   f.N = g.N; f.K = g.K;
+  const bool several = g.experts > 1;      // (the *_rest operands are of no use otherwise)
+  if (((uintptr_t)g.A | (several ? (uintptr_t)g.A_rest : 0)) & 15) return fail(MOEP_EUNSUPPORTED, "%s: A must be 16-byte aligned", name);
+  f.c_by_word = (((uintptr_t)g.C | (several ? (uintptr_t)g.C_rest : 0)) & 15) != 0;
   if (g.experts < 1 || g.experts > 65535 || (g.tile_expert && g.experts != 1)) return fail(MOEP_EINVAL, "%s: bad batch count %d", name, g.experts);
   auto m_tiles = [&](int tm) { return g.tile_expert ? g.max_m_tiles * (GEMM_BM / tm) : ceil_div(g.M, tm); };
   auto n_tiles = [&](int tb) { return ceil_div(g.N, g.epilogue == EPI_SWIGLU ? tb / 2 : tb); };

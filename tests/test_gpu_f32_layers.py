@@ -63,3 +63,24 @@ def test_fp32_outputs_do_not_depend_on_the_batch(E, H, F, T):
         torch.cuda.synchronize()
         assert torch.equal(lg_p, lg[t0:t0 + rows]) and torch.equal(Y_p, Y[:, t0:t0 + rows].contiguous())
         assert torch.equal(skip_p, skip[t0:t0 + rows]) and torch.equal(out_p, out[t0:t0 + rows])
+
+
+@pytest.mark.parametrize("E,H,F,T", [(8, 192, 128, 700), (3, 64, 60, 33), (8, 64, 128, 9001)])
+@pytest.mark.parametrize("offset", [1, 2])
+def test_fp32_expert_outputs_at_four_byte_alignment(E, H, F, T, offset):
+    """Outputs whose rows are not 16-byte aligned are the bits of aligned ones, and nothing is written around them."""
+    _, layer = small_layer("f32", E, 2, H, F, T, index=33)
+    d = to_dev(layer)
+    ws = [d[n] for n in NAMES]
+    _, Y = pkg.moe_expert_outputs(*ws)
+    ranked = pkg.moe_expert_outputs_ranked(*ws, 2)
+    buf = torch.full((E * T * H + 8,), 7.0, device="cuda:0")
+    shifted = buf[offset:offset + E * T * H].view(E, T, H)
+    pkg.moe_expert_outputs(*ws, Y=shifted)
+    torch.cuda.synchronize()
+    assert shifted.data_ptr() % 16 == 4 * offset and torch.equal(shifted, Y)
+    assert torch.all(buf[:offset] == 7.0) and torch.all(buf[offset + E * T * H:] == 7.0)
+    part = buf[offset:offset + 2 * T * H].view(2 * T, H)
+    pkg.moe_expert_outputs_ranked(*ws, 2, out=(*[torch.empty_like(v) for v in ranked[:3]], part))
+    torch.cuda.synchronize()
+    assert torch.equal(part, ranked[3])
