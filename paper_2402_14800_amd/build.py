@@ -90,5 +90,17 @@ def kernel_resource_usage(src: str) -> dict:
     return usage
 
 
+def device_assembly(src: str) -> str:
+    """The compiler's gfx950 assembly of one source file (device side only)."""
+    import tempfile
+
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "dev.s")
+        r = subprocess.run([HIPCC, *FLAGS, "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", out], capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")
+        return open(out).read()
+
+
 if __name__ == "__main__":
     print(build())

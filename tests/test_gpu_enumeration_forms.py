@@ -53,3 +53,29 @@ def test_fp32_gram_at_row_lengths_and_alignments(E, H, T):
         got = loss.cpu().numpy().astype(np.float64)
         assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * np.abs(ref).max())
         assert int(amin.item()) == int(np.argmin(got))
+
+
+@pytest.mark.parametrize("E,H,T,n", [(8, 37, 11, 3), (8, 260, 9, 8), (20, 33, 5, 4), (4, 64, 7, 3)])
+def test_fp32_ranked_gram_at_row_lengths_and_alignments(E, H, T, n):
+    """The same for the rows of the rank-limited pass, in any order behind slot_of: each token's n best-ranked experts."""
+    logits, Y = wl.make_enumeration_inputs(E, T, H, "f32", seed=7 * E + H)
+    k, r = 2, E - 1
+    order = oracle.routing_order(logits.numpy())[:, :n]
+    slots = np.random.Generator(np.random.PCG64(E + H)).permutation(T * n).reshape(T, n)
+    rows = torch.empty((T * n, H), dtype=torch.float32)
+    for t in range(T):
+        for j in range(n):
+            rows[slots[t, j]] = Y[order[t, j], t]
+    lg = logits.to("cuda:0")
+    experts = torch.from_numpy(order.astype(np.int32)).to("cuda:0")
+    slot_of = torch.from_numpy(slots.astype(np.int32)).to("cuda:0")
+    buf = torch.empty(T * n * H + 1, dtype=torch.float32, device="cuda:0")
+    shifted = buf[1:].view(T * n, H)
+    shifted.copy_(rows)
+    ref, _, _ = oracle.prune_enumerate_gram_form(wl.to_f64(logits), wl.to_f64(Y), k, r)
+    for Yr in (rows.to("cuda:0"), shifted):
+        loss, amin, _, _ = pkg.prune_enumerate_ranked(lg, experts, slot_of, Yr, k, r)
+        torch.cuda.synchronize()
+        got = loss.cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * np.abs(ref).max())
+        assert int(amin.item()) == int(np.argmin(got))

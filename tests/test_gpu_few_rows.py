@@ -107,17 +107,33 @@ def test_weights_in_place_give_the_bits_of_packed_weights(E, H, F, T, n):
         assert torch.equal(bits(Yr[slot[:, j].long()]), bits(Y[experts[:, j].long(), t]))
 
 
-@pytest.mark.parametrize("E,H,F,T", [(1, 64, 64, 32769), (2, 320, 192, 8193), (8, 192, 320, 1025)])
-def test_half_width_tiles_give_the_bits_of_full_width_tiles(E, H, F, T):
-    """One token more makes 129 tiles of 128 (or the launch of twice as many rows leaves one round), and the GEMMs walk tiles
-    of another width: the rows both batches hold are the same bits, dense and through the tile order of the routed pass."""
+@pytest.mark.parametrize("E,H,F,T,prefixes,grouped_crosses", [
+    (1, 64, 64, 32769, (32768, 16384, 100), True),        # 129 tiles against 128
+    (2, 320, 192, 8193, (8192, 4096, 100), False),
+    (4, 576, 448, 12000, (8000, 5000, 300), True),        # several experts and N tiles, the last of them ragged in both widths
+    (7, 320, 832, 18000, (9000, 2000, 400), True),
+])
+def test_half_width_tiles_give_the_bits_of_full_width_tiles(E, H, F, T, prefixes, grouped_crosses):
+    """Launches of more than 128 full-width tiles walk those, smaller ones tiles of half the width: the rows that both batches
+    hold are the same bits, dense and through the tile order of the routed pass."""
     _, layer = small_layer("bf16", E, 2, H, F, T, index=26)
     d = to_dev(layer)
     rest = [d[n] for n in NAMES[1:]]
     _, many = pkg.moe_expert_outputs(d["x"], *rest)
     _, experts, slot, Yr = pkg.moe_expert_outputs_ranked(d["x"], *rest, 1)
     torch.cuda.synchronize()
-    for rows in (T - 1, T // 2, 100):
+
+    def full_width(rows):
+        """Whether the (gate/up, down) launches of the dense and of the routed pass take full-width tiles."""
+        of_expert = np.bincount(experts[:rows, 0].cpu().numpy(), minlength=E)
+        m_tiles = E * -(-rows // 256), int(sum(-(-c // 256) for c in of_expert))
+        return [tuple(m * -(-n // cols) > 128 for n, cols in ((F, 128), (H, 256))) for m in m_tiles]
+
+    widths = [full_width(rows) for rows in (T, *prefixes)]
+    for launch in (0, 1):                                  # gate/up, down
+        assert {w[0][launch] for w in widths} == {True, False}
+        assert not grouped_crosses or {w[1][launch] for w in widths} == {True, False}
+    for rows in prefixes:
         x = d["x"][:rows].contiguous()
         _, Y = pkg.moe_expert_outputs(x, *rest)
         _, experts_s, slot_s, Yr_s = pkg.moe_expert_outputs_ranked(x, *rest, 1)
