@@ -441,10 +441,11 @@ __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ log
 // per-position guards from the token loop.
 // A token costs a lane a wait for its record (scalar loads) and a short dependent chain, so a tile is dealt to SCORE_STRANDS
 // strands of wavefronts (threadIdx.y), whose sums are added in LDS in strand order (28 and 70 subsets, E 8: 2048
-// tokens 46 -> 18 us for both, 262144 tokens 232 -> 131 us).
+// tokens 46 -> 18 us for both, 262144 tokens 232 -> 131 us).  !STRANDS: one strand, nothing to hand over, the workgroups no
+// larger than they have to be (1820 subsets of 16 ranks, 20000 tokens: 391 us through the other form, 357 so).
 constexpr int SCORE_STRANDS = 8;
-template <int CAP, bool EXACT>
-__global__ __launch_bounds__(1024) void score_kernel(const float* __restrict__ rec, int64_t T,
+template <int CAP, bool EXACT, bool STRANDS>
+__global__ __launch_bounds__(STRANDS ? 1024 : 256) void score_kernel(const float* __restrict__ rec, int64_t T,
                                                     int tok_tile, int E, int r, int kk, int kfull,
                                                     int n_act_rt, uint32_t n_sub,
                                                     float* __restrict__ partial,
@@ -460,7 +461,7 @@ __global__ __launch_bounds__(1024) void score_kernel(const float* __restrict__ r
   const int64_t t_begin = (int64_t)blockIdx.y * tok_tile;
   const int64_t t_end = t_begin + tok_tile < T ? t_begin + tok_tile : T;
 
-  const int strand = __builtin_amdgcn_readfirstlane((int)threadIdx.y), strands = blockDim.y;
+  const int strand = STRANDS ? __builtin_amdgcn_readfirstlane((int)threadIdx.y) : 0, strands = STRANDS ? (int)blockDim.y : 1;
 
   float total = 0.f;
   uint32_t same_cnt = 0;
@@ -523,17 +524,20 @@ __global__ __launch_bounds__(1024) void score_kernel(const float* __restrict__ r
     same_cnt += (same && live) ? 1u : 0u;
     total += same ? 0.f : q;
   }
-  __shared__ float s_total[1024];
-  __shared__ uint32_t s_same[1024];
-  const int at = threadIdx.y * blockDim.x + threadIdx.x;
-  s_total[at] = total;
-  s_same[at] = same_cnt;
-  __syncthreads();
+  if constexpr (STRANDS) {
+    __shared__ float s_total[1024];
+    __shared__ uint32_t s_same[1024];
+    const int at = threadIdx.y * blockDim.x + threadIdx.x;
+    s_total[at] = total;
+    s_same[at] = same_cnt;
+    __syncthreads();
+    if (strand == 0)
+      for (int w = 1; w < strands; ++w) {
+        total += s_total[w * blockDim.x + threadIdx.x];
+        same_cnt += s_same[w * blockDim.x + threadIdx.x];
+      }
+  }
   if (strand == 0 && live) {
-    for (int w = 1; w < strands; ++w) {
-      total += s_total[w * blockDim.x + threadIdx.x];
-      same_cnt += s_same[w * blockDim.x + threadIdx.x];
-    }
     partial[(int64_t)blockIdx.y * n_sub + sub] = total;
     partial_cnt[(int64_t)blockIdx.y * n_sub + sub] = same_cnt;
   }
@@ -927,12 +931,17 @@ static void launch_score(const EnumPlan& p, const float* rec, float* partial, ui
   // 126 us without, 150 with; 2024 subsets of 23 ranks, 3000 tokens: 391 without, 329 with).
   const int most = threads == 256 && (int64_t)grid.x * grid.y >= 1024 ? 1 : SCORE_STRANDS;
   const int strands = 1024 / threads < most ? 1024 / threads : most;
-  if (p.n_act == CAP)
-    hipLaunchKernelGGL((score_kernel<CAP, true>), grid, dim3(threads, strands), 0, s, rec, p.T, p.tok_tile, p.E, p.r,
-                       p.kk, p.k, p.n_act, (uint32_t)p.n_sub, partial, pcnt);
-  else
-    hipLaunchKernelGGL((score_kernel<CAP, false>), grid, dim3(threads, strands), 0, s, rec, p.T, p.tok_tile, p.E, p.r,
-                       p.kk, p.k, p.n_act, (uint32_t)p.n_sub, partial, pcnt);
+#define MOEP_SCORE(EXACT, STRANDS)                                                                                     \
+  hipLaunchKernelGGL((score_kernel<CAP, EXACT, STRANDS>), grid, dim3(threads, strands), 0, s, rec, p.T, p.tok_tile, p.E, \
+                     p.r, p.kk, p.k, p.n_act, (uint32_t)p.n_sub, partial, pcnt)
+  if (p.n_act == CAP) {
+    if (strands > 1) MOEP_SCORE(true, true);
+    else MOEP_SCORE(true, false);
+  } else {
+    if (strands > 1) MOEP_SCORE(false, true);
+    else MOEP_SCORE(false, false);
+  }
+#undef MOEP_SCORE
 }
 
 int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep_dtype dt,

@@ -22,6 +22,8 @@ pytestmark = pytest.mark.gpu
     (17, 4, 9, 6, 64, "bf16"),         # capacity 12 with more than 16 experts
     (18, 1, 16, 100, 64, "bf16"),      # capacity 4 with more than 16 experts
     (13, 2, 7, 50, 64, "bf16"),        # 8 active ranks of 13 experts, 1716 subsets
+    (16, 4, 4, 4033, 64, "bf16"),      # 1820 subsets: 8 x 127 workgroups with strands (16 ranks, all in use)
+    (16, 4, 4, 4065, 64, "bf16"),      # 8 x 128 workgroups: one strand
 ])
 def test_enumeration_at_the_edges_of_its_forms(E, k, r, T, H, dtype):
     logits, Y = wl.make_enumeration_inputs(E, T, H, dtype, seed=77 + E + T)
