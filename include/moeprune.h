@@ -221,10 +221,10 @@ int moe_forward_pruned_skip(const void* x, const void* Wgate, const void* W1, co
                             void* hip_stream);
 
 /* ---- packed expert weights (serving loops) ----------------------------------- */
-/* The bf16 expert GEMMs read their operands in a blocked layout; the forward calls above re-lay
- * the layer's expert weights out on every call (a read and a write of all of them).  A caller
- * that runs the same layer many times (token generation with dynamic skipping, Sec. 3.3 and the
- * speed-up table of Sec. 4) does it once:
+/* The bf16 expert GEMMs read operands fastest in a blocked layout.  The calls on row-major weights read
+ * those where they lie, in smaller pieces, or with many tokens (more than 6144 rows per expert) re-lay them
+ * out on every call, a read and a write of all of them.  A caller that runs the same layer many times
+ * (token generation with dynamic skipping, Sec. 3.3 and the speed-up table of Sec. 4) does it once:
  *   moe_packed_weights_bytes: size of the packed copy of W1, W3, W2 (0 if dt is not MOEP_BF16 or
  *     H, F are not multiples of 64);
  *   moe_pack_weights: W1, W3 [E,F,H], W2 [E,H,F] -> packed (device, caller-owned, 256-byte

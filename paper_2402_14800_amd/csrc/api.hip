@@ -297,8 +297,8 @@ static int expert_outputs(const void* x, const void* Wgate, const void* W1, cons
   }
   if (dt == MOEP_BF16) {
     // Operands are packed once per call into the blocked layout of the packed GEMM (x; many rows: every expert's
-    // weights, unless the caller has done that already; fewer rows read them in place); h stays in that layout between the two projections
-    // and never exists row-major.  Each projection is ONE launch over a batch of experts.
+    // weights, unless the caller has done that already; fewer rows read them in place); h stays in that layout between
+    // the two projections and never exists row-major.  Each projection is ONE launch over a batch of experts.
     const int eb = experts_per_launch(T, E, F);
     const size_t h_bytes = packed_a_bytes(T, F);
     char* hp = (char*)ws;
@@ -518,7 +518,8 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
   }
   if (dt == MOEP_BF16) {
     // Packed-operand path: the routed rows of x are gathered into one 256-row block per tile, every
-    // expert's weights are re-laid out (many rows) or read in place, and h stays in the packed layout between the two projections.
+    // expert's weights are re-laid out (many rows) or read in place, and h stays in the packed layout between the two
+    // projections.
     const int32_t* slot_token = (const int32_t*)(w + p.off_slot_token);
     const int32_t* tile_expert = (const int32_t*)(w + p.off_tile_expert);
     const int32_t* tile_row0 = (const int32_t*)(w + p.off_tile_row0);

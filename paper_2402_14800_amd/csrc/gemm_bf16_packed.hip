@@ -1,5 +1,6 @@
 // bf16 GEMM for gfx950 on PACKED operands: C = epilogue(A B^T), fp32 accumulate on the MFMA units
-// (v_mfma_f32_16x16x32_bf16).  Every bf16 expert GEMM runs here: the dense pass (every expert on every
+// (v_mfma_f32_16x16x32_bf16).  The bf16 expert GEMMs with more than a few dozen rows per expert
+// (gemm_few.hip takes those with fewer): the dense pass (every expert on every
 // token, Sec. 3.1 / Sec. 3.2) and, in grouped mode, the routed rows of the skipping forward (Sec. 3.3)
 // and of the rank-limited pass.  The operands are re-read many times; re-laying them out once is
 // almost free.

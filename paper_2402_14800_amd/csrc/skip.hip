@@ -511,8 +511,8 @@ int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_ex
       return fail(MOEP_EUNSUPPORTED, "moe_forward_skip: too many tiles for the tile order tables");
     p->off_order_up = take((size_t)(TILE_ORDER_HEADER + gemm_tiles * n_up) * 4);
     p->off_order_down = take((size_t)(TILE_ORDER_HEADER + gemm_tiles * n_down) * 4);
-    // packed-operand GEMMs: h and the gathered x hold one 256-row block per tile; every expert's weights
-    // are re-laid out once per call
+    // packed-operand GEMMs: h and the gathered x hold one 256-row block per tile; room for a packed copy of every
+    // expert's weights, which calls with many rows per expert on row-major weights make
     p->off_h = take(packed_a_bytes(gemm_tiles * GEMM_BM, F));
     p->off_xp = take(packed_a_bytes(gemm_tiles * GEMM_BM, H));
     p->off_w13 = take((size_t)E * packed_b_bytes(F, H, true));
