@@ -9,7 +9,7 @@
 // multiplies it; nothing is shared and there is no barrier.  A wavefront takes 32 output columns (gate/up: 32 gate and the
 // 32 up rows of the same columns) x up to 64 rows and walks all of K.  What keeps the memory busy is the bytes in flight: with
 // 16 KB rings eight wavefronts fit a compute unit, and a launch of no more than four per compute unit takes rings of 40 KB
-// instead (DEEP_RING), 16 to 36 KB of weights in flight for each.
+// instead (DEEP_RING), 12 to 36 KB of weights in flight for each.
 // Rows of A (x through a token list, or h) are read as MFMA fragments from L1/L2: a few hundred KB.
 //
 // Weights come either as the caller stores them (row-major [N, K]) or in the blocked layout of moe_pack_weights; the same
