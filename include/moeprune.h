@@ -222,8 +222,8 @@ int moe_forward_pruned_skip(const void* x, const void* Wgate, const void* W1, co
 
 /* ---- packed expert weights (serving loops) ----------------------------------- */
 /* The bf16 expert GEMMs read operands fastest in a blocked layout.  The calls on row-major weights read
- * those where they lie, in smaller pieces, or with many tokens (more than 6144 rows per expert) re-lay them
- * out on every call, a read and a write of all of them.  A caller that runs the same layer many times
+ * those where they lie, or with many tokens (more than 32768 rows per expert) re-lay them out on every call,
+ * a read and a write of all of them.  A caller that runs the same layer many times
  * (token generation with dynamic skipping, Sec. 3.3 and the speed-up table of Sec. 4) does it once:
  *   moe_packed_weights_bytes: size of the packed copy of W1, W3, W2 (0 if dt is not MOEP_BF16 or
  *     H, F are not multiples of 64);

@@ -223,13 +223,13 @@ static int experts_per_launch(int64_t T, int E, int F) {
 }
 
 // Whether the GEMMs read row-major expert weights where they lie or from a blocked copy made first.  Making the copy
-// costs a read and a write of all weights whatever the batch (1.1 ms at 2.8 GB); without it the GEMMs run a few percent
-// longer (64-byte instead of 1 KB pieces).  Both grow with the weights, so the line is a number of rows per expert
+// costs a read and a write of all weights whatever the batch (1.1 ms at 2.8 GB); without it the GEMMs run 1 to 2 %
+// longer.  Both grow with the weights, so the line is a number of rows per expert
 // (routed calls: nominal, with no token skipped).  In place against packed first, us per call:
-// Mixtral shape, skipping forward, T = 777 (194 rows) 925 / 1903, 16384 (4096) 7137 / 7680, 32768 (8192) 13852 / 13930;
-// E 8, H 1024, F 3584: ranked, 3001 rows 694 / 737, 12288 rows 2136 / 2107; dense, 16384 rows 2477 / 2412;
-// E 16, H 2048, F 5632: dense, 1024 rows 1098 / 1465, 8192 rows 6883 / 6826.
-static constexpr int64_t IN_PLACE_MAX_ROWS = 6144;
+// Mixtral shape, skipping forward, T = 32768 (8192 rows) 13280 / 14287, 65536 26700 / 27400, 100000 (25000 rows) 40180 / 40910;
+// E 8, H 1024, F 3584: ranked, 9216 rows 1568 / 1652; dense, 16384 rows 2354 / 2398, 32768 rows 4479 / 4501;
+// E 16, H 2048, F 5632: dense, 8192 rows 6499 / 6811, 16384 rows 12907 / 13070.
+static constexpr int64_t IN_PLACE_MAX_ROWS = 32768;
 
 static size_t expert_outputs_workspace_bf16(int64_t T, int E, int H, int F, bool weights_prepacked) {
   size_t need = align256((size_t)experts_per_launch(T, E, F) * packed_a_bytes(T, F)) + align256(packed_a_bytes(T, H));

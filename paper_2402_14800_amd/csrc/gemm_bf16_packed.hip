@@ -16,9 +16,12 @@
 // reordered so that the transposed accumulator tiles give each lane 8 consecutive output columns, and
 // for the gate/up projection a block holds 128 rows of W1 followed by the same 128 rows of W3.
 //
-// BROW: the weight operand is read as the caller stores it, row-major, and the same LDS image is made by the loads' lane
-// addresses (each brings 16 rows x 64 bytes; both permutations above are in the address).  The same products in the same
-// order, hence the same bits, 2 to 8 % slower than on packed weights, without the packing pass.
+// BROW: the weight operand is read as the caller stores it, row-major, in whole 128-byte lines: a "unit" is half of the
+// tile's weight rows (gate/up: the rows of one branch) over TWO slices, and a step loads one unit where it would load one
+// slice of all rows; the row permutation is in the loads' lane addresses.  Half lines, one slice of all rows per step, had
+// come at about 4 TB/s, fetched twice.  The same products in the same order, hence the same bits.  Skipping forward,
+// Mixtral shape, T = 300 826 -> 697 us, 777 851 -> 712, 1500 1194 -> 1075, 6000 2886 -> 2710; 1 to 2 % slower than on
+// packed weights where the matrix rate is the bound, without the packing pass.
 //
 // Kernel.  One workgroup of 256 threads (4 wavefronts, 2 along M x 2 along N, one per SIMD) owns a
 // 256 x 256 tile of the accumulator (256 x 128 outputs in SwiGLU mode); a wavefront owns 128 x 128 =
@@ -70,8 +73,8 @@ constexpr int SYNC_POLLS = 64;                // bound of a workgroup's wait for
 constexpr uint32_t SYNC_EVERY = 4;            // tiles between two line-ups (1: 0.9 % slower; the L2 hit rate is the same)
 constexpr int NS = 5;                       // ring stages
 constexpr int SLICE = 256 * 64;             // one operand block: 256 rows x 32 bf16
-constexpr int STAGE = 2 * SLICE;            // A block then B block
-constexpr int LDS_BYTES = NS * STAGE;       // 160 KB
+constexpr int RING = NS * SLICE;            // bytes of one operand's ring
+constexpr int LDS_BYTES = 2 * RING;         // A's ring, then B's: 160 KB
 static_assert(GEMM_BM == 256, "tiles are 256 rows");
 static_assert((NS - 1) % 2 == 0, "the loader must be an even number of slices ahead (steps come in pairs)");
 
@@ -196,23 +199,24 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
   constexpr uint32_t GROUP_M = (EPI == EPI_SWIGLU ? GEMM_GROUP_M_SWIGLU : GEMM_GROUP_M_STORE) * NG / 8;
   // weight blocks of the tile's expert (BROW: the first of this wavefront's 64 or 32 weight rows; rows come in whole groups of
   // 64, a group beyond the last one re-reads that, its products are never stored)
-  const int64_t pitch = (int64_t)nsl * 64;
-  auto b_tile = [&](int tm_, int tn_, int e_) {
+  const int pitch = nsl * 64;
+  const int brow_group = NG == 8 ? 32 * wave_u : 32 * (wave_u >> 1);
+  const int brow_uni = NG == 8 ? 0 : 4 * (wave_u & 1) * pitch;
+  auto b_tile = [&](int tm_, int tn_, int e_, int unit) {
     const char* b;
     if (BROW) {
-      constexpr int ROWS = 8 * NG;                // weight rows that a wavefront brings per slice
-      const int row = EPI == EPI_SWIGLU ? tn_ * (2 * ROWS) + (wave_u & 1) * ROWS : tn_ * (4 * ROWS) + wave_u * ROWS;
-      b = (EPI == EPI_SWIGLU && wave_u >= 2 ? p.B1 : p.B) + (int64_t)min(row, p.N - ROWS) * pitch;
+      // a unit: 16 NG rows of either branch, or half of the tile's 32 NG; a wavefront brings 4 NG of them
+      const int row = EPI == EPI_SWIGLU ? tn_ * (16 * NG) : tn_ * (32 * NG) + unit * (16 * NG);
+      b = (EPI == EPI_SWIGLU && unit ? p.B1 : p.B) + (int64_t)min(row + brow_group, p.N - 32) * pitch + brow_uni;
     } else if (NG == 8) {
       b = p.B + ((size_t)tn_ * nsl) * SLICE + wave_u * 4096;
     } else {                                      // half a block: 128 rows, or 64 gate rows and the same 64 up rows
       b = p.B + ((size_t)(tn_ >> 1) * nsl) * SLICE +
           (EPI == EPI_SWIGLU ? (tn_ & 1) * 4096 + (wave_u >> 1) * 8192 + (wave_u & 1) * 2048 : (tn_ & 1) * 8192 + wave_u * 2048);
     }
-    b += (int64_t)(GROUPED ? p.tile_expert[tm_] : e_) * p.b_expert_bytes;
+    b += (int64_t)(GROUPED ? __builtin_amdgcn_readfirstlane(p.tile_expert[tm_]) : e_) * p.b_expert_bytes;
     return b;
   };
-  constexpr int B_STEP = BROW ? 64 : SLICE;       // bytes from a slice of the weights to the next
   // Dense: e = the GEMM of a batched launch the tile belongs to; each of them is dealt to the XCDs exactly as a
   // launch of its own would be when its tile count is a multiple of 8 and the launch takes several rounds, else the batch
   // is one flat run of tiles (in a single round that keeps an expert's operands on one XCD).
@@ -248,6 +252,10 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
       tm = (int)(first_m + in_group % gm);
       tn = (int)(in_group / gm);
     }
+    // (the divisions above went through vector registers)
+    tm = __builtin_amdgcn_readfirstlane(tm);
+    tn = __builtin_amdgcn_readfirstlane(tn);
+    e = __builtin_amdgcn_readfirstlane(e);
   };
 
   // ---- loader state (all wave-uniform) ----------------------------------------------------------
@@ -257,37 +265,52 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
   int tm_ld, tn_ld, e_ld;
   decode(L_ld, tm_ld, tn_ld, e_ld);
   const char* a_ld = p.A + (int64_t)e_ld * p.a_expert_bytes + ((size_t)tm_ld * nsl) * SLICE + wave_u * 4096;
-  const char* b_ld = b_tile(tm_ld, tn_ld, e_ld);
+  const char* b_ld = b_tile(tm_ld, tn_ld, e_ld, 0);
+  // BROW: from the tile's first unit to its second
+  const int64_t b1_branch = p.B1 - p.B;
+  int b1_rows = BROW && EPI != EPI_SWIGLU ? (int)(b_tile(tm_ld, tn_ld, e_ld, 1) - b_ld) : 0;
   int s_ld = 0;
   int st_ld = 0;                      // byte offset of the stage the next slice goes to
   bool ld_ok = true;
-  const uint32_t lane_off = lane * 16;
+  const int lane_off = lane * 16;
   typedef __attribute__((address_space(3))) char lds_char;
-  typedef const __attribute__((address_space(1))) void* gptr_t;
   lds_char* const lds3 = (lds_char*)lds;
-  // per-lane global addresses of this wavefront's part of the next slice (kept in registers so that the
+  // packed: per-lane global addresses of this wavefront's part of the next slice (kept in registers so that the
   // step that issues the loads has no address arithmetic to do first)
   const char* ga = a_ld + lane_off;
   const char* gb = b_ld + lane_off;
-  // BROW: 1 KB of a block holds 16 rows of 64 bytes; lane l brings row 4 (l / 16) + (l / 4) % 4 of them, i.e. weight row
-  // 8 (l / 16) + (l / 4) % 4 (+ 4 for odd KBs, + 32 from one pair of KBs to the next), chunk (l % 4) ^ (l / 16).
-  // (the instruction's offset moves both addresses: what it adds to the global one is taken off the uniform base)
-  const uint32_t brow_off = (uint32_t)((8 * (lane >> 4) + ((lane >> 2) & 3)) * (int)pitch + (((lane & 3) ^ (lane >> 4)) << 4));
-#define MOEP_LOAD1(q)                                                                           \
-  __builtin_amdgcn_global_load_lds((gptr_t)((q) < 4 ? ga : !BROW ? gb :                           \
-      b_ld + ((((q) & 2) ? 32 : 0) * pitch + (((q) & 1) ? 4 : 0) * pitch - ((q) & 3) * 1024) + brow_off), \
-      (__attribute__((address_space(3))) void*)(lds3 + st_ld + ((q) < 4 ? wave_u * 4096 : SLICE + wave_u * (NG * 512))), 16, \
-      ((q) & 3) * 1024, 0);
+  // BROW: lane l brings position l % 8 of LDS row 8 j + l / 8 of a group of 32, j = 0 .. 3 the load: weight row
+  // (l / 8) % 4 + 8 (l / 32) + 16 (j % 2) + 4 (j / 2), chunk (l % 8) ^ (4 (j % 2) + l / 16).
+  const int brow_even = (8 * (lane >> 5) + ((lane >> 3) & 3)) * pitch + (((lane & 7) ^ (lane >> 4)) << 4);
+  const int brow_odd = brow_even ^ 64;
+  // BROW loads go through buffer descriptors: a scalar base, a 32-bit lane offset and a scalar offset, so that a step has no
+  // vector additions to do for its addresses (with 64-bit vector addresses it had 8, and too few registers left to spread the
+  // loads over the step).  On packed operands, one address register pair each, plain loads are 1 % faster.
+  typedef __attribute__((address_space(3))) void* lds_t;
+  typedef const __attribute__((address_space(1))) void* gptr_t;
+#define MOEP_BUFFER_LOAD(base, lane_offset, offset, dst, imm)                                   \
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)(base), 0, -1, 0x00027000), \
+      (lds_t)(lds3 + (dst)), 16, lane_offset, offset, imm, 0);
+#define MOEP_LOAD_A(q)                                                                          \
+  if constexpr (!BROW) __builtin_amdgcn_global_load_lds((gptr_t)ga, (lds_t)(lds3 + st_ld + wave_u * 4096), 16, (q) * 1024, 0); \
+  else MOEP_BUFFER_LOAD(a_ld, lane_off, 0, st_ld + wave_u * 4096, (q) * 1024)
+#define MOEP_LOAD_B(q, unit)                                                                    \
+  if constexpr (!BROW) __builtin_amdgcn_global_load_lds((gptr_t)gb, (lds_t)(lds3 + RING + st_ld + wave_u * (NG * 512)), 16, (q) * 1024, 0); \
+  else MOEP_BUFFER_LOAD(b_ld + ((unit) ? (EPI == EPI_SWIGLU ? b1_branch : (int64_t)b1_rows) : 0),  \
+                        (q) & 1 ? brow_odd : brow_even, (16 * ((q) & 1) + 4 * ((q) >> 1)) * pitch, \
+                        RING + st_ld + wave_u * (NG * 512) + (q) * 1024, 0)
   // After a slice has been issued: next slice, next stage (branch-free, so that it can be scheduled into
   // the shadow of the MFMAs).  Past the end of the workgroup's stream the loader stays on its last slice:
   // the re-reads are in bounds and land in stages nobody reads again, every step issues the same loads and
   // the wait counts below hold to the end.
-#define MOEP_ADVANCE_LOADER()                                                                   \
+#define MOEP_ADVANCE_LOADER(unit)                                                               \
   {                                                                                             \
-    a_ld += ld_ok ? SLICE : 0; b_ld += ld_ok ? B_STEP : 0;                                      \
+    a_ld += ld_ok ? SLICE : 0;                                                                  \
+    if (!BROW) b_ld += ld_ok ? SLICE : 0;                                                       \
+    else if (unit) b_ld += ld_ok ? 128 : 0;                                                     \
     s_ld += ld_ok ? 1 : 0;                                                                      \
-    st_ld = st_ld + STAGE == LDS_BYTES ? 0 : st_ld + STAGE;                                     \
-    ga = a_ld + lane_off; gb = b_ld + lane_off;                                                 \
+    st_ld = st_ld + SLICE == RING ? 0 : st_ld + SLICE;                                          \
+    if (!BROW) { ga = a_ld + lane_off; gb = b_ld + lane_off; }                                  \
   }
   // The workgroups of an XCD start every SYNC_EVERY-th round of tiles together: they share operand panels through the
   // XCD's L2 only while they walk K within a few steps of each other, and left alone they settle, from
@@ -344,24 +367,42 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
     if (L_ld < nblk) {                                                                          \
       decode(L_ld, tm_ld, tn_ld, e_ld);                                                         \
       a_ld = p.A + (int64_t)e_ld * p.a_expert_bytes + ((size_t)tm_ld * nsl) * SLICE + wave_u * 4096; \
-      b_ld = b_tile(tm_ld, tn_ld, e_ld);                                                        \
+      b_ld = b_tile(tm_ld, tn_ld, e_ld, 0);                                                     \
+      if (BROW && EPI != EPI_SWIGLU) b1_rows = (int)(b_tile(tm_ld, tn_ld, e_ld, 1) - b_ld);      \
     } else {                                                                                    \
       ld_ok = false;                                                                            \
-      a_ld -= SLICE; b_ld -= B_STEP;                                                            \
+      a_ld -= SLICE;                                                                            \
+      b_ld -= BROW ? 128 : SLICE;                                                               \
     }                                                                                           \
-    ga = a_ld + lane_off; gb = b_ld + lane_off;                                                 \
+    if (!BROW) { ga = a_ld + lane_off; gb = b_ld + lane_off; }                                  \
   }
 
   // ---- fragment addresses -------------------------------------------------------------------------
   // MFMA 16x16x32: lane l supplies row (l & 15) and k-values 8 (l >> 4) .. + 7 of both operands, i.e.
-  // chunk (l >> 4) of the row, found at position chunk ^ ((row >> 2) & 3); tile rows are multiples of 16
+  // chunk (l >> 4) of the row, found at the position that the layout gives it; tile rows are multiples of 16
   // apart, so the permutation depends on the lane only and every fragment is base + constant.
   const int frow = lane & 15, fk = lane >> 4;
   const int fpos = (fk ^ ((frow >> 2) & 3)) << 4;
   const int a_fb = (wm * 128 + frow) * 64 + fpos;
-  const int b_fb = SLICE + ((EPI == EPI_SWIGLU ? wn * (NG * 8) : wn * (NG * 16)) + frow) * 64 + fpos;
+  // BROW: rows of 128 bytes, two slices wide, chunk c of row r at position c ^ ((r >> 1) & 7); a slice's fragments lie in the
+  // pair's two units (gate rows in one, up rows in the other; plain: wavefront column wn's rows are unit wn).
+  const int b_fb = RING + (BROW ? ((EPI == EPI_SWIGLU ? wn * (NG * 8) : 0) + frow) * 128 + ((fk ^ ((frow >> 1) & 7)) << 4)
+                                : ((EPI == EPI_SWIGLU ? wn * (NG * 8) : wn * (NG * 16)) + frow) * 64 + fpos);
   int st_rd = 0;                      // byte offset of the stage the next fragment read takes
-  int ra = a_fb, rb = b_fb;           // the same, added to the lane's fragment offsets
+  int ra = a_fb;                      // the same, added to the lane's fragment offsets
+  int rb = b_fb, rb1 = b_fb;          // BROW, gate/up: rb1 = the up rows' unit
+  int su = 0;                         // BROW: byte offset of the first unit of the pair of slices to be read next
+#define MOEP_NEXT_UNIT(u) ((u) + SLICE == RING ? 0 : (u) + SLICE)
+  // fragment addresses of the second (half 1) or first slice of the pair at `su`; after the second one the next pair's turn
+#define MOEP_B_ADDRESS(half)                                                                    \
+  if (BROW) {                                                                                   \
+    const int su1 = MOEP_NEXT_UNIT(su);                                                         \
+    rb = (b_fb ^ ((half) * 64)) + (EPI == EPI_SWIGLU || !wn ? su : su1);                        \
+    rb1 = (b_fb ^ ((half) * 64)) + su1;                                                         \
+    if (half) su = MOEP_NEXT_UNIT(su1);                                                         \
+  } else {                                                                                      \
+    rb = b_fb + st_rd;                                                                          \
+  }
 
   f32x4 acc[8][NG];
 #define MOEP_ZERO_ACC()                                                                         \
@@ -372,7 +413,8 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
   // B tile j of a wavefront: SwiGLU: gate tiles 0 .. NG/2 - 1 and up tiles (NG 16 rows further) of the same
   // 8 NG columns; otherwise NG consecutive 16-row tiles.
 #define MOEP_RB(slot, j)                                                                        \
-  fb[slot][j] = *(const bf16x8*)(lds + rb + (EPI == EPI_SWIGLU ? ((j) / (NG / 2)) * (NG * 1024) + ((j) % (NG / 2)) * 1024 : (j) * 1024));
+  fb[slot][j] = *(const bf16x8*)(lds + (!BROW ? rb + (EPI == EPI_SWIGLU ? ((j) / (NG / 2)) * (NG * 1024) + ((j) % (NG / 2)) * 1024 : (j) * 1024) \
+      : EPI == EPI_SWIGLU ? ((j) < NG / 2 ? rb : rb1) + ((j) % (NG / 2)) * 2048 : rb + (j) * 2048));
 #define MOEP_RA(slot, i) fa[slot][i] = *(const bf16x8*)(lds + ra + (i) * 1024);
   // (B fragments visited back and forth, so that only one operand changes from one MFMA to the next: 0.6 % faster)
 #define MOEP_MFMA(slot)                                                                         \
@@ -383,16 +425,23 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
   // Source order = wanted issue order (a direct load writes LDS, so the compiler keeps it ordered with
   // the fragment reads around it): two fragment reads, one direct load, eight times over, spread over
   // the first 48 of the step's 64 MFMAs by the scheduling groups below.
-#define MOEP_READS_LOADS(slot)                                                                  \
+// (BROW: the weights' loads first, which the waits below count on; the unit is the one of the step that issues them, slot ^ 1)
+#define MOEP_LOADN(n, unit)                                                                     \
+  {                                                                                             \
+    constexpr int nb_ = NG / 2;                                                                 \
+    if constexpr (BROW) { if constexpr ((n) < nb_) { MOEP_LOAD_B(n, unit) } else { MOEP_LOAD_A((n) - nb_) } } \
+    else { if constexpr ((n) < 4) { MOEP_LOAD_A(n) } else { MOEP_LOAD_B((n) - 4, unit) } }       \
+  }
+#define MOEP_READS_LOADS(slot, unit)                                                            \
   if constexpr (NG == 8) {                                                                      \
-    MOEP_RB(slot, 0) MOEP_RB(slot, 1) MOEP_LOAD1(0) MOEP_RB(slot, 2) MOEP_RB(slot, 3) MOEP_LOAD1(1) \
-    MOEP_RB(slot, 4) MOEP_RB(slot, 5) MOEP_LOAD1(2) MOEP_RB(slot, 6) MOEP_RB(slot, 7) MOEP_LOAD1(3) \
-    MOEP_RA(slot, 0) MOEP_RA(slot, 1) MOEP_LOAD1(4) MOEP_RA(slot, 2) MOEP_RA(slot, 3) MOEP_LOAD1(5) \
-    MOEP_RA(slot, 4) MOEP_RA(slot, 5) MOEP_LOAD1(6) MOEP_RA(slot, 6) MOEP_RA(slot, 7) MOEP_LOAD1(7) \
+    MOEP_RB(slot, 0) MOEP_RB(slot, 1) MOEP_LOADN(0, unit) MOEP_RB(slot, 2) MOEP_RB(slot, 3) MOEP_LOADN(1, unit) \
+    MOEP_RB(slot, 4) MOEP_RB(slot, 5) MOEP_LOADN(2, unit) MOEP_RB(slot, 6) MOEP_RB(slot, 7) MOEP_LOADN(3, unit) \
+    MOEP_RA(slot, 0) MOEP_RA(slot, 1) MOEP_LOADN(4, unit) MOEP_RA(slot, 2) MOEP_RA(slot, 3) MOEP_LOADN(5, unit) \
+    MOEP_RA(slot, 4) MOEP_RA(slot, 5) MOEP_LOADN(6, unit) MOEP_RA(slot, 6) MOEP_RA(slot, 7) MOEP_LOADN(7, unit) \
   } else {                                                                                      \
-    MOEP_RB(slot, 0) MOEP_RB(slot, 1) MOEP_LOAD1(0) MOEP_RB(slot, 2) MOEP_RB(slot, 3) MOEP_LOAD1(1) \
-    MOEP_RA(slot, 0) MOEP_RA(slot, 1) MOEP_LOAD1(2) MOEP_RA(slot, 2) MOEP_RA(slot, 3) MOEP_LOAD1(3) \
-    MOEP_RA(slot, 4) MOEP_RA(slot, 5) MOEP_LOAD1(4) MOEP_RA(slot, 6) MOEP_RA(slot, 7) MOEP_LOAD1(5) \
+    MOEP_RB(slot, 0) MOEP_RB(slot, 1) MOEP_LOADN(0, unit) MOEP_RB(slot, 2) MOEP_RB(slot, 3) MOEP_LOADN(1, unit) \
+    MOEP_RA(slot, 0) MOEP_RA(slot, 1) MOEP_LOADN(2, unit) MOEP_RA(slot, 2) MOEP_RA(slot, 3) MOEP_LOADN(3, unit) \
+    MOEP_RA(slot, 4) MOEP_RA(slot, 5) MOEP_LOADN(4, unit) MOEP_RA(slot, 6) MOEP_RA(slot, 7) MOEP_LOADN(5, unit) \
   }
 #define MOEP_READS(slot)                                                                        \
   _Pragma("unroll") for (int j_ = 0; j_ < NG; ++j_) { MOEP_RB(slot, j_) }                       \
@@ -413,23 +462,29 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
   // Loads complete in issue order, so "at most 8 (half-width tiles: 6) outstanding" means that everything but the slice issued in
   // this step has landed, in particular the two slices whose fragments are read before the next barrier
   // (stores of an epilogue only add to the count).
-  constexpr int VM_MAIN = 4 + NG / 2;
-  constexpr int W_MAIN = 0x0070 | (VM_MAIN & 15) | ((VM_MAIN >> 4) << 14);
+  // BROW: a pair's second unit is issued one step before the first slice that needs it is read, so there is a barrier after
+  // every step.  Before an odd step all but the loads from the newest unit's slice of A on have to have landed, before an even
+  // step all but those of the two newest steps.  (The unit that an odd step's loads overwrite was read in the step before:
+  // those reads are back, lgkmcnt 0, before the barrier.)
+  constexpr int STEP_LOADS = 4 + NG / 2;
+  constexpr auto wait_for = [](int vm) { return 0x0070 | (vm & 15) | ((vm >> 4) << 14); };
+  constexpr int W_MAIN = wait_for(BROW ? 2 * STEP_LOADS : STEP_LOADS), W_ODD = wait_for(STEP_LOADS + 4);
   // One step: multiply the slice whose fragments are in `slot`; meanwhile fetch the slice NS - 1 ahead and
   // read the next slice's fragments into the other slot.  The barrier at the end of every second step tells
   // every wavefront that the next two slices have landed for all of them and that all of them have read
   // the fragments of the two stages that the next two steps' loads overwrite.
 #define MOEP_STEP(slot, BAR)                                                                    \
   {                                                                                             \
-    MOEP_READS_LOADS((slot) ^ 1)                                                                \
+    MOEP_READS_LOADS((slot) ^ 1, slot)                                                          \
     MOEP_MFMA(slot)                                                                             \
     MOEP_SCHED(true)                                                                            \
-    MOEP_ADVANCE_LOADER()                                                                       \
-    st_rd = st_rd + STAGE == LDS_BYTES ? 0 : st_rd + STAGE;                                     \
-    ra = a_fb + st_rd; rb = b_fb + st_rd;                                                       \
+    MOEP_ADVANCE_LOADER(slot)                                                                   \
+    st_rd = st_rd + SLICE == RING ? 0 : st_rd + SLICE;                                          \
+    ra = a_fb + st_rd;                                                                          \
+    MOEP_B_ADDRESS(slot)                                                                        \
     __builtin_amdgcn_sched_barrier(0);                                                          \
-    if (BAR) {                                                                                  \
-      __builtin_amdgcn_s_waitcnt(W_MAIN);                                                       \
+    if (BAR || BROW) {                                                                          \
+      __builtin_amdgcn_s_waitcnt(BAR ? W_MAIN : W_ODD);                                         \
       __builtin_amdgcn_s_barrier();                                                             \
     }                                                                                           \
     __builtin_amdgcn_sched_barrier(0);                                                          \
@@ -437,18 +492,23 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
 
   // ---- prologue: the first NS - 1 slices of this workgroup's stream -----------------------------------
 #pragma unroll 1
-  for (int n = 0; n < NS - 1; ++n) {
-    MOEP_LOAD1(0) MOEP_LOAD1(1) MOEP_LOAD1(2) MOEP_LOAD1(3) MOEP_LOAD1(4) MOEP_LOAD1(5)
-    if constexpr (NG == 8) { MOEP_LOAD1(6) MOEP_LOAD1(7) }
-    MOEP_ADVANCE_LOADER()
+  for (int n = 0; n < NS - 1; n += 2) {
+#define MOEP_LOADS(unit)                                                                        \
+    MOEP_LOADN(0, unit) MOEP_LOADN(1, unit) MOEP_LOADN(2, unit) MOEP_LOADN(3, unit) MOEP_LOADN(4, unit) MOEP_LOADN(5, unit) \
+    if constexpr (NG == 8) { MOEP_LOADN(6, unit) MOEP_LOADN(7, unit) }                          \
+    MOEP_ADVANCE_LOADER(unit)
+    MOEP_LOADS(0)
+    MOEP_LOADS(1)
     MOEP_NEXT_LOAD_TILE()
   }
   __builtin_amdgcn_s_waitcnt(0x0070);
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
+  MOEP_B_ADDRESS(0)
   MOEP_READS(0)
-  st_rd = STAGE;
-  ra = a_fb + st_rd; rb = b_fb + st_rd;
+  st_rd = SLICE;
+  ra = a_fb + st_rd;
+  MOEP_B_ADDRESS(1)
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): stage 0 is overwritten by the second step's loads, and
   __builtin_amdgcn_s_barrier();         // no barrier separates it from these reads otherwise
@@ -546,7 +606,13 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
     decode(L_mm, tm, tn, e_mm);
   }
   __builtin_amdgcn_s_waitcnt(0x0070);   // the re-reads still in flight target this workgroup's LDS
-#undef MOEP_LOAD1
+#undef MOEP_BUFFER_LOAD
+#undef MOEP_LOAD_A
+#undef MOEP_LOAD_B
+#undef MOEP_LOADN
+#undef MOEP_LOADS
+#undef MOEP_NEXT_UNIT
+#undef MOEP_B_ADDRESS
 #undef MOEP_ADVANCE_LOADER
 #undef MOEP_NEXT_LOAD_TILE
 #undef MOEP_ZERO_ACC

@@ -107,6 +107,23 @@ def test_weights_in_place_give_the_bits_of_packed_weights(E, H, F, T, n):
         assert torch.equal(bits(Yr[slot[:, j].long()]), bits(Y[experts[:, j].long(), t]))
 
 
+@pytest.mark.parametrize("E,H,F,T", [(2, 64, 64, 32768), (2, 64, 64, 32769), (1, 192, 320, 32768), (5, 64, 8256, 700)])
+def test_whole_line_loads_of_weights_give_the_bits_of_packed_weights(E, H, F, T):
+    """Weights read in units of two slices: at the row count up to which that is done, at K = 64 (a pair of slices per tile, so
+    that the loader changes tile in every pair) with more tiles than compute units, and at column counts that end inside a
+    unit (64 and 320 of 256 or 128 columns)."""
+    _, layer = small_layer("bf16", E, 2, H, F, T, index=27)
+    d = to_dev(layer)
+    packed = pkg.moe_pack_weights(d["W1"], d["W3"], d["W2"])
+    _, Y = pkg.moe_expert_outputs(*[d[n] for n in NAMES])
+    _, Y_p = pkg.moe_expert_outputs_packed(d["x"], d["Wgate"], packed, F)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(Y), bits(Y_p))
+    rows = torch.tensor([0, T // 2, T - 1])
+    _, ref = oracle.expert_outputs(*[wl.to_f64(v) for v in (layer["x"][rows], *[layer[n] for n in NAMES[1:]])])
+    check_outputs(wl.to_f64(Y[:, rows.to(Y.device)].contiguous()), ref, "Y")
+
+
 @pytest.mark.parametrize("E,H,F,T,prefixes,grouped_crosses", [
     (1, 64, 64, 32769, (32768, 16384, 100), True),        # 129 tiles against 128
     (2, 320, 192, 8193, (8192, 4096, 100), False),
