@@ -121,8 +121,10 @@ static inline int gemm_tile_columns(bool gate_up, bool half) { return (gate_up ?
 // dense pass of 64 tokens 798 -> 739 us; with 896 gate/up tiles taken as 7 half rounds for 4 the former was 790 us, and 160
 // tiles as two half rounds for one cost 445 -> 507 us (E 16, H 2048, F 5632, top-4, 1001 tokens).
 __host__ __device__ static inline bool half_width_pays(int64_t tiles) { return tiles <= 128; }
-// A tile order starts with a header: word TILE_ORDER_HALF says whether its entries are half-width tiles.
-constexpr int TILE_ORDER_HEADER = 4, TILE_ORDER_HALF = 0;
+// 16-row groups that a wavefront multiplies in a launch whose tallest tile has `rows` rows: 8 (256 rows), 6 or 4
+__host__ __device__ static inline int gemm_row_groups(int64_t rows) { return rows <= 128 ? 4 : rows <= 192 ? 6 : 8; }
+// A tile order starts with a header: whether its entries are half-width tiles, and the launch's row groups.
+constexpr int TILE_ORDER_HEADER = 4, TILE_ORDER_HALF = 0, TILE_ORDER_ROW_GROUPS = 1;
 
 int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name);
 

@@ -154,7 +154,7 @@ struct KArgs {
   int N;                  // output columns
   int nsl;                // K / 32
   int m_tiles, n_tiles;   // n_tiles: of the width the launch walks (grouped: of half the width)
-  int n_tiles_full, half_width;
+  int n_tiles_full, half_width, row_groups;
   // grouped mode (rows partitioned into per-expert segments, tile t = rows tile_row0[t] .. of expert
   // tile_expert[t]; A and a packed C are indexed by TILE, a row-major C by row)
   const int32_t* tile_expert; const int32_t* tile_row0; const int32_t* seg_end; const int32_t* tiles_in_use;
@@ -177,9 +177,16 @@ struct KArgs {
 // that ever not so, the line-ups would group the wrong workgroups and cost time, never a result.
 __device__ unsigned long long g_round_count[8 * 8];
 
-// NG: accumulator tiles of a wavefront along N: 8, or 4 for tiles of half the width.
-template <int EPI, bool GROUPED, bool BROW, int NG>
-__device__ __forceinline__ void gemm_body(const KArgs& p) {
+// NG: accumulator tiles of a wavefront along N: 8, or 4 for tiles of half the width.  MG: along M: 8, or 6 or 4 for launches
+// none of whose tiles has more than 192 or 128 rows (the rows beyond are neither fetched nor multiplied).
+template <int EPI, bool GROUPED, bool BROW, int NG, int MG>
+__device__ __forceinline__ void gemm_body() {
+  // (the kernel's arguments, through a pointer the compiler cannot see through: it would load what all bodies use before it
+  // picks one, and hold it in scalar registers that the loops need)
+  typedef const __attribute__((address_space(4))) KArgs* args_t;
+  args_t args = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(args));
+  const __attribute__((address_space(4))) KArgs& p = *args;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -264,7 +271,7 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
   if (L_ld >= nblk) return;
   int tm_ld, tn_ld, e_ld;
   decode(L_ld, tm_ld, tn_ld, e_ld);
-  const char* a_ld = p.A + (int64_t)e_ld * p.a_expert_bytes + ((size_t)tm_ld * nsl) * SLICE + wave_u * 4096;
+  const char* a_ld = p.A + (int64_t)e_ld * p.a_expert_bytes + ((size_t)tm_ld * nsl) * SLICE + wave_u * (MG * 512);
   const char* b_ld = b_tile(tm_ld, tn_ld, e_ld, 0);
   // BROW: from the tile's first unit to its second
   const int64_t b1_branch = p.B1 - p.B;
@@ -292,8 +299,8 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)(base), 0, -1, 0x00027000), \
       (lds_t)(lds3 + (dst)), 16, lane_offset, offset, imm, 0);
 #define MOEP_LOAD_A(q)                                                                          \
-  if constexpr (!BROW) __builtin_amdgcn_global_load_lds((gptr_t)ga, (lds_t)(lds3 + st_ld + wave_u * 4096), 16, (q) * 1024, 0); \
-  else MOEP_BUFFER_LOAD(a_ld, lane_off, 0, st_ld + wave_u * 4096, (q) * 1024)
+  if constexpr (!BROW) __builtin_amdgcn_global_load_lds((gptr_t)ga, (lds_t)(lds3 + st_ld + wave_u * (MG * 512)), 16, (q) * 1024, 0); \
+  else MOEP_BUFFER_LOAD(a_ld, lane_off, 0, st_ld + wave_u * (MG * 512), (q) * 1024)
 #define MOEP_LOAD_B(q, unit)                                                                    \
   if constexpr (!BROW) __builtin_amdgcn_global_load_lds((gptr_t)gb, (lds_t)(lds3 + RING + st_ld + wave_u * (NG * 512)), 16, (q) * 1024, 0); \
   else MOEP_BUFFER_LOAD(b_ld + ((unit) ? (EPI == EPI_SWIGLU ? b1_branch : (int64_t)b1_rows) : 0),  \
@@ -366,7 +373,7 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
     }                                                                                           \
     if (L_ld < nblk) {                                                                          \
       decode(L_ld, tm_ld, tn_ld, e_ld);                                                         \
-      a_ld = p.A + (int64_t)e_ld * p.a_expert_bytes + ((size_t)tm_ld * nsl) * SLICE + wave_u * 4096; \
+      a_ld = p.A + (int64_t)e_ld * p.a_expert_bytes + ((size_t)tm_ld * nsl) * SLICE + wave_u * (MG * 512); \
       b_ld = b_tile(tm_ld, tn_ld, e_ld, 0);                                                     \
       if (BROW && EPI != EPI_SWIGLU) b1_rows = (int)(b_tile(tm_ld, tn_ld, e_ld, 1) - b_ld);      \
     } else {                                                                                    \
@@ -383,7 +390,7 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
   // apart, so the permutation depends on the lane only and every fragment is base + constant.
   const int frow = lane & 15, fk = lane >> 4;
   const int fpos = (fk ^ ((frow >> 2) & 3)) << 4;
-  const int a_fb = (wm * 128 + frow) * 64 + fpos;
+  const int a_fb = (wm * (MG * 16) + frow) * 64 + fpos;
   // BROW: rows of 128 bytes, two slices wide, chunk c of row r at position c ^ ((r >> 1) & 7); a slice's fragments lie in the
   // pair's two units (gate rows in one, up rows in the other; plain: wavefront column wn's rows are unit wn).
   const int b_fb = RING + (BROW ? ((EPI == EPI_SWIGLU ? wn * (NG * 8) : 0) + frow) * 128 + ((fk ^ ((frow >> 1) & 7)) << 4)
@@ -404,12 +411,12 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
     rb = b_fb + st_rd;                                                                          \
   }
 
-  f32x4 acc[8][NG];
+  f32x4 acc[MG][NG];
 #define MOEP_ZERO_ACC()                                                                         \
-  _Pragma("unroll") for (int i = 0; i < 8; ++i)                                                 \
+  _Pragma("unroll") for (int i = 0; i < MG; ++i)                                                \
     _Pragma("unroll") for (int j = 0; j < NG; ++j)                                              \
       _Pragma("unroll") for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
-  bf16x8 fa[2][8], fb[2][NG];
+  bf16x8 fa[2][MG], fb[2][NG];
   // B tile j of a wavefront: SwiGLU: gate tiles 0 .. NG/2 - 1 and up tiles (NG 16 rows further) of the same
   // 8 NG columns; otherwise NG consecutive 16-row tiles.
 #define MOEP_RB(slot, j)                                                                        \
@@ -418,57 +425,55 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
 #define MOEP_RA(slot, i) fa[slot][i] = *(const bf16x8*)(lds + ra + (i) * 1024);
   // (B fragments visited back and forth, so that only one operand changes from one MFMA to the next: 0.6 % faster)
 #define MOEP_MFMA(slot)                                                                         \
-  _Pragma("unroll") for (int i = 0; i < 8; ++i)                                                 \
+  _Pragma("unroll") for (int i = 0; i < MG; ++i)                                                \
     _Pragma("unroll") for (int jj = 0; jj < NG; ++jj) {                                         \
       const int j = (i & 1) ? NG - 1 - jj : jj;                                                 \
       acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[slot][j], fa[slot][i], acc[i][j], 0, 0, 0); }
   // Source order = wanted issue order (a direct load writes LDS, so the compiler keeps it ordered with
-  // the fragment reads around it): two fragment reads, one direct load, eight times over, spread over
-  // the first 48 of the step's 64 MFMAs by the scheduling groups below.
+  // the fragment reads around it): two fragment reads, one direct load, over and over, spread over
+  // the step's MFMAs by the scheduling groups below.
 // (BROW: the weights' loads first, which the waits below count on; the unit is the one of the step that issues them, slot ^ 1)
 #define MOEP_LOADN(n, unit)                                                                     \
   {                                                                                             \
-    constexpr int nb_ = NG / 2;                                                                 \
-    if constexpr (BROW) { if constexpr ((n) < nb_) { MOEP_LOAD_B(n, unit) } else { MOEP_LOAD_A((n) - nb_) } } \
-    else { if constexpr ((n) < 4) { MOEP_LOAD_A(n) } else { MOEP_LOAD_B((n) - 4, unit) } }       \
+    constexpr int nb_ = NG / 2, na_ = MG / 2;                                                   \
+    if constexpr ((n) < na_ + nb_) {                                                            \
+      if constexpr (BROW) { if constexpr ((n) < nb_) { MOEP_LOAD_B(n, unit) } else { MOEP_LOAD_A((n) - nb_) } } \
+      else { if constexpr ((n) < na_) { MOEP_LOAD_A(n) } else { MOEP_LOAD_B((n) - na_, unit) } } \
+    }                                                                                           \
   }
+#define MOEP_READN(slot, n)                                                                     \
+  { if constexpr ((n) < NG) { MOEP_RB(slot, n) } else if constexpr ((n) < NG + MG) { MOEP_RA(slot, (n) - NG) } }
 #define MOEP_READS_LOADS(slot, unit)                                                            \
-  if constexpr (NG == 8) {                                                                      \
-    MOEP_RB(slot, 0) MOEP_RB(slot, 1) MOEP_LOADN(0, unit) MOEP_RB(slot, 2) MOEP_RB(slot, 3) MOEP_LOADN(1, unit) \
-    MOEP_RB(slot, 4) MOEP_RB(slot, 5) MOEP_LOADN(2, unit) MOEP_RB(slot, 6) MOEP_RB(slot, 7) MOEP_LOADN(3, unit) \
-    MOEP_RA(slot, 0) MOEP_RA(slot, 1) MOEP_LOADN(4, unit) MOEP_RA(slot, 2) MOEP_RA(slot, 3) MOEP_LOADN(5, unit) \
-    MOEP_RA(slot, 4) MOEP_RA(slot, 5) MOEP_LOADN(6, unit) MOEP_RA(slot, 6) MOEP_RA(slot, 7) MOEP_LOADN(7, unit) \
-  } else {                                                                                      \
-    MOEP_RB(slot, 0) MOEP_RB(slot, 1) MOEP_LOADN(0, unit) MOEP_RB(slot, 2) MOEP_RB(slot, 3) MOEP_LOADN(1, unit) \
-    MOEP_RA(slot, 0) MOEP_RA(slot, 1) MOEP_LOADN(2, unit) MOEP_RA(slot, 2) MOEP_RA(slot, 3) MOEP_LOADN(3, unit) \
-    MOEP_RA(slot, 4) MOEP_RA(slot, 5) MOEP_LOADN(4, unit) MOEP_RA(slot, 6) MOEP_RA(slot, 7) MOEP_LOADN(5, unit) \
-  }
+    MOEP_READN(slot, 0) MOEP_READN(slot, 1) MOEP_LOADN(0, unit) MOEP_READN(slot, 2) MOEP_READN(slot, 3) MOEP_LOADN(1, unit) \
+    MOEP_READN(slot, 4) MOEP_READN(slot, 5) MOEP_LOADN(2, unit) MOEP_READN(slot, 6) MOEP_READN(slot, 7) MOEP_LOADN(3, unit) \
+    MOEP_READN(slot, 8) MOEP_READN(slot, 9) MOEP_LOADN(4, unit) MOEP_READN(slot, 10) MOEP_READN(slot, 11) MOEP_LOADN(5, unit) \
+    MOEP_READN(slot, 12) MOEP_READN(slot, 13) MOEP_LOADN(6, unit) MOEP_READN(slot, 14) MOEP_READN(slot, 15) MOEP_LOADN(7, unit)
 #define MOEP_READS(slot)                                                                        \
   _Pragma("unroll") for (int j_ = 0; j_ < NG; ++j_) { MOEP_RB(slot, j_) }                       \
-  _Pragma("unroll") for (int i_ = 0; i_ < 8; ++i_) { MOEP_RA(slot, i_) }
+  _Pragma("unroll") for (int i_ = 0; i_ < MG; ++i_) { MOEP_RA(slot, i_) }
   // Two MFMAs, a fragment read, two MFMAs, a fragment read, two MFMAs, a direct load: never more than one
-  // memory instruction between two MFMAs (1 % faster than 3 + read + 3 + read + load).  Half-width tiles: one MFMA
-  // before the load.
-#define MOEP_SCHED(LOADS)                                                                       \
-  _Pragma("unroll") for (int q_ = 0; q_ < (NG == 8 ? 8 : 6); ++q_) {                            \
-    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                          \
+  // memory instruction between two MFMAs (1 % faster than 3 + read + 3 + read + load).  Smaller tiles have fewer MFMAs for them.
+#define MOEP_SCHED()                                                                            \
+  _Pragma("unroll") for (int q_ = 0; q_ < (MG + NG) / 2; ++q_) {                                \
+    constexpr int per_ = 2 * MG * NG / (MG + NG);                                               \
+    __builtin_amdgcn_sched_group_barrier(0x008, per_ > 3 ? 2 : 1, 0);                           \
     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                          \
-    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                          \
+    __builtin_amdgcn_sched_group_barrier(0x008, per_ > 4 ? 2 : 1, 0);                           \
     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                          \
-    __builtin_amdgcn_sched_group_barrier(0x008, NG == 8 ? 2 : 1, 0);                            \
-    if (LOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                               \
+    __builtin_amdgcn_sched_group_barrier(0x008, per_ > 5 ? 2 : 1, 0);                           \
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                          \
   }
   // s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, lgkmcnt in bits 11:8 (0 here), expcnt 6:4 left at 7.
-  // Loads complete in issue order, so "at most 8 (half-width tiles: 6) outstanding" means that everything but the slice issued in
+  // Loads complete in issue order, so "at most STEP_LOADS outstanding" means that everything but the slice issued in
   // this step has landed, in particular the two slices whose fragments are read before the next barrier
   // (stores of an epilogue only add to the count).
   // BROW: a pair's second unit is issued one step before the first slice that needs it is read, so there is a barrier after
   // every step.  Before an odd step all but the loads from the newest unit's slice of A on have to have landed, before an even
   // step all but those of the two newest steps.  (The unit that an odd step's loads overwrite was read in the step before:
   // those reads are back, lgkmcnt 0, before the barrier.)
-  constexpr int STEP_LOADS = 4 + NG / 2;
+  constexpr int STEP_LOADS = MG / 2 + NG / 2;
   constexpr auto wait_for = [](int vm) { return 0x0070 | (vm & 15) | ((vm >> 4) << 14); };
-  constexpr int W_MAIN = wait_for(BROW ? 2 * STEP_LOADS : STEP_LOADS), W_ODD = wait_for(STEP_LOADS + 4);
+  constexpr int W_MAIN = wait_for(BROW ? 2 * STEP_LOADS : STEP_LOADS), W_ODD = wait_for(STEP_LOADS + MG / 2);
   // One step: multiply the slice whose fragments are in `slot`; meanwhile fetch the slice NS - 1 ahead and
   // read the next slice's fragments into the other slot.  The barrier at the end of every second step tells
   // every wavefront that the next two slices have landed for all of them and that all of them have read
@@ -477,7 +482,7 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
   {                                                                                             \
     MOEP_READS_LOADS((slot) ^ 1, slot)                                                          \
     MOEP_MFMA(slot)                                                                             \
-    MOEP_SCHED(true)                                                                            \
+    MOEP_SCHED()                                                                                \
     MOEP_ADVANCE_LOADER(slot)                                                                   \
     st_rd = st_rd + SLICE == RING ? 0 : st_rd + SLICE;                                          \
     ra = a_fb + st_rd;                                                                          \
@@ -494,8 +499,8 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
 #pragma unroll 1
   for (int n = 0; n < NS - 1; n += 2) {
 #define MOEP_LOADS(unit)                                                                        \
-    MOEP_LOADN(0, unit) MOEP_LOADN(1, unit) MOEP_LOADN(2, unit) MOEP_LOADN(3, unit) MOEP_LOADN(4, unit) MOEP_LOADN(5, unit) \
-    if constexpr (NG == 8) { MOEP_LOADN(6, unit) MOEP_LOADN(7, unit) }                          \
+    MOEP_LOADN(0, unit) MOEP_LOADN(1, unit) MOEP_LOADN(2, unit) MOEP_LOADN(3, unit)             \
+    MOEP_LOADN(4, unit) MOEP_LOADN(5, unit) MOEP_LOADN(6, unit) MOEP_LOADN(7, unit)             \
     MOEP_ADVANCE_LOADER(unit)
     MOEP_LOADS(0)
     MOEP_LOADS(1)
@@ -548,8 +553,8 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
     }
     char* const c_base = (char*)p.C + (GROUPED ? (int64_t)0 : (int64_t)e_mm * p.c_expert_bytes);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int prow = wm * 128 + i * 16 + (lane_e & 15);          // row inside the tile
+    for (int i = 0; i < MG; ++i) {
+      const int prow = wm * (MG * 16) + i * 16 + (lane_e & 15);          // row inside the tile
       const int64_t r = row0 + prow;
       if (r >= row_end) continue;
       if (EPI == EPI_SWIGLU) {
@@ -610,6 +615,7 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
 #undef MOEP_LOAD_A
 #undef MOEP_LOAD_B
 #undef MOEP_LOADN
+#undef MOEP_READN
 #undef MOEP_LOADS
 #undef MOEP_NEXT_UNIT
 #undef MOEP_B_ADDRESS
@@ -625,6 +631,10 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
 #undef MOEP_STEP
 }
 
+// The body is picked by the launch's row groups and tile width.  Row groups: of a launch whose tallest tile has up to 128 or 192
+// rows only those are fetched and multiplied.  Skipping forward, Mixtral shape, T = 300 (75 rows per expert) 705 -> 607 us, 450
+// 731 -> 640, 777 706 -> 645; dense pass of 128 tokens 748 -> 652, of 192 808 -> 754.  They are bodies of their own: with one
+// accumulator array and a loop per height the register allocator spilled some 400 registers around the loops.
 // A launch with so few tiles that compute units would stand idle walks tiles of half the width instead, 256 x 128
 // accumulator columns (64 outputs in SwiGLU mode), bits unchanged.  Half-width tiles cost well over half the time of full
 // ones (the same rows of A per step), so they only pay while they still fit one round (half_width_pays).  Grouped launches
@@ -633,8 +643,15 @@ __device__ __forceinline__ void gemm_body(const KArgs& p) {
 template <int EPI, bool GROUPED, bool BROW>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_packed_kernel(KArgs p) {
-  if (GROUPED ? p.tile_order[TILE_ORDER_HALF] != 0 : p.half_width != 0) gemm_body<EPI, GROUPED, BROW, 4>(p);
-  else gemm_body<EPI, GROUPED, BROW, 8>(p);
+  const bool half = GROUPED ? p.tile_order[TILE_ORDER_HALF] != 0 : p.half_width != 0;
+  const uint32_t mg = GROUPED ? p.tile_order[TILE_ORDER_ROW_GROUPS] : (uint32_t)p.row_groups;
+#define MOEP_BODY(NG)                                                                           \
+  if (mg > 6) gemm_body<EPI, GROUPED, BROW, NG, 8>();                                          \
+  else if (mg > 4) gemm_body<EPI, GROUPED, BROW, NG, 6>();                                     \
+  else gemm_body<EPI, GROUPED, BROW, NG, 4>();
+  if (half) { MOEP_BODY(4) }
+  else { MOEP_BODY(8) }
+#undef MOEP_BODY
 }
 
 // Per-device launch state, filled on a device's first launch under a mutex (first calls from several host threads are
@@ -779,6 +796,7 @@ int launch_gemm_bf16_packed(const PackedGemmArgs& g, hipStream_t s, const char* 
   const int64_t n_tiles = grouped || half ? n_half : n_full;
   if (m_tiles * n_tiles * g.experts >= ((int64_t)1 << 31)) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
   k.m_tiles = (int)m_tiles; k.n_tiles = (int)n_tiles; k.n_tiles_full = (int)n_full; k.half_width = half ? 1 : 0;
+  k.row_groups = gemm_row_groups(g.M);
   Timed t(name, s);
 #define MOEP_GEMM_CASE(EPI, GROUPED) \
   return g.b_row_major ? launch<EPI, GROUPED, true>(k, s) : launch<EPI, GROUPED, false>(k, s)

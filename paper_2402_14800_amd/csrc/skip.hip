@@ -67,17 +67,64 @@ __global__ __launch_bounds__(RB) void route_kernel(const float* __restrict__ log
   if ((int)threadIdx.x < E) counts[(int64_t)blockIdx.x * E + threadIdx.x] = cnt[threadIdx.x];
 }
 
-// seg_end holds 2 E + 1 ints: the E segment ends, then the index of each expert's first tile (E + 1 entries,
-// the last one being the number of tiles in use).  One workgroup: strands of consecutive routing blocks are summed per
+// Rows per tile of a routed 256-row GEMM: 256, or SHORT_TILE_ROWS where its two launches are shorter with that.  What they cost
+// is the rounds of 256 tiles (compute units) that they take, each as many steps as its K is deep; a step of a 192-row tile
+// costs 13/16 of a 256-row one's (6/8 of the products, but the same weights), and a launch of half-width tiles, which fits
+// one round, 10/16 of a round.  256 / 192 rows, us per call: Mixtral shape, T = 1500 (about 281 rows per expert, two tiles
+// either way) 1089 / 947, T = 3000 1689 / 1630, T = 2000 (375 rows: two or three tiles) 1095 / 1316; E 8, H 1024, F 3584,
+// T = 1500 127 / 113; E 16, H 2048, F 5632, top-4, T = 1500 (a 257th tile in the down projection) 499 / 553.
+struct Shorten { int n_up = 0, n_down = 0, k_up = 0, k_down = 0; };   // full-width N tiles of the launches; n_up = 0: tiles as given
+constexpr int SHORT_TILE_ROWS = 192;
+
+// The experts' segments and tiles from their row counts, by one wavefront: lane e < E holds expert e's count.  begin and
+// first_tile: [E + 1], in LDS.
+struct Segments { int32_t* seg_end; int32_t* tile_expert; int max_tiles, tile_rows; Shorten shorten; };
+__device__ __forceinline__ void lay_out_segments(int lane, int E, int count, const Segments& s, int* begin, int* first_tile,
+                                                 int* rows_of_tile) {
+  const int c = lane < E ? count : 0;
+  int tile_rows = s.tile_rows;
+  if (s.shorten.n_up != 0) {
+    int tall = (c + GEMM_BM - 1) / GEMM_BM, shortened = (c + SHORT_TILE_ROWS - 1) / SHORT_TILE_ROWS;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      tall += __shfl_xor(tall, off, 64);
+      shortened += __shfl_xor(shortened, off, 64);
+    }
+    auto launch = [](int64_t tiles, int k) { return (half_width_pays(tiles) ? 10 : 16 * ((tiles + 255) >> 8)) * (int64_t)k; };
+    auto both = [&](int64_t t) { return launch(t * s.shorten.n_up, s.shorten.k_up) + launch(t * s.shorten.n_down, s.shorten.k_down); };
+    if (shortened <= s.max_tiles && 13 * both(shortened) < 16 * both(tall)) tile_rows = SHORT_TILE_ROWS;
+  }
+  const int tiles = (c + tile_rows - 1) / tile_rows;
+  int end = c, tile_end = tiles;                 // inclusive sums over the lanes
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int a = __shfl_up(end, off, 64), b = __shfl_up(tile_end, off, 64);
+    end += lane >= off ? a : 0;
+    tile_end += lane >= off ? b : 0;
+  }
+  if (lane <= E) {
+    begin[lane] = end - c;
+    first_tile[lane] = tile_end - tiles;
+    s.seg_end[E + lane] = tile_end - tiles;
+    if (lane < E) s.seg_end[lane] = end;
+  }
+  if (lane == E) {
+    s.tile_expert[s.max_tiles] = tile_end;       // number of tiles in use, read by the grouped GEMMs
+    s.seg_end[2 * E + 1] = tile_rows;
+    *rows_of_tile = tile_rows;
+  }
+}
+
+// seg_end holds 2 E + 2 ints: the E segment ends, then the index of each expert's first tile (E + 1 entries,
+// the last one being the number of tiles in use), then the rows per tile.  One workgroup: strands of consecutive routing blocks are summed per
 // expert, a scan over the strands gives each its base, and the tile map is filled by all threads (one thread per expert
 // over all blocks, and one thread for the map: the dispatch of 32768 tokens took 45 us with that, now 18).
 constexpr int SCAN_THREADS = 1024;
 __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(int32_t* __restrict__ counts, int64_t n_blocks,
-                                                   int E, int32_t* __restrict__ seg_end,
-                                                   int32_t* __restrict__ tile_expert,
-                                                   int32_t* __restrict__ tile_row0, int max_tiles, int tile_rows) {
+                                                   int E, int32_t* __restrict__ tile_row0, Segments seg) {
   __shared__ int part[SCAN_THREADS];           // [strand][32 experts]
   __shared__ int begin[33], first_tile[33];
+  __shared__ int rows_of_tile;
   constexpr int STRANDS = SCAN_THREADS / 32;
   const int e = threadIdx.x & 31, strand = threadIdx.x >> 5;
   const int64_t per = (n_blocks + STRANDS - 1) / STRANDS;
@@ -94,19 +141,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(int32_t* __restrict_
     part[threadIdx.x] += v;
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    int run = 0, tiles = 0;
-    for (int i = 0; i < E; ++i) {
-      const int c = part[(STRANDS - 1) * 32 + i];
-      begin[i] = run;
-      first_tile[i] = tiles;
-      run += c;
-      tiles += (c + tile_rows - 1) / tile_rows;
-    }
-    begin[E] = run;
-    first_tile[E] = tiles;
-    tile_expert[max_tiles] = tiles;          // number of tiles in use, read by the grouped GEMMs
-  }
+  if (threadIdx.x < 64)
+    lay_out_segments(threadIdx.x, E, part[(STRANDS - 1) * 32 + (threadIdx.x & 31)], seg, begin, first_tile, &rows_of_tile);
   __syncthreads();
   if (e < E) {
     int run = begin[e] + part[threadIdx.x] - sum;
@@ -116,16 +152,14 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(int32_t* __restrict_
       run += c;
     }
   }
-  if ((int)threadIdx.x < E) seg_end[threadIdx.x] = begin[threadIdx.x + 1];
-  if ((int)threadIdx.x <= E) seg_end[E + threadIdx.x] = first_tile[threadIdx.x];
-  for (int i = threadIdx.x; i < max_tiles; i += SCAN_THREADS) {
+  for (int i = threadIdx.x; i < seg.max_tiles; i += SCAN_THREADS) {
     int o = -1, row = 0;
     if (i < first_tile[E]) {
       o = 0;
       while (first_tile[o + 1] <= i) ++o;
-      row = begin[o] + (i - first_tile[o]) * tile_rows;
+      row = begin[o] + (i - first_tile[o]) * rows_of_tile;
     }
-    tile_expert[i] = o;
+    seg.tile_expert[i] = o;
     tile_row0[i] = row;
   }
 }
@@ -138,15 +172,21 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(int32_t* __restrict_
 // blockIdx.y: 0 the gate/up projection's table, 1 the down projection's.  The width of the tiles is decided here, from the
 // number of tiles the routing made, and noted in the table's header.
 struct OrderArgs { uint32_t* order; int n_full, n_half, group_m; };
-__global__ __launch_bounds__(256) void order_kernel(const int32_t* __restrict__ expert_first, int E, OrderArgs up,
+__global__ __launch_bounds__(256) void order_kernel(const int32_t* __restrict__ expert_end, int E, OrderArgs up,
                                                     OrderArgs down) {
+  const int32_t* const expert_first = expert_end + E;
   const OrderArgs a = blockIdx.y ? down : up;
   __shared__ int first[33];
   if ((int)threadIdx.x <= E) first[threadIdx.x] = expert_first[threadIdx.x];
   __syncthreads();
   const bool half = half_width_pays((int64_t)first[E] * a.n_full);
   const int n_tiles = half ? a.n_half : a.n_full;
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.order[TILE_ORDER_HALF] = half ? 1u : 0u;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    int most = 0;                                          // rows of one expert
+    for (int e = 0; e < E; ++e) most = max(most, expert_end[e] - (e ? expert_end[e - 1] : 0));
+    a.order[TILE_ORDER_HALF] = half ? 1u : 0u;
+    a.order[TILE_ORDER_ROW_GROUPS] = (uint32_t)gemm_row_groups(min(most, expert_end[2 * E + 1]));
+  }
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (q >= (int64_t)first[E] * n_tiles) return;
   int e = 0;
@@ -387,11 +427,12 @@ template <int K, bool TOP2, int EMAX>
 __global__ __launch_bounds__(DISPATCH_ONE_MAX) void dispatch_one_kernel(
     const float* __restrict__ logits, int T, int E, bool vec, uint32_t kept, float theta, double beta, uint8_t* __restrict__ skip_mask,
     int32_t* __restrict__ n_used, int32_t* __restrict__ experts, int32_t* __restrict__ slot_token,
-    float* __restrict__ slot_scale, int32_t* __restrict__ slot_dest, int32_t* __restrict__ pos, int32_t* __restrict__ seg_end,
-    int32_t* __restrict__ tile_expert, int32_t* __restrict__ tile_row0, int max_tiles, int tile_rows) {
+    float* __restrict__ slot_scale, int32_t* __restrict__ slot_dest, int32_t* __restrict__ pos, int32_t* __restrict__ tile_row0,
+    Segments seg) {
   constexpr int WAVES = DISPATCH_ONE_MAX / 64;
   __shared__ int wave_base[WAVES][32];     // counts, then first slots, of (wavefront, expert)
   __shared__ int begin[33], first_tile[33];
+  __shared__ int rows_of_tile;
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const bool live = t < T;
@@ -430,40 +471,24 @@ __global__ __launch_bounds__(DISPATCH_ONE_MAX) void dispatch_one_kernel(
   }
   __syncthreads();
   const int waves = blockDim.x >> 6;
-  if (t < E) {                              // slots before (wavefront, expert t) within the expert's segment
-    int run = 0;
-    for (int v = 0; v < waves; ++v) {
-      const int c = wave_base[v][t];
-      wave_base[v][t] = run;
-      run += c;
-    }
-    begin[t + 1] = run;                     // for now: the expert's rows
-  }
-  __syncthreads();
-  if (t == 0) {
-    int run = 0, tiles = 0;
-    begin[0] = 0;
-    for (int e = 0; e < E; ++e) {
-      const int c = begin[e + 1];
-      first_tile[e] = tiles;
-      seg_end[E + e] = tiles;
-      tiles += (c + tile_rows - 1) / tile_rows;
-      run += c;
-      begin[e + 1] = run;
-      seg_end[e] = run;
-    }
-    first_tile[E] = tiles;
-    seg_end[2 * E] = tiles;
-    tile_expert[max_tiles] = tiles;         // number of tiles in use, read by the grouped GEMMs
+  if (wave == 0) {
+    int run = 0;                            // slots before (wavefront, expert t) within the expert's segment, then its rows
+    if (t < E)
+      for (int v = 0; v < waves; ++v) {
+        const int c = wave_base[v][t];
+        wave_base[v][t] = run;
+        run += c;
+      }
+    lay_out_segments(t, E, run, seg, begin, first_tile, &rows_of_tile);
   }
   __syncthreads();
   if (t < E)
     for (int i = first_tile[t]; i < first_tile[t + 1]; ++i) {
-      tile_expert[i] = t;
-      tile_row0[i] = begin[t] + (i - first_tile[t]) * tile_rows;
+      seg.tile_expert[i] = t;
+      tile_row0[i] = begin[t] + (i - first_tile[t]) * rows_of_tile;
     }
-  for (int i = first_tile[E] + t; i < max_tiles; i += blockDim.x) {
-    tile_expert[i] = -1;
+  for (int i = first_tile[E] + t; i < seg.max_tiles; i += blockDim.x) {
+    seg.tile_expert[i] = -1;
     tile_row0[i] = 0;
   }
   if (!live) return;
@@ -499,7 +524,7 @@ int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_ex
   p->off_slot_dest = take((size_t)p->max_slots * 4);
   p->off_pos = take((size_t)T * ks * 4 * 3);           // pos, experts, weights: [T,ks] each
   p->off_counts = take((size_t)n_blocks * E * 4);
-  p->off_seg_end = take((size_t)(2 * E + 1) * 4);          // segment ends, then each expert's first tile
+  p->off_seg_end = take((size_t)(2 * E + 2) * 4);          // segment ends, then each expert's first tile, then rows per tile
   p->off_tile_expert = take((size_t)(map_tiles + 1) * 4);   // + the count of tiles in use
   p->off_tile_row0 = take((size_t)map_tiles * 4);
   p->packed = dt == MOEP_BF16;
@@ -526,17 +551,23 @@ int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_ex
   return MOEP_OK;
 }
 
+static Segments segments(const SkipPlan& p, char* ws) {
+  Segments s = {(int32_t*)(ws + p.off_seg_end), (int32_t*)(ws + p.off_tile_expert), (int)p.max_tiles, p.tile_rows, {}};
+  if (p.packed && !p.few) s.shorten = {(int)ceil_div(p.F, GEMM_BN_SWIGLU), (int)ceil_div(p.H, GEMM_BN_STORE), p.H, p.F};
+  return s;
+}
+
 // Tile order tables of the two grouped projections (bf16 path), from the tile map scan_kernel has just written.
 static void launch_order_tables(const SkipPlan& p, char* ws, hipStream_t s) {
   if (!p.packed || p.few) return;
-  const int32_t* expert_first = (const int32_t*)(ws + p.off_seg_end) + p.E;
+  const int32_t* expert_end = (const int32_t*)(ws + p.off_seg_end);
   const OrderArgs up = {(uint32_t*)(ws + p.off_order_up), (int)ceil_div(p.F, gemm_tile_columns(true, false)),
                         (int)ceil_div(p.F, gemm_tile_columns(true, true)), GEMM_GROUP_M_SWIGLU};
   const OrderArgs down = {(uint32_t*)(ws + p.off_order_down), (int)ceil_div(p.H, gemm_tile_columns(false, false)),
                           (int)ceil_div(p.H, gemm_tile_columns(false, true)), GEMM_GROUP_M_STORE};
   // entries of the larger table: p.max_tiles full-width tiles, or the few half-width ones that half_width_pays allows
   const int64_t n = p.max_tiles * (up.n_full > down.n_full ? up.n_full : down.n_full);
-  hipLaunchKernelGGL(order_kernel, dim3((unsigned)ceil_div(n > 512 ? n : 512, 256), 2), dim3(256), 0, s, expert_first, p.E,
+  hipLaunchKernelGGL(order_kernel, dim3((unsigned)ceil_div(n > 512 ? n : 512, 256), 2), dim3(256), 0, s, expert_end, p.E,
                      up, down);
 }
 
@@ -556,8 +587,7 @@ int launch_skip_routing(const SkipPlan& p, const float* logits, uint32_t kept_ma
   hipLaunchKernelGGL((dispatch_one_kernel<2, true, EMAX>), dim3(1), dim3((unsigned)ceil_div(T, 64) * 64), 0, s, logits,  \
                      (int)T, p.E, vec, kept_mask, theta, 0.0, skip_mask, (int32_t*)nullptr, top2,                        \
                      (int32_t*)(ws + p.off_slot_token), (float*)(ws + p.off_slot_scale),                                 \
-                     (int32_t*)(ws + p.off_slot_dest), pos, (int32_t*)(ws + p.off_seg_end),                              \
-                     (int32_t*)(ws + p.off_tile_expert), (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows)
+                     (int32_t*)(ws + p.off_slot_dest), pos, (int32_t*)(ws + p.off_tile_row0), segments(p, ws))
     if (p.E <= 8) MOEP_ONE(8);
     else if (p.E <= 16) MOEP_ONE(16);
     else MOEP_ONE(32);
@@ -574,8 +604,7 @@ int launch_skip_routing(const SkipPlan& p, const float* logits, uint32_t kept_ma
   else MOEP_ROUTE(32);
 #undef MOEP_ROUTE
   hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, counts, n_blocks, p.E,
-                     (int32_t*)(ws + p.off_seg_end), (int32_t*)(ws + p.off_tile_expert),
-                     (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows);
+                     (int32_t*)(ws + p.off_tile_row0), segments(p, ws));
   launch_order_tables(p, ws, s);
   hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)n_blocks), dim3(RB), 0, s, top2, tw, skip_mask,
                      counts, T, p.E, (int32_t*)(ws + p.off_slot_token),
@@ -621,8 +650,7 @@ int launch_skip_topk_routing(const SkipPlan& p, const float* logits, uint32_t ke
 #define MOEP_ONE(KK, EMAX)                                                                                             \
   hipLaunchKernelGGL((dispatch_one_kernel<KK, false, EMAX>), dim3(1), dim3((unsigned)ceil_div(T, 64) * 64), 0, s,      \
                      logits, (int)T, p.E, vec, kept_mask, 0.0f, (double)beta, (uint8_t*)nullptr, n_used, topk,         \
-                     slot_token, slot_scale, slot_dest, pos, (int32_t*)(ws + p.off_seg_end),                           \
-                     (int32_t*)(ws + p.off_tile_expert), (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows)
+                     slot_token, slot_scale, slot_dest, pos, (int32_t*)(ws + p.off_tile_row0), segments(p, ws))
 #define MOEP_ONE_CASE(KK)                                                                                              \
   case KK:                                                                                                             \
     if (p.E <= 16) MOEP_ONE(KK, 16);                                                                                   \
@@ -659,8 +687,7 @@ int launch_skip_topk_routing(const SkipPlan& p, const float* logits, uint32_t ke
 #undef MOEP_ROUTE_CASE
 #undef MOEP_ROUTE
   hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, counts, n_blocks, p.E,
-                     (int32_t*)(ws + p.off_seg_end), (int32_t*)(ws + p.off_tile_expert),
-                     (int32_t*)(ws + p.off_tile_row0), (int)p.max_tiles, p.tile_rows);
+                     (int32_t*)(ws + p.off_tile_row0), segments(p, ws));
   launch_order_tables(p, ws, s);
 #define MOEP_SCATTER_CASE(KK)                                                                  \
   case KK:                                                                                    \

@@ -215,3 +215,38 @@ def test_streamed_weights_give_the_bits_of_many_rows():
     _, Y_p = pkg.moe_expert_outputs_packed(part, rest[0], packed, F)
     torch.cuda.synchronize()
     assert torch.equal(bits(Y_r), bits(Y[:, :33].contiguous())) and torch.equal(bits(Y_p), bits(Y_r))
+
+
+@pytest.mark.parametrize("E,H,F,T,kept,rows", [
+    (4, 128, 320, 300, 0b0011, 300),       # every kept expert gets all 300 rows: two tiles of 192 for two of 256
+    (3, 64, 192, 384, 0b0101, 384),        # two full tiles of 192
+    (3, 64, 192, 385, 0b0101, 385),        # three of 192 against two of 256: 256
+    (2, 192, 448, 129, 0b11, 129),         # one tile of 192 rows
+    (2, 192, 448, 128, 0b11, 128),         # one of 128
+    (2, 64, 64, 192, 0b11, 192),
+    (2, 64, 64, 193, 0b11, 193),           # one of 256
+    (2, 128, 320, 2300, 0b11, 2300),       # 12 tiles of 192 for 9 of 256, by the three-kernel dispatch
+    (6, 64, 8256, 800, 0b101011, 0),       # more tiles than compute units
+])
+def test_short_tiles_give_the_bits_of_full_ones(E, H, F, T, kept, rows):
+    """Routed launches whose tiles are 256, 192 or 128 rows tall, without skipping, in place and on packed weights: the same
+    bits as the token's rows in a batch whose experts fill 256-row tiles, and as the dense pass of the same rows."""
+    _, layer = small_layer("bf16", E, 2, H, F, 6144, index=28)
+    d = to_dev(layer)
+    rest = [d[n] for n in NAMES[1:]]
+    packed = pkg.moe_pack_weights(d["W1"], d["W3"], d["W2"])
+    out_many, _, _, _ = pkg.moe_forward_skip(d["x"], *rest, 0.0, kept_mask=kept)
+    x = d["x"][:T].contiguous()
+    out, _, _, top = pkg.moe_forward_skip(x, *rest, 0.0, kept_mask=kept)
+    out_p, _, _, _ = pkg.moe_forward_pruned_skip_packed(x, d["Wgate"], packed, F, 0.0, kept_mask=kept)
+    _, Y = pkg.moe_expert_outputs(x, *rest)
+    _, Y_many = pkg.moe_expert_outputs(d["x"], *rest)
+    torch.cuda.synchronize()
+    if rows:                               # what the routing was made to give
+        counts = np.bincount(top.cpu().numpy().reshape(-1), minlength=E)
+        assert all(counts[e] == (rows if kept >> e & 1 else 0) for e in range(E))
+    assert torch.equal(bits(out), bits(out_many[:T].contiguous())) and torch.equal(bits(out_p), bits(out))
+    assert torch.equal(bits(Y), bits(Y_many[:, :T].contiguous()))
+    pick = torch.tensor([0, T // 2, T - 1])
+    _, ref = oracle.expert_outputs(*[wl.to_f64(v) for v in (layer["x"][pick], *[layer[n] for n in NAMES[1:]])])
+    check_outputs(wl.to_f64(Y[:, pick.to(Y.device)].contiguous()), ref, "Y")
