@@ -246,6 +246,10 @@ struct EnumPlan {
   bool use_lut;      // many subsets, few selections per token: score through per-token selection tables
   int n_combo;       // C(n_act, kk): selections per token
   int lut_spl;       // subsets per lane of the table scorer (0 without it)
+  int fused_threads; // up to 16 experts: tables and look-ups in one kernel, its workgroup (0: not taken),
+  int fused_spl;     //   subsets per lane,
+  int fused_tg;      //   tokens per barrier
+  size_t fused_lds;  //   and dynamic LDS
   // workspace carving (byte offsets)
   size_t off_gram, off_rec, off_masks, off_partial, off_partial_cnt, off_qtab, off_sel, off_selbits, off_nib, total;
 };
@@ -262,7 +266,7 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
                      char* ws, hipStream_t s, const RankedSource* ranked = nullptr, bool reuse_gram = false);
 
 // fp64 sum of n_tiles partial sums per subset (partial[tile * n_sub + subset]) in a fixed order -> loss; sum of the
-// partial counts -> *unaffected (may be NULL; `cleared`: already 0); lowest-index argmin and its kept mask
+// partial counts (NULL: *unaffected holds it already) -> *unaffected (may be NULL; `cleared`: already 0); lowest-index argmin and its kept mask
 int launch_reduce_argmin(const float* partial, const uint32_t* partial_cnt, int64_t n_tiles, int64_t n_sub, int E,
                          int r, float* loss, int32_t* argmin, uint32_t* argmin_mask, int64_t* unaffected, bool cleared,
                          hipStream_t s);

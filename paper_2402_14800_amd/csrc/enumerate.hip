@@ -18,10 +18,10 @@
 //               (scalar loads); each lane walks the rank positions, takes the first min(k,r) whose
 //               expert is in its mask, forms d explicitly and evaluates d^T G d.  A pair whose
 //               selection equals the full top-k contributes exactly 0 and is counted.
-//   score (many subsets)  A token's error depends on the subset only through WHICH of its first n_act ranked experts
-//               are kept, and then only through the first min(k,r) of those: C(n_act, min(k,r)) possible selections per
-//               token against C(E,r) subsets (495 against 12870 for E = 16, k = 4, r = 8).  qtable evaluates the error
-//               of every selection once per token; score_lut then needs, per (subset, token), a few table look-ups:
+//   score (many subsets; up to 16 experts through fused_score_lut_kernel, which keeps the tables in LDS)
+//               A token's error depends on the subset only through WHICH of its first n_act ranked experts are kept, and
+//               then only through the first min(k,r) of those: C(n_act, min(k,r)) possible selections per token against
+//               C(E,r) subsets (495 against 12870 for E = 16, k = 4, r = 8).  qtable evaluates the error of every selection once per token; score_lut then needs, per (subset, token), a few table look-ups:
 //               kept mask -> pattern of kept rank positions (nibble tables built per token from its order),
 //               pattern -> selection index (one table per launch), selection index -> error.
 //   reduce      loss[i] = sum over token tiles of the partial sums, in a fixed order (fp64 adds).
@@ -544,6 +544,7 @@ __global__ __launch_bounds__(STRANDS ? 1024 : 256) void score_kernel(const float
 }
 
 // ------------------------------------------------------------------ scoring through per-token selection tables
+// More than 16 experts: half masks have up to 65536 patterns, too many for the tables of the fused scorer further down.
 // Rank of the selection made by the kept-position pattern `pat` (bit j = the token's j-th ranked expert is kept):
 // the first kk set bits, as a kk-subset of the n_act positions, indexed in lexicographic order (index 0 = positions
 // 0 .. kk-1 = the selection of the full layer when kk = k).  Patterns with fewer than kk bits belong to no subset.
@@ -708,6 +709,441 @@ __global__ __launch_bounds__(256, 3) void score_lut_kernel(const float* __restri
   }
 }
 
+// ------------------------------------------------------------------ scoring through tables that never leave the LDS
+// Up to 16 experts.  A workgroup owns a tile of tokens and ALL subsets; per group of `tg` tokens it
+//   1. evaluates the error of every selection: U = G d for 64 selections of a token on v_mfma_f32_16x16x4_f32 (fp32 products and
+//      sums), then d^T U.  A lane holds VP = ceil(CAP / 4) positions of one selection of each 16; the matrix instruction's
+//      operand and result layouts agree on them, and sums over positions are three row swaps per 64 selections;
+//   2. spreads the errors over all 2^nb patterns of kept rank positions (a thread writes the same patterns for every
+//      token: their selection indices stay in registers), so that
+//   3. a (subset, token) pair is ONE look-up: pattern -> error.
+// The pattern of a subset is that of its kept experts among the first eight (low) plus that of its kept experts among the
+// rest (high).  In lexicographic order the subsets with one low part are neighbours, ordered by their high part; a lane
+// takes SPL neighbours, so that it looks up its low pattern once per token and reads SPL consecutive high ones.  A word
+// holds the patterns of two tokens, as byte offsets of their entries.
+// Where pattern `pat` of a token is kept: its bits from 5 up are folded onto the five that choose the bank, by columns of
+// which no three cancel.  The patterns of a wavefront differ in the positions of the few experts that vary among its lanes,
+// any of the n_act: 2.0 different addresses in the fullest bank of 32 lanes, 9.3 without the fold.  The fold is linear over
+// XOR, and low and high patterns share no bit: the tables hold folded ones, the look-up XORs two of them.
+// What bounds it: no single unit.  E 16, k 4, 65536 tokens, r = 8 (495 selections, 12870 subsets): 384 us, where the tables in
+// global memory and their look-ups took 234 + 664; r = 12 (70, 1820): 82 us, 42 + 109 before; 33 tokens of r = 8, the whole
+// call: 150 -> 57 us.  Left out one at a time, of the 384: phase 1 140 us, phase 2 64, phase 3 57, the pattern tables 19; about
+// 45 are set-up and the partial sums.  Phase 1 by fp32 FMAs with the record in scalar registers took 230 VALU operations
+// per 64 selections and token where it takes 100 and 12 matrix instructions now, records in the LDS.
+constexpr int FUSED_MAX_E = 16, FUSED_PER_THREAD = 4;        // patterns per thread and pass of phase 2
+__device__ __forceinline__ uint32_t fold_column(int j) {     // of rank position j
+  constexpr uint32_t fold[7] = {7, 11, 13, 14, 19, 21, 22};
+  uint32_t c = 1u << j;
+#pragma unroll
+  for (int i = 0; i < 7; ++i) c ^= j == 5 + i ? fold[i] : 0u;
+  return c;
+}
+// A token pair's pattern tables: 256 low masks, then the high masks by their number of experts, each number from an even place
+// on (8-byte reads), with room for the last lane to read past the end.
+constexpr int FUSED_LOW = 8, FUSED_TAB = 256 + 256 + 32, FUSED_ERRORS = 1024;   // (errors of a group: tokens x whole chunks of 64)
+__host__ __device__ constexpr int fused_pattern_bits(int n_act) { return n_act < 6 ? 6 : n_act; }   // tables of whole wavefronts
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// Rows (16 lanes) r of four values a, b, c, d, added over r: row g of the result is the sum of value g.
+__device__ __forceinline__ float rows_to_sums(float a, float b, float c, float d) {
+  const u32x2 ab = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  const u32x2 cd = __builtin_amdgcn_permlane16_swap(__float_as_uint(c), __float_as_uint(d), false, false);
+  const float x = __uint_as_float(ab[0]) + __uint_as_float(ab[1]), y = __uint_as_float(cd[0]) + __uint_as_float(cd[1]);
+  const u32x2 xy = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(xy[0]) + __uint_as_float(xy[1]);
+}
+// v[g] = row g of x, in every row
+__device__ __forceinline__ void rows_to_all(float x, float (&v)[4]) {
+  const u32x2 h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const u32x2 w = __builtin_amdgcn_permlane16_swap(h[i], h[i], false, false);
+    v[2 * i] = __uint_as_float(w[0]);
+    v[2 * i + 1] = __uint_as_float(w[1]);
+  }
+}
+
+// The error of one selection whose logits all lie far below the token's maximum: Eq. 1 relative to the largest SELECTED one
+// (see score_kernel).  Rare, and written to need few registers.
+template <int CAP>
+__device__ __forceinline__ float far_selection_error(const float* R, uint32_t bits) {
+  const float m = R[CAP + __ffs(bits) - 1];
+  float sum = 0.f, q = 0.f;
+#pragma unroll 1
+  for (int j = 0; j < CAP; ++j) sum += (bits >> j) & 1u ? __expf(R[CAP + j] - m) : 0.f;
+  const float inv = __builtin_amdgcn_rcpf(sum);
+  const float* g = R + 3 * CAP;
+#pragma unroll 1
+  for (int i = 0; i < CAP; ++i) {
+    float u = 0.f, di = 0.f;
+#pragma unroll 1
+    for (int j = i; j < CAP; ++j) {
+      const float d = fmaf((bits >> j) & 1u ? __expf(R[CAP + j] - m) : 0.f, inv, -R[2 * CAP + j]);
+      if (j == i) di = d;
+      u = fmaf(*g++, d, u);
+    }
+    q = fmaf(di, u, q);
+  }
+  return q;
+}
+
+// (lo or hi half of a) ^ (the same half of b)
+template <int HALF>
+__device__ __forceinline__ uint32_t xor_half(uint32_t a, uint32_t b) {
+  uint32_t d;
+  if constexpr (HALF == 0)
+    asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_0" : "=v"(d) : "v"(a), "v"(b));
+  else
+    asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:WORD_1" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+typedef __attribute__((address_space(3))) const float* lds_float;
+
+template <int CAP, int SPL>
+__global__ __launch_bounds__(1024, 8) void fused_score_lut_kernel(const float* __restrict__ rec_all, int64_t T, int tok_tile, int E,
+                                                               int r, int kk, int kfull, int n_act, int n_combo,
+                                                               uint32_t n_sub, int tg, float* __restrict__ partial,
+                                                               unsigned long long* __restrict__ unaffected) {
+  constexpr int RS = rec_size(CAP), VP = (CAP + 3) / 4;
+  const int eh = E - FUSED_LOW, nb = fused_pattern_bits(n_act), chunks = (n_combo + 63) >> 6;
+  extern __shared__ uint32_t smem[];                                   // (the only LDS of the kernel: at address 0)
+  float* const ptab = (float*)smem;                                    // tg x 2^nb
+  float* const s_q = ptab + (tg << nb);                                // tg x chunks x 64
+  uint32_t* const s_mine = (uint32_t*)(s_q + FUSED_ERRORS);            // a word per thread
+  uint16_t* const s_bits = (uint16_t*)(s_mine + 1024);                 // chunks x 64: selections
+  uint16_t* const s_selbits = s_bits + LUT_MAX_COMBO;                  // the same by lane
+  uint16_t* const s_hpos = s_selbits + LUT_MAX_COMBO;                  // 2^eh
+  uint2* const s_off = (uint2*)(s_hpos + 256);                         // a wavefront's places in a record
+  float* const s_rec = (float*)(s_off + 64);                           // 2 x tg x RS: records of this and the next group
+  uint32_t* const s_tab = (uint32_t*)(s_rec + 2 * tg * RS);            // 2 x tg / 2 x FUSED_TAB
+  const int tid = threadIdx.x, threads = blockDim.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = threads >> 6;
+  const int64_t t_begin = (int64_t)blockIdx.x * tok_tile;
+  const int count = (int)(T - t_begin < tok_tile ? T - t_begin : tok_tile);    // tokens of this workgroup
+  const float* const rec = rec_all + t_begin * RS;
+
+  // records of the group from token g0 on: a quad per thread (tg RS <= 4 x 256)
+  const bool fetching = 4 * tid < tg * RS;
+  auto fetch = [&](int g0) {
+    uint32_t at = 16u * (uint32_t)tid;
+    asm volatile("" : "+v"(at));
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (fetching && (int)at < 4 * (count - g0) * RS) v = *(const float4*)((const char*)(rec + (int64_t)g0 * RS) + at);
+    return v;
+  };
+  if (fetching) ((float4*)s_rec)[tid] = fetch(0);
+
+  // ---- set-up.  In the place of the pattern tables: the binomials, the walk of four rank positions at a time, and for every
+  // mask of eight experts its place among those of as many experts and the first subset with it as low part.  Every chain of
+  // dependent look-ups here is short: the workgroups of a launch start together, and all wait for it.
+  uint16_t* const s_binom = (uint16_t*)ptab;                           // 17 x 17
+  uint32_t* const s_walk = smem + 160;                                 // [position / 4][experts still to find][their pattern]
+  uint8_t* const s_lowmask = (uint8_t*)(s_tab + tg * FUSED_TAB);       // place -> low mask
+  uint16_t* const s_first = (uint16_t*)(s_lowmask + 256);              // low mask -> subset
+  for (int i = tid; i < 17 * 17; i += threads) s_binom[i] = (uint16_t)c_binom.v[i / 17][i % 17];
+  for (int i = tid; i < tg * FUSED_TAB; i += threads) s_tab[i] = 0u;
+  for (int c = n_combo + tid; c < chunks * 64; c += threads) s_bits[c] = (uint16_t)((1u << kk) - 1u);   // idle lanes: selection 0
+  __syncthreads();
+  auto binom = [&](int n, int k) { return (uint32_t)s_binom[n * 17 + k]; };
+  // steps of the lexicographic rank: an element not taken, with k still to come among n - 1 further ones, skips C(n - 1, k - 1)
+  auto skipped = [&](bool taken, int n, int k) { return taken || k <= 0 ? 0u : binom(n - 1, k - 1); };
+  const int walks = (n_act + 3) >> 2;
+  for (int i = tid; i < walks * (kk + 1) * 16; i += threads) {
+    const int from = 4 * (i / ((kk + 1) * 16));
+    int k = (i >> 4) % (kk + 1);
+    uint32_t idx = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (from + e < n_act) {
+        const bool taken = (i >> e) & 1;
+        idx += skipped(taken, n_act - from - e, k);
+        k -= taken && k > 0;
+      }
+    s_walk[i] = idx | (uint32_t)k << 16;
+  }
+  if (tid < 256) {
+    const int m = tid, count8 = __popc((uint32_t)m);
+    int kl = count8, kh = count8, kr = r;
+    uint32_t low = 0, high = 0, begin = 0, low_place = 0, high_place = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool taken = (m >> e) & 1;
+      low += skipped(taken, 8 - e, kl);
+      if (e < eh) high += skipped(taken, eh - e, kh);
+      begin += skipped(taken, E - e, kr);
+      kl -= taken;
+      kh -= taken;
+      kr -= taken;
+      low_place += e < count8 ? binom(8, e) : 0u;
+      high_place += e < count8 && e <= eh ? (binom(eh, e) + 1u) & ~1u : 0u;
+    }
+    s_lowmask[low_place + low] = (uint8_t)m;
+    s_first[m] = (uint16_t)begin;                        // (meaningless, and never asked for, with more than r experts)
+    if (m < (1 << eh)) s_hpos[m] = (uint16_t)(high_place + high);
+  }
+  // this lane's subsets: h experts of the high part, entry q of those
+  int lanes = 0, mine = -1, q = 0, place = 0;
+  {
+    int at = 0;
+#pragma unroll
+    for (int h = 0; h <= FUSED_MAX_E - FUSED_LOW; ++h) {
+      const int a = h <= r ? r - h : FUSED_LOW + 1, nh = (int)c_binom.v[eh][h];     // (more of a half than it has: 0 ways)
+      const int here = (int)c_binom.v[FUSED_LOW][a] * ((nh + SPL - 1) / SPL);
+      if (tid >= lanes && tid < lanes + here) { mine = h; q = tid - lanes; place = at; }
+      lanes += here;
+      at += (nh + 1) & ~1;
+    }
+  }
+  const bool scoring = wave * 64 < lanes;
+  __syncthreads();
+  uint32_t lowm = 0;                                     // low part
+  int hoff = 0;                                          // place of the first high part
+  {
+    uint32_t word = 0;                                   // first subset, how many
+    if (mine >= 0) {
+      const int a = r - mine, nl = (int)binom(FUSED_LOW, a), nh = (int)binom(eh, mine);
+      const int seg = (int)(((float)q + 0.5f) * __builtin_amdgcn_rcpf((float)nl));   // q / nl: below 1024 / 70, exact
+      uint32_t low_place = 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) low_place += e < a ? binom(8, e) : 0u;
+      lowm = s_lowmask[low_place + (uint32_t)(q - seg * nl)];
+      hoff = place + seg * SPL;
+      const int left = nh - seg * SPL;
+      word = ((uint32_t)s_first[lowm] + (uint32_t)(seg * SPL)) | (uint32_t)(left < SPL ? left : SPL) << 16;
+    }
+    s_mine[tid] = word;                                  // not needed before the end
+  }
+  // this thread's patterns: byte offsets of their selections' errors
+  uint32_t sel[FUSED_PER_THREAD];
+#pragma unroll
+  for (int n = 0; n < FUSED_PER_THREAD; ++n) {
+    uint32_t pat = (uint32_t)(tid + n * threads) & ((1u << nb) - 1u), idx = 0;   // bits from 5 up lie where they are
+    const uint32_t high = pat >> 5;
+    constexpr uint32_t fold[7] = {7, 11, 13, 14, 19, 21, 22};
+#pragma unroll
+    for (int j = 0; j < 7; ++j) pat ^= (uint32_t)__builtin_amdgcn_sbfe((int)high, j, 1) & fold[j];
+    int k = kk;
+#pragma unroll
+    for (int w = 0; w < 3; ++w)
+      if (w < walks) {
+        const uint32_t step = s_walk[(w * (kk + 1) + k) * 16 + ((pat >> (4 * w)) & 15u)];
+        idx += step & 0xffffu;
+        k = (int)(step >> 16);
+      }
+    if (k == 0 && __popc(pat) == kk && pat < (1u << n_act)) s_bits[idx] = (uint16_t)pat;
+    sel[n] = 4u * (k == 0 ? idx : (n_combo > 1 ? 1u : 0u));   // too few bits: no subset has this pattern
+  }
+  // where a lane's matrix row (a place for each of VP columns) and columns lie in a record, in bytes; beyond CAP or below the
+  // diagonal: the record's last word, which is 0
+  if (tid < 64) {
+    const int row = tid >> 4, slot = tid & 15, pr = VP * (slot >> 2) + (slot & 3);
+    uint16_t off[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int v = 0; v < VP; ++v) {
+      const int j = VP * row + v;
+      const bool upper = j < CAP && (slot & 3) < VP && pr <= j;
+      off[v] = (uint16_t)(4 * (upper ? 3 * CAP + pr * CAP - pr * (pr - 1) / 2 + j - pr : RS - 1));
+    }
+    s_off[tid] = make_uint2(off[0] | (uint32_t)off[1] << 16, off[2]);
+  }
+  __syncthreads();
+  for (int c = tid; c < chunks * 64; c += threads) {
+    // for this place's lane: bit g VP + v = position VP (lane / 16) + v of selection 16 g + lane % 16 of the 64
+    uint32_t word = 0;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      word |= (((uint32_t)s_bits[(c & ~63) + 16 * g + (c & 15)] >> (VP * ((c >> 4) & 3))) & ((1u << VP) - 1u)) << (g * VP);
+    s_selbits[c] = (uint16_t)word;
+  }
+  float total[SPL];
+#pragma unroll
+  for (int s = 0; s < SPL; ++s) total[s] = 0.f;
+  // Pattern tables of the token pairs of the group from token g0 on, a wavefront per pair from the last one down (the last
+  // may have no subsets): lane = (low or high half, nibble of it, value), then the masks of 64 lanes at a time.
+  auto build_tables = [&](int ntok, const float* records, uint32_t* tabs) {
+#pragma unroll 1
+    for (int pr = waves - 1 - wave; 2 * pr < ntok; pr += waves) {
+      int lane = tid & 63, active = n_act;               // nothing derived from these is worth a register across the loop
+      asm volatile("" : "+v"(lane), "+s"(active));
+      const uint32_t m = (uint32_t)(lane & 15) << (4 * (lane >> 4));
+      uint32_t ordw[2][VP], word = 0;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int w = 0; w < VP; ++w)
+          ordw[h][w] = __builtin_amdgcn_readfirstlane(__float_as_int(records[(2 * pr + h) * RS + rec_order_off(CAP) + w]));
+#pragma unroll
+      for (int j = 0; j < CAP; ++j) {
+        const uint32_t column = j < active ? fold_column(j) << 2 : 0u;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t e = (ordw[h][j >> 2] >> (8 * (j & 3))) & 0x1fu;
+          word ^= (column << (16 * h)) & (uint32_t)__builtin_amdgcn_sbfe((int)m, e, 1);
+        }
+      }
+      uint32_t* tab = tabs + pr * FUSED_TAB;
+      const uint32_t l0 = __shfl(word, lane & 15), h0 = __shfl(word, 32 + (lane & 15));
+#pragma unroll
+      for (int c = 0; c < 256; c += 64) tab[c + lane] = l0 ^ __shfl(word, 16 + ((c + lane) >> 4));
+#pragma unroll
+      for (int c = 0; c < 256; c += 64) {
+        const uint32_t pat = h0 ^ __shfl(word, 48 + ((c + lane) >> 4));   // (every lane takes part)
+        if (c + lane < (1 << eh)) tab[256 + s_hpos[c + lane]] = pat;
+      }
+    }
+  };
+  // Phase 1 for the ntok tokens of a group.
+  auto errors = [&](int ntok, const float* records) {
+    int lane = tid & 63;
+    asm volatile("" : "+v"(lane));
+    const uint2 off = s_off[lane];
+    for (int job = wave; job < ((ntok + 1) & ~1) * chunks; job += waves) {
+      const int tk = job / chunks, chunk = job - tk * chunks;
+      float q = 0.f;                                   // a group's last token may have no partner: errors of 0
+      if (tk < ntok) {
+        const float* R = records + tk * RS;
+        float ga[VP], ex[VP], aw[VP];
+#pragma unroll
+        for (int v = 0; v < VP; ++v) {
+          const int j = VP * (lane >> 4) + v;
+          const bool in = 4 * VP == CAP || j < CAP;
+          ga[v] = *(const float*)((const char*)R + (v == 0 ? off.x & 0xffffu : v == 1 ? off.x >> 16 : off.y));
+          ex[v] = R[in ? j : RS - 1];
+          aw[v] = R[in ? 2 * CAP + j : RS - 1];
+        }
+        const int word = s_selbits[chunk * 64 + lane];
+        float d[4][VP], part[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+#pragma unroll
+          for (int v = 0; v < VP; ++v) {
+            d[g][v] = __uint_as_float(__float_as_uint(ex[v]) & (uint32_t)__builtin_amdgcn_sbfe(word, g * VP + v, 1));
+            part[g] = v == 0 ? d[g][v] : part[g] + d[g][v];
+          }
+        }
+        const float sum = rows_to_sums(part[0], part[1], part[2], part[3]);
+        float inv[4];
+        rows_to_all(__builtin_amdgcn_rcpf(sum), inv);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          f32x4 u = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int v = 0; v < VP; ++v) d[g][v] = fmaf(d[g][v], inv[g], -aw[v]);
+#pragma unroll
+          for (int v = 0; v < VP; ++v) u = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[v], d[g][v], u, 0, 0, 0);
+          part[g] = d[g][0] * u[0];
+#pragma unroll
+          for (int v = 1; v < VP; ++v) part[g] = fmaf(d[g][v], u[v], part[g]);
+        }
+        q = rows_to_sums(part[0], part[1], part[2], part[3]);
+        const int c = chunk * 64 + lane;
+        if (__any(sum < 1e-30f)) {
+          if (sum < 1e-30f) q = far_selection_error<CAP>(R, s_bits[c]);
+        }
+        if (kk == kfull && c == 0) q = 0.f;
+      }
+      s_q[job * 64 + lane] = q;
+    }
+  };
+  // Phase 3.
+  auto look_up = [&](int pairs, const uint32_t* tabs) {
+    for (int pr = 0; pr < pairs; ++pr) {
+      const uint32_t* tab = tabs + pr * FUSED_TAB;
+      const uint32_t at = (uint32_t)(8 * pr) << nb;                   // address of the pair's first table
+      const uint32_t pl = tab[lowm] ^ (at | (at + (4u << nb)) << 16);
+      const uint2* ph = (const uint2*)(tab + 256 + hoff);
+#pragma unroll
+      for (int s = 0; s < SPL; s += 2) {
+        const uint2 h = ph[s >> 1];
+        total[s] += *(lds_float)(uintptr_t)xor_half<0>(pl, h.x);
+        total[s] += *(lds_float)(uintptr_t)xor_half<1>(pl, h.x);
+        total[s + 1] += *(lds_float)(uintptr_t)xor_half<0>(pl, h.y);
+        total[s + 1] += *(lds_float)(uintptr_t)xor_half<1>(pl, h.y);
+      }
+    }
+  };
+
+  // Between two barriers: phase 2 of a group; then its phase 3 and phase 1 of the next one.  Half of a SIMD's wavefronts take
+  // these two in the other order, so that look-ups (LDS) and errors (VALU, matrix unit) run beside each other.
+  const bool errors_first = (wave >> 2) & 1;
+  int buf = 1;                                           // of records and pattern tables of the group that is looked up
+  for (int g0 = -tg; g0 < count; g0 += tg, buf ^= 1) {
+    const int here = g0 < 0 ? 0 : count - g0 < tg ? count - g0 : tg, pairs = (here + 1) >> 1;
+    const int left = count - g0 - tg, after = left < tg ? left : tg;
+    {
+      uint32_t at = 4u * (uint32_t)tid;
+      asm volatile("" : "+v"(at));
+      const int end = (2 * pairs) << nb;
+      for (int f = 0; f < end; f += FUSED_PER_THREAD * threads) {
+        float e[FUSED_PER_THREAD];
+#pragma unroll
+        for (int n = 0; n < FUSED_PER_THREAD; ++n) {     // (beyond the group's tokens: read within s_q, not written)
+          int tk = (f + n * threads + wave * 64) >> nb;
+          tk = tk < tg ? tk : tg - 1;
+          e[n] = *(const float*)((const char*)s_q + ((uint32_t)(tk * chunks * 256) + sel[n]));
+        }
+#pragma unroll
+        for (int n = 0; n < FUSED_PER_THREAD; ++n)
+          if (f + n * threads + wave * 64 < end) *(float*)((char*)ptab + ((uint32_t)(4 * (f + n * threads)) + at)) = e[n];
+      }
+    }
+    __syncthreads();
+    const float4 next = fetch(g0 + 2 * tg);
+    const float* const records = s_rec + (buf ^ 1) * tg * RS;
+    if (after > 0) build_tables(after, records, s_tab + (buf ^ 1) * (tg / 2) * FUSED_TAB);
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+      if (errors_first == (half == 0)) {
+        if (after > 0) errors(after, records);
+      } else if (scoring) {
+        look_up(pairs, s_tab + buf * (tg / 2) * FUSED_TAB);
+      }
+    }
+    if (fetching) ((float4*)(s_rec + buf * tg * RS))[tid] = next;      // last read before the barrier before
+    __syncthreads();
+  }
+  {
+    int me = tid;
+    asm volatile("" : "+v"(me));
+    const uint32_t word = s_mine[me];                    // this thread's own word
+    float* const out = partial + (int64_t)blockIdx.x * n_sub + (word & 0xffffu);
+    const int live = (int)(word >> 16);
+    if (live == SPL) {
+      __builtin_memcpy(out, total, sizeof(total));       // 16 bytes a store, at any place
+    } else {
+#pragma unroll
+      for (int s = 0; s < SPL; ++s)
+        if (s < live) out[s] = total[s];
+    }
+  }
+  if (unaffected && kk == kfull) {
+    // pairs whose selection is the full layer's: the subsets that keep the token's first k experts
+    unsigned long long same = 0;
+    for (int i = tid; i < count; i += threads) {
+      const uint32_t* const ordw = (const uint32_t*)(rec + (int64_t)i * RS + rec_order_off(CAP));
+      uint32_t top = 0;
+      for (int j = 0; j < kk; ++j) top |= 1u << ((ordw[j >> 2] >> (8 * (j & 3))) & 0x1fu);
+      const int distinct = __popc(top);
+      same += c_binom.v[E - distinct][r - distinct];
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) same += __shfl_xor(same, off, 64);
+    if (same && (tid & 63) == 0) atomicAdd(unaffected, same);          // integer: order does not matter
+  }
+}
+
+// Lanes of the fused scorer with spl subsets each (E > FUSED_LOW).
+int fused_lanes(int E, int r, int spl) {
+  int64_t lanes = 0;
+  for (int h = 0; h <= E - FUSED_LOW && h <= r; ++h)
+    if (r - h <= FUSED_LOW) lanes += binomial(FUSED_LOW, r - h) * ceil_div(binomial(E - FUSED_LOW, h), spl);
+  return (int)lanes;
+}
+size_t fused_lds(int n_act, int rec_floats, int tg) {
+  return (((size_t)tg << fused_pattern_bits(n_act)) + FUSED_ERRORS + 1024 + LUT_MAX_COMBO + 128 + 128 + tg * (2 * rec_floats + FUSED_TAB)) * 4 +
+         256 + 512;
+}
+
 // ------------------------------------------------------------------ reduce + argmin
 __global__ __launch_bounds__(256) void zero_i64_kernel(unsigned long long* p) { *p = 0ull; }
 
@@ -729,9 +1165,10 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
   double s = 0.0;
   unsigned long long c = 0;
   if (sub < n_sub)
+#pragma unroll 8
     for (int64_t i = strand; i < n_tiles; i += STRANDS) {
       s += (double)partial[i * n_sub + sub];
-      c += partial_cnt[i * n_sub + sub];
+      if (partial_cnt) c += partial_cnt[i * n_sub + sub];
     }
   ss[threadIdx.x] = s;
   sc[threadIdx.x] = c;
@@ -806,7 +1243,7 @@ __global__ __launch_bounds__(1024) void reduce_one_kernel(const float* __restric
 #pragma unroll 4
       for (int i = strand; i < n_tiles; i += strands) {
         s += (double)partial[(int64_t)i * n_sub + sub];
-        c += partial_cnt[(int64_t)i * n_sub + sub];
+        if (partial_cnt) c += partial_cnt[(int64_t)i * n_sub + sub];
       }
     ss[threadIdx.x] = s;
     __syncthreads();
@@ -878,6 +1315,7 @@ int plan_enumerate(int64_t T, int E, int H, int k, int r, EnumPlan* p) {
   p->use_lut = p->n_sub >= 512 && p->n_act <= LUT_MAX_ACT && n_combo <= LUT_MAX_COMBO;
   p->lut_spl = 0;
   if (p->use_lut) {
+    // (The fused scorer, up to 16 experts, has a shape of its own below; the sizes here are then those of the workspace.)
     // Subsets per lane: the choice that leaves the fewest idle slots in the last workgroup of 256 lanes, among those
     // whose look-up addresses (one per subset and mask nibble, the same for every token) fit the register file.
     int64_t best = 0;
@@ -919,6 +1357,31 @@ int plan_enumerate(int64_t T, int E, int H, int k, int r, EnumPlan* p) {
     p->off_nib = off; off += align256((size_t)((T + 1) / 2) * ((E + 3) / 4) * 16 * sizeof(uint32_t));
   }
   p->total = off > 0 ? off : 256;
+  p->fused_threads = 0;
+  if (p->use_lut && E <= FUSED_MAX_E && T > 0) {
+    // Subsets per lane: 4 where that takes no more than 1024 lanes, else 14 (12870 subsets: 928 lanes).
+    p->fused_spl = fused_lanes(E, r, 4) <= 1024 ? 4 : 14;
+    int threads = 256;
+    while (threads < fused_lanes(E, r, p->fused_spl) || threads * FUSED_PER_THREAD < (1 << p->n_act)) threads <<= 1;
+    // Tokens per barrier: 8, fewer where their tables would keep the compute unit from its workgroups or exceed 64 KB.
+    int tg = 8;
+    const int chunks = (p->n_combo + 63) / 64, per_cu = threads <= 512 ? 4 : 2;
+    while (tg > 2 && (fused_lds(p->n_act, p->rec_floats, tg) > (size_t)(per_cu == 2 ? 64 : 40) * 1024 || tg * chunks * 64 > FUSED_ERRORS)) tg >>= 1;
+    p->fused_tg = tg;
+    p->fused_lds = fused_lds(p->n_act, p->rec_floats, tg);
+    if (threads <= 1024 && p->fused_lds <= 64 * 1024) {
+      p->fused_threads = threads;
+      // One resident round of equal workgroups on 256 compute units, tiles of 8 tokens at least; their partial sums take
+      // the place of the tables and counts of the scorer above.
+      int64_t want = 256 * per_cu;
+      const int64_t room = (int64_t)((p->off_sel - p->off_partial) / ((size_t)p->n_sub * sizeof(float)));
+      want = want < room ? want : room;
+      int64_t tile = ceil_div(ceil_div(T, want), tg) * tg;
+      tile = tile < 8 ? 8 : tile;
+      p->tok_tile = (int)tile;
+      p->n_tok_tiles = ceil_div(T, tile);
+    }
+  }
   return MOEP_OK;
 }
 
@@ -1037,7 +1500,26 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
 #undef MOEP_PREP_LAUNCH
       MOEP_HIP(hipGetLastError());
     }
-    if (p.use_lut) {
+    if (p.fused_threads) {
+      Timed t("subset_score_tables", s);
+#define MOEP_FUSED(C, S)                                                                                               \
+  hipLaunchKernelGGL((fused_score_lut_kernel<C, S>), dim3((unsigned)p.n_tok_tiles), dim3(p.fused_threads), p.fused_lds, \
+                     s, rec, p.T, p.tok_tile, p.E, p.r, p.kk, p.k, p.n_act, p.n_combo, (uint32_t)p.n_sub, p.fused_tg,  \
+                     partial, (unsigned long long*)unaffected)
+#define MOEP_FUSED_CASE(C)                                                                                             \
+  case C:                                                                                                              \
+    if (p.fused_spl == 4) MOEP_FUSED(C, 4);                                                                            \
+    else MOEP_FUSED(C, 14);                                                                                            \
+    break;
+      switch (cap) {
+        MOEP_FUSED_CASE(4) MOEP_FUSED_CASE(6) MOEP_FUSED_CASE(8) MOEP_FUSED_CASE(12)
+        default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no selection table for %d active ranks", p.n_act);
+      }
+#undef MOEP_FUSED_CASE
+#undef MOEP_FUSED
+      MOEP_HIP(hipGetLastError());
+      pcnt = nullptr;                                    // counted already
+    } else if (p.use_lut) {
       Timed t("subset_score_tables", s);
       float* qtab = (float*)(ws + p.off_qtab);
       uint16_t* sel = (uint16_t*)(ws + p.off_sel);
@@ -1066,11 +1548,7 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
 #define MOEP_LUT_LAUNCH(N, S)                                                                                     \
   hipLaunchKernelGGL((score_lut_kernel<N, S>), grid, dim3(256), 0, s, qtab, (const uint32_t*)nibtab, sel, p.T, p.tok_tile, p.E,    \
                      p.r, p.n_act, p.n_combo, count_same, (uint32_t)p.n_sub, partial, pcnt)
-      // 512 subsets or more with at most 12 active ranks: 12 experts at least, three nibbles
-      switch (nib * 100 + p.lut_spl) {
-        case 308: MOEP_LUT_LAUNCH(3, 8); break;
-        case 408: MOEP_LUT_LAUNCH(4, 8); break;
-        case 417: MOEP_LUT_LAUNCH(4, 17); break;         // (up to 12 experts never have the subsets for it)
+      switch (nib * 100 + p.lut_spl) {                   // (up to 16 experts: above)
         case 508: MOEP_LUT_LAUNCH(5, 8); break;
         case 608: MOEP_LUT_LAUNCH(6, 8); break;
         case 708: MOEP_LUT_LAUNCH(7, 8); break;
@@ -1107,6 +1585,7 @@ constexpr int64_t REDUCE_ONE_MAX = 32768;
 int launch_reduce_argmin(const float* partial, const uint32_t* pcnt, int64_t n_tiles, int64_t n_sub, int E, int r,
                          float* loss, int32_t* argmin, uint32_t* argmin_mask, int64_t* unaffected, bool cleared,
                          hipStream_t s) {
+  if (!pcnt) unaffected = nullptr;                       // counted elsewhere
   Timed t("loss_reduce_argmin", s);
   if (n_tiles * n_sub <= REDUCE_ONE_MAX && n_sub <= REDUCE_ONE_MAX) {
     int S = 1;

@@ -81,3 +81,31 @@ def test_fp32_ranked_gram_at_row_lengths_and_alignments(E, H, T, n):
         got = loss.cpu().numpy().astype(np.float64)
         assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * np.abs(ref).max())
         assert int(amin.item()) == int(np.argmin(got))
+
+
+@pytest.mark.parametrize("E,k,r,T,spread", [
+    (16, 1, 13, 5, 1),        # 4 active ranks: pattern tables of 64 entries, 256 threads
+    (16, 2, 13, 17, 60),      # 5 ranks; logits so far apart that a pruned layer's exponentials underflow
+    (16, 2, 12, 41, 1),       # 6 ranks in records of 6: positions beyond the record
+    (16, 2, 11, 300, 60),     # 7 ranks in records of 8, 14 subsets per lane
+    (13, 4, 9, 9, 1),         # 5 experts in the high half: fewer masks than lanes
+    (12, 3, 6, 1, 1),         # 9 ranks, a token without partner
+    (12, 3, 6, 1030, 60),
+    (16, 4, 11, 77, 1),       # 9 ranks, 126 selections: the last 64 partly filled
+    (15, 2, 7, 130, 1),       # 10 ranks, 4 tokens per barrier
+    (16, 4, 9, 33, 1),        # 11 ranks, 330 selections
+    (16, 4, 8, 3, 60),        # 12 ranks, 495 selections, 12870 subsets
+    (16, 4, 8, 1027, 1),      # several tiles, the last one short
+])
+def test_scoring_with_tables_in_lds(E, k, r, T, spread):
+    logits, Y = wl.make_enumeration_inputs(E, T, 64, "bf16", seed=11 * E + T)
+    logits = logits * spread
+    loss, amin, amask, unaff = pkg.prune_enumerate(logits.to("cuda:0"), Y.to("cuda:0"), k, r)
+    torch.cuda.synchronize()
+    ref, _, masks = oracle.prune_enumerate_gram_form(wl.to_f64(logits), wl.to_f64(Y), k, r)
+    got = loss.cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * np.abs(ref).max())
+    assert int(amin.item()) == int(np.argmin(got))
+    assert (int(amask.item()) & 0xFFFFFFFF) == int(masks[int(amin.item())])
+    import math
+    assert int(unaff.item()) == T * math.comb(E - k, r - k)
