@@ -25,9 +25,10 @@ namespace moep {
 namespace {
 
 constexpr int CB = 256;            // threads of the multi-workgroup kernels
-// select_one: at most 8192 tokens (8 per thread, their keys 32 KB of LDS) and 16384 logits, which one compute unit reads
-// as fast as the other form launches its kernels (E 8: 2048 tokens 14 us against 18, 4096 tokens 21 against 18).
-constexpr int ONE_MAX = 8192, ONE_LOGITS = 16384;
+// select_one: at most 8192 tokens (8 per thread, their keys 32 KB of LDS) and 65536 logits, which one compute unit reads
+// as fast as the other form launches its kernels (us, on logits just written: E 8, 4001 tokens 11 against 18, 8192 tokens
+// 15 / 18; E 16, 4001 tokens 15 / 19, 6000 tokens 19 / 19; E 32, 2048 tokens 19 / 20, 3000 tokens 24 / 21).
+constexpr int ONE_MAX = 8192, ONE_LOGITS = 65536;
 constexpr int BITS = 11, BINS = 1 << BITS, PASSES = 3;
 
 struct SelectState {          // per wanted rank q in {0, 1}

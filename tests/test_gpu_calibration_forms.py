@@ -25,6 +25,7 @@ def logits_on_gpu(T, E, seed, offset=0, rounding=None):
     (1, 2, 0, None), (2048, 8, 0, None), (2049, 8, 0, None), (512, 32, 0, None), (513, 32, 1, None),
     (8192, 2, 0, None), (8193, 2, 0, None), (3277, 5, 0, None), (3276, 5, 0, None), (4097, 16, 2, None),
     (2000, 8, 0, 4.0), (30001, 8, 0, 4.0), (140001, 4, 0, 2.0),
+    (8192, 8, 0, 4.0), (8193, 8, 0, None), (4096, 16, 0, None), (2048, 32, 1, 4.0), (2049, 32, 0, None),
 ])
 def test_beta_at_every_form(T, E, offset, rounding):
     lg, dev = logits_on_gpu(T, E, 31 + T, offset, rounding)
