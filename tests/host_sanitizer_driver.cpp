@@ -7,6 +7,7 @@
 #include <cstring>
 #include <vector>
 
+#include "enum_plan.h"
 #include "moeprune.h"
 
 static int failures = 0;
@@ -85,6 +86,24 @@ int main() {
     EXPECT(moe_packed_weights_bytes(8, 4096, 14336, MOEP_F32) == 0 && moe_packed_weights_bytes(8, 100, 64, MOEP_BF16) == 0);
     EXPECT(skip_calibrate_beta_workspace(0) == 0 && skip_calibrate_beta_workspace(1) > 0);
   }
+
+  // ---- plans of the subset enumeration: the token tiles cover the batch, their partial sums lie within the workspace in front
+  // of what follows them, and the table scorers add at most 1024 tokens in fp32 before the fp64 sum over the tiles (with more
+  // than 16 experts as long as the tiles fit the grid's second dimension)
+  const int64_t plan_Ts[] = {1, 7, 33, 777, 4096, 5000, 16384, 65536, 262144, 524289, ((int64_t)1 << 20) + 1, (int64_t)5 << 20, (int64_t)1 << 26};
+  for (int E = 1; E <= 32; ++E)
+    for (int k = 1; k <= E && k <= 16; ++k)
+      for (int r = 1; r <= E; ++r) {
+        if (binom(E, r) > ((int64_t)1 << 24)) continue;
+        for (int64_t T : plan_Ts) {
+          moep::EnumPlan q;
+          EXPECT(moep::plan_enumerate(T, E, 64, k, r, &q) == MOEP_OK);
+          EXPECT(q.tok_tile >= 1 && q.n_tok_tiles * q.tok_tile >= T && (q.n_tok_tiles - 1) * q.tok_tile < T);
+          const size_t sums = (size_t)q.n_tok_tiles * q.n_sub * sizeof(float);
+          EXPECT(q.off_partial + sums <= (q.fused_threads ? q.off_sel : q.off_partial_cnt) && q.off_sel <= q.total);
+          if (q.use_lut) EXPECT(q.tok_tile <= 1024 || (!q.fused_threads && T > (int64_t)65535 * 1024));
+        }
+      }
 
   // ---- argument errors: every call must come back with a status and a message, having launched nothing
   void* p = (void*)(uintptr_t)(1 << 20);          // never dereferenced on the host

@@ -2,7 +2,7 @@
 
 Builds the library a second time with the sanitizers on its HOST code (device code as usual), builds
 tests/host_sanitizer_driver.cpp against it, and runs the driver in a child process: subset rank / unrank over
-every index, workspace planning over a grid of shapes, and the argument-error path of every entry point.  The
+every index, workspace planning over a grid of shapes, the plans of the subset enumeration, and the argument-error path of every entry point.  The
 driver launches no kernel; a sanitizer report or a failed check makes it exit non-zero.  No GPU needed."""
 import os
 import subprocess
@@ -19,7 +19,8 @@ def test_host_logic_under_address_and_undefined_behaviour_sanitizers(tmp_path):
     exe = str(tmp_path / "host_sanitizer_driver")
     clang = CLANG if os.path.exists(CLANG) else "/opt/rocm/lib/llvm/bin/clang++"
     cmd = [clang, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
-           "-shared-libsan", "-I", os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "host_sanitizer_driver.cpp"),
+           "-shared-libsan", "-I", os.path.join(ROOT, "include"), "-I", build.CSRC,
+           os.path.join(ROOT, "tests", "host_sanitizer_driver.cpp"),
            "-o", exe, "-L", libdir, "-lmoeprune_hostsan", f"-Wl,-rpath,{libdir}", "-Wl,-rpath,/opt/rocm/lib",
            "-Wl,-rpath," + os.path.dirname(subprocess.run([clang, "-print-file-name=libclang_rt.asan-x86_64.so"],
                                                           capture_output=True, text=True).stdout.strip())]
