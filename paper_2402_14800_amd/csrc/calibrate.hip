@@ -25,10 +25,20 @@ namespace moep {
 namespace {
 
 constexpr int CB = 256;            // threads of the multi-workgroup kernels
-// select_one: at most 8192 tokens (8 per thread, their keys 32 KB of LDS) and 65536 logits, which one compute unit reads
-// as fast as the other form launches its kernels (us, on logits just written: E 8, 4001 tokens 11 against 18, 8192 tokens
-// 15 / 18; E 16, 4001 tokens 15 / 19, 6000 tokens 19 / 19; E 32, 2048 tokens 19 / 20, 3000 tokens 24 / 21).
-constexpr int ONE_MAX = 8192, ONE_LOGITS = 65536;
+// select_one: at most 8192 tokens (8 per thread, their keys 32 KB of LDS), and as many logits as one compute unit reads as
+// fast as the other form launches its kernels.  That depends on how it reads them: rows in 16-byte pieces; word by word; word
+// by word with rows a multiple of 32 bytes apart, where a wavefront's words crowd into few sets of the L1.  Just outside the
+// line on the left, inside it on the right, one launch / five, us on logits just written:
+//   pieces, E <= 16   6000 x 16 19 / 19           4096 x 16 16 / 18,  8192 x 8 15 / 18
+//   pieces, E > 16    3276 x 20 21.9 / 18.8, 2048 x 32 20.4 / 19.4    2457 x 20 18.1 / 18.5, 1755 x 28 18 / 19
+//   words, E <= 16    7021 x 7 17.3 / 17.1, 5461 x 9 19.3 / 17.8      4444 x 9 17.3 / 17.8,  5714 x 7 14.7 / 17.3
+//   words, E > 16     2352 x 17 20.7 / 19.2, 1428 x 28 20.6 / 20.6    1927 x 17 18.5 / 19.5
+//   words, 32 bytes   4096 x 8 21.5 / 17.8, 1024 x 32 23.4 / 22.1     2500 x 8 and 625 x 32 faster by more than 1
+constexpr int ONE_MAX = 8192;
+int64_t one_logits(int E, bool vec) {
+  if (vec) return E <= 16 ? 65536 : 49152;
+  return E % 8 == 0 ? 24576 : E <= 16 ? 40000 : 32768;
+}
 constexpr int BITS = 11, BINS = 1 << BITS, PASSES = 3;
 
 struct SelectState {          // per wanted rank q in {0, 1}
@@ -203,7 +213,7 @@ int launch_calibrate_beta(const float* logits, int64_t T, int E, uint32_t kept_m
                           char* ws, hipStream_t s) {
   Timed t("skip_calibrate_beta", s);
   const bool vec = logits_vec(logits, E);
-  if (T <= ONE_MAX && T * E <= ONE_LOGITS) {
+  if (T <= ONE_MAX && T * E <= one_logits(E, vec)) {
 #define MOEP_ONE(EMAX) \
   hipLaunchKernelGGL(select_one_kernel<EMAX>, dim3(1), dim3(1024), 0, s, logits, (int)T, E, vec, kept_mask, beta_out)
     if (E <= 8) MOEP_ONE(8);
