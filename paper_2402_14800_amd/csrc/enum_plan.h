@@ -16,7 +16,6 @@ struct EnumPlan {
   int64_t n_tok_tiles;
   bool use_lut;      // many subsets, few selections per token: score through per-token selection tables
   int n_combo;       // C(n_act, kk): selections per token
-  int lut_spl;       // subsets per lane of the table scorer (0 without it)
   int fused_threads; // up to 16 experts: tables and look-ups in one kernel, its workgroup (0: not taken),
   int fused_spl;     //   subsets per lane,
   int fused_tg;      //   tokens per barrier

@@ -630,23 +630,24 @@ __global__ __launch_bounds__(256) void qtable_kernel(const float* __restrict__ r
   }
 }
 
-// Lane = SPL subsets, loop over a tile of tokens, LUT_TG tokens per barrier (double-buffered in LDS).  Per pair:
-// one look-up per nibble of the kept mask (lanes of a wavefront hold neighbouring subsets: few distinct entries, no
-// bank conflicts), one of the pattern's selection index, one of that selection's error.
-constexpr int LUT_TG = 8, LUT_MAX_ACT = 12, LUT_MAX_COMBO = 512, LUT_MAX_ADDR = 68;
+// Lane = LUT_SPL subsets (their look-up addresses, one per subset and mask nibble, stay in registers), loop over a tile of
+// tokens, LUT_TG tokens per barrier (double-buffered in LDS).  Per pair: one look-up per nibble of the kept mask (lanes of a
+// wavefront hold neighbouring subsets: few distinct entries, no bank conflicts), one of the pattern's selection index, one of
+// that selection's error.
+constexpr int LUT_TG = 8, LUT_SPL = 8, LUT_MAX_ACT = 12, LUT_MAX_COMBO = 512;
 // Where the pattern table keeps pattern `pat` in LDS: pattern bits 6..10 folded onto the bits that choose the bank.
 // The patterns of a wavefront's 64 subsets differ in the few rank positions of the experts that vary among them, any
 // of the n_act; left to bits 1..5 alone the bank would ignore the rest and they would queue on a few banks.
 __device__ __forceinline__ uint32_t lut_swizzle(uint32_t pat) { return pat ^ ((pat >> 5) & 0x3eu); }
 
-template <int NIB, int SPL>    // NIB = nibbles of the kept mask: ceil(E / 4)
+template <int NIB>             // nibbles of the kept mask: ceil(E / 4), 5 to 8
 __global__ __launch_bounds__(256, 3) void score_lut_kernel(const float* __restrict__ qtab,
                                                         const uint32_t* __restrict__ nibtab,
                                                         const uint16_t* __restrict__ sel, int64_t T, int tok_tile,
                                                         int E, int r, int n_act, int n_combo, bool count_same,
                                                         uint32_t n_sub, float* __restrict__ partial,
                                                         uint32_t* __restrict__ partial_cnt) {
-  constexpr int NT = NIB * 16;                           // nibble-table entries per token
+  constexpr int SPL = LUT_SPL, NT = NIB * 16;            // nibble-table entries per token
   __shared__ uint16_t s_sel[1 << LUT_MAX_ACT];
   __shared__ uint32_t s_nib[2][LUT_TG / 2 * NT];
   __shared__ float s_q[2][LUT_TG * LUT_MAX_COMBO];
@@ -695,7 +696,7 @@ __global__ __launch_bounds__(256, 3) void score_lut_kernel(const float* __restri
           same_cnt += si1 == 0 ? 1u : 0u;
         }
         // about 32 look-ups in flight at a time: more only costs registers
-        if ((s + 1) % (NIB <= 4 ? 8 : 4) == 0) __builtin_amdgcn_sched_barrier(0);
+        if ((s + 1) % 4 == 0) __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -1313,20 +1314,17 @@ int plan_enumerate(int64_t T, int E, int H, int k, int r, EnumPlan* p) {
   const int64_t n_combo = binomial(p->n_act, p->kk);
   p->n_combo = (int)(n_combo < (1 << 20) ? n_combo : (1 << 20));
   p->use_lut = p->n_sub >= 512 && p->n_act <= LUT_MAX_ACT && n_combo <= LUT_MAX_COMBO;
-  p->lut_spl = 0;
+  const bool fused = p->use_lut && E <= FUSED_MAX_E;
   if (p->use_lut) {
-    // (The fused scorer, up to 16 experts, has a shape of its own below; the sizes here are then those of the workspace.)
-    // Subsets per lane: the choice that leaves the fewest idle slots in the last workgroup of 256 lanes, among those
-    // whose look-up addresses (one per subset and mask nibble, the same for every token) fit the register file.
-    int64_t best = 0;
-    for (int spl : {8, 17}) {
-      if (spl > 8 && spl * ((E + 3) / 4) > LUT_MAX_ADDR) continue;
-      const int64_t slots = ceil_div(p->n_sub, 256 * spl) * spl;
-      if (!p->lut_spl || slots < best) { p->lut_spl = spl; best = slots; }
-    }
+    // Up to 16 experts the fused scorer has a shape of its own, below; the shape here then only gives the size of the
+    // workspace, which is the one that callers reserved for tables in memory and that the limit of prune_enumerate_static goes
+    // by.  Of the room behind the records it takes what its partial sums need; sizing it by those alone would make some sizes
+    // larger (16 experts, r = 7, one expert per token: up to 70000 tokens) and so refuse batches that were accepted.
+    // Subsets per lane there: 8 or 17, whichever leaves fewer idle slots in the last workgroup of 256 lanes.
+    const bool wide = fused && ceil_div(p->n_sub, 256 * 17) * 17 < ceil_div(p->n_sub, 256 * LUT_SPL) * LUT_SPL;
     // Workgroups of equal length, about as many as a 256-CU part holds at once (three per CU by their LDS): tiles
     // of whole token groups, 32 to 1024 tokens.
-    const int64_t sub_blocks = ceil_div(p->n_sub, 256 * p->lut_spl);
+    const int64_t sub_blocks = ceil_div(p->n_sub, 256 * (wide ? 17 : LUT_SPL));
     const int64_t want_tiles = sub_blocks < 768 ? 768 / sub_blocks : 1;
     int64_t tile = ceil_div(ceil_div(T, want_tiles), LUT_TG) * LUT_TG;
     tile = tile < 32 ? 32 : tile > 1024 ? 1024 : tile;
@@ -1358,7 +1356,7 @@ int plan_enumerate(int64_t T, int E, int H, int k, int r, EnumPlan* p) {
   }
   p->total = off > 0 ? off : 256;
   p->fused_threads = 0;
-  if (p->use_lut && E <= FUSED_MAX_E && T > 0) {
+  if (fused && T > 0) {
     // Subsets per lane: 4 where that takes no more than 1024 lanes, else 14 (12870 subsets: 928 lanes).
     p->fused_spl = fused_lanes(E, r, 4) <= 1024 ? 4 : 14;
     int threads = 256;
@@ -1369,20 +1367,18 @@ int plan_enumerate(int64_t T, int E, int H, int k, int r, EnumPlan* p) {
     while (tg > 2 && (fused_lds(p->n_act, p->rec_floats, tg) > (size_t)(per_cu == 2 ? 64 : 40) * 1024 || tg * chunks * 64 > FUSED_ERRORS)) tg >>= 1;
     p->fused_tg = tg;
     p->fused_lds = fused_lds(p->n_act, p->rec_floats, tg);
-    if (threads <= 1024 && p->fused_lds <= 64 * 1024) {
-      p->fused_threads = threads;
-      // One resident round of equal workgroups on 256 compute units, tiles of 8 tokens at least; several rounds where a lane
-      // would otherwise add more than 1024 tokens in fp32 (relative error of such sums of positive terms, simulated: 2^20 tokens
-      // by 1024 1.1e-8, by 2048 2.3e-8; 2^22 tokens by 1024 0.5e-8, by 8192 7.5e-8).  Their partial sums take the place of the
-      // tables and counts of the scorer above.
-      int64_t want = 256 * per_cu;
-      const int64_t room = (int64_t)((p->off_sel - p->off_partial) / ((size_t)p->n_sub * sizeof(float)));
-      want = want < room ? want : room;
-      int64_t tile = ceil_div(ceil_div(T, want), tg) * tg;
-      tile = tile < 8 ? 8 : tile > 1024 ? 1024 : tile;
-      p->tok_tile = (int)tile;
-      p->n_tok_tiles = ceil_div(T, tile);
-    }
+    p->fused_threads = threads;
+    // One resident round of equal workgroups on 256 compute units, tiles of 8 tokens at least; several rounds where a lane
+    // would otherwise add more than 1024 tokens in fp32 (relative error of such sums of positive terms, simulated: 2^20 tokens
+    // by 1024 1.1e-8, by 2048 2.3e-8; 2^22 tokens by 1024 0.5e-8, by 8192 7.5e-8).  Their partial sums take the place of the
+    // tables and counts of the scorer above.
+    int64_t want = 256 * per_cu;
+    const int64_t room = (int64_t)((p->off_sel - p->off_partial) / ((size_t)p->n_sub * sizeof(float)));
+    want = want < room ? want : room;
+    int64_t tile = ceil_div(ceil_div(T, want), tg) * tg;
+    tile = tile < 8 ? 8 : tile > 1024 ? 1024 : tile;
+    p->tok_tile = (int)tile;
+    p->n_tok_tiles = ceil_div(T, tile);
   }
   return MOEP_OK;
 }
@@ -1508,16 +1504,16 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
   hipLaunchKernelGGL((fused_score_lut_kernel<C, S>), dim3((unsigned)p.n_tok_tiles), dim3(p.fused_threads), p.fused_lds, \
                      s, rec, p.T, p.tok_tile, p.E, p.r, p.kk, p.k, p.n_act, p.n_combo, (uint32_t)p.n_sub, p.fused_tg,  \
                      partial, (unsigned long long*)unaffected)
-#define MOEP_FUSED_CASE(C)                                                                                             \
-  case C:                                                                                                              \
-    if (p.fused_spl == 4) MOEP_FUSED(C, 4);                                                                            \
-    else MOEP_FUSED(C, 14);                                                                                            \
-    break;
-      switch (cap) {
-        MOEP_FUSED_CASE(4) MOEP_FUSED_CASE(6) MOEP_FUSED_CASE(8) MOEP_FUSED_CASE(12)
+      switch (cap * 100 + p.fused_spl) {                 // (4 active ranks: 560 subsets, 4 per lane)
+        case 404: MOEP_FUSED(4, 4); break;
+        case 604: MOEP_FUSED(6, 4); break;
+        case 614: MOEP_FUSED(6, 14); break;
+        case 804: MOEP_FUSED(8, 4); break;
+        case 814: MOEP_FUSED(8, 14); break;
+        case 1204: MOEP_FUSED(12, 4); break;
+        case 1214: MOEP_FUSED(12, 14); break;
         default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no selection table for %d active ranks", p.n_act);
       }
-#undef MOEP_FUSED_CASE
 #undef MOEP_FUSED
       MOEP_HIP(hipGetLastError());
       pcnt = nullptr;                                    // counted already
@@ -1531,33 +1527,31 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
       uint16_t* nibtab = (uint16_t*)(ws + p.off_nib);
       const int nib = (p.E + 3) / 4;
       const dim3 qgrid((unsigned)p.T), qblock(p.n_combo <= 64 ? 64 : 256);
+#define MOEP_QTABLE(C, EXACT)                                                                                     \
+  hipLaunchKernelGGL((qtable_kernel<C, EXACT>), qgrid, qblock, 0, s, rec, p.kk, p.k, p.n_act, p.n_combo, selbits, qtab, nib, nibtab)
 #define MOEP_QTABLE_CASE(C)                                                                                       \
   case C:                                                                                                         \
-    if (p.n_act == C)                                                                                             \
-      hipLaunchKernelGGL((qtable_kernel<C, true>), qgrid, qblock, 0, s, rec, p.kk, p.k, p.n_act, p.n_combo,       \
-                         selbits, qtab, nib, nibtab);                                                             \
-    else                                                                                                          \
-      hipLaunchKernelGGL((qtable_kernel<C, false>), qgrid, qblock, 0, s, rec, p.kk, p.k, p.n_act, p.n_combo,      \
-                         selbits, qtab, nib, nibtab);                                                             \
+    if (p.n_act == C) MOEP_QTABLE(C, true);                                                                       \
+    else MOEP_QTABLE(C, false);                                                                                   \
     break;
       switch (cap) {
-        MOEP_QTABLE_CASE(2) MOEP_QTABLE_CASE(4) MOEP_QTABLE_CASE(6) MOEP_QTABLE_CASE(8) MOEP_QTABLE_CASE(12)
+        case 4: MOEP_QTABLE(4, true); break;             // (up to 3 active ranks have fewer than 512 subsets)
+        MOEP_QTABLE_CASE(6) MOEP_QTABLE_CASE(8) MOEP_QTABLE_CASE(12)
         default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no selection table for %d active ranks", p.n_act);
       }
 #undef MOEP_QTABLE_CASE
-      const dim3 grid((unsigned)ceil_div(p.n_sub, 256 * p.lut_spl), (unsigned)p.n_tok_tiles);
+#undef MOEP_QTABLE
+      const dim3 grid((unsigned)ceil_div(p.n_sub, 256 * LUT_SPL), (unsigned)p.n_tok_tiles);
       const bool count_same = p.kk == p.k;
-#define MOEP_LUT_LAUNCH(N, S)                                                                                     \
-  hipLaunchKernelGGL((score_lut_kernel<N, S>), grid, dim3(256), 0, s, qtab, (const uint32_t*)nibtab, sel, p.T, p.tok_tile, p.E,    \
+#define MOEP_LUT_LAUNCH(N)                                                                                        \
+  hipLaunchKernelGGL((score_lut_kernel<N>), grid, dim3(256), 0, s, qtab, (const uint32_t*)nibtab, sel, p.T, p.tok_tile, p.E,    \
                      p.r, p.n_act, p.n_combo, count_same, (uint32_t)p.n_sub, partial, pcnt)
-      switch (nib * 100 + p.lut_spl) {                   // (up to 16 experts: above)
-        case 508: MOEP_LUT_LAUNCH(5, 8); break;
-        case 608: MOEP_LUT_LAUNCH(6, 8); break;
-        case 708: MOEP_LUT_LAUNCH(7, 8); break;
-        case 808: MOEP_LUT_LAUNCH(8, 8); break;
-        default:
-          return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no table scorer for %d experts, %d subsets per lane", p.E,
-                      p.lut_spl);
+      switch (nib) {                                     // (up to 16 experts: above)
+        case 5: MOEP_LUT_LAUNCH(5); break;
+        case 6: MOEP_LUT_LAUNCH(6); break;
+        case 7: MOEP_LUT_LAUNCH(7); break;
+        case 8: MOEP_LUT_LAUNCH(8); break;
+        default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no table scorer for %d experts", p.E);
       }
 #undef MOEP_LUT_LAUNCH
       MOEP_HIP(hipGetLastError());

@@ -89,7 +89,7 @@ int main() {
 
   // ---- plans of the subset enumeration: the token tiles cover the batch, their partial sums lie within the workspace in front
   // of what follows them, and the table scorers add at most 1024 tokens in fp32 before the fp64 sum over the tiles (with more
-  // than 16 experts as long as the tiles fit the grid's second dimension)
+  // than 16 experts as long as the tiles fit the grid's second dimension).  Every plan of the table scorers has a kernel.
   const int64_t plan_Ts[] = {1, 7, 33, 777, 4096, 5000, 16384, 65536, 262144, 524289, ((int64_t)1 << 20) + 1, (int64_t)5 << 20, (int64_t)1 << 26};
   for (int E = 1; E <= 32; ++E)
     for (int k = 1; k <= E && k <= 16; ++k)
@@ -101,6 +101,13 @@ int main() {
           EXPECT(q.tok_tile >= 1 && q.n_tok_tiles * q.tok_tile >= T && (q.n_tok_tiles - 1) * q.tok_tile < T);
           const size_t sums = (size_t)q.n_tok_tiles * q.n_sub * sizeof(float);
           EXPECT(q.off_partial + sums <= (q.fused_threads ? q.off_sel : q.off_partial_cnt) && q.off_sel <= q.total);
+          EXPECT((q.fused_threads != 0) == (q.use_lut && E <= 16));
+          if (q.fused_threads) {
+            EXPECT(q.fused_threads >= 256 && q.fused_threads <= 1024 && q.fused_lds <= 64 * 1024 && q.tok_tile % q.fused_tg == 0);
+            EXPECT(q.n_act >= 4 && q.n_act <= 12 && (q.fused_spl == 4 || (q.fused_spl == 14 && q.n_act > 4)));
+          } else if (q.use_lut) {
+            EXPECT(q.n_act >= 4 && q.n_act <= 12);
+          }
           if (q.use_lut) EXPECT(q.tok_tile <= 1024 || (!q.fused_threads && T > (int64_t)65535 * 1024));
         }
       }
