@@ -1,8 +1,9 @@
 """What the compiler made of the GEMM kernel: all 256 accumulator registers of a wavefront in the AGPR half of
 its register file, one wavefront per SIMD, and nothing spilled to scratch memory in any instantiation (a spill
 inside the K loop costs far more than the few registers it saves; outside it, it still means the loop's
-register budget was exceeded somewhere); and what it made of the few-rows GEMM, whose waits count loads.  Compiles the device
-code; no GPU needed."""
+register budget was exceeded somewhere); the order of the loads that the hand-counted waits of this kernel and of the few-rows
+GEMM rely on; and the registers of the table scorers, whose launches are planned by residency.  Compiles the device code; no
+GPU needed."""
 import re
 
 import pytest
@@ -30,15 +31,85 @@ def test_pack_kernel_is_light(gemm_usage):
     assert pack and all(u["ScratchSize"] == 0 for u in pack)
 
 
-def test_table_scorer_keeps_three_wavefronts_per_simd_without_spilling():
-    """The look-up scorer is planned as one resident round of workgroups, three per CU: every instantiation has to
-    fit three wavefronts per SIMD with its per-subset look-up addresses in registers, not in scratch memory."""
-    usage = build.kernel_resource_usage("enumerate.hip")
-    luts = {n: u for n, u in usage.items() if "score_lut_kernel" in n}
-    assert len(luts) >= 7
+@pytest.fixture(scope="module")
+def enumerate_usage():
+    return build.kernel_resource_usage("enumerate.hip")
+
+
+def test_table_scorer_keeps_three_wavefronts_per_simd_without_spilling(enumerate_usage):
+    """The look-up scorer of more than 16 experts is planned as one resident round of workgroups, three per CU: every
+    instantiation has to fit three wavefronts per SIMD with its per-subset look-up addresses in registers, not in scratch memory."""
+    luts = {n: u for n, u in enumerate_usage.items() if re.search(r"\d+score_lut_kernel", n)}
+    assert len(luts) == 4                        # 5 to 8 nibbles of the kept mask
     for name, u in luts.items():
         assert u["ScratchSize"] == 0 and u["VGPRs Spill"] == 0, (name, u)
         assert u["Occupancy"] >= 3, (name, u)
+
+
+def test_fused_table_scorer_keeps_eight_wavefronts_per_simd_without_spilling(enumerate_usage):
+    """The scorer with tables in LDS is planned as two workgroups of 1024 threads or four of 512 per CU: eight wavefronts per
+    SIMD, hence at most 64 vector registers, and none in scratch memory."""
+    fused = {n: u for n, u in enumerate_usage.items() if "fused_score_lut_kernel" in n}
+    assert len(fused) == 7                       # records of 4 to 12 ranks, 4 or 14 subsets per lane (4 ranks: 4)
+    for name, u in fused.items():
+        assert u["ScratchSize"] == 0 and u["VGPRs Spill"] == 0, (name, u)
+        assert u["Occupancy"] == 8, (name, u)
+
+
+def k_loops(kernel):
+    """The single-block loops of a kernel's lines that multiply on the matrix units, each as its number of MFMAs and its
+    vector-memory operations, waits for them and barriers in order; a load as the register of its lane offset."""
+    label = at = None
+    for i, line in enumerate(kernel):
+        if m := re.match(r"(\.LBB\d+_\d+):", line):
+            label, at = m.group(1), i
+        elif (m := re.match(r"\s+s_cbranch\S*\s+(\.LBB\d+_\d+)", line)) and m.group(1) == label:
+            ops = []
+            for word in (w for w in map(str.split, kernel[at:i]) if w):
+                if word[0].startswith(("global_", "buffer_", "flat_", "scratch_")):
+                    assert "lds" in word[-1] or "_lds_" in word[0], word                 # nothing but loads into the ring
+                    ops.append(word[1].rstrip(","))
+                elif word[0] == "s_barrier":
+                    ops.append(word[0])
+                elif word[0] == "s_waitcnt" and (m := re.search(r"vmcnt\((\d+)\)", " ".join(word))):
+                    ops.append(int(m.group(1)))
+            mfmas = sum("v_mfma_f32_16x16x32_bf16" in x for x in kernel[at:i])
+            if mfmas:
+                yield mfmas, ops
+
+
+def test_packed_gemm_waits_for_the_loads_it_means():
+    """A wavefront of the 256-row GEMM waits until all but its newest N loads have landed.  Blocked weights: N loads are a step's,
+    every second step.  Row-major weights: in front of an odd step the newest step's and the A loads of the one before, which is
+    right only if every step issues its weight loads BEFORE its A loads; a load merged, dropped or moved by the compiler would be
+    a silent race.  Checked in all six bodies (tile widths and heights) of every instantiation."""
+    text = build.device_assembly("gemm_bf16_packed.hip").splitlines()
+    starts = [i for i, line in enumerate(text) if re.match(r"_ZN\S*gemm_packed_kernel\S*:", line)]
+    assert len(starts) == 10                     # 3 epilogues, dense (2 of them) or grouped, 2 weight layouts
+    for start in starts:
+        row_major = re.search(r"kernelILi\d+ELb[01]ELb([01])E", text[start]).group(1) == "1"
+        bodies = set()
+        for mfmas, ops in k_loops(text[start:next(i for i in range(start, len(text)) if ".Lfunc_end" in text[i])]):
+            at = [i for i, o in enumerate(ops) if o == "s_barrier"]
+            steps = [ops[b:e] for b, e in zip([0] + [i + 1 for i in at], at)]
+            assert ops[-1] == "s_barrier" and len(steps) == (2 if row_major else 1), (text[start], ops)
+            assert all(isinstance(s[-1], int) and not any(isinstance(o, int) for o in s[:-1]) for s in steps), (text[start], ops)
+            loads, waits = [s[:-1] for s in steps], [s[-1] for s in steps]
+            if row_major:                        # weights by two lane offsets in turn, then the rows of A by a third
+                w = max(i for i, o in enumerate(loads[0]) if o != loads[0][-1]) + 1
+                a = len(loads[0]) - w
+                for step in loads:
+                    assert len(step) == w + a and w % 2 == 0, (text[start], ops)
+                    assert len(set(step[0:w:2])) == len(set(step[1:w:2])) == len(set(step[w:])) == 1, (text[start], ops)
+                    assert len({step[0], step[1], step[w]}) == 3, (text[start], ops)
+                assert waits == [w + 2 * a, 2 * (w + a)], (text[start], ops)
+                assert mfmas == 2 * (2 * w) * (2 * a), (text[start], mfmas)
+                bodies.add((2 * w, 2 * a))
+            else:
+                assert len(loads[0]) == 2 * waits[0], (text[start], ops)
+                bodies.add((mfmas, waits[0]))
+        tiles = [(ng, mg) for ng in (4, 8) for mg in (4, 6, 8)]
+        assert bodies == ({*tiles} if row_major else {(2 * ng * mg, (ng + mg) // 2) for ng, mg in tiles}), (text[start], bodies)
 
 
 def few_rows_body(text, header):
