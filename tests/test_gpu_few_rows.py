@@ -88,8 +88,8 @@ def test_expert_outputs_of_few_rows_are_those_of_many(E, H, F, T):
 
 @pytest.mark.parametrize("E,H,F,T,n", [(2, 64, 64, 6144, 1), (2, 64, 64, 6145, 1), (3, 192, 448, 300, 2), (4, 320, 1088, 257, 4)])
 def test_weights_in_place_give_the_bits_of_packed_weights(E, H, F, T, n):
-    """Around the row count up to which the GEMMs read row-major weights where they lie, and at column counts that end
-    inside a tile (64, 192 and 320 of 256 columns, 448 and 1088 of 128)."""
+    """Row-major weights read where they lie, at even and odd row counts and at column counts that end inside a tile (64, 192 and
+    320 of 256 columns, 448 and 1088 of 128); the row count up to which that is done: the two tests below."""
     _, layer = small_layer("bf16", E, 2, H, F, T, index=24)
     d = to_dev(layer)
     ws = [d[n_] for n_ in NAMES]
@@ -122,6 +122,47 @@ def test_whole_line_loads_of_weights_give_the_bits_of_packed_weights(E, H, F, T)
     rows = torch.tensor([0, T // 2, T - 1])
     _, ref = oracle.expert_outputs(*[wl.to_f64(v) for v in (layer["x"][rows], *[layer[n] for n in NAMES[1:]])])
     check_outputs(wl.to_f64(Y[:, rows.to(Y.device)].contiguous()), ref, "Y")
+
+
+@pytest.mark.parametrize("E,H,F,k", [(2, 64, 64, 2), (4, 192, 320, 3)])
+def test_routed_weights_packed_inside_the_call_give_the_bits_of_weights_in_place(E, H, F, k):
+    """The skipping forwards around the nominal 32768 rows per expert beyond which a call re-lays the weights out itself: the
+    last batch that reads them in place, the first that does not, and that one on weights packed before."""
+    last, last_k = 32768 * E // 2, 32768 * E // k           # tokens: 2 T and k T up to 32768 E
+    _, layer = small_layer("bf16", E, 2, H, F, max(last, last_k) + 1, index=30)
+    d = to_dev(layer)
+    rest = [d[n] for n in NAMES[1:]]
+    packed = pkg.moe_pack_weights(d["W1"], d["W3"], d["W2"])
+    x, inside = d["x"][:last + 1].contiguous(), d["x"][:last].contiguous()
+
+    def launches(call, *args):
+        """The call's outputs, and how often it packed weights."""
+        pkg.kernel_timing_enable(True)
+        pkg.kernel_timing_reset()
+        got = call(*args)
+        torch.cuda.synchronize()
+        names = [name for name, _ in pkg.kernel_timing_records()]
+        pkg.kernel_timing_enable(False)
+        return (*got, names.count("pack_w"))
+
+    out, skip, lg, _, packs = launches(pkg.moe_forward_skip, x, *rest, 0.6)
+    out_i, skip_i, _, _, packs_i = launches(pkg.moe_forward_skip, inside, *rest, 0.6)
+    out_k, used, lg_k, _, packs_k = launches(pkg.moe_forward_skip_topk, d["x"][:last_k + 1].contiguous(), *rest, k, 0.1)
+    out_ki, used_i, _, _, packs_ki = launches(pkg.moe_forward_skip_topk, d["x"][:last_k].contiguous(), *rest, k, 0.1)
+    out_p, skip_p, _, _ = pkg.moe_forward_pruned_skip_packed(x, d["Wgate"], packed, F, 0.6)
+    torch.cuda.synchronize()
+    assert (packs, packs_i, packs_k, packs_ki) == (2, 0, 2, 0)      # W1 with W3, and W2
+    assert torch.equal(bits(out), bits(out_p)) and torch.equal(skip, skip_p)
+    assert torch.equal(bits(out[:last]), bits(out_i)) and torch.equal(skip[:last], skip_i)
+    assert torch.equal(bits(out_k[:last_k]), bits(out_ki)) and torch.equal(used[:last_k], used_i)
+    rows = torch.tensor([0, last // 3, last - 1, last])
+    few = [wl.to_f64(v) for v in (layer["x"][rows], *[layer[n] for n in NAMES[1:]])]
+    ref, _, _, _ = oracle.forward_skip(*few, float(np.float32(0.6)), logits=lg[rows.to(lg.device)].cpu().numpy())
+    check_outputs(wl.to_f64(out[rows.to(out.device)].contiguous()), ref, "out")
+    rows = torch.tensor([0, last_k // 3, last_k - 1, last_k])
+    few[0] = wl.to_f64(layer["x"][rows])
+    ref, _, _ = oracle.forward_skip_topk(*few, k, float(np.float32(0.1)), logits=lg_k[rows.to(lg_k.device)].cpu().numpy())
+    check_outputs(wl.to_f64(out_k[rows.to(out_k.device)].contiguous()), ref, "out")
 
 
 @pytest.mark.parametrize("E,H,F,T,prefixes,grouped_crosses", [
