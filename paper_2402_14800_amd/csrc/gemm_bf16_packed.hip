@@ -30,10 +30,13 @@
 // the step that multiplies slice g a wavefront also issues its 8 direct loads of slice g + NS - 1 (one
 // per 6 MFMAs, into the stage whose fragments were read two steps ago) and reads the fragments of slice
 // g + 1 into the other half of a double-buffered fragment register set: 64 MFMAs, 16 LDS reads and 8
-// loads per step.  Loads are spread evenly over the step, never issued in bursts.  The wavefronts
-// meet at a barrier every SECOND step only: before it each waits until all but its 8 newest loads have
-// landed, which covers the two slices read in the two steps that follow; the stage a step's loads
-// overwrite was last read two steps earlier, i.e. before the previous barrier.
+// loads per step.  Loads are spread evenly over the step, never issued in bursts.  On blocked weights the
+// wavefronts meet at a barrier every SECOND step only: before it each waits until all but the newest step's
+// loads have landed, which covers the two slices read in the two steps that follow; the stage a step's loads
+// overwrite was last read two steps earlier, i.e. before the previous barrier.  On row-major weights (BROW) there is a
+// barrier after every step, since the second unit of a pair of slices is issued one step before it is read (wait counts
+// at W_MAIN and W_ODD).  In a body of half width (NG = 4) or for short tiles (MG = 6 or 4) a wavefront's step has
+// MG x NG MFMAs, MG + NG reads and (MG + NG) / 2 loads.
 // Workgroups are persistent (one per compute unit) and the ring runs across tile boundaries: while the
 // last slices of a tile are multiplied and its epilogue runs, the first slices of the workgroup's next
 // tile are already being fetched.  The loader changes tile only BETWEEN runs of steps (a tile's steps
@@ -56,6 +59,7 @@
 // Grouped launches read that order from a table the dispatch kernels lay out, with the groups of M tiles
 // aligned to the experts' segments (a group that straddled two experts would share no weight panel).
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 
@@ -182,7 +186,8 @@ __device__ unsigned long long g_round_count[8 * 8];
 template <int EPI, bool GROUPED, bool BROW, int NG, int MG>
 __device__ __forceinline__ void gemm_body() {
   // (the kernel's arguments, through a pointer the compiler cannot see through: it would load what all bodies use before it
-  // picks one, and hold it in scalar registers that the loops need)
+  // picks one, and hold it in scalar registers that the loops need; they start the kernel-argument segment, being the only
+  // parameter: asserted at the kernel)
   typedef const __attribute__((address_space(4))) KArgs* args_t;
   args_t args = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(args));
@@ -653,6 +658,8 @@ void gemm_packed_kernel(KArgs p) {
   else { MOEP_BODY(8) }
 #undef MOEP_BODY
 }
+static_assert(std::is_same<decltype(gemm_packed_kernel<EPI_STORE, false, false>), void(KArgs)>::value &&
+              std::is_trivially_copyable<KArgs>::value, "gemm_body finds KArgs at the start of the kernel-argument segment");
 
 // Per-device launch state, filled on a device's first launch under a mutex (first calls from several host threads are
 // safe): the compute-unit count, and whether the dynamic LDS limits have been raised.  They are raised for EVERY expert
