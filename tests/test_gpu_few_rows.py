@@ -291,3 +291,30 @@ def test_short_tiles_give_the_bits_of_full_ones(E, H, F, T, kept, rows):
     pick = torch.tensor([0, T // 2, T - 1])
     _, ref = oracle.expert_outputs(*[wl.to_f64(v) for v in (layer["x"][pick], *[layer[n] for n in NAMES[1:]])])
     check_outputs(wl.to_f64(Y[:, pick.to(Y.device)].contiguous()), ref, "Y")
+
+
+@pytest.mark.parametrize("rounds", [5, 9])
+def test_a_partly_filled_last_round_takes_no_longer_than_a_full_one(rounds):
+    """The persistent workgroups of the 256-row GEMM line up after every fourth tile.  Where some have their last tile just then,
+    the others wait for the arrivals of that line-up only: with fewer tiles in the last round a launch is not slower."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("tile counts for 256 compute units")
+    E, H, T = 8, 512, 1024                 # 4 row tiles of 8 experts: 32 gate/up tiles per 128 columns, 8 columns of them a round
+
+    def gate_up_ms(columns):
+        F = 128 * columns
+        gen = torch.Generator(device="cuda:0")
+        gen.manual_seed(41)
+        x, Wg, W1, W3, W2 = (torch.randn(s, generator=gen, device="cuda:0").mul_(0.05).to(torch.bfloat16)
+                             for s in ((T, H), (E, H), (E, F, H), (E, F, H), (E, H, F)))
+        pkg.kernel_timing_enable(True)
+        pkg.kernel_timing_reset()
+        for _ in range(12):
+            pkg.moe_expert_outputs(x, Wg, W1, W3, W2)
+        torch.cuda.synchronize()
+        ms = [t for name, t in pkg.kernel_timing_records() if name == "gemm_gate_up_swiglu"]
+        pkg.kernel_timing_enable(False)
+        assert len(ms) == 12
+        return min(ms)
+
+    assert gate_up_ms(8 * rounds - 6) <= 1.05 * gate_up_ms(8 * rounds)
