@@ -526,7 +526,8 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
     const int32_t* seg_end = (const int32_t*)(w + p.off_seg_end);
     const int32_t* tiles_in_use = tile_expert + p.max_tiles;
     if (int st = launch_pack_a_gathered_bf16(x, H, slot_token, tile_expert, tile_row0, seg_end, tiles_in_use,
-                                             p.max_tiles, H, w + p.off_xp, s, "pack_x_routed")) return st;
+                                             (const uint32_t*)(w + p.off_order_up), p.max_tiles, H, w + p.off_xp, s,
+                                             "pack_x_routed")) return st;
     const char* w13 = w + p.off_w13;
     const char* w2 = w + p.off_w2;
     const bool in_place = !packed && p.max_slots <= IN_PLACE_MAX_ROWS * p.E;

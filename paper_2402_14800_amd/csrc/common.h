@@ -168,7 +168,7 @@ int launch_pack_a_bf16(const void* X, int64_t ld, int64_t rows, int K, void* dst
 // grouped: block row p of tile t = row rows_of[tile_row0[t] + p] of X
 int launch_pack_a_gathered_bf16(const void* X, int64_t ld, const int32_t* rows_of, const int32_t* tile_expert,
                                 const int32_t* tile_row0, const int32_t* seg_end, const int32_t* tiles_in_use,
-                                int64_t max_tiles, int K, void* dst, hipStream_t s, const char* name);
+                                const uint32_t* tile_order, int64_t max_tiles, int K, void* dst, hipStream_t s, const char* name);
 // W1 != nullptr: gate/up pair (blocks of 128 rows of W0 followed by the same 128 rows of W1); `experts`
 // consecutive [N, K] matrices are packed into consecutive packed_b_bytes blocks
 int launch_pack_b_bf16(const void* W0, const void* W1, int N, int K, int experts, void* dst, hipStream_t s,

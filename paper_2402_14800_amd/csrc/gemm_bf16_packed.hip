@@ -94,7 +94,8 @@ __host__ __device__ constexpr int perm32(int p) {
 // mode 2: gate/up weight pair, 128 output columns per tile: block row p < 128 = row 128 t + perm32(p) of
 //         W0, block row p >= 128 = row 128 t + perm32(p - 128) of W1.
 // mode 3: gathered A operand of a grouped GEMM: block row p of tile t = source row rows_of[tile_row0[t] + p]
-//         (the rows routed to the tile's expert, Sec. 3.3); tiles beyond the number in use are left alone.
+//         (the rows routed to the tile's expert, Sec. 3.3); tiles beyond the number in use are left alone, and so are
+//         the rows that the launch's bodies do not fetch (16 rows x 2 for each of tile_order's row groups).
 // Rows beyond the last one re-read the last row (their products are never stored).
 // One workgroup moves a pair of slices (64 k-values) of one tile, so that whole 128-byte lines are read;
 // blockIdx.z selects the expert of a weight stack.
@@ -105,7 +106,7 @@ struct PackArgs {
   int64_t rows;           // valid source rows (modes 0..2)
   int64_t src_expert_chunks, dst_expert_chunks;   // per-expert strides (blockIdx.z)
   const int32_t* rows_of; const int32_t* tile_expert; const int32_t* tile_row0; const int32_t* seg_end;
-  const int32_t* tiles_in_use;
+  const int32_t* tiles_in_use; const uint32_t* tile_order;
   int nsl;                // K / 32
   int mode;
 };
@@ -117,35 +118,42 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs p) {
   const u32x4* W1 = p.W1 + (int64_t)blockIdx.z * p.src_expert_chunks;
   u32x4* dst = p.dst + (int64_t)blockIdx.z * p.dst_expert_chunks;
   int64_t g_row0 = 0, g_end = 0;
+  int groups = 8;
   if (p.mode == 3) {
     if (t >= *p.tiles_in_use) return;
+    groups = (int)p.tile_order[TILE_ORDER_ROW_GROUPS];
     g_row0 = p.tile_row0[t];
     g_end = p.seg_end[p.tile_expert[t]];
   }
+  auto move = [&](auto pieces) {             // of 32 rows; a loop of its own for each number, all its loads in flight together
 #pragma unroll
-  for (int it = 0; it < 8; ++it) {
-    const int q = it * 256 + threadIdx.x;    // 2048 chunks: 256 rows x 8 chunks of a 128-byte line
-    const int row = q >> 3, c8 = q & 7;
-    const u32x4* src = W0;
-    int64_t r;
-    if (p.mode == 3) {
-      int64_t slot = g_row0 + row;
-      if (slot >= g_end) slot = g_end - 1;
-      r = p.rows_of[slot];
-    } else {
-      if (p.mode == 0) r = (int64_t)t * 256 + row;
-      else if (p.mode == 1) r = (int64_t)t * 256 + perm32(row);
-      else {
-        r = (int64_t)t * 128 + perm32(row & 127);
-        if (row >= 128) src = W1;
+    for (int it = 0; it < decltype(pieces)::value; ++it) {
+      const int q = it * 256 + threadIdx.x;    // 2048 chunks: 256 rows x 8 chunks of a 128-byte line
+      const int row = q >> 3, c8 = q & 7;
+      const u32x4* src = W0;
+      int64_t r;
+      if (p.mode == 3) {
+        int64_t slot = g_row0 + row;
+        if (slot >= g_end) slot = g_end - 1;
+        r = p.rows_of[slot];
+      } else {
+        if (p.mode == 0) r = (int64_t)t * 256 + row;
+        else if (p.mode == 1) r = (int64_t)t * 256 + perm32(row);
+        else {
+          r = (int64_t)t * 128 + perm32(row & 127);
+          if (row >= 128) src = W1;
+        }
+        if (r >= p.rows) r = p.rows - 1;
       }
-      if (r >= p.rows) r = p.rows - 1;
+      const u32x4 v = src[r * p.ld_chunks + (int64_t)sp * 8 + c8];
+      const int s = 2 * sp + (c8 >> 2);
+      const int pos = (c8 & 3) ^ ((row >> 2) & 3);
+      dst[((int64_t)t * p.nsl + s) * 1024 + row * 4 + pos] = v;
     }
-    const u32x4 v = src[r * p.ld_chunks + (int64_t)sp * 8 + c8];
-    const int s = 2 * sp + (c8 >> 2);
-    const int pos = (c8 & 3) ^ ((row >> 2) & 3);
-    dst[((int64_t)t * p.nsl + s) * 1024 + row * 4 + pos] = v;
-  }
+  };
+  if (groups > 6) move(std::integral_constant<int, 8>{});
+  else if (groups > 4) move(std::integral_constant<int, 6>{});
+  else move(std::integral_constant<int, 4>{});
 }
 
 // ---- GEMM --------------------------------------------------------------------------------------
@@ -745,12 +753,12 @@ int launch_pack_a_bf16(const void* X, int64_t ld, int64_t rows, int K, void* dst
 
 int launch_pack_a_gathered_bf16(const void* X, int64_t ld, const int32_t* rows_of, const int32_t* tile_expert,
                                 const int32_t* tile_row0, const int32_t* seg_end, const int32_t* tiles_in_use,
-                                int64_t max_tiles, int K, void* dst, hipStream_t s, const char* name) {
+                                const uint32_t* tile_order, int64_t max_tiles, int K, void* dst, hipStream_t s, const char* name) {
   if (ld % 8) return fail(MOEP_EUNSUPPORTED, "%s: leading dimension must be a multiple of 8", name);
   PackArgs p = {};
   p.W0 = (const u32x4*)X; p.dst = (u32x4*)dst; p.ld_chunks = ld / 8; p.mode = 3;
   p.rows_of = rows_of; p.tile_expert = tile_expert; p.tile_row0 = tile_row0; p.seg_end = seg_end;
-  p.tiles_in_use = tiles_in_use;
+  p.tiles_in_use = tiles_in_use; p.tile_order = tile_order;
   return launch_pack(p, max_tiles, K, 1, s, name);
 }
 
