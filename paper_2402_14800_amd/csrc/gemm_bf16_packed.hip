@@ -645,8 +645,9 @@ __device__ __forceinline__ void gemm_body() {
 }
 
 // The body is picked by the launch's row groups and tile width.  Row groups: of a launch whose tallest tile has up to 128 or 192
-// rows only those are fetched and multiplied.  Skipping forward, Mixtral shape, T = 300 (75 rows per expert) 705 -> 607 us, 450
-// 731 -> 640, 777 706 -> 645; dense pass of 128 tokens 748 -> 652, of 192 808 -> 754.  They are bodies of their own: with one
+// rows only those are fetched and multiplied.  By themselves, without the cut into shorter tiles (Shorten in skip.hip), us per
+// skipping forward, Mixtral shape, median of three processes each way: T = 300 (75 rows per expert) 712 -> 598, 450 719 -> 600,
+// 777 737 -> 659; dense pass of 128 tokens 700 -> 581, of 192 707 -> 631.  They are bodies of their own: with one
 // accumulator array and a loop per height the register allocator spilled some 400 registers around the loops.
 // A launch with so few tiles that compute units would stand idle walks tiles of half the width instead, 256 x 128
 // accumulator columns (64 outputs in SwiGLU mode), bits unchanged.  Half-width tiles cost well over half the time of full

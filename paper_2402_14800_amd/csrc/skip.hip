@@ -71,8 +71,10 @@ __global__ __launch_bounds__(RB) void route_kernel(const float* __restrict__ log
 // is the rounds of 256 tiles (compute units) that they take, each as many steps as its K is deep; a step of a 192-row tile
 // costs 13/16 of a 256-row one's (6/8 of the products, but the same weights), and a launch of half-width tiles, which fits
 // one round, 10/16 of a round.  256 / 192 rows, us per call: Mixtral shape, T = 1500 (about 281 rows per expert, two tiles
-// either way) 1089 / 947, T = 3000 1689 / 1630, T = 2000 (375 rows: two or three tiles) 1095 / 1316; E 8, H 1024, F 3584,
-// T = 1500 127 / 113; E 16, H 2048, F 5632, top-4, T = 1500 (a 257th tile in the down projection) 499 / 553.
+// either way) 1081 / 938, T = 3000 1687 / 1586, T = 2000 (375 rows: two or three tiles) 1116 / 1323; E 8, H 1024, F 3584,
+// T = 1500 131 / 111, T = 6000 261 / 247; E 16, H 2048, F 5632, top-4, T = 1200 497 / 438, T = 1500 (a 257th tile in the down
+// projection) 515 / 563; E 32, H 512, F 1472, T = 8192 159 / 150.  Where K is a few hundred the rule can be wrong by a few
+// percent: E 4, H 4096, F 512, top-4, T = 1024 (two rounds of 16 slices for one) 129 / 135.
 struct Shorten { int n_up = 0, n_down = 0, k_up = 0, k_down = 0; };   // full-width N tiles of the launches; n_up = 0: tiles as given
 constexpr int SHORT_TILE_ROWS = 192;
 
