@@ -8,6 +8,7 @@
 
 #include "enum_plan.h"
 #include "moeprune.h"
+#include "tile_plan.h"
 
 namespace moep {
 
@@ -117,11 +118,6 @@ constexpr int GEMM_GROUP_M_SWIGLU = 8, GEMM_GROUP_M_STORE = 4;
 // output columns per tile; half-width tiles for launches that would leave compute units without a tile
 constexpr int GEMM_BN_SWIGLU = 128, GEMM_BN_STORE = 256;
 static inline int gemm_tile_columns(bool gate_up, bool half) { return (gate_up ? GEMM_BN_SWIGLU : GEMM_BN_STORE) >> (half ? 1 : 0); }
-// Whether a launch of `tiles` full-width tiles is shorter with twice as many of half the width, on 256 compute units: while
-// they still fit one round.  Forward of 777 tokens at the Mixtral shape (128 tiles in its down projection) 764 -> 716 us,
-// dense pass of 64 tokens 798 -> 739 us; with 896 gate/up tiles taken as 7 half rounds for 4 the former was 790 us, and 160
-// tiles as two half rounds for one cost 445 -> 507 us (E 16, H 2048, F 5632, top-4, 1001 tokens).
-__host__ __device__ static inline bool half_width_pays(int64_t tiles) { return tiles <= 128; }
 // 16-row groups that a wavefront multiplies in a launch whose tallest tile has `rows` rows: 8 (256 rows), 6 or 4
 __host__ __device__ static inline int gemm_row_groups(int64_t rows) { return rows <= 128 ? 4 : rows <= 192 ? 6 : 8; }
 // A tile order starts with a header: whether its entries are half-width tiles, and the launch's row groups.

@@ -645,7 +645,7 @@ __device__ __forceinline__ void gemm_body() {
 }
 
 // The body is picked by the launch's row groups and tile width.  Row groups: of a launch whose tallest tile has up to 128 or 192
-// rows only those are fetched and multiplied.  By themselves, without the cut into shorter tiles (Shorten in skip.hip), us per
+// rows only those are fetched and multiplied.  By themselves, without the cut into shorter tiles (tile_plan.h), us per
 // skipping forward, Mixtral shape, median of three processes each way: T = 300 (75 rows per expert) 712 -> 598, 450 719 -> 600,
 // 777 737 -> 659; dense pass of 128 tokens 700 -> 581, of 192 707 -> 631.  They are bodies of their own: with one
 // accumulator array and a loop per height the register allocator spilled some 400 registers around the loops.

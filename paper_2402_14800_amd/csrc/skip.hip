@@ -67,17 +67,6 @@ __global__ __launch_bounds__(RB) void route_kernel(const float* __restrict__ log
   if ((int)threadIdx.x < E) counts[(int64_t)blockIdx.x * E + threadIdx.x] = cnt[threadIdx.x];
 }
 
-// Rows per tile of a routed 256-row GEMM: 256, or SHORT_TILE_ROWS where its two launches are shorter with that.  What they cost
-// is the rounds of 256 tiles (compute units) that they take, each as many steps as its K is deep; a step of a 192-row tile
-// costs 13/16 of a 256-row one's (6/8 of the products, but the same weights), and a launch of half-width tiles, which fits
-// one round, 10/16 of a round.  256 / 192 rows, us per call: Mixtral shape, T = 1500 (about 281 rows per expert, two tiles
-// either way) 1081 / 938, T = 3000 1687 / 1586, T = 2000 (375 rows: two or three tiles) 1116 / 1323; E 8, H 1024, F 3584,
-// T = 1500 131 / 111, T = 6000 261 / 247; E 16, H 2048, F 5632, top-4, T = 1200 497 / 438, T = 1500 (a 257th tile in the down
-// projection) 515 / 563; E 32, H 512, F 1472, T = 8192 159 / 150.  Where K is a few hundred the rule can be wrong by a few
-// percent: E 4, H 4096, F 512, top-4, T = 1024 (two rounds of 16 slices for one) 129 / 135.
-struct Shorten { int n_up = 0, n_down = 0, k_up = 0, k_down = 0; };   // full-width N tiles of the launches; n_up = 0: tiles as given
-constexpr int SHORT_TILE_ROWS = 192;
-
 // The experts' segments and tiles from their row counts, by one wavefront: lane e < E holds expert e's count.  begin and
 // first_tile: [E + 1], in LDS.
 struct Segments { int32_t* seg_end; int32_t* tile_expert; int max_tiles, tile_rows; Shorten shorten; };
@@ -92,9 +81,7 @@ __device__ __forceinline__ void lay_out_segments(int lane, int E, int count, con
       tall += __shfl_xor(tall, off, 64);
       shortened += __shfl_xor(shortened, off, 64);
     }
-    auto launch = [](int64_t tiles, int k) { return (half_width_pays(tiles) ? 10 : 16 * ((tiles + 255) >> 8)) * (int64_t)k; };
-    auto both = [&](int64_t t) { return launch(t * s.shorten.n_up, s.shorten.k_up) + launch(t * s.shorten.n_down, s.shorten.k_down); };
-    if (shortened <= s.max_tiles && 13 * both(shortened) < 16 * both(tall)) tile_rows = SHORT_TILE_ROWS;
+    if (shortened <= s.max_tiles && short_tiles_pay(s.shorten, tall, shortened)) tile_rows = SHORT_TILE_ROWS;
   }
   const int tiles = (c + tile_rows - 1) / tile_rows;
   int end = c, tile_end = tiles;                 // inclusive sums over the lanes

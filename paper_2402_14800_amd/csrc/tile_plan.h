@@ -1,0 +1,40 @@
+// How the 256-row GEMM's launches are cut into tiles.  Plain arithmetic, without HIP: the dispatch kernels call it, and so does a
+// program built on the CPU that checks it.
+#pragma once
+
+#include <stdint.h>
+
+namespace moep {
+
+// Whether a launch of `tiles` full-width tiles is shorter with twice as many of half the width, on 256 compute units: while
+// they still fit one round.  Forward of 777 tokens at the Mixtral shape (128 tiles in its down projection) 764 -> 716 us,
+// dense pass of 64 tokens 798 -> 739 us; with 896 gate/up tiles taken as 7 half rounds for 4 the former was 790 us, and 160
+// tiles as two half rounds for one cost 445 -> 507 us (E 16, H 2048, F 5632, top-4, 1001 tokens).
+constexpr bool half_width_pays(int64_t tiles) { return tiles <= 128; }
+
+// Rows per tile of a routed launch: 256, or SHORT_TILE_ROWS where the call's two launches are shorter with that.  What they
+// cost is the rounds of 256 tiles (compute units) that they take, each as many steps as its K is deep and the epilogue: about
+// 4 steps of 32 for the SwiGLU one, 24 for the row-scaled one, whose loads wait for each other.  A 192-row tile costs 13/16 of a
+// 256-row one (6/8 of the products, but the same weights), and a launch of half-width tiles, which fits one round, 10/16 of a
+// round.  256 / 192 rows, us per call: Mixtral shape, T = 1500 (about 281 rows per expert, two tiles either way) 1081 / 938,
+// T = 3000 1687 / 1586, T = 2000 (375 rows: two or three tiles) 1116 / 1323; E 8, H 1024, F 3584, T = 1500 131 / 111,
+// T = 6000 261 / 247; E 16, H 2048, F 5632, top-4, T = 1200 497 / 438, T = 1500 (a 257th tile in the down projection)
+// 515 / 563; E 32, H 512, F 1472, T = 8192 159 / 150.  The epilogues matter where K is a few hundred (E 32, H 3136, F 128,
+// T = 3006, three rounds of 4 steps for two: 148 / 166; E 32, H 1664, F 64, top-4, T = 1591 101 / 107).  Of 138 random shapes
+// (H 64 to 4096, F 64 to 12800, 150 to 900 rows per expert) that the depths alone would cut, into another number of rounds, the
+// epilogues leave 15 whole: six 3 to 8 % faster so, one 8 % slower, the rest within 2 %.  The other 123 gain 5.5 % on average;
+// five of them lose 4 to 10 % (the worst E 4, H 1088, F 8128, T = 412 135 / 148, twice as many tiles of half the width).
+struct Shorten { int n_up = 0, n_down = 0, k_up = 0, k_down = 0; };   // full-width N tiles of the launches; n_up = 0: tiles as given
+constexpr int SHORT_TILE_ROWS = 192;
+constexpr int EPILOGUE_UP = 4 * 32, EPILOGUE_DOWN = 24 * 32;          // in units of K
+
+// `tall`, `shortened`: M tiles of 256 and of SHORT_TILE_ROWS rows
+constexpr int64_t launch_cost(int64_t tiles, int k) { return (half_width_pays(tiles) ? 10 : 16 * ((tiles + 255) >> 8)) * (int64_t)k; }
+constexpr int64_t routed_cost(const Shorten& s, int64_t m_tiles) {
+  return launch_cost(m_tiles * s.n_up, s.k_up + EPILOGUE_UP) + launch_cost(m_tiles * s.n_down, s.k_down + EPILOGUE_DOWN);
+}
+constexpr bool short_tiles_pay(const Shorten& s, int64_t tall, int64_t shortened) {
+  return 13 * routed_cost(s, shortened) < 16 * routed_cost(s, tall);
+}
+
+}  // namespace moep

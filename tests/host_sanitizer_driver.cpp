@@ -9,6 +9,7 @@
 
 #include "enum_plan.h"
 #include "moeprune.h"
+#include "tile_plan.h"
 
 static int failures = 0;
 #define EXPECT(cond)                                                          \
@@ -111,6 +112,18 @@ int main() {
           if (q.use_lut) EXPECT(q.tok_tile <= 1024 || (!q.fused_threads && T > (int64_t)65535 * 1024));
         }
       }
+
+  // ---- tiles of a routed call: shorter ones where they make it shorter (us of whole calls, 256 / 192 rows, at tile_plan.h)
+  {
+    auto pays = [](int H, int F, int tall, int shortened) {
+      return moep::short_tiles_pay({(F + 127) / 128, (H + 255) / 256, H, F}, tall, shortened);
+    };
+    EXPECT(pays(4096, 14336, 16, 16) && !pays(4096, 14336, 16, 20));         // two tiles per expert either way; half of them three
+    EXPECT(pays(192, 4736, 16, 20) && pays(256, 1536, 23, 24));              // as many rounds
+    EXPECT(pays(128, 8640, 33, 48) && pays(512, 9408, 16, 18));              // more, short of what the shorter steps save
+    // a third round, or a second, of a few steps and a whole epilogue
+    EXPECT(!pays(3136, 128, 32, 45) && !pays(1664, 64, 32, 54) && !pays(1984, 128, 32, 40) && !pays(1920, 64, 64, 79));
+  }
 
   // ---- argument errors: every call must come back with a status and a message, having launched nothing
   void* p = (void*)(uintptr_t)(1 << 20);          // never dereferenced on the host
