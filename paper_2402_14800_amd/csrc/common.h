@@ -120,8 +120,9 @@ constexpr int GEMM_BN_SWIGLU = 128, GEMM_BN_STORE = 256;
 static inline int gemm_tile_columns(bool gate_up, bool half) { return (gate_up ? GEMM_BN_SWIGLU : GEMM_BN_STORE) >> (half ? 1 : 0); }
 // 16-row groups that a wavefront multiplies in a launch whose tallest tile has `rows` rows: 8 (256 rows), 6 or 4
 __host__ __device__ static inline int gemm_row_groups(int64_t rows) { return rows <= 128 ? 4 : rows <= 192 ? 6 : 8; }
-// A tile order starts with a header: whether its entries are half-width tiles, and the launch's row groups.
-constexpr int TILE_ORDER_HEADER = 4, TILE_ORDER_HALF = 0, TILE_ORDER_ROW_GROUPS = 1;
+// A tile order starts with a header: how many of its entries are full-width tiles, how many half-width ones (these come after
+// the others), and the launch's row groups.
+constexpr int TILE_ORDER_HEADER = 4, TILE_ORDER_HALF = 0, TILE_ORDER_ROW_GROUPS = 1, TILE_ORDER_FULL = 2;
 
 int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name);
 
@@ -146,7 +147,7 @@ struct PackedGemmArgs {
   const int32_t* tiles_in_use = nullptr;
   int64_t max_m_tiles = 0;
   // Grouped mode: the order in which the launch walks its tiles: TILE_ORDER_HEADER words, then entry i = (M tile << 12) |
-  // N tile, tiles_in_use x n_tiles entries (see order_kernel in skip.hip).
+  // N tile (see order_kernel in skip.hip).
   const uint32_t* tile_order = nullptr;
   // Dense batched mode: `experts` GEMMs of the same shape in one launch; expert e reads A + e a_expert_bytes
   // (0: every expert reads the same A), B + e packed_b_bytes(..), and writes C + e c_expert_bytes.

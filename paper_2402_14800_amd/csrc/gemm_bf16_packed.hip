@@ -165,8 +165,8 @@ struct KArgs {
   int64_t M, ldc;
   int N;                  // output columns
   int nsl;                // K / 32
-  int m_tiles, n_tiles;   // n_tiles: of the width the launch walks (grouped: of half the width)
-  int n_tiles_full, half_width, row_groups;
+  int m_tiles, n_tiles;   // dense; n_tiles: of the width the launch walks
+  int half_width, row_groups;
   // grouped mode (rows partitioned into per-expert segments, tile t = rows tile_row0[t] .. of expert
   // tile_expert[t]; A and a packed C are indexed by TILE, a row-major C by row)
   const int32_t* tile_expert; const int32_t* tile_row0; const int32_t* seg_end; const int32_t* tiles_in_use;
@@ -208,10 +208,11 @@ __device__ __forceinline__ void gemm_body() {
   const int wm = wave_u >> 1, wn = wave_u & 1;
   const int nsl = p.nsl;
   // Grouped launches are sized for the largest possible tile map; only its leading entries hold work.
-  const uint32_t m_tiles = GROUPED ? (uint32_t)*p.tiles_in_use : (uint32_t)p.m_tiles;
-  const uint32_t n_tiles = GROUPED && NG == 8 ? (uint32_t)p.n_tiles_full : (uint32_t)p.n_tiles;
+  // Grouped: full-width tiles come first in the order, half-width ones after them.
+  const uint32_t m_tiles = (uint32_t)p.m_tiles, n_tiles = (uint32_t)p.n_tiles;
   const uint32_t per_expert = m_tiles * n_tiles;
-  const uint32_t nblk = GROUPED ? per_expert : per_expert * (uint32_t)p.experts;
+  const uint32_t nblk = GROUPED ? p.tile_order[NG == 8 ? TILE_ORDER_FULL : TILE_ORDER_HALF] : per_expert * (uint32_t)p.experts;
+  const uint32_t order_at = TILE_ORDER_HEADER + (GROUPED && NG == 4 ? p.tile_order[TILE_ORDER_FULL] : 0u);
   const uint32_t G = gridDim.x;
 
   // Logical tile id -> (tm, tn).  Ids i, i + 8, ... belong to XCD i % 8 (the grid is a multiple of 8 or
@@ -246,7 +247,7 @@ __device__ __forceinline__ void gemm_body() {
       // the order of the tiles was laid out by the caller (groups of M tiles aligned to experts, see order_kernel);
       // XCD x walks entries x per + min(x, rem) ... of it
       const uint32_t per = nblk >> 3, rem = nblk & 7;
-      const uint32_t v = p.tile_order[TILE_ORDER_HEADER + xcd * per + (xcd < rem ? xcd : rem) + j];
+      const uint32_t v = p.tile_order[order_at + xcd * per + (xcd < rem ? xcd : rem) + j];
       e = 0;
       tm = (int)(v >> 12);
       tn = (int)(v & 4095u);
@@ -676,14 +677,16 @@ __device__ __forceinline__ void gemm_body() {
 template <int EPI, bool GROUPED, bool BROW>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_packed_kernel(KArgs p) {
+  const bool full = GROUPED ? p.tile_order[TILE_ORDER_FULL] != 0 : p.half_width == 0;
   const bool half = GROUPED ? p.tile_order[TILE_ORDER_HALF] != 0 : p.half_width != 0;
   const uint32_t mg = GROUPED ? p.tile_order[TILE_ORDER_ROW_GROUPS] : (uint32_t)p.row_groups;
 #define MOEP_BODY(NG)                                                                           \
   if (mg > 6) gemm_body<EPI, GROUPED, BROW, NG, 8>();                                          \
   else if (mg > 4) gemm_body<EPI, GROUPED, BROW, NG, 6>();                                     \
   else gemm_body<EPI, GROUPED, BROW, NG, 4>();
+  if (full) { MOEP_BODY(8) }
+  if (GROUPED && full && half) __builtin_amdgcn_s_barrier();   // (the ring begins anew: all have read what it held)
   if (half) { MOEP_BODY(4) }
-  else { MOEP_BODY(8) }
 #undef MOEP_BODY
 }
 static_assert(std::is_same<decltype(gemm_packed_kernel<EPI_STORE, false, false>), void(KArgs)>::value &&
@@ -830,7 +833,7 @@ int launch_gemm_bf16_packed(const PackedGemmArgs& g, hipStream_t s, const char* 
   const bool half = !grouped && half_width_pays(m_tiles * n_full * g.experts);
   const int64_t n_tiles = grouped || half ? n_half : n_full;
   if (m_tiles * n_tiles * g.experts >= ((int64_t)1 << 31)) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
-  k.m_tiles = (int)m_tiles; k.n_tiles = (int)n_tiles; k.n_tiles_full = (int)n_full; k.half_width = half ? 1 : 0;
+  k.m_tiles = (int)m_tiles; k.n_tiles = (int)n_tiles; k.half_width = half ? 1 : 0;
   k.row_groups = gemm_row_groups(g.M);
   Timed t(name, s);
 #define MOEP_GEMM_CASE(EPI, GROUPED) \

@@ -160,21 +160,27 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(int32_t* __restrict_
 // group may be smaller.  Entry = (M tile << 12) | N tile.
 // blockIdx.y: 0 the gate/up projection's table, 1 the down projection's.  The width of the tiles is decided here, from the
 // number of tiles the routing made, and noted in the table's header.
-struct OrderArgs { uint32_t* order; int n_full, n_half, group_m; };
+struct OrderArgs { uint32_t* order; int n_full, n_half, group_m, k; };
 __global__ __launch_bounds__(256) void order_kernel(const int32_t* __restrict__ expert_end, int E, OrderArgs up,
                                                     OrderArgs down) {
   const int32_t* const expert_first = expert_end + E;
   const OrderArgs a = blockIdx.y ? down : up;
   __shared__ int first[33];
-  if ((int)threadIdx.x <= E) first[threadIdx.x] = expert_first[threadIdx.x];
+  __shared__ int most;                                     // rows of one expert
+  if (threadIdx.x == 0) most = 0;
   __syncthreads();
-  const bool half = half_width_pays((int64_t)first[E] * a.n_full);
+  if ((int)threadIdx.x <= E) first[threadIdx.x] = expert_first[threadIdx.x];
+  if ((int)threadIdx.x < E) atomicMax(&most, expert_end[threadIdx.x] - (threadIdx.x ? expert_end[threadIdx.x - 1] : 0));
+  __syncthreads();
+  const int row_groups = gemm_row_groups(min(most, expert_end[2 * E + 1]));
+  const int64_t tiles = (int64_t)first[E] * a.n_full;
+  const bool half = half_width_pays(tiles);
   const int n_tiles = half ? a.n_half : a.n_full;
+  const int64_t tail = tail_tiles(tiles, a.n_full, a.n_half, a.k, row_groups);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    int most = 0;                                          // rows of one expert
-    for (int e = 0; e < E; ++e) most = max(most, expert_end[e] - (e ? expert_end[e - 1] : 0));
-    a.order[TILE_ORDER_HALF] = half ? 1u : 0u;
-    a.order[TILE_ORDER_ROW_GROUPS] = (uint32_t)gemm_row_groups(min(most, expert_end[2 * E + 1]));
+    a.order[TILE_ORDER_HALF] = half ? (uint32_t)(first[E] * a.n_half) : (uint32_t)(2 * tail);
+    a.order[TILE_ORDER_FULL] = half ? 0u : (uint32_t)(tiles - tail);
+    a.order[TILE_ORDER_ROW_GROUPS] = (uint32_t)row_groups;
   }
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (q >= (int64_t)first[E] * n_tiles) return;
@@ -189,7 +195,13 @@ __global__ __launch_bounds__(256) void order_kernel(const int32_t* __restrict__ 
   const int gm = c - first_m < group_m ? c - first_m : group_m;
   const int in_group = (int)(qe - g * gsz);
   const int tn = in_group / gm, m = first_m + in_group % gm;
-  a.order[TILE_ORDER_HEADER + q] = ((uint32_t)(first[e] + m) << 12) | (uint32_t)tn;
+  const uint32_t row = (uint32_t)(first[e] + m) << 12;
+  if (tail > 0 && q >= tiles - tail) {                     // (an odd number of half tiles along N: the last one has no columns)
+    a.order[TILE_ORDER_HEADER + 2 * q - (tiles - tail)] = row | (uint32_t)(2 * tn);
+    a.order[TILE_ORDER_HEADER + 2 * q - (tiles - tail) + 1] = row | (uint32_t)(2 * tn + 1);
+  } else {
+    a.order[TILE_ORDER_HEADER + q] = row | (uint32_t)tn;
+  }
 }
 
 __global__ __launch_bounds__(RB) void scatter_kernel(const int32_t* __restrict__ top2,
@@ -551,10 +563,10 @@ static void launch_order_tables(const SkipPlan& p, char* ws, hipStream_t s) {
   if (!p.packed || p.few) return;
   const int32_t* expert_end = (const int32_t*)(ws + p.off_seg_end);
   const OrderArgs up = {(uint32_t*)(ws + p.off_order_up), (int)ceil_div(p.F, gemm_tile_columns(true, false)),
-                        (int)ceil_div(p.F, gemm_tile_columns(true, true)), GEMM_GROUP_M_SWIGLU};
+                        (int)ceil_div(p.F, gemm_tile_columns(true, true)), GEMM_GROUP_M_SWIGLU, p.H};
   const OrderArgs down = {(uint32_t*)(ws + p.off_order_down), (int)ceil_div(p.H, gemm_tile_columns(false, false)),
-                          (int)ceil_div(p.H, gemm_tile_columns(false, true)), GEMM_GROUP_M_STORE};
-  // entries of the larger table: p.max_tiles full-width tiles, or the few half-width ones that half_width_pays allows
+                          (int)ceil_div(p.H, gemm_tile_columns(false, true)), GEMM_GROUP_M_STORE, p.F};
+  // a thread per full-width tile of the larger table, or per half-width one of the few that half_width_pays allows
   const int64_t n = p.max_tiles * (up.n_full > down.n_full ? up.n_full : down.n_full);
   hipLaunchKernelGGL(order_kernel, dim3((unsigned)ceil_div(n > 512 ? n : 512, 256), 2), dim3(256), 0, s, expert_end, p.E,
                      up, down);

@@ -12,6 +12,18 @@ namespace moep {
 // tiles as two half rounds for one cost 445 -> 507 us (E 16, H 2048, F 5632, top-4, 1001 tokens).
 constexpr bool half_width_pays(int64_t tiles) { return tiles <= 128; }
 
+// Full-width tiles at the end of a routed launch of `tiles` that are walked as two of half the width each: those of a last round
+// that half of the compute units would otherwise sit out.  us per call, without / with: E 16, H 2304, F 2368, T = 3133
+// (2.4 rounds) 339 / 315; E 8, H 1920, F 7168, top-4, T = 2240 778 / 723; E 8, H 4096, F 14336, T = 969 899 / 882.  Below
+// TAIL_MIN_K what a tile saves goes into the second ring's fill (E 4, H 576, F 4032, top-4, T = 544 92 / 97; E 8, H 896, F 1984,
+// T = 2427 109 / 111).  Not with tiles of up to 128 rows (row_groups 4), whose
+// steps are the load of the weights: E 8, H 4096, F 14336, T = 262 581 / 606, E 16, H 2048, F 5632, T = 900 275 / 286.  n_full, n_half: tiles of either width along N; the launch's table has room for n_half per M tile, which
+// is enough for both kinds where n_half > n_full.
+constexpr int TAIL_MIN_K = 1024;
+constexpr int64_t tail_tiles(int64_t tiles, int n_full, int n_half, int k, int row_groups) {
+  return tiles > 256 && n_half > n_full && k >= TAIL_MIN_K && row_groups > 4 && half_width_pays(tiles & 255) ? tiles & 255 : 0;
+}
+
 // Rows per tile of a routed launch: 256, or SHORT_TILE_ROWS where the call's two launches are shorter with that.  What they
 // cost is the rounds of 256 tiles (compute units) that they take, each as many steps as its K is deep and the epilogue: about
 // 4 steps of 32 for the SwiGLU one, 24 for the row-scaled one, whose loads wait for each other.  A 192-row tile costs 13/16 of a

@@ -318,3 +318,36 @@ def test_a_partly_filled_last_round_takes_no_longer_than_a_full_one(rounds):
         return min(ms)
 
     assert gate_up_ms(8 * rounds - 6) <= 1.05 * gate_up_ms(8 * rounds)
+
+
+@pytest.mark.parametrize("H,F,T", [
+    (1024, 5504, 600),        # gate/up: 6 x 43 tiles, one round of 256 and 2 tiles as 4 of half the width
+    (1024, 5440, 600),        # the same with 85 half-width columns: the last tile's second half has none
+    (1088, 8192, 600),        # 384 tiles: the most that are halved
+    (1024, 8256, 600),        # 390: none
+    (11008, 1024, 600),       # down: 6 x 43 tiles
+    (960, 5504, 600),         # few K steps: none
+    (1024, 16576, 385),       # 4 x 130 tiles, three rounds
+])
+def test_a_last_round_of_half_width_tiles_gives_the_same_bits(H, F, T):
+    """Routed launches whose last round has 1 to 128 tiles walk those as twice as many of half the width: the bits of the same
+    rows in a batch without such a round and of the dense pass, row-major and packed weights, scaled and plain rows."""
+    E = 2
+    _, layer = small_layer("bf16", E, 2, H, F, T, index=33)
+    d = to_dev(layer)
+    rest = [d[n] for n in NAMES[1:]]
+    packed = pkg.moe_pack_weights(d["W1"], d["W3"], d["W2"])
+    out, skip, _, _ = pkg.moe_forward_skip(d["x"], *rest, 0.6)
+    out_all, _, _, _ = pkg.moe_forward_skip(d["x"], *rest, 0.0)                     # every expert gets all T rows
+    out_p, _, _, _ = pkg.moe_forward_pruned_skip_packed(d["x"], d["Wgate"], packed, F, 0.0)
+    _, experts, slot_of, Yr = pkg.moe_expert_outputs_ranked(d["x"], *rest, E)
+    _, Y = pkg.moe_expert_outputs(d["x"], *rest)
+    part = d["x"][:190].contiguous()
+    few, few_skip, _, _ = pkg.moe_forward_skip(part, *rest, 0.6)
+    few_all, _, _, _ = pkg.moe_forward_skip(part, *rest, 0.0)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(out_all), bits(out_p)) and torch.equal(skip[:190], few_skip)
+    assert torch.equal(bits(out[:190].contiguous()), bits(few)) and torch.equal(bits(out_all[:190].contiguous()), bits(few_all))
+    rows = Yr[slot_of.reshape(-1).long()].reshape(T, E, H)                          # [token, rank]
+    want = Y.permute(1, 0, 2)[torch.arange(T, device=Y.device)[:, None], experts.long()]
+    assert torch.equal(bits(rows.contiguous()), bits(want.contiguous()))
