@@ -147,7 +147,7 @@ struct PackedGemmArgs {
   const int32_t* tiles_in_use = nullptr;
   int64_t max_m_tiles = 0;
   // Grouped mode: the order in which the launch walks its tiles: TILE_ORDER_HEADER words, then entry i = (M tile << 12) |
-  // N tile (see order_kernel in skip.hip).
+  // N tile (see write_order in skip.hip).
   const uint32_t* tile_order = nullptr;
   // Dense batched mode: `experts` GEMMs of the same shape in one launch; expert e reads A + e a_expert_bytes
   // (0: every expert reads the same A), B + e packed_b_bytes(..), and writes C + e c_expert_bytes.

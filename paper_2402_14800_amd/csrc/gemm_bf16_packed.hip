@@ -244,7 +244,7 @@ __device__ __forceinline__ void gemm_body() {
   auto decode = [&](uint32_t L, int& tm, int& tn, int& e) {
     const uint32_t xcd = L & 7, j = L >> 3;
     if (GROUPED) {
-      // the order of the tiles was laid out by the caller (groups of M tiles aligned to experts, see order_kernel);
+      // the order of the tiles was laid out by the caller (groups of M tiles aligned to experts, see write_order in skip.hip);
       // XCD x walks entries x per + min(x, rem) ... of it
       const uint32_t per = nblk >> 3, rem = nblk & 7;
       const uint32_t v = p.tile_order[order_at + xcd * per + (xcd < rem ? xcd : rem) + j];

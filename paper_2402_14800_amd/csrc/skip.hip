@@ -5,12 +5,13 @@
 //            skip iff delta < theta = fp32(ln beta) (theta = -inf for beta = 0), weights
 //            a0 = 1 / (1 + rho), a1 = rho / (1 + rho), rho = exp(delta); a0 = 1 when skipped.
 //            Also counts, per block of 256 tokens, the rows each expert receives.
-//   scan     turns the counts into each (block, expert)'s first slot, each expert's segment end,
-//            and the map from M tiles (256 rows, or 64) to (expert, first row) that the grouped GEMMs walk
-//            (entry [max_tiles] of the expert list holds the number of tiles in use).
-//            (a batch of up to 512 tokens goes through route, scan and scatter in ONE workgroup, dispatch_one)
-//   scatter  writes slot -> token and slot -> weight lists and token -> slot positions.  Within an
-//            expert's segment the rows are in ascending token order, so the result is reproducible.
+//   place    turns the counts into each (block, expert)'s first slot and each expert's segment end, and writes the map from
+//            M tiles (256 or 192 rows, or 64) to (expert, first row) that the grouped GEMMs walk (entry [max_tiles] of the
+//            expert list holds the number of tiles in use), the order in which they walk it, the slot -> token and
+//            slot -> weight lists and the token -> slot positions.  Within an expert's segment the rows are in ascending
+//            token order, so the result is reproducible.
+//            (up to some hundred tokens go through route and place in ONE workgroup, dispatch_one; beyond 65536 a kernel of its
+//            own, scan, turns the counts into first slots)
 //   combine  out[t] = slot_out[pos0] (+ slot_out[pos1] unless skipped); the down projection has
 //            already multiplied each slot by its weight.  No atomics anywhere on this path.
 //
@@ -26,9 +27,18 @@ namespace moep {
 namespace {
 
 constexpr int RB = 256;     // tokens per routing block
-// Most tokens that the one-workgroup dispatch takes: one thread each; up to here it is shorter than the three kernels
-// it replaces (their counts and lists would go through memory twice for nothing).
-constexpr int DISPATCH_ONE_MAX = 512;
+// Most tokens that the one-workgroup dispatch takes, one thread each, and most entries of the tile orders: there it is shorter
+// than the two kernels it stands for.  In two / in one, us: Mixtral shape (E 8, H 4096, F 14336), top-2, T = 300 12.2 / 10.6,
+// 777 13.0 / 11.2, 1000 13.0 / 12.1; top-4, 500 14.0 / 13.4, 600 14.2 / 15.0; E 32, H 384, F 4096, top-2, 500 14.3 / 13.5,
+// 600 15.2 / 19.6, top-4, 200 18.1 / 14.7, 400 18.8 / 22.8; 3072 entries, 1000 tokens 14.7 / 18.2.  Routing, slots, the map of
+// tiles and their order in launches of their own took 19 to 27 us from 513 tokens on.
+constexpr int DISPATCH_ONE_MAX = 1024, DISPATCH_ONE_ORDER_MAX = 2048;
+static int dispatch_one_tokens(int E, int slots) {
+  const int most = 2 * DISPATCH_ONE_MAX / slots;
+  return (most > DISPATCH_ONE_MAX ? DISPATCH_ONE_MAX : most < 256 ? 256 : most) >> (E > 16 ? 1 : 0);
+}
+// Most routing blocks whose counts every workgroup of the place kernel adds up for itself (E 8: 8 KB of counts each).
+constexpr int64_t PLACE_MAX_BLOCKS = 256;
 
 struct Top2 { int e0, e1; float a0, a1; bool skip; };
 
@@ -67,19 +77,21 @@ __global__ __launch_bounds__(RB) void route_kernel(const float* __restrict__ log
   if ((int)threadIdx.x < E) counts[(int64_t)blockIdx.x * E + threadIdx.x] = cnt[threadIdx.x];
 }
 
-// The experts' segments and tiles from their row counts, by one wavefront: lane e < E holds expert e's count.  begin and
-// first_tile: [E + 1], in LDS.
+// The experts' segments and tiles from their row counts, by one wavefront: lane e < E holds expert e's count.  publish: to
+// memory as well.
 struct Segments { int32_t* seg_end; int32_t* tile_expert; int max_tiles, tile_rows; Shorten shorten; };
-__device__ __forceinline__ void lay_out_segments(int lane, int E, int count, const Segments& s, int* begin, int* first_tile,
-                                                 int* rows_of_tile) {
+struct Layout { int begin[33], first_tile[33], rows_of_tile, most_rows; };         // in LDS; the first two [E + 1]
+__device__ __forceinline__ void lay_out_segments(int lane, int E, int count, const Segments& s, Layout& out, bool publish) {
   const int c = lane < E ? count : 0;
-  int tile_rows = s.tile_rows;
-  if (s.shorten.n_up != 0) {
+  int tile_rows = s.tile_rows, most = c;
+  if (s.shorten.n_up != 0) {                     // the 256-row GEMMs
     int tall = (c + GEMM_BM - 1) / GEMM_BM, shortened = (c + SHORT_TILE_ROWS - 1) / SHORT_TILE_ROWS;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
       tall += __shfl_xor(tall, off, 64);
       shortened += __shfl_xor(shortened, off, 64);
+      const int m = __shfl_xor(most, off, 64);
+      most = m > most ? m : most;
     }
     if (shortened <= s.max_tiles && short_tiles_pay(s.shorten, tall, shortened)) tile_rows = SHORT_TILE_ROWS;
   }
@@ -92,28 +104,84 @@ __device__ __forceinline__ void lay_out_segments(int lane, int E, int count, con
     tile_end += lane >= off ? b : 0;
   }
   if (lane <= E) {
-    begin[lane] = end - c;
-    first_tile[lane] = tile_end - tiles;
-    s.seg_end[E + lane] = tile_end - tiles;
-    if (lane < E) s.seg_end[lane] = end;
+    out.begin[lane] = end - c;
+    out.first_tile[lane] = tile_end - tiles;
+    if (publish) {
+      s.seg_end[E + lane] = tile_end - tiles;
+      if (lane < E) s.seg_end[lane] = end;
+    }
   }
   if (lane == E) {
-    s.tile_expert[s.max_tiles] = tile_end;       // number of tiles in use, read by the grouped GEMMs
-    s.seg_end[2 * E + 1] = tile_rows;
-    *rows_of_tile = tile_rows;
+    if (publish) {
+      s.tile_expert[s.max_tiles] = tile_end;     // number of tiles in use, read by the grouped GEMMs
+      s.seg_end[2 * E + 1] = tile_rows;
+    }
+    out.rows_of_tile = tile_rows;
+    out.most_rows = most;
+  }
+}
+
+// The expert whose tiles, n_tiles per M tile, tile q is one of: the last e with first_tile[e] n_tiles <= q (five look-ups;
+// expert after expert it was one per expert, each waiting for the one before).
+__device__ __forceinline__ int expert_of_tile(const Layout& l, int E, uint32_t n_tiles, uint32_t q) {
+  int e = 0;
+#pragma unroll
+  for (int step = 16; step >= 1; step >>= 1)
+    if (e + step < E && (uint32_t)l.first_tile[e + step] * n_tiles <= q) e += step;
+  return e;
+}
+
+// The map of tiles, entries i0, i0 + step, ...
+__device__ __forceinline__ void write_tile_map(const Layout& l, int E, const Segments& seg, int32_t* tile_row0, int64_t i0, int64_t step) {
+  for (int64_t i = i0; i < seg.max_tiles; i += step) {
+    const bool used = i < l.first_tile[E];
+    const int e = expert_of_tile(l, E, 1, (uint32_t)i);
+    seg.tile_expert[i] = used ? e : -1;
+    tile_row0[i] = used ? l.begin[e] + ((int)i - l.first_tile[e]) * l.rows_of_tile : 0;
+  }
+}
+
+// The order in which a grouped GEMM launch walks its tiles.  The launch gives every XCD a contiguous run of this
+// list; within a run, 32 consecutive entries are in flight together and share operand panels through the XCD's L2.
+// Entries are grouped per EXPERT: group_m consecutive M tiles of one expert, walked along N (all group_m tiles of
+// one N tile, then the next N tile), so that the tiles in flight share the same few weight panels; an expert's last
+// group may be smaller.  Entry = (M tile << 12) | N tile.  The width of the tiles is decided here, from the number of tiles the
+// routing made, and noted in the header.  A thread takes tiles q0, q0 + step, ...
+struct OrderArgs { uint32_t* order; int n_full, n_half, group_m, k; };     // order NULL: none is wanted
+__device__ __forceinline__ void write_order(const Layout& l, int E, const OrderArgs& a, uint32_t q0, uint32_t step) {
+  const int row_groups = gemm_row_groups(l.most_rows < l.rows_of_tile ? l.most_rows : l.rows_of_tile);
+  const uint32_t m_tiles = (uint32_t)l.first_tile[E], tiles = m_tiles * (uint32_t)a.n_full;
+  const bool half = half_width_pays(tiles);
+  const uint32_t n_tiles = (uint32_t)(half ? a.n_half : a.n_full), most_m = (uint32_t)(half ? a.group_m / 2 : a.group_m);
+  const uint32_t tail = (uint32_t)tail_tiles(tiles, a.n_full, a.n_half, a.k, row_groups), full = half ? 0u : tiles - tail;
+  if (q0 == 0) {
+    a.order[TILE_ORDER_HALF] = half ? m_tiles * n_tiles : 2 * tail;
+    a.order[TILE_ORDER_FULL] = full;
+    a.order[TILE_ORDER_ROW_GROUPS] = (uint32_t)row_groups;
+  }
+  for (uint32_t q = q0; q < m_tiles * n_tiles; q += step) {
+    const int e = expert_of_tile(l, E, n_tiles, q);
+    const uint32_t first = (uint32_t)l.first_tile[e], qe = q - first * n_tiles, c = (uint32_t)l.first_tile[e + 1] - first;
+    const uint32_t g = qe / (most_m * n_tiles), first_m = g * most_m, gm = c - first_m < most_m ? c - first_m : most_m;
+    const uint32_t in_group = qe - g * (most_m * n_tiles), tn = in_group / gm, row = (first + first_m + in_group - tn * gm) << 12;
+    if (tail > 0 && q >= full) {                           // (an odd number of half tiles along N: the last one has no columns)
+      a.order[TILE_ORDER_HEADER + 2 * q - full] = row | (2 * tn);
+      a.order[TILE_ORDER_HEADER + 2 * q - full + 1] = row | (2 * tn + 1);
+    } else {
+      a.order[TILE_ORDER_HEADER + q] = row | tn;
+    }
   }
 }
 
 // seg_end holds 2 E + 2 ints: the E segment ends, then the index of each expert's first tile (E + 1 entries,
 // the last one being the number of tiles in use), then the rows per tile.  One workgroup: strands of consecutive routing blocks are summed per
-// expert, a scan over the strands gives each its base, and the tile map is filled by all threads (one thread per expert
-// over all blocks, and one thread for the map: the dispatch of 32768 tokens took 45 us with that, now 18).
+// expert, and a scan over the strands gives each its base (one thread per expert over all blocks: the dispatch of 32768 tokens
+// took 45 us with that, 18 so).
 constexpr int SCAN_THREADS = 1024;
 __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(int32_t* __restrict__ counts, int64_t n_blocks,
-                                                   int E, int32_t* __restrict__ tile_row0, Segments seg) {
+                                                   int E, Segments seg) {
   __shared__ int part[SCAN_THREADS];           // [strand][32 experts]
-  __shared__ int begin[33], first_tile[33];
-  __shared__ int rows_of_tile;
+  __shared__ Layout lay;
   constexpr int STRANDS = SCAN_THREADS / 32;
   const int e = threadIdx.x & 31, strand = threadIdx.x >> 5;
   const int64_t per = (n_blocks + STRANDS - 1) / STRANDS;
@@ -131,119 +199,16 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(int32_t* __restrict_
     __syncthreads();
   }
   if (threadIdx.x < 64)
-    lay_out_segments(threadIdx.x, E, part[(STRANDS - 1) * 32 + (threadIdx.x & 31)], seg, begin, first_tile, &rows_of_tile);
+    lay_out_segments(threadIdx.x, E, part[(STRANDS - 1) * 32 + (threadIdx.x & 31)], seg, lay, true);
   __syncthreads();
   if (e < E) {
-    int run = begin[e] + part[threadIdx.x] - sum;
+    int run = lay.begin[e] + part[threadIdx.x] - sum;
     for (int64_t b = b0; b < b1; ++b) {
       const int c = counts[b * E + e];
       counts[b * E + e] = run;
       run += c;
     }
   }
-  for (int i = threadIdx.x; i < seg.max_tiles; i += SCAN_THREADS) {
-    int o = -1, row = 0;
-    if (i < first_tile[E]) {
-      o = 0;
-      while (first_tile[o + 1] <= i) ++o;
-      row = begin[o] + (i - first_tile[o]) * rows_of_tile;
-    }
-    seg.tile_expert[i] = o;
-    tile_row0[i] = row;
-  }
-}
-
-// The order in which a grouped GEMM launch walks its tiles.  The launch gives every XCD a contiguous run of this
-// list; within a run, 32 consecutive entries are in flight together and share operand panels through the XCD's L2.
-// Entries are grouped per EXPERT: group_m consecutive M tiles of one expert, walked along N (all group_m tiles of
-// one N tile, then the next N tile), so that the tiles in flight share the same few weight panels; an expert's last
-// group may be smaller.  Entry = (M tile << 12) | N tile.
-// blockIdx.y: 0 the gate/up projection's table, 1 the down projection's.  The width of the tiles is decided here, from the
-// number of tiles the routing made, and noted in the table's header.
-struct OrderArgs { uint32_t* order; int n_full, n_half, group_m, k; };
-__global__ __launch_bounds__(256) void order_kernel(const int32_t* __restrict__ expert_end, int E, OrderArgs up,
-                                                    OrderArgs down) {
-  const int32_t* const expert_first = expert_end + E;
-  const OrderArgs a = blockIdx.y ? down : up;
-  __shared__ int first[33];
-  __shared__ int most;                                     // rows of one expert
-  if (threadIdx.x == 0) most = 0;
-  __syncthreads();
-  if ((int)threadIdx.x <= E) first[threadIdx.x] = expert_first[threadIdx.x];
-  if ((int)threadIdx.x < E) atomicMax(&most, expert_end[threadIdx.x] - (threadIdx.x ? expert_end[threadIdx.x - 1] : 0));
-  __syncthreads();
-  const int row_groups = gemm_row_groups(min(most, expert_end[2 * E + 1]));
-  const int64_t tiles = (int64_t)first[E] * a.n_full;
-  const bool half = half_width_pays(tiles);
-  const int n_tiles = half ? a.n_half : a.n_full;
-  const int64_t tail = tail_tiles(tiles, a.n_full, a.n_half, a.k, row_groups);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    a.order[TILE_ORDER_HALF] = half ? (uint32_t)(first[E] * a.n_half) : (uint32_t)(2 * tail);
-    a.order[TILE_ORDER_FULL] = half ? 0u : (uint32_t)(tiles - tail);
-    a.order[TILE_ORDER_ROW_GROUPS] = (uint32_t)row_groups;
-  }
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (q >= (int64_t)first[E] * n_tiles) return;
-  int e = 0;
-  while (e + 1 < E && (int64_t)first[e + 1] * n_tiles <= q) ++e;
-  const int64_t qe = q - (int64_t)first[e] * n_tiles;
-  const int c = first[e + 1] - first[e];
-  const int group_m = half ? a.group_m / 2 : a.group_m;
-  const int64_t gsz = (int64_t)group_m * n_tiles;
-  const int g = (int)(qe / gsz);
-  const int first_m = g * group_m;
-  const int gm = c - first_m < group_m ? c - first_m : group_m;
-  const int in_group = (int)(qe - g * gsz);
-  const int tn = in_group / gm, m = first_m + in_group % gm;
-  const uint32_t row = (uint32_t)(first[e] + m) << 12;
-  if (tail > 0 && q >= tiles - tail) {                     // (an odd number of half tiles along N: the last one has no columns)
-    a.order[TILE_ORDER_HEADER + 2 * q - (tiles - tail)] = row | (uint32_t)(2 * tn);
-    a.order[TILE_ORDER_HEADER + 2 * q - (tiles - tail) + 1] = row | (uint32_t)(2 * tn + 1);
-  } else {
-    a.order[TILE_ORDER_HEADER + q] = row | (uint32_t)tn;
-  }
-}
-
-__global__ __launch_bounds__(RB) void scatter_kernel(const int32_t* __restrict__ top2,
-                                                     const float* __restrict__ tw,
-                                                     const uint8_t* __restrict__ skip_mask,
-                                                     const int32_t* __restrict__ base, int64_t T,
-                                                     int E, int32_t* __restrict__ slot_token,
-                                                     float* __restrict__ slot_scale,
-                                                     int32_t* __restrict__ slot_dest,
-                                                     int32_t* __restrict__ pos) {
-  __shared__ int wave_cnt[RB / 64][32];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t t = (int64_t)blockIdx.x * RB + threadIdx.x;
-  const bool live = t < T;
-  const int e0 = live ? top2[2 * t] : -1;
-  const int e1 = (live && !skip_mask[t]) ? top2[2 * t + 1] : -1;
-  const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  int rank0 = 0, rank1 = 0;
-  for (int e = 0; e < E; ++e) {
-    const unsigned long long b0 = __ballot(e0 == e), b1 = __ballot(e1 == e);
-    const int before = __popcll(b0 & below) + __popcll(b1 & below);
-    if (e0 == e) rank0 = before;
-    if (e1 == e) rank1 = before;
-    if (lane == 0) wave_cnt[wave][e] = __popcll(b0) + __popcll(b1);
-  }
-  __syncthreads();
-  if (!live) return;
-  int p0 = base[(int64_t)blockIdx.x * E + e0] + rank0;
-  for (int w = 0; w < wave; ++w) p0 += wave_cnt[w][e0];
-  slot_token[p0] = (int32_t)t;
-  slot_scale[p0] = tw[2 * t];
-  slot_dest[p0] = e1 >= 0 ? -1 : (int32_t)t;      // a skipped token's only slot (weight 1) is the token's output
-  pos[2 * t] = p0;
-  int p1 = -1;
-  if (e1 >= 0) {
-    p1 = base[(int64_t)blockIdx.x * E + e1] + rank1;
-    for (int w = 0; w < wave; ++w) p1 += wave_cnt[w][e1];
-    slot_token[p1] = (int32_t)t;
-    slot_scale[p1] = tw[2 * t + 1];
-    slot_dest[p1] = -1;
-  }
-  pos[2 * t + 1] = p1;
 }
 
 __device__ __forceinline__ uint32_t bf16_rne(float f) {
@@ -348,33 +313,87 @@ __global__ __launch_bounds__(RB) void route_topk_kernel(const float* __restrict_
   if ((int)threadIdx.x < E) counts[(int64_t)blockIdx.x * E + threadIdx.x] = cnt[threadIdx.x];
 }
 
-template <int K>
-__global__ __launch_bounds__(RB) void scatter_topk_kernel(const int32_t* __restrict__ topk,
-                                                          const float* __restrict__ tw,
-                                                          const int32_t* __restrict__ n_used,
-                                                          const int32_t* __restrict__ base, int64_t T,
-                                                          int E, int32_t* __restrict__ slot_token,
-                                                          float* __restrict__ slot_scale,
-                                                          int32_t* __restrict__ slot_dest,
-                                                          int32_t* __restrict__ pos) {
+// Workgroups 0 .. blocks of 256 tokens - 1 place their tokens' slots, the others write the tile orders.  scanned: counts
+// holds first slots and the layout is in seg.seg_end; otherwise every workgroup adds up the counts of all blocks.
+// TOP2: the top-2 rule with its skip mask; else the generalised rule with its counts.
+template <int K, bool TOP2>
+__global__ __launch_bounds__(RB) void place_kernel(const int32_t* __restrict__ experts, const float* __restrict__ tw,
+                                                   const uint8_t* __restrict__ skip_mask, const int32_t* __restrict__ n_used,
+                                                   const int32_t* __restrict__ counts, int n_blocks, bool scanned, int64_t T, int E,
+                                                   int32_t* __restrict__ slot_token, float* __restrict__ slot_scale,
+                                                   int32_t* __restrict__ slot_dest, int32_t* __restrict__ pos,
+                                                   int32_t* __restrict__ tile_row0, Segments seg, OrderArgs up, OrderArgs down) {
+  constexpr int STRANDS = RB / 32;
+  __shared__ int total[RB], before[RB];        // [strand][32 experts]
   __shared__ int wave_cnt[RB / 64][32];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t t = (int64_t)blockIdx.x * RB + threadIdx.x;
+  __shared__ Layout lay;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int block = blockIdx.x;
+  const int e32 = tid & 31, strand = tid >> 5;
+  if (scanned) {
+    if (tid <= E) {
+      lay.begin[tid] = tid ? seg.seg_end[tid - 1] : 0;
+      lay.first_tile[tid] = seg.seg_end[E + tid];
+    }
+    if (tid == 0) {
+      int most = 0;
+      for (int e = 0, last = 0; e < E; ++e) {
+        const int end = seg.seg_end[e];
+        most = end - last > most ? end - last : most;
+        last = end;
+      }
+      lay.most_rows = most;
+      lay.rows_of_tile = seg.seg_end[2 * E + 1];
+    }
+    if (tid < E && block < n_blocks) before[tid] = counts[(int64_t)block * E + tid];
+    __syncthreads();
+  } else {
+    int all = 0, mine = 0;
+    if (e32 < E)
+#pragma unroll 4
+      for (int b = strand; b < n_blocks; b += STRANDS) {
+        const int c = counts[b * E + e32];
+        all += c;
+        mine += b < block ? c : 0;
+      }
+    total[tid] = all;
+    before[tid] = mine;
+    __syncthreads();
+    if (tid < 64) {
+      all = mine = 0;
+#pragma unroll
+      for (int s = 0; s < STRANDS; ++s) {
+        all += total[s * 32 + e32];
+        mine += before[s * 32 + e32];
+      }
+      lay_out_segments(lane, E, all, seg, lay, block == 0);
+      if (lane < E) before[lane] = lay.begin[lane] + mine;           // (lane's own entry; all sums of the wavefront are done)
+    }
+    __syncthreads();
+  }
+  write_tile_map(lay, E, seg, tile_row0, (int64_t)block * RB + tid, (int64_t)gridDim.x * RB);
+  if (block >= n_blocks) {
+    const uint32_t q = (uint32_t)(block - n_blocks) * RB + tid, step = (gridDim.x - n_blocks) * RB;
+    write_order(lay, E, up, q, step);
+    write_order(lay, E, down, q, step);
+    return;
+  }
+  const int64_t t = (int64_t)block * RB + tid;
   const bool live = t < T;
-  const int nu = live ? n_used[t] : 0;
+  const int nu = !live ? 0 : TOP2 ? (skip_mask[t] ? 1 : 2) : n_used[t];
   int es[K], rank[K];
 #pragma unroll
-  for (int m = 0; m < K; ++m) { es[m] = m < nu ? topk[t * K + m] : -1; rank[m] = 0; }
+  for (int m = 0; m < K; ++m) { es[m] = m < nu ? experts[t * K + m] : -1; rank[m] = 0; }
   const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   for (int e = 0; e < E; ++e) {             // a token routes to an expert at most once
     bool has = false;
 #pragma unroll
     for (int m = 0; m < K; ++m) has |= es[m] == e;
     const unsigned long long b = __ballot(has);
-    const int before = __popcll(b & below);
+    const int ahead = __popcll(b & below);
 #pragma unroll
     for (int m = 0; m < K; ++m)
-      if (es[m] == e) rank[m] = before;
+      if (es[m] == e) rank[m] = ahead;
     if (lane == 0) wave_cnt[wave][e] = __popcll(b);
   }
   __syncthreads();
@@ -383,7 +402,7 @@ __global__ __launch_bounds__(RB) void scatter_topk_kernel(const int32_t* __restr
   for (int m = 0; m < K; ++m) {
     int p = -1;
     if (es[m] >= 0) {
-      p = base[(int64_t)blockIdx.x * E + es[m]] + rank[m];
+      p = before[es[m]] + rank[m];
       for (int w = 0; w < wave; ++w) p += wave_cnt[w][es[m]];
       slot_token[p] = (int32_t)t;
       slot_scale[p] = tw[t * K + m];
@@ -421,19 +440,17 @@ __global__ __launch_bounds__(256) void combine_topk_kernel(const float4* __restr
 }
 
 // ---- the whole dispatch in one workgroup ----------------------------------------------------
-// route, scan and scatter for a batch that fits one workgroup (a thread per token): three launches of 4 to 5 us each,
-// all of it latency, become one.  Same outputs as the three, entry for entry.  TOP2: the top-2 rule with its skip
-// mask; else the generalised rule with its counts.  tw is not written: the weights go straight to the slots.
+// route and place for a batch that fits one workgroup (a thread per token): two launches, all of it latency, become one.
+// Same outputs as the two, entry for entry.  tw is not written: the weights go straight to the slots.
 template <int K, bool TOP2, int EMAX>
 __global__ __launch_bounds__(DISPATCH_ONE_MAX) void dispatch_one_kernel(
     const float* __restrict__ logits, int T, int E, bool vec, uint32_t kept, float theta, double beta, uint8_t* __restrict__ skip_mask,
     int32_t* __restrict__ n_used, int32_t* __restrict__ experts, int32_t* __restrict__ slot_token,
     float* __restrict__ slot_scale, int32_t* __restrict__ slot_dest, int32_t* __restrict__ pos, int32_t* __restrict__ tile_row0,
-    Segments seg) {
+    Segments seg, OrderArgs up, OrderArgs down) {
   constexpr int WAVES = DISPATCH_ONE_MAX / 64;
   __shared__ int wave_base[WAVES][32];     // counts, then first slots, of (wavefront, expert)
-  __shared__ int begin[33], first_tile[33];
-  __shared__ int rows_of_tile;
+  __shared__ Layout lay;
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const bool live = t < T;
@@ -480,24 +497,20 @@ __global__ __launch_bounds__(DISPATCH_ONE_MAX) void dispatch_one_kernel(
         wave_base[v][t] = run;
         run += c;
       }
-    lay_out_segments(t, E, run, seg, begin, first_tile, &rows_of_tile);
+    lay_out_segments(t, E, run, seg, lay, true);
   }
   __syncthreads();
-  if (t < E)
-    for (int i = first_tile[t]; i < first_tile[t + 1]; ++i) {
-      seg.tile_expert[i] = t;
-      tile_row0[i] = begin[t] + (i - first_tile[t]) * rows_of_tile;
-    }
-  for (int i = first_tile[E] + t; i < seg.max_tiles; i += blockDim.x) {
-    seg.tile_expert[i] = -1;
-    tile_row0[i] = 0;
+  write_tile_map(lay, E, seg, tile_row0, t, blockDim.x);
+  if (up.order) {
+    write_order(lay, E, up, t, blockDim.x);
+    write_order(lay, E, down, t, blockDim.x);
   }
   if (!live) return;
 #pragma unroll
   for (int m = 0; m < K; ++m) {
     int p = -1;
     if (m < used) {
-      p = begin[es[m]] + wave_base[wave][es[m]] + rank[m];
+      p = lay.begin[es[m]] + wave_base[wave][es[m]] + rank[m];
       slot_token[p] = t;
       slot_scale[p] = w[m];
       slot_dest[p] = used == 1 ? t : -1;    // a token's only slot (weight 1) is the token's output
@@ -558,18 +571,40 @@ static Segments segments(const SkipPlan& p, char* ws) {
   return s;
 }
 
-// Tile order tables of the two grouped projections (bf16 path), from the tile map scan_kernel has just written.
-static void launch_order_tables(const SkipPlan& p, char* ws, hipStream_t s) {
-  if (!p.packed || p.few) return;
-  const int32_t* expert_end = (const int32_t*)(ws + p.off_seg_end);
-  const OrderArgs up = {(uint32_t*)(ws + p.off_order_up), (int)ceil_div(p.F, gemm_tile_columns(true, false)),
-                        (int)ceil_div(p.F, gemm_tile_columns(true, true)), GEMM_GROUP_M_SWIGLU, p.H};
-  const OrderArgs down = {(uint32_t*)(ws + p.off_order_down), (int)ceil_div(p.H, gemm_tile_columns(false, false)),
-                          (int)ceil_div(p.H, gemm_tile_columns(false, true)), GEMM_GROUP_M_STORE, p.F};
-  // a thread per full-width tile of the larger table, or per half-width one of the few that half_width_pays allows
-  const int64_t n = p.max_tiles * (up.n_full > down.n_full ? up.n_full : down.n_full);
-  hipLaunchKernelGGL(order_kernel, dim3((unsigned)ceil_div(n > 512 ? n : 512, 256), 2), dim3(256), 0, s, expert_end, p.E,
-                     up, down);
+// Tile orders of the two grouped projections (bf16 path), and how many tiles of full width there can be.
+struct Orders { OrderArgs up = {}, down = {}; int64_t entries = 0; };
+static Orders orders(const SkipPlan& p, char* ws) {
+  Orders o;
+  if (!p.packed || p.few) return o;
+  o.up = {(uint32_t*)(ws + p.off_order_up), (int)ceil_div(p.F, gemm_tile_columns(true, false)),
+          (int)ceil_div(p.F, gemm_tile_columns(true, true)), GEMM_GROUP_M_SWIGLU, p.H};
+  o.down = {(uint32_t*)(ws + p.off_order_down), (int)ceil_div(p.H, gemm_tile_columns(false, false)),
+            (int)ceil_div(p.H, gemm_tile_columns(false, true)), GEMM_GROUP_M_STORE, p.F};
+  o.entries = p.max_tiles * (o.up.n_full + o.down.n_full);
+  return o;
+}
+static bool dispatch_in_one(const SkipPlan& p, const Orders& o) {
+  return p.T <= dispatch_one_tokens(p.E, p.ks) && o.entries <= DISPATCH_ONE_ORDER_MAX;
+}
+// Its threads: one per token, and more of them where there are many tiles to put in order.
+static unsigned dispatch_one_threads(const SkipPlan& p, const Orders& o) {
+  const int64_t wanted = ceil_div(p.T, 64), tiles = ceil_div(o.entries, 2 * 64), most = DISPATCH_ONE_MAX / 64;
+  return (unsigned)(64 * (wanted > tiles ? wanted : tiles < most ? tiles : most));
+}
+
+template <int K, bool TOP2>
+static void launch_place(const SkipPlan& p, const Orders& o, const int32_t* experts, const float* tw, const uint8_t* skip_mask,
+                         const int32_t* n_used, int32_t* pos, char* ws, hipStream_t s) {
+  int32_t* counts = (int32_t*)(ws + p.off_counts);
+  const int64_t n_blocks = ceil_div(p.T, RB);
+  const bool scan = n_blocks > PLACE_MAX_BLOCKS;
+  if (scan)
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, counts, n_blocks, p.E, segments(p, ws));
+  const int64_t order_blocks = ceil_div(o.entries, 2 * RB);
+  hipLaunchKernelGGL((place_kernel<K, TOP2>), dim3((unsigned)(n_blocks + order_blocks)), dim3(RB), 0, s, experts, tw, skip_mask,
+                     n_used, counts, (int)n_blocks, scan, p.T, p.E, (int32_t*)(ws + p.off_slot_token),
+                     (float*)(ws + p.off_slot_scale), (int32_t*)(ws + p.off_slot_dest), pos, (int32_t*)(ws + p.off_tile_row0),
+                     segments(p, ws), o.up, o.down);
 }
 
 int launch_skip_routing(const SkipPlan& p, const float* logits, uint32_t kept_mask, float beta, uint8_t* skip_mask,
@@ -583,17 +618,17 @@ int launch_skip_routing(const SkipPlan& p, const float* logits, uint32_t kept_ma
   const float theta = beta > 0.0f ? (float)std::log((double)beta) : -INFINITY;
   Timed t("skip_route_dispatch", s);
   const bool vec = logits_vec(logits, p.E);
-  if (T <= DISPATCH_ONE_MAX) {
+  const Orders o = orders(p, ws);
+  if (dispatch_in_one(p, o)) {
 #define MOEP_ONE(EMAX)                                                                                                   \
-  hipLaunchKernelGGL((dispatch_one_kernel<2, true, EMAX>), dim3(1), dim3((unsigned)ceil_div(T, 64) * 64), 0, s, logits,  \
+  hipLaunchKernelGGL((dispatch_one_kernel<2, true, EMAX>), dim3(1), dim3(dispatch_one_threads(p, o)), 0, s, logits,  \
                      (int)T, p.E, vec, kept_mask, theta, 0.0, skip_mask, (int32_t*)nullptr, top2,                        \
                      (int32_t*)(ws + p.off_slot_token), (float*)(ws + p.off_slot_scale),                                 \
-                     (int32_t*)(ws + p.off_slot_dest), pos, (int32_t*)(ws + p.off_tile_row0), segments(p, ws))
+                     (int32_t*)(ws + p.off_slot_dest), pos, (int32_t*)(ws + p.off_tile_row0), segments(p, ws), o.up, o.down)
     if (p.E <= 8) MOEP_ONE(8);
     else if (p.E <= 16) MOEP_ONE(16);
     else MOEP_ONE(32);
 #undef MOEP_ONE
-    launch_order_tables(p, ws, s);
     MOEP_HIP(hipGetLastError());
     return MOEP_OK;
   }
@@ -604,12 +639,7 @@ int launch_skip_routing(const SkipPlan& p, const float* logits, uint32_t kept_ma
   else if (p.E <= 16) MOEP_ROUTE(16);
   else MOEP_ROUTE(32);
 #undef MOEP_ROUTE
-  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, counts, n_blocks, p.E,
-                     (int32_t*)(ws + p.off_tile_row0), segments(p, ws));
-  launch_order_tables(p, ws, s);
-  hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)n_blocks), dim3(RB), 0, s, top2, tw, skip_mask,
-                     counts, T, p.E, (int32_t*)(ws + p.off_slot_token),
-                     (float*)(ws + p.off_slot_scale), (int32_t*)(ws + p.off_slot_dest), pos);
+  launch_place<2, true>(p, o, top2, tw, skip_mask, nullptr, pos, ws, s);
   MOEP_HIP(hipGetLastError());
   return MOEP_OK;
 }
@@ -647,11 +677,12 @@ int launch_skip_topk_routing(const SkipPlan& p, const float* logits, uint32_t ke
   int32_t* slot_dest = (int32_t*)(ws + p.off_slot_dest);
   Timed t("skip_route_dispatch", s);
   const bool vec = logits_vec(logits, p.E);
-  if (T <= DISPATCH_ONE_MAX) {
+  const Orders o = orders(p, ws);
+  if (dispatch_in_one(p, o)) {
 #define MOEP_ONE(KK, EMAX)                                                                                             \
-  hipLaunchKernelGGL((dispatch_one_kernel<KK, false, EMAX>), dim3(1), dim3((unsigned)ceil_div(T, 64) * 64), 0, s,      \
+  hipLaunchKernelGGL((dispatch_one_kernel<KK, false, EMAX>), dim3(1), dim3(dispatch_one_threads(p, o)), 0, s,      \
                      logits, (int)T, p.E, vec, kept_mask, 0.0f, (double)beta, (uint8_t*)nullptr, n_used, topk,         \
-                     slot_token, slot_scale, slot_dest, pos, (int32_t*)(ws + p.off_tile_row0), segments(p, ws))
+                     slot_token, slot_scale, slot_dest, pos, (int32_t*)(ws + p.off_tile_row0), segments(p, ws), o.up, o.down)
 #define MOEP_ONE_CASE(KK)                                                                                              \
   case KK:                                                                                                             \
     if (p.E <= 16) MOEP_ONE(KK, 16);                                                                                   \
@@ -666,7 +697,6 @@ int launch_skip_topk_routing(const SkipPlan& p, const float* logits, uint32_t ke
     }
 #undef MOEP_ONE_CASE
 #undef MOEP_ONE
-    launch_order_tables(p, ws, s);
     MOEP_HIP(hipGetLastError());
     return MOEP_OK;
   }
@@ -687,14 +717,8 @@ int launch_skip_topk_routing(const SkipPlan& p, const float* logits, uint32_t ke
   }
 #undef MOEP_ROUTE_CASE
 #undef MOEP_ROUTE
-  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, counts, n_blocks, p.E,
-                     (int32_t*)(ws + p.off_tile_row0), segments(p, ws));
-  launch_order_tables(p, ws, s);
 #define MOEP_SCATTER_CASE(KK)                                                                  \
-  case KK:                                                                                    \
-    hipLaunchKernelGGL(scatter_topk_kernel<KK>, dim3((unsigned)n_blocks), dim3(RB), 0, s, topk, tw, \
-                       n_used, counts, T, p.E, slot_token, slot_scale, slot_dest, pos);       \
-    break;
+  case KK: launch_place<KK, false>(p, o, topk, tw, nullptr, n_used, pos, ws, s); break;
   switch (K) {
     MOEP_SCATTER_CASE(1) MOEP_SCATTER_CASE(2) MOEP_SCATTER_CASE(3) MOEP_SCATTER_CASE(4)
     MOEP_SCATTER_CASE(5) MOEP_SCATTER_CASE(6) MOEP_SCATTER_CASE(7) MOEP_SCATTER_CASE(8)

@@ -351,3 +351,37 @@ def test_a_last_round_of_half_width_tiles_gives_the_same_bits(H, F, T):
     rows = Yr[slot_of.reshape(-1).long()].reshape(T, E, H)                          # [token, rank]
     want = Y.permute(1, 0, 2)[torch.arange(T, device=Y.device)[:, None], experts.long()]
     assert torch.equal(bits(rows.contiguous()), bits(want.contiguous()))
+
+
+@pytest.mark.parametrize("E,H,F,T", [
+    (8, 64, 64, 1024), (8, 64, 64, 1025),      # the largest batch of the one-workgroup dispatch, and the next
+    (32, 64, 192, 1024), (32, 64, 192, 2049),  # all experts, several routing blocks
+    (32, 64, 64, 512), (32, 64, 64, 513),      # with 32 experts
+    (8, 64, 16192, 1000), (8, 64, 16256, 1000),  # 16 tiles of 127 + 1 columns, the most entries of tile order, and more
+    (8, 64, 64, 65536), (8, 64, 64, 65537),    # the most routing blocks whose counts every workgroup adds up, and one more
+])
+def test_dispatch_gives_every_token_its_experts(E, H, F, T):
+    """Around the hand-overs of the dispatch: tokens at both ends and in the middle of the batch get the bits that they get in a
+    batch of their own, by the top-2 rule and by the generalised one, and every rank its row in the rank-limited pass."""
+    _, layer = small_layer("bf16", E, 3, H, F, T, index=34)
+    d = to_dev(layer)
+    rest = [d[n] for n in NAMES[1:]]
+    kept = (1 << E) - 1 - (2 if E > 4 else 0)
+    out, skip, lg, top = pkg.moe_forward_skip(d["x"], *rest, 0.6, kept_mask=kept)
+    out_k, used, _, experts = pkg.moe_forward_skip_topk(d["x"], *rest, 3, 0.1)
+    _, ranked, slot_of, Yr = pkg.moe_expert_outputs_ranked(d["x"], *rest, 3)
+    for t0 in (0, T // 2 - 100, T - 200):
+        part = d["x"][t0:t0 + 200].contiguous()
+        o, s, _, e = pkg.moe_forward_skip(part, *rest, 0.6, kept_mask=kept)
+        o_k, u, _, e_k = pkg.moe_forward_skip_topk(part, *rest, 3, 0.1)
+        _, Y = pkg.moe_expert_outputs(part, *rest)
+        torch.cuda.synchronize()
+        at = slice(t0, t0 + 200)
+        assert torch.equal(s, skip[at]) and torch.equal(e, top[at]) and torch.equal(u, used[at]) and torch.equal(e_k, experts[at])
+        assert torch.equal(bits(o), bits(out[at].contiguous())) and torch.equal(bits(o_k), bits(out_k[at].contiguous()))
+        rows = Yr[slot_of[at].reshape(-1).long()].reshape(200, 3, H)
+        want = Y.permute(1, 0, 2)[torch.arange(200, device=Y.device)[:, None], ranked[at].long()]
+        assert torch.equal(bits(rows.contiguous()), bits(want.contiguous()))
+    want = lg.masked_fill(~torch.tensor([bool(kept >> e & 1) for e in range(E)], device=lg.device), float("-inf"))
+    assert torch.equal(torch.argsort(want, dim=1, descending=True, stable=True)[:, :2].to(torch.int32), top)
+    assert torch.equal(torch.sort(slot_of.reshape(-1)).values, torch.arange(3 * T, dtype=torch.int32, device=lg.device))
