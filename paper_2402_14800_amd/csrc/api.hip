@@ -411,8 +411,8 @@ int prune_enumerate(const float* logits, const void* Y, int64_t T, int E, int H,
   if (!loss || !argmin || !argmin_mask) return fail(MOEP_EINVAL, "%s: NULL loss, argmin or argmin_mask", who);
   if (T > 0 && (!logits || !Y)) return fail(MOEP_EINVAL, "%s: NULL logits or Y", who);
   if (int st = check_ws(ws, ws_bytes, p.total, who)) return st;
-  return launch_enumerate(p, logits, Y, dt, loss, argmin, argmin_mask, unaffected_pairs,
-                          (char*)ws, (hipStream_t)hip_stream);
+  const EnumJob job = {p, loss, argmin, argmin_mask, unaffected_pairs};
+  return launch_enumerate(&job, 1, logits, Y, dt, (char*)ws, p.total, (hipStream_t)hip_stream);
 }
 
 // Eq. 3 as written (no Gram matrices): the alternative the Gram path is measured against.
@@ -466,16 +466,22 @@ int prune_enumerate_multi(const float* logits, const void* Y, int64_t T, int E, 
     need = p.total > need ? p.total : need;
   }
   if (int st = check_ws(ws, ws_bytes, need, who)) return st;
+  // up to RECORD_SETS of them share a Gram pass that writes their records, more share one that leaves its matrices in memory
+  EnumJob jobs[RECORD_SETS];
+  const bool together = n_r <= RECORD_SETS;
   int64_t off = 0;
   for (int i = 0; i < n_r; ++i) {
-    EnumPlan p;
-    plan_enumerate(T, E, H, k, rs[i], &p);
-    if (int st = launch_enumerate(p, logits, Y, dt, loss + off, argmin + i, argmin_mask + i,
-                                  unaffected_pairs ? unaffected_pairs + i : nullptr, (char*)ws,
-                                  (hipStream_t)hip_stream, nullptr, i > 0)) return st;
-    off += p.n_sub;
+    EnumJob& j = jobs[together ? i : 0];
+    plan_enumerate(T, E, H, k, rs[i], &j.plan);
+    j.loss = loss + off;
+    j.argmin = argmin + i;
+    j.argmin_mask = argmin_mask + i;
+    j.unaffected = unaffected_pairs ? unaffected_pairs + i : nullptr;
+    off += j.plan.n_sub;
+    if (!together)
+      if (int st = launch_enumerate_from_gram(j, logits, Y, dt, (char*)ws, (hipStream_t)hip_stream, nullptr, i > 0)) return st;
   }
-  return MOEP_OK;
+  return together ? launch_enumerate(jobs, n_r, logits, Y, dt, (char*)ws, need, (hipStream_t)hip_stream) : MOEP_OK;
 }
 
 // ------------------------------------------------------------------ moe_forward_skip
@@ -804,8 +810,8 @@ int prune_enumerate_ranked(const float* logits, const int32_t* ranked_experts, c
     return fail(MOEP_EINVAL, "%s: NULL logits, ranked_experts, slot_of or Yr", who);
   if (int st = check_ws(ws, ws_bytes, p.total, who)) return st;
   RankedSource src{slot_of, ranked_experts, n_rank};
-  return launch_enumerate(p, logits, Yr, dt, loss, argmin, argmin_mask, unaffected_pairs, (char*)ws,
-                          (hipStream_t)hip_stream, &src);
+  const EnumJob job = {p, loss, argmin, argmin_mask, unaffected_pairs};
+  return launch_enumerate(&job, 1, logits, Yr, dt, (char*)ws, p.total, (hipStream_t)hip_stream, &src);
 }
 
 }  // extern "C"

@@ -240,9 +240,18 @@ struct RankedSource {
   const int32_t* experts;
   int n_rank;
 };
-int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep_dtype dt,
-                     float* loss, int32_t* argmin, uint32_t* argmin_mask, int64_t* unaffected,
-                     char* ws, hipStream_t s, const RankedSource* ranked = nullptr, bool reuse_gram = false);
+// One r, and where its results go.
+struct EnumJob {
+  EnumPlan plan;
+  float* loss; int32_t* argmin; uint32_t* argmin_mask; int64_t* unaffected;   // unaffected may be NULL
+};
+constexpr int RECORD_SETS = 4;                             // most jobs that share a launch
+// Every job on the same logits and Y, up to RECORD_SETS of them; ws_bytes: the largest of their plans' totals.
+int launch_enumerate(const EnumJob* jobs, int n, const float* logits, const void* Y, moep_dtype dt, char* ws, size_t ws_bytes,
+                     hipStream_t s, const RankedSource* ranked = nullptr);
+// One job through Gram matrices at the start of the workspace (reuse_gram: they are there already, from another r).
+int launch_enumerate_from_gram(const EnumJob& job, const float* logits, const void* Y, moep_dtype dt, char* ws, hipStream_t s,
+                               const RankedSource* ranked, bool reuse_gram);
 
 // fp64 sum of n_tiles partial sums per subset (partial[tile * n_sub + subset]) in a fixed order -> loss; sum of the
 // partial counts (NULL: *unaffected holds it already) -> *unaffected (may be NULL; `cleared`: already 0); lowest-index argmin and its kept mask

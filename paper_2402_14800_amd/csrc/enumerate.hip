@@ -61,6 +61,20 @@ __global__ __launch_bounds__(256) void masks_kernel(int E, int r, uint32_t n_sub
   if (i < n_sub) masks[i] = unrank_device(E, r, i);
 }
 
+// ------------------------------------------------------------------ record layout
+// Per token, CAP = capacity >= n_act, all fp32 unless noted:
+//   [0, CAP)            ex_j  = exp(l_j - l_0), l in rank order (0 beyond n_act)
+//   [CAP, 2 CAP)        l_j
+//   [2 CAP, 3 CAP)      a_j   = full-layer Eq. 1 weight of rank j (0 for j >= k)
+//   [3 CAP, 3 CAP + CAP (CAP + 1) / 2)   Gram in rank order, row-major upper triangle,
+//                       diagonal as is, off-diagonal entries doubled
+//   then ceil(CAP / 4) words: expert index of rank j in byte j
+__host__ __device__ constexpr int rec_tri(int cap) { return cap * (cap + 1) / 2; }
+__host__ __device__ constexpr int rec_order_off(int cap) { return 3 * cap + rec_tri(cap); }
+__host__ __device__ constexpr int rec_size(int cap) {
+  return (rec_order_off(cap) + (cap + 3) / 4 + 3) & ~3;
+}
+
 // ------------------------------------------------------------------ Gram, bf16 (MFMA)
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -92,19 +106,46 @@ __device__ __forceinline__ uint4 load_streaming(const uint4* p) {
 // F32: rows of floats, four v_mfma_f32_16x16x4_f32 per 16-byte chunk and 16 rows (the same register as both operands again;
 // fp32 products and sums); E 8, H 512, 1501 tokens 47 -> 9 us against a wavefront per token with a shuffle tree per
 // pair of experts, which re-read every row E times.
+//
+// Records: for up to RECORD_SETS values of r the wavefront goes on to write its tokens' records itself, from the 16 x 16 products
+// in its LDS, and the Gram matrices never go to memory (recs.n = 0: they do, for the prep kernel).  The pass waits for memory
+// with 128 KB in flight on every compute unit, which covers the extra work; E 16, H 2048, 65536 tokens, two r: @GRAM@
+struct RecordArgs {
+  const float* logits;
+  int n, k;
+  struct { float* rec; unsigned long long* clear; int cap, n_act, floats; } set[RECORD_SETS];   // clear: counter to be zeroed, or NULL
+};
+__device__ __forceinline__ void wavefront_sync() {         // LDS written by other lanes of the wavefront
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <bool F32, int EPAD, bool RANKED, bool STREAM>
 __global__ __launch_bounds__(256) void gram_kernel(const uint4* __restrict__ Y,
                                                         const int32_t* __restrict__ slot_of,
                                                         const int32_t* __restrict__ experts,
                                                         float* __restrict__ G, int64_t T, int E, int n,
-                                                        int H) {
-  constexpr int TPT = 16 / EPAD;
+                                                        int H, RecordArgs recs) {
+  constexpr int TPT = 16 / EPAD, LPT = 4 * EPAD;           // tokens per tile, lanes per token
   __shared__ uint4 stage[4][16 * 64];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int64_t tile = (int64_t)blockIdx.x * 4 + wave;
   const int64_t t0 = tile * TPT;
-  if (t0 >= T) return;
+  if (blockIdx.x == 0 && threadIdx.x < RECORD_SETS && (int)threadIdx.x < recs.n && recs.set[threadIdx.x].clear)
+    *recs.set[threadIdx.x].clear = 0ull;
+  if (recs.n == 0 && t0 >= T) return;
+  // Records: what they need beside the products is made while the first rows are on their way: per token (lane lt of token tq),
+  // by rank, exp, logit, full-layer weight and row of the products, per 4 ranks the experts, and a word that stays 0; per set the
+  // place of each word's value in those (or its row and column of the triangle).
+  __shared__ uint32_t s_token[4][TPT][4 * 16 + 4 + 4];
+  __shared__ uint16_t s_word[RECORD_SETS][rec_size(EPAD)];
+  constexpr int AT_L = 16, AT_A = 32, AT_ROW = 48, AT_ORDER = 64, AT_ZERO = 68, TRIANGLE = 0x8000;
+  const int tq = lane / LPT, lt = lane % LPT;
+  const bool some = recs.n > 0 && t0 + tq < T;
+  const float logit = some && lt < E ? recs.logits[(t0 + tq) * E + lt] : 0.f;
+  const int expert = RANKED && some && lt < n ? experts[(t0 + tq) * n + lt] : 0;
   uint4* st = stage[wave];
   const int chunks = H / (F32 ? 4 : 8);                 // 16-byte chunks per row
   const int nkb = (chunks + 63) / 64;                   // blocks of 1 KB of every row
@@ -128,6 +169,72 @@ __global__ __launch_bounds__(256) void gram_kernel(const uint4* __restrict__ Y,
     v[j] = !(rvalid[j] && (kb) * 64 + lane < chunks) ? make_uint4(0, 0, 0, 0)                    \
            : STREAM ? load_streaming(&rowp[j][(kb) * 64]) : rowp[j][(kb) * 64];
   MOEP_GRAM_FETCH(0)
+  if (recs.n > 0) {
+    uint32_t* const tok = s_token[wave][tq];
+    float* const lg = (float*)st + tq * 64;                // (the stage is not in use yet)
+    int* const rank_of = (int*)lg + 16;
+    int* const place = (int*)lg + 32;                      // RANKED: expert -> its row
+    if (lt < 16) {
+      lg[lt] = logit;
+      if (RANKED) place[lt] = 0;
+    }
+    wavefront_sync();
+    if (RANKED && lt < n) place[expert] = lt;
+    if (lt < 16) {                                         // rank = experts that precede this one (as in prep_kernel)
+      int rank = 0;
+#pragma unroll
+      for (int f = 0; f < (RANKED ? 16 : EPAD); ++f) {
+        const float lf = lg[f];
+        rank += f < E && f != lt && (lf > logit || (lf == logit && f < lt)) ? 1 : 0;
+      }
+      rank_of[lt] = lt < E ? rank : 255;
+    }
+    wavefront_sync();
+    if (lt < 16) {                                         // lane = rank
+      int here = 0;
+      float l = 0.f;
+#pragma unroll
+      for (int e = 0; e < (RANKED ? 16 : EPAD); ++e)
+        if (rank_of[e] == lt) { here = e; l = lg[e]; }
+      tok[AT_L + lt] = __float_as_uint(l);
+      tok[AT_ROW + lt] = (uint32_t)(tq * EPAD + (RANKED ? place[here] : here));
+      rank_of[lt] = here;
+    }
+    wavefront_sync();
+    if (lt < 16) tok[lt] = __float_as_uint(expf(__uint_as_float(tok[AT_L + lt]) - __uint_as_float(tok[AT_L])));
+    wavefront_sync();
+    if (lt < 16) {
+      float den = 0.f;
+      for (int j = 0; j < recs.k; ++j) den += __uint_as_float(tok[j]);
+      tok[AT_A + lt] = lt < recs.k ? __float_as_uint(__uint_as_float(tok[lt]) / den) : 0u;
+      if (lt < 4) {
+        uint32_t packed = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) packed |= (uint32_t)rank_of[4 * lt + b] << (8 * b);
+        tok[AT_ORDER + lt] = packed;
+        tok[AT_ZERO + lt] = 0u;
+      }
+    }
+    for (int i = 0; i < recs.n; ++i) {
+      const int cap = recs.set[i].cap, n_act = recs.set[i].n_act, w = threadIdx.x;
+      const int order_at = rec_order_off(cap);
+      uint32_t word = AT_ZERO;
+      if (w < 3 * cap) {
+        const int which = w < cap ? 0 : w < 2 * cap ? 1 : 2, j = w - which * cap;
+        if (j < n_act) word = (uint32_t)(16 * which + j);
+      } else if (w < order_at) {
+        int j = w - 3 * cap, a = 0;                        // row a of the triangle, column a + j
+        while (j >= cap - a) { j -= cap - a; ++a; }
+        if (a + j < n_act) word = TRIANGLE | (uint32_t)(a | (a + j) << 4);
+      } else if (w < order_at + (cap + 3) / 4) {
+        const int q = w - order_at, left = n_act - 4 * q;  // experts of this word: all four, or the first ones
+        if (left > 0) word = (uint32_t)(AT_ORDER + q) | (uint32_t)(left < 4 ? left : 0) << 8;
+      }
+      if (w < recs.set[i].floats) s_word[i][w] = (uint16_t)word;
+    }
+    __syncthreads();
+    if (t0 >= T) return;
+  }
   for (int kb = 0; kb < nkb; ++kb) {
 #pragma unroll
     for (int j = 0; j < 16; ++j) st[j * 64 + (lane ^ j)] = v[j];
@@ -154,6 +261,33 @@ __global__ __launch_bounds__(256) void gram_kernel(const uint4* __restrict__ Y,
 #undef MOEP_GRAM_FETCH
   // Accumulator layout of the 16x16 tile: register v of lane l = row 4 (l / 16) + v, column l % 16.
   const int col = lane & 15;
+  if (recs.n > 0) {
+    float* const g = (float*)st;                           // the products, in the place of the stage
+    wavefront_sync();
+#pragma unroll
+    for (int vv = 0; vv < 4; ++vv) g[(4 * (lane >> 4) + vv) * 16 + col] = acc0[vv] + acc1[vv];
+    wavefront_sync();
+    if (t0 + tq >= T) return;
+    const uint32_t* const tok = s_token[wave][tq];
+    for (int i = 0; i < recs.n; ++i) {
+      const int floats = recs.set[i].floats;
+      uint32_t* const out = (uint32_t*)recs.set[i].rec + (t0 + tq) * floats;
+      for (int w = lt; w < floats; w += LPT) {
+        const uint32_t word = s_word[i][w];
+        uint32_t v;
+        if (word & TRIANGLE) {
+          const uint32_t a = word & 15u, b = (word >> 4) & 15u;
+          const float x = g[tok[AT_ROW + a] * 16 + tok[AT_ROW + b]];
+          v = __float_as_uint(a == b ? x : 2.0f * x);
+        } else {
+          v = tok[word & 0xffu];
+          if (word >> 8) v &= 0xffffffffu >> (8 * (4 - (word >> 8)));
+        }
+        out[w] = v;
+      }
+    }
+    return;
+  }
   const int cj = col % EPAD;
   const int64_t ct = t0 + col / EPAD;
   if (ct >= T || cj >= (RANKED ? n : E)) return;
@@ -299,20 +433,7 @@ __global__ __launch_bounds__(256) void gram_ranked_f32_kernel(const float* __res
     }
 }
 
-// ------------------------------------------------------------------ record layout
-// Per token, CAP = capacity >= n_act, all fp32 unless noted:
-//   [0, CAP)            ex_j  = exp(l_j - l_0), l in rank order (0 beyond n_act)
-//   [CAP, 2 CAP)        l_j
-//   [2 CAP, 3 CAP)      a_j   = full-layer Eq. 1 weight of rank j (0 for j >= k)
-//   [3 CAP, 3 CAP + CAP (CAP + 1) / 2)   Gram in rank order, row-major upper triangle,
-//                       diagonal as is, off-diagonal entries doubled
-//   then ceil(CAP / 4) words: expert index of rank j in byte j
-__host__ __device__ constexpr int rec_tri(int cap) { return cap * (cap + 1) / 2; }
-__host__ __device__ constexpr int rec_order_off(int cap) { return 3 * cap + rec_tri(cap); }
-__host__ __device__ constexpr int rec_size(int cap) {
-  return (rec_order_off(cap) + (cap + 3) / 4 + 3) & ~3;
-}
-
+// ------------------------------------------------------------------ records from Gram matrices
 // One thread per token.  STAGED: the thread builds its record in LDS (rec_floats + 1 words apart: no bank conflicts)
 // and the workgroup then writes its tokens' records, which are consecutive in memory, in 16-byte pieces; otherwise
 // (records too large for the LDS) every thread writes its own record word by word.
@@ -1148,21 +1269,34 @@ size_t fused_lds(int n_act, int rec_floats, int tg) {
 // ------------------------------------------------------------------ reduce + argmin
 __global__ __launch_bounds__(256) void zero_i64_kernel(unsigned long long* p) { *p = 0ull; }
 
+// Partial sums to be reduced: those of one r, or of several in one launch.
+struct ReduceJob {
+  const float* partial; const uint32_t* partial_cnt;      // partial_cnt NULL: counted elsewhere
+  int64_t n_tiles;
+  uint32_t n_sub, first_block;                            // first_block: of reduce_kernel
+  int S, r;                                               // S: reduce_one_kernel's subsets at a time
+  float* loss; unsigned long long* unaffected; int32_t* argmin; uint32_t* argmin_mask;
+};
+struct ReduceSet { int n; ReduceJob job[RECORD_SETS]; };
+
 // A workgroup adds the partial sums of SUBS neighbouring subsets: thread (strand, j) adds tiles strand,
 // strand + 256 / SUBS, ... of subset j in fp64, then a tree over the strands; the order depends on nothing but
 // the tile count and SUBS.  SUBS = 1 suits a handful of subsets; with thousands, SUBS = 32 reads the partial
 // sums (subset index fastest) in 128-byte runs.
 template <int SUBS>
-__global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ partial,
-                                                     const uint32_t* __restrict__ partial_cnt,
-                                                     int64_t n_tiles, uint32_t n_sub,
-                                                     float* __restrict__ loss,
-                                                     unsigned long long* unaffected) {
+__global__ __launch_bounds__(256) void reduce_kernel(ReduceSet set) {
+  int which = 0;
+  while (which + 1 < set.n && blockIdx.x >= set.job[which + 1].first_block) ++which;
+  const ReduceJob& job = set.job[which];
+  const float* __restrict__ const partial = job.partial;
+  const uint32_t* __restrict__ const partial_cnt = job.partial_cnt;
+  const int64_t n_tiles = job.n_tiles;
+  const uint32_t n_sub = job.n_sub;
   constexpr int STRANDS = 256 / SUBS;
   __shared__ double ss[256];
   __shared__ unsigned long long sc[256];
   const int j = threadIdx.x % SUBS, strand = threadIdx.x / SUBS;
-  const uint32_t sub = blockIdx.x * SUBS + j;
+  const uint32_t sub = (blockIdx.x - job.first_block) * SUBS + j;
   double s = 0.0;
   unsigned long long c = 0;
   if (sub < n_sub)
@@ -1182,14 +1316,15 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
     __syncthreads();
   }
   if (strand == 0 && sub < n_sub) {
-    loss[sub] = (float)ss[threadIdx.x];
-    if (unaffected && sc[threadIdx.x]) atomicAdd(unaffected, sc[threadIdx.x]);   // integer: order does not matter
+    job.loss[sub] = (float)ss[threadIdx.x];
+    if (job.unaffected && sc[threadIdx.x]) atomicAdd(job.unaffected, sc[threadIdx.x]);   // integer: order does not matter
   }
 }
 
-__global__ __launch_bounds__(1024) void argmin_kernel(const float* __restrict__ loss,
-                                                      uint32_t n_sub, int E, int r,
-                                                      int32_t* argmin, uint32_t* argmin_mask) {
+__global__ __launch_bounds__(1024) void argmin_kernel(ReduceSet set, int E) {
+  const ReduceJob& job = set.job[blockIdx.x];
+  const float* __restrict__ const loss = job.loss;
+  const uint32_t n_sub = job.n_sub;
   __shared__ float sv[1024];
   __shared__ uint32_t si[1024];
   float best = INFINITY;
@@ -1216,19 +1351,20 @@ __global__ __launch_bounds__(1024) void argmin_kernel(const float* __restrict__ 
   }
   if (threadIdx.x == 0) {
     const uint32_t i = si[0] == 0xffffffffu ? 0u : si[0];
-    *argmin = (int32_t)i;
-    *argmin_mask = unrank_device(E, r, i);
+    *job.argmin = (int32_t)i;
+    *job.argmin_mask = unrank_device(E, job.r, i);
   }
 }
 
-// reduce and argmin in one workgroup, for few partial sums: thread (strand, j) adds tiles strand, strand + strands, ... of
+// reduce and argmin in one workgroup per r, for few partial sums: thread (strand, j) adds tiles strand, strand + strands, ... of
 // subsets j, j + S, ... in fp64 (S = the power of two from n_sub up, at most 1024), a tree over the strands, then the
 // workgroup's argmin.  Also writes the count of unaffected pairs, so that nothing has to be cleared first.
-__global__ __launch_bounds__(1024) void reduce_one_kernel(const float* __restrict__ partial,
-                                                          const uint32_t* __restrict__ partial_cnt, int n_tiles,
-                                                          uint32_t n_sub, int S, int E, int r, float* __restrict__ loss,
-                                                          unsigned long long* __restrict__ unaffected,
-                                                          int32_t* __restrict__ argmin, uint32_t* __restrict__ argmin_mask) {
+__global__ __launch_bounds__(1024) void reduce_one_kernel(ReduceSet set, int E) {
+  const ReduceJob& job = set.job[blockIdx.x];
+  const float* __restrict__ const partial = job.partial;
+  const uint32_t* __restrict__ const partial_cnt = job.partial_cnt;
+  const int n_tiles = (int)job.n_tiles, S = job.S;
+  const uint32_t n_sub = job.n_sub;
   __shared__ double ss[1024];
   __shared__ unsigned long long sc[1024];
   __shared__ float sv[1024];
@@ -1254,7 +1390,7 @@ __global__ __launch_bounds__(1024) void reduce_one_kernel(const float* __restric
     }
     if (strand == 0 && sub < n_sub) {
       const float v = (float)ss[threadIdx.x];
-      loss[sub] = v;
+      job.loss[sub] = v;
       if (v < best || bi == 0xffffffffu) { best = v; bi = sub; }   // ascending: first minimum wins
     }
   }
@@ -1277,10 +1413,10 @@ __global__ __launch_bounds__(1024) void reduce_one_kernel(const float* __restric
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    if (unaffected) *unaffected = sc[0];
+    if (job.unaffected) *job.unaffected = sc[0];
     const uint32_t i = si[0] == 0xffffffffu ? 0u : si[0];
-    *argmin = (int32_t)i;
-    *argmin_mask = unrank_device(E, r, i);
+    *job.argmin = (int32_t)i;
+    *job.argmin_mask = unrank_device(E, job.r, i);
   }
 }
 
@@ -1405,9 +1541,143 @@ static void launch_score(const EnumPlan& p, const float* rec, float* partial, ui
 #undef MOEP_SCORE
 }
 
-int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep_dtype dt,
-                     float* loss, int32_t* argmin, uint32_t* argmin_mask, int64_t* unaffected,
-                     char* ws, hipStream_t s, const RankedSource* ranked, bool reuse_gram) {
+// Whether the Gram kernel can write the records itself: up to 16 experts, rows of whole 16-byte chunks.
+static bool gram_writes_records(const EnumPlan& p, const void* Y, moep_dtype dt) {
+  return p.E <= 16 && (dt == MOEP_BF16 || (p.H % 4 == 0 && ((uintptr_t)Y & 15) == 0));
+}
+
+// G: where the Gram matrices go; recs.n > 0: records instead.
+static int launch_gram(const EnumPlan& p, const void* Y, moep_dtype dt, float* G, const RecordArgs& recs,
+                       const RankedSource* ranked, hipStream_t s) {
+  Timed t("gram", s);
+  const unsigned per_tok_blocks = (unsigned)ceil_div(p.T, 4);
+  // streaming loads for a Y beyond half a GB
+  const bool stream = (double)p.T * (ranked ? ranked->n_rank : p.E) * p.H * 2.0 >= 512.0 * 1024 * 1024;
+#define MOEP_GRAM_LAUNCH(EPAD, RANKED, GRID, ...)                                                                  \
+  do {                                                                                                             \
+    if (dt != MOEP_BF16)                                                                                           \
+      hipLaunchKernelGGL((gram_kernel<true, EPAD, RANKED, false>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__, recs); \
+    else if (stream)                                                                                               \
+      hipLaunchKernelGGL((gram_kernel<false, EPAD, RANKED, true>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__, recs); \
+    else                                                                                                           \
+      hipLaunchKernelGGL((gram_kernel<false, EPAD, RANKED, false>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__, recs); \
+  } while (0)
+  // fp32 rows that are not whole 16-byte chunks go through the kernels that read word by word
+  const bool by_word = dt != MOEP_BF16 && (p.H % 4 || ((uintptr_t)Y & 15));
+  if (by_word && ranked)
+    hipLaunchKernelGGL(gram_ranked_f32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const float*)Y, ranked->slot_of,
+                       ranked->experts, G, p.T, p.E, ranked->n_rank, p.H);
+  else if (by_word)
+    hipLaunchKernelGGL(gram_f32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const float*)Y, G, p.T, p.E, p.H);
+  else if (ranked) {
+    const int n = ranked->n_rank;
+    if (n <= 4)
+      MOEP_GRAM_LAUNCH(4, true, (unsigned)ceil_div(p.T, 16), (const uint4*)Y, ranked->slot_of, ranked->experts, G,
+                       p.T, p.E, n, p.H);
+    else if (n <= 8)
+      MOEP_GRAM_LAUNCH(8, true, (unsigned)ceil_div(p.T, 8), (const uint4*)Y, ranked->slot_of, ranked->experts, G,
+                       p.T, p.E, n, p.H);
+    else
+      MOEP_GRAM_LAUNCH(16, true, per_tok_blocks, (const uint4*)Y, ranked->slot_of, ranked->experts, G, p.T, p.E, n,
+                       p.H);
+  } else if (p.E <= 4) {
+    MOEP_GRAM_LAUNCH(4, false, (unsigned)ceil_div(p.T, 16), (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
+  } else if (p.E <= 8) {
+    MOEP_GRAM_LAUNCH(8, false, (unsigned)ceil_div(p.T, 8), (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
+  } else if (p.E <= 16) {
+    MOEP_GRAM_LAUNCH(16, false, per_tok_blocks, (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
+  } else if (dt == MOEP_BF16) {
+    hipLaunchKernelGGL(gram_bf16_32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const uint4*)Y, G, p.T, p.E, p.H);
+  } else {
+    hipLaunchKernelGGL(gram_f32_32_kernel, dim3((unsigned)ceil_div(p.T, 2)), dim3(128), 0, s, (const uint4*)Y, G, p.T, p.E, p.H);
+  }
+#undef MOEP_GRAM_LAUNCH
+  MOEP_HIP(hipGetLastError());
+  return MOEP_OK;
+}
+
+// Partial sums of every subset's error over tiles of tokens, from the records; the tables of the scorer of more than 16 experts
+// lie where the plan has them.
+static int launch_scores(const EnumPlan& p, const float* rec, float* partial, uint32_t* pcnt, char* ws, int64_t* unaffected,
+                         hipStream_t s) {
+  const int cap = capacity_for(p.n_act);
+  if (p.fused_threads) {
+    Timed t("subset_score_tables", s);
+#define MOEP_FUSED(C, S)                                                                                               \
+  hipLaunchKernelGGL((fused_score_lut_kernel<C, S>), dim3((unsigned)p.n_tok_tiles), dim3(p.fused_threads), p.fused_lds, \
+                   s, rec, p.T, p.tok_tile, p.E, p.r, p.kk, p.k, p.n_act, p.n_combo, (uint32_t)p.n_sub, p.fused_tg,  \
+                   partial, (unsigned long long*)unaffected)
+    switch (cap * 100 + p.fused_spl) {                 // (4 active ranks: 560 subsets, 4 per lane)
+      case 404: MOEP_FUSED(4, 4); break;
+      case 604: MOEP_FUSED(6, 4); break;
+      case 614: MOEP_FUSED(6, 14); break;
+      case 804: MOEP_FUSED(8, 4); break;
+      case 814: MOEP_FUSED(8, 14); break;
+      case 1204: MOEP_FUSED(12, 4); break;
+      case 1214: MOEP_FUSED(12, 14); break;
+      default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no selection table for %d active ranks", p.n_act);
+    }
+#undef MOEP_FUSED
+    MOEP_HIP(hipGetLastError());
+  } else if (p.use_lut) {
+    Timed t("subset_score_tables", s);
+    float* qtab = (float*)(ws + p.off_qtab);
+    uint16_t* sel = (uint16_t*)(ws + p.off_sel);
+    uint16_t* selbits = (uint16_t*)(ws + p.off_selbits);
+    hipLaunchKernelGGL(selidx_kernel, dim3((unsigned)ceil_div((int64_t)1 << p.n_act, 256)), dim3(256), 0, s, p.n_act,
+                       p.kk, sel, selbits);
+    uint16_t* nibtab = (uint16_t*)(ws + p.off_nib);
+    const int nib = (p.E + 3) / 4;
+    const dim3 qgrid((unsigned)p.T), qblock(p.n_combo <= 64 ? 64 : 256);
+#define MOEP_QTABLE(C, EXACT)                                                                                     \
+  hipLaunchKernelGGL((qtable_kernel<C, EXACT>), qgrid, qblock, 0, s, rec, p.kk, p.k, p.n_act, p.n_combo, selbits, qtab, nib, nibtab)
+#define MOEP_QTABLE_CASE(C)                                                                                       \
+  case C:                                                                                                         \
+  if (p.n_act == C) MOEP_QTABLE(C, true);                                                                       \
+  else MOEP_QTABLE(C, false);                                                                                   \
+  break;
+    switch (cap) {
+      case 4: MOEP_QTABLE(4, true); break;             // (up to 3 active ranks have fewer than 512 subsets)
+      MOEP_QTABLE_CASE(6) MOEP_QTABLE_CASE(8) MOEP_QTABLE_CASE(12)
+      default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no selection table for %d active ranks", p.n_act);
+    }
+#undef MOEP_QTABLE_CASE
+#undef MOEP_QTABLE
+    const dim3 grid((unsigned)ceil_div(p.n_sub, 256 * LUT_SPL), (unsigned)p.n_tok_tiles);
+    const bool count_same = p.kk == p.k;
+#define MOEP_LUT_LAUNCH(N)                                                                                        \
+  hipLaunchKernelGGL((score_lut_kernel<N>), grid, dim3(256), 0, s, qtab, (const uint32_t*)nibtab, sel, p.T, p.tok_tile, p.E,    \
+                   p.r, p.n_act, p.n_combo, count_same, (uint32_t)p.n_sub, partial, pcnt)
+    switch (nib) {                                     // (up to 16 experts: above)
+      case 5: MOEP_LUT_LAUNCH(5); break;
+      case 6: MOEP_LUT_LAUNCH(6); break;
+      case 7: MOEP_LUT_LAUNCH(7); break;
+      case 8: MOEP_LUT_LAUNCH(8); break;
+      default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no table scorer for %d experts", p.E);
+    }
+#undef MOEP_LUT_LAUNCH
+    MOEP_HIP(hipGetLastError());
+  } else {
+    Timed t("subset_score", s);
+    switch (cap) {
+      case 2: launch_score<2>(p, rec, partial, pcnt, s); break;
+      case 4: launch_score<4>(p, rec, partial, pcnt, s); break;
+      case 6: launch_score<6>(p, rec, partial, pcnt, s); break;
+      case 8: launch_score<8>(p, rec, partial, pcnt, s); break;
+      case 12: launch_score<12>(p, rec, partial, pcnt, s); break;
+      case 16: launch_score<16>(p, rec, partial, pcnt, s); break;
+      case 32: launch_score<32>(p, rec, partial, pcnt, s); break;
+      default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no scorer for %d active ranks", p.n_act);
+    }
+    MOEP_HIP(hipGetLastError());
+  }
+  return MOEP_OK;
+}
+
+int launch_enumerate_from_gram(const EnumJob& job, const float* logits, const void* Y, moep_dtype dt, char* ws, hipStream_t s,
+                               const RankedSource* ranked, bool reuse_gram) {
+  const EnumPlan& p = job.plan;
+  int64_t* const unaffected = job.unaffected;
   float* G = (float*)(ws + p.off_gram);
   float* rec = (float*)(ws + p.off_rec);
   float* partial = (float*)(ws + p.off_partial);
@@ -1417,50 +1687,7 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
     // The Gram matrices do not depend on r: a caller that scores several r on the same logits and Y (and the same
     // workspace: G sits at its start whatever r is) computes them once.
     if (!reuse_gram) {
-      Timed t("gram", s);
-      const unsigned per_tok_blocks = (unsigned)ceil_div(p.T, 4);
-      // streaming loads for a Y beyond half a GB
-      const bool stream = (double)p.T * (ranked ? ranked->n_rank : p.E) * p.H * 2.0 >= 512.0 * 1024 * 1024;
-#define MOEP_GRAM_LAUNCH(EPAD, RANKED, GRID, ...)                                                                  \
-  do {                                                                                                             \
-    if (dt != MOEP_BF16)                                                                                           \
-      hipLaunchKernelGGL((gram_kernel<true, EPAD, RANKED, false>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__);      \
-    else if (stream)                                                                                               \
-      hipLaunchKernelGGL((gram_kernel<false, EPAD, RANKED, true>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__);      \
-    else                                                                                                           \
-      hipLaunchKernelGGL((gram_kernel<false, EPAD, RANKED, false>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__);     \
-  } while (0)
-      // fp32 rows that are not whole 16-byte chunks go through the kernels that read word by word
-      const bool by_word = dt != MOEP_BF16 && (p.H % 4 || ((uintptr_t)Y & 15));
-      if (by_word && ranked)
-        hipLaunchKernelGGL(gram_ranked_f32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const float*)Y, ranked->slot_of,
-                           ranked->experts, G, p.T, p.E, ranked->n_rank, p.H);
-      else if (by_word)
-        hipLaunchKernelGGL(gram_f32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const float*)Y, G, p.T, p.E, p.H);
-      else if (ranked) {
-        const int n = ranked->n_rank;
-        if (n <= 4)
-          MOEP_GRAM_LAUNCH(4, true, (unsigned)ceil_div(p.T, 16), (const uint4*)Y, ranked->slot_of, ranked->experts, G,
-                           p.T, p.E, n, p.H);
-        else if (n <= 8)
-          MOEP_GRAM_LAUNCH(8, true, (unsigned)ceil_div(p.T, 8), (const uint4*)Y, ranked->slot_of, ranked->experts, G,
-                           p.T, p.E, n, p.H);
-        else
-          MOEP_GRAM_LAUNCH(16, true, per_tok_blocks, (const uint4*)Y, ranked->slot_of, ranked->experts, G, p.T, p.E, n,
-                           p.H);
-      } else if (p.E <= 4) {
-        MOEP_GRAM_LAUNCH(4, false, (unsigned)ceil_div(p.T, 16), (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
-      } else if (p.E <= 8) {
-        MOEP_GRAM_LAUNCH(8, false, (unsigned)ceil_div(p.T, 8), (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
-      } else if (p.E <= 16) {
-        MOEP_GRAM_LAUNCH(16, false, per_tok_blocks, (const uint4*)Y, nullptr, nullptr, G, p.T, p.E, 0, p.H);
-      } else if (dt == MOEP_BF16) {
-        hipLaunchKernelGGL(gram_bf16_32_kernel, dim3(per_tok_blocks), dim3(256), 0, s, (const uint4*)Y, G, p.T, p.E, p.H);
-      } else {
-        hipLaunchKernelGGL(gram_f32_32_kernel, dim3((unsigned)ceil_div(p.T, 2)), dim3(128), 0, s, (const uint4*)Y, G, p.T, p.E, p.H);
-      }
-#undef MOEP_GRAM_LAUNCH
-      MOEP_HIP(hipGetLastError());
+      if (int st = launch_gram(p, Y, dt, G, RecordArgs{}, ranked, s)) return st;
     }
     {
       Timed t("routing_prep", s);
@@ -1498,109 +1725,95 @@ int launch_enumerate(const EnumPlan& p, const float* logits, const void* Y, moep
 #undef MOEP_PREP_LAUNCH
       MOEP_HIP(hipGetLastError());
     }
-    if (p.fused_threads) {
-      Timed t("subset_score_tables", s);
-#define MOEP_FUSED(C, S)                                                                                               \
-  hipLaunchKernelGGL((fused_score_lut_kernel<C, S>), dim3((unsigned)p.n_tok_tiles), dim3(p.fused_threads), p.fused_lds, \
-                     s, rec, p.T, p.tok_tile, p.E, p.r, p.kk, p.k, p.n_act, p.n_combo, (uint32_t)p.n_sub, p.fused_tg,  \
-                     partial, (unsigned long long*)unaffected)
-      switch (cap * 100 + p.fused_spl) {                 // (4 active ranks: 560 subsets, 4 per lane)
-        case 404: MOEP_FUSED(4, 4); break;
-        case 604: MOEP_FUSED(6, 4); break;
-        case 614: MOEP_FUSED(6, 14); break;
-        case 804: MOEP_FUSED(8, 4); break;
-        case 814: MOEP_FUSED(8, 14); break;
-        case 1204: MOEP_FUSED(12, 4); break;
-        case 1214: MOEP_FUSED(12, 14); break;
-        default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no selection table for %d active ranks", p.n_act);
-      }
-#undef MOEP_FUSED
-      MOEP_HIP(hipGetLastError());
-      pcnt = nullptr;                                    // counted already
-    } else if (p.use_lut) {
-      Timed t("subset_score_tables", s);
-      float* qtab = (float*)(ws + p.off_qtab);
-      uint16_t* sel = (uint16_t*)(ws + p.off_sel);
-      uint16_t* selbits = (uint16_t*)(ws + p.off_selbits);
-      hipLaunchKernelGGL(selidx_kernel, dim3((unsigned)ceil_div((int64_t)1 << p.n_act, 256)), dim3(256), 0, s, p.n_act,
-                         p.kk, sel, selbits);
-      uint16_t* nibtab = (uint16_t*)(ws + p.off_nib);
-      const int nib = (p.E + 3) / 4;
-      const dim3 qgrid((unsigned)p.T), qblock(p.n_combo <= 64 ? 64 : 256);
-#define MOEP_QTABLE(C, EXACT)                                                                                     \
-  hipLaunchKernelGGL((qtable_kernel<C, EXACT>), qgrid, qblock, 0, s, rec, p.kk, p.k, p.n_act, p.n_combo, selbits, qtab, nib, nibtab)
-#define MOEP_QTABLE_CASE(C)                                                                                       \
-  case C:                                                                                                         \
-    if (p.n_act == C) MOEP_QTABLE(C, true);                                                                       \
-    else MOEP_QTABLE(C, false);                                                                                   \
-    break;
-      switch (cap) {
-        case 4: MOEP_QTABLE(4, true); break;             // (up to 3 active ranks have fewer than 512 subsets)
-        MOEP_QTABLE_CASE(6) MOEP_QTABLE_CASE(8) MOEP_QTABLE_CASE(12)
-        default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no selection table for %d active ranks", p.n_act);
-      }
-#undef MOEP_QTABLE_CASE
-#undef MOEP_QTABLE
-      const dim3 grid((unsigned)ceil_div(p.n_sub, 256 * LUT_SPL), (unsigned)p.n_tok_tiles);
-      const bool count_same = p.kk == p.k;
-#define MOEP_LUT_LAUNCH(N)                                                                                        \
-  hipLaunchKernelGGL((score_lut_kernel<N>), grid, dim3(256), 0, s, qtab, (const uint32_t*)nibtab, sel, p.T, p.tok_tile, p.E,    \
-                     p.r, p.n_act, p.n_combo, count_same, (uint32_t)p.n_sub, partial, pcnt)
-      switch (nib) {                                     // (up to 16 experts: above)
-        case 5: MOEP_LUT_LAUNCH(5); break;
-        case 6: MOEP_LUT_LAUNCH(6); break;
-        case 7: MOEP_LUT_LAUNCH(7); break;
-        case 8: MOEP_LUT_LAUNCH(8); break;
-        default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no table scorer for %d experts", p.E);
-      }
-#undef MOEP_LUT_LAUNCH
-      MOEP_HIP(hipGetLastError());
-    } else {
-      Timed t("subset_score", s);
-      switch (cap) {
-        case 2: launch_score<2>(p, rec, partial, pcnt, s); break;
-        case 4: launch_score<4>(p, rec, partial, pcnt, s); break;
-        case 6: launch_score<6>(p, rec, partial, pcnt, s); break;
-        case 8: launch_score<8>(p, rec, partial, pcnt, s); break;
-        case 12: launch_score<12>(p, rec, partial, pcnt, s); break;
-        case 16: launch_score<16>(p, rec, partial, pcnt, s); break;
-        case 32: launch_score<32>(p, rec, partial, pcnt, s); break;
-        default: return fail(MOEP_EUNSUPPORTED, "prune_enumerate: no scorer for %d active ranks", p.n_act);
-      }
-      MOEP_HIP(hipGetLastError());
-    }
+    if (int st = launch_scores(p, rec, partial, pcnt, ws, unaffected, s)) return st;
   }
-  return launch_reduce_argmin(partial, pcnt, p.T > 0 ? p.n_tok_tiles : 0, p.n_sub, p.E, p.r, loss, argmin, argmin_mask,
-                              unaffected, p.T > 0, s);
+  return launch_reduce_argmin(partial, p.fused_threads ? nullptr : pcnt, p.T > 0 ? p.n_tok_tiles : 0, p.n_sub, p.E, p.r, job.loss,
+                              job.argmin, job.argmin_mask, unaffected, p.T > 0, s);
 }
 
 // Partial sums that one workgroup reduces as fast as three launches follow each other (28 + 70 subsets, 2048 tokens: 15 us
 // for both against 26).
 constexpr int64_t REDUCE_ONE_MAX = 32768;
 
-int launch_reduce_argmin(const float* partial, const uint32_t* pcnt, int64_t n_tiles, int64_t n_sub, int E, int r,
-                         float* loss, int32_t* argmin, uint32_t* argmin_mask, int64_t* unaffected, bool cleared,
-                         hipStream_t s) {
-  if (!pcnt) unaffected = nullptr;                       // counted elsewhere
+// `cleared`: the counters are 0 already.
+static int reduce_argmin(ReduceSet set, int E, bool cleared, hipStream_t s) {
+  int64_t all = 0, most = 0;
+  for (int i = 0; i < set.n; ++i) {
+    ReduceJob& j = set.job[i];
+    if (!j.partial_cnt) j.unaffected = nullptr;            // counted elsewhere
+    all = j.n_tiles * j.n_sub > all ? j.n_tiles * j.n_sub : all;
+    most = j.n_sub > most ? j.n_sub : most;
+  }
   Timed t("loss_reduce_argmin", s);
-  if (n_tiles * n_sub <= REDUCE_ONE_MAX && n_sub <= REDUCE_ONE_MAX) {
-    int S = 1;
-    while (S < n_sub && S < 1024) S <<= 1;
-    hipLaunchKernelGGL(reduce_one_kernel, dim3(1), dim3(1024), 0, s, partial, pcnt, (int)n_tiles, (uint32_t)n_sub, S, E, r,
-                       loss, (unsigned long long*)unaffected, argmin, argmin_mask);
+  if (all <= REDUCE_ONE_MAX && most <= REDUCE_ONE_MAX) {
+    for (int i = 0; i < set.n; ++i)
+      for (set.job[i].S = 1; set.job[i].S < set.job[i].n_sub && set.job[i].S < 1024;) set.job[i].S <<= 1;
+    hipLaunchKernelGGL(reduce_one_kernel, dim3(set.n), dim3(1024), 0, s, set, E);
     MOEP_HIP(hipGetLastError());
     return MOEP_OK;
   }
-  if (unaffected && !cleared) hipLaunchKernelGGL(zero_i64_kernel, dim3(1), dim3(1), 0, s, (unsigned long long*)unaffected);
-  if (n_sub >= 1024)
-    hipLaunchKernelGGL(reduce_kernel<32>, dim3((unsigned)ceil_div(n_sub, 32)), dim3(256), 0, s, partial, pcnt,
-                       n_tiles, (uint32_t)n_sub, loss, (unsigned long long*)unaffected);
-  else
-    hipLaunchKernelGGL(reduce_kernel<1>, dim3((unsigned)n_sub), dim3(256), 0, s, partial, pcnt, n_tiles,
-                       (uint32_t)n_sub, loss, (unsigned long long*)unaffected);
-  hipLaunchKernelGGL(argmin_kernel, dim3(1), dim3(1024), 0, s, loss, (uint32_t)n_sub, E, r, argmin, argmin_mask);
+  const int subs = most >= 1024 ? 32 : 1;
+  uint32_t blocks = 0;
+  for (int i = 0; i < set.n; ++i) {
+    ReduceJob& j = set.job[i];
+    if (j.unaffected && !cleared) hipLaunchKernelGGL(zero_i64_kernel, dim3(1), dim3(1), 0, s, j.unaffected);
+    j.first_block = blocks;
+    blocks += (uint32_t)ceil_div(j.n_sub, subs);
+  }
+  if (subs == 32) hipLaunchKernelGGL(reduce_kernel<32>, dim3(blocks), dim3(256), 0, s, set);
+  else hipLaunchKernelGGL(reduce_kernel<1>, dim3(blocks), dim3(256), 0, s, set);
+  hipLaunchKernelGGL(argmin_kernel, dim3(set.n), dim3(1024), 0, s, set, E);
   MOEP_HIP(hipGetLastError());
   return MOEP_OK;
+}
+
+int launch_reduce_argmin(const float* partial, const uint32_t* pcnt, int64_t n_tiles, int64_t n_sub, int E, int r,
+                         float* loss, int32_t* argmin, uint32_t* argmin_mask, int64_t* unaffected, bool cleared,
+                         hipStream_t s) {
+  ReduceSet set = {};
+  set.n = 1;
+  set.job[0] = {partial, pcnt, n_tiles, (uint32_t)n_sub, 0, 0, r, loss, (unsigned long long*)unaffected, argmin, argmin_mask};
+  return reduce_argmin(set, E, cleared, s);
+}
+
+int launch_enumerate(const EnumJob* jobs, int n, const float* logits, const void* Y, moep_dtype dt, char* ws, size_t ws_bytes,
+                     hipStream_t s, const RankedSource* ranked) {
+  // The Gram pass does not depend on r.  Where the records of every r, their partial sums and counts fit the workspace (which
+  // has room for Gram matrices), it writes the records itself.
+  size_t off = 0, at_rec[RECORD_SETS], at_partial[RECORD_SETS], at_cnt[RECORD_SETS];
+  auto take = [&](size_t bytes) { const size_t o = off; off += align256(bytes); return o; };
+  const EnumPlan& p0 = jobs[0].plan;
+  bool direct = p0.T > 0 && gram_writes_records(p0, Y, dt);
+  for (int i = 0; direct && i < n; ++i) {
+    const EnumPlan& p = jobs[i].plan;
+    const size_t sums = (size_t)p.n_tok_tiles * p.n_sub * sizeof(float);
+    at_rec[i] = take((size_t)p.T * p.rec_floats * sizeof(float));
+    at_partial[i] = take(sums);
+    at_cnt[i] = take(p.fused_threads ? 0 : sums);
+  }
+  if (!direct || off > ws_bytes) {
+    for (int i = 0; i < n; ++i)
+      if (int st = launch_enumerate_from_gram(jobs[i], logits, Y, dt, ws, s, ranked, i > 0)) return st;
+    return MOEP_OK;
+  }
+  RecordArgs recs = {};
+  recs.logits = logits;
+  recs.n = n;
+  recs.k = p0.k;
+  ReduceSet set = {};
+  set.n = n;
+  for (int i = 0; i < n; ++i) {
+    const EnumJob& j = jobs[i];
+    const EnumPlan& p = j.plan;
+    recs.set[i] = {(float*)(ws + at_rec[i]), (unsigned long long*)j.unaffected, capacity_for(p.n_act), p.n_act, p.rec_floats};
+    set.job[i] = {(const float*)(ws + at_partial[i]), p.fused_threads ? nullptr : (const uint32_t*)(ws + at_cnt[i]), p.n_tok_tiles,
+                  (uint32_t)p.n_sub, 0, 0, p.r, j.loss, (unsigned long long*)j.unaffected, j.argmin, j.argmin_mask};
+  }
+  if (int st = launch_gram(p0, Y, dt, nullptr, recs, ranked, s)) return st;
+  for (int i = 0; i < n; ++i)
+    if (int st = launch_scores(jobs[i].plan, recs.set[i].rec, (float*)(ws + at_partial[i]), (uint32_t*)(ws + at_cnt[i]), ws,
+                               jobs[i].unaffected, s)) return st;
+  return reduce_argmin(set, p0.E, true, s);
 }
 
 int launch_subset_masks(int E, int r, int64_t n_sub, uint32_t* masks, hipStream_t s) {

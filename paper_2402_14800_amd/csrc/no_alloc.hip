@@ -65,6 +65,6 @@ extern "C" int prune_enumerate_static(const float* logits, const void* Y, int64_
   if (int st = scratch_on_current_device(&ws)) return st;
   // Nothing in the scratch has to start at zero: the Gram, record and partial-sum kernels write every
   // element that a later kernel of the same call reads.
-  return launch_enumerate(p, logits, Y, dt, loss, argmin, argmin_mask, unaffected_pairs, ws,
-                          (hipStream_t)hip_stream);
+  const EnumJob job = {p, loss, argmin, argmin_mask, unaffected_pairs};
+  return launch_enumerate(&job, 1, logits, Y, dt, ws, p.total, (hipStream_t)hip_stream);
 }
