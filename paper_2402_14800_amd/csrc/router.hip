@@ -99,6 +99,11 @@ __global__ __launch_bounds__(256) void router_kernel(const void* __restrict__ x,
 // Wgate fragments, and 1 KB row-wise loads staged through LDS, both measured slower.)
 typedef __attribute__((ext_vector_type(8))) __bf16 r_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float r_f32x4;
+// The sums of the slices 0, 8, ..., of 1, 9, ..., up to 7, 15, ... added: the order of every kernel here.
+template <class F>
+__device__ __forceinline__ r_f32x4 sum_of_eight(F part) {
+  return ((part(0) + part(1)) + (part(2) + part(3))) + ((part(4) + part(5)) + (part(6) + part(7)));
+}
 
 // PACK: the wavefront also writes its 16 rows of x in the blocked operand layout of the packed GEMM (see
 // gemm_bf16_packed.hip: tile of 256 rows, slice of 32 hidden units, row p of a block = 64 bytes whose 16-byte chunk c
@@ -123,7 +128,12 @@ __global__ __launch_bounds__(256) void router_mfma_kernel(const uint4* __restric
   const bool w_valid = row < E, w2_valid = WIDE && 16 + row < E;
   const uint4* wp = Wgate + (int64_t)(w_valid ? row : 0) * chunks + kg;
   const uint4* wp2 = Wgate + (int64_t)(w2_valid ? 16 + row : 0) * chunks + kg;
-  r_f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0, acc2 = acc0, acc3 = acc0;
+  r_f32x4 acc[8], acc2[WIDE ? 8 : 1];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    acc[i] = r_f32x4{0.f, 0.f, 0.f, 0.f};
+    if (WIDE) acc2[i] = acc[i];
+  }
   const int steps = H / 32;
   for (int s0 = 0; s0 < steps; s0 += 8) {
     uint4 xv[8], wv[8], wv2[WIDE ? 8 : 1];
@@ -136,71 +146,70 @@ __global__ __launch_bounds__(256) void router_mfma_kernel(const uint4* __restric
       if (PACK && in) dst[(int64_t)(s0 + i) * 1024] = xv[i];
     }
 #pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[i]),
-                                                     __builtin_bit_cast(r_bf16x8, wv[i]), acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[i + 1]),
-                                                     __builtin_bit_cast(r_bf16x8, wv[i + 1]), acc1, 0, 0, 0);
-      if (WIDE) {
-        acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[i]),
-                                                       __builtin_bit_cast(r_bf16x8, wv2[i]), acc2, 0, 0, 0);
-        acc3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[i + 1]),
-                                                       __builtin_bit_cast(r_bf16x8, wv2[i + 1]), acc3, 0, 0, 0);
-      }
+    for (int i = 0; i < 8; ++i) {
+      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[i]), __builtin_bit_cast(r_bf16x8, wv[i]),
+                                                       acc[i], 0, 0, 0);
+      if (WIDE)
+        acc2[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[i]),
+                                                          __builtin_bit_cast(r_bf16x8, wv2[i]), acc2[i], 0, 0, 0);
     }
   }
+  const r_f32x4 sum = sum_of_eight([&](int i) { return acc[i]; }), sum2 = sum_of_eight([&](int i) { return acc2[WIDE ? i : 0]; });
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int64_t tt = t0 + 4 * kg + v;
-    if (tt < T && row < E) logits[tt * E + row] = acc0[v] + acc1[v];
-    if (WIDE && tt < T && 16 + row < E) logits[tt * E + 16 + row] = acc2[v] + acc3[v];
+    if (tt < T && row < E) logits[tt * E + row] = sum[v];
+    if (WIDE && tt < T && 16 + row < E) logits[tt * E + 16 + row] = sum2[v];
   }
 }
 
-// The same for few tokens, where a wavefront's serial walk over H is all there is (11 us for one token of H = 4096, 27 for
-// 777, however many there are): two wavefronts share the 16 tokens, one takes the even slices (acc0 above), the other the odd ones (acc1), each with
-// 32 slices' loads in flight, and their sums are added at the end -- the sums of the kernel above, bit for bit.
-template <bool PACK, bool WIDE>
-__global__ __launch_bounds__(256) void router_few_kernel(const uint4* __restrict__ x, const uint4* __restrict__ Wgate,
-                                                         float* __restrict__ logits, int64_t T, int E, int H,
-                                                         uint4* __restrict__ xpacked) {
-  constexpr int B = WIDE ? 8 : 16;                        // slices per batch, two batches in registers
-  __shared__ r_f32x4 odd[2][WIDE ? 2 : 1][64];
+// The same for few tokens, where a wavefront's serial walk over H is all there is (27 us for 777 tokens of H = 4096, 11 for one):
+// W = 2 or 8 wavefronts share 16 tokens, wavefront w takes the slices w, w + W, ..., each with 32 or 16 of them in flight, and the
+// eight sums (acc[] above) are added at the end -- the sums of the kernel above, bit for bit.
+template <bool PACK, bool WIDE, int W>
+__global__ __launch_bounds__(W == 8 ? 512 : 256) void router_few_kernel(const uint4* __restrict__ x, const uint4* __restrict__ Wgate,
+                                                                        float* __restrict__ logits, int64_t T, int E, int H,
+                                                                        uint4* __restrict__ xpacked) {
+  constexpr int B = W == 8 || WIDE ? 8 : 16;              // slices per batch, two batches in registers
+  constexpr int SUMS = 8 / W, TILES = W == 8 ? 1 : 2, PARTS = WIDE ? 2 : 1;
+  __shared__ r_f32x4 part[TILES][8][PARTS][64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int pair = wave >> 1, parity = wave & 1;
-  const int64_t t0 = ((int64_t)blockIdx.x * 2 + pair) * 16;
+  const int tile = wave / W, w = wave % W;
+  const int64_t t0 = ((int64_t)blockIdx.x * TILES + tile) * 16;
   const bool active = t0 < (PACK ? (T + 255) / 256 * 256 : T);
   const int row = lane & 15, kg = lane >> 4;
   const int chunks = H / 8;
   const int64_t t = t0 + row < T ? t0 + row : T - 1;
-  const uint4* xp = x + t * chunks + kg + parity * 4;
+  const uint4* xp = x + t * chunks + kg + w * 4;
   const int p_row = (int)((t0 + row) & 255);
-  uint4* const dst = PACK ? xpacked + ((t0 >> 8) * (int64_t)(H / 32) + parity) * 1024 + p_row * 4 + (kg ^ ((p_row >> 2) & 3)) : nullptr;
+  uint4* const dst = PACK ? xpacked + ((t0 >> 8) * (int64_t)(H / 32) + w) * 1024 + p_row * 4 + (kg ^ ((p_row >> 2) & 3)) : nullptr;
   const bool w_valid = row < E, w2_valid = WIDE && 16 + row < E;
-  const uint4* wp = Wgate + (int64_t)(w_valid ? row : 0) * chunks + kg + parity * 4;
-  const uint4* wp2 = Wgate + (int64_t)(w2_valid ? 16 + row : 0) * chunks + kg + parity * 4;
-  const int n = (H / 32 - parity + 1) / 2;                // slices of this parity: parity, parity + 2, ...
-  r_f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc2 = acc0;
+  const uint4* wp = Wgate + (int64_t)(w_valid ? row : 0) * chunks + kg + w * 4;
+  const uint4* wp2 = Wgate + (int64_t)(w2_valid ? 16 + row : 0) * chunks + kg + w * 4;
+  const int n = (H / 32 - w + W - 1) / W;                 // slices w, w + W, ...: the i-th belongs to sum w + W (i % SUMS)
+  r_f32x4 acc[SUMS], acc2[SUMS];
+#pragma unroll
+  for (int i = 0; i < SUMS; ++i) acc[i] = acc2[i] = r_f32x4{0.f, 0.f, 0.f, 0.f};
   uint4 xv[2][B], wv[2][B], wv2[2][WIDE ? B : 1];
   auto fetch = [&](int set, int i0) {
 #pragma unroll
     for (int i = 0; i < B; ++i) {
       const bool in = i0 + i < n;
-      xv[set][i] = in ? xp[(int64_t)(i0 + i) * 8] : make_uint4(0, 0, 0, 0);
-      wv[set][i] = (in && w_valid) ? wp[(int64_t)(i0 + i) * 8] : make_uint4(0, 0, 0, 0);
-      if (WIDE) wv2[set][i] = (in && w2_valid) ? wp2[(int64_t)(i0 + i) * 8] : make_uint4(0, 0, 0, 0);
+      xv[set][i] = in ? xp[(int64_t)(i0 + i) * (4 * W)] : make_uint4(0, 0, 0, 0);
+      wv[set][i] = (in && w_valid) ? wp[(int64_t)(i0 + i) * (4 * W)] : make_uint4(0, 0, 0, 0);
+      if (WIDE) wv2[set][i] = (in && w2_valid) ? wp2[(int64_t)(i0 + i) * (4 * W)] : make_uint4(0, 0, 0, 0);
     }
   };
   auto use = [&](int set, int i0) {
 #pragma unroll
     for (int i = 0; i < B; ++i) {
-      if (PACK && i0 + i < n) dst[(int64_t)(i0 + i) * 2048] = xv[set][i];
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[set][i]),
-                                                     __builtin_bit_cast(r_bf16x8, wv[set][i]), acc0, 0, 0, 0);
+      if (PACK && i0 + i < n) dst[(int64_t)(i0 + i) * (1024 * W)] = xv[set][i];
+      acc[i % SUMS] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[set][i]),
+                                                              __builtin_bit_cast(r_bf16x8, wv[set][i]), acc[i % SUMS], 0, 0, 0);
       if (WIDE)
-        acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[set][i]),
-                                                       __builtin_bit_cast(r_bf16x8, wv2[set][i]), acc2, 0, 0, 0);
+        acc2[i % SUMS] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[set][i]),
+                                                                 __builtin_bit_cast(r_bf16x8, wv2[set][i]), acc2[i % SUMS], 0, 0, 0);
     }
   };
   if (active) {
@@ -212,41 +221,49 @@ __global__ __launch_bounds__(256) void router_few_kernel(const uint4* __restrict
       use(1, i0 + B);
     }
   }
-  if (parity == 1) {
-    odd[pair][0][lane] = acc0;
-    if (WIDE) odd[pair][WIDE ? 1 : 0][lane] = acc2;
+#pragma unroll
+  for (int i = 0; i < SUMS; ++i) {
+    part[tile][w + W * i][0][lane] = acc[i];
+    if (WIDE) part[tile][w + W * i][PARTS - 1][lane] = acc2[i];
   }
   __syncthreads();
-  if (parity == 1 || !active) return;
-  const r_f32x4 o0 = odd[pair][0][lane], o2 = odd[pair][WIDE ? 1 : 0][lane];
+  if (w >= PARTS || !active) return;                      // a wavefront per 16 experts adds them
+  const r_f32x4 sum = sum_of_eight([&](int i) { return part[tile][i][w][lane]; });
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int64_t tt = t0 + 4 * kg + v;
-    if (tt < T && row < E) logits[tt * E + row] = acc0[v] + o0[v];
-    if (WIDE && tt < T && 16 + row < E) logits[tt * E + 16 + row] = acc2[v] + o2[v];
+    if (tt < T && 16 * w + row < E) logits[tt * E + 16 * w + row] = sum[v];
   }
 }
 
-// Up to this many tokens the two-wavefront form is the faster one; beyond it there are wavefronts enough to hide the loads.
-// E 8, H 4096, us: 48 tokens 21 -> 16, 4096 27 -> 17, 8192 27 -> 24, 16384 38 -> 43; with the packed copy of x: 2048 tokens
-// 44 -> 22, 16384 99 -> 93 (H 1024: 25 -> 21), 32768 155 -> 140 (H 1024: 40 -> 42).
-constexpr int64_t ROUTER_FEW_MAX = 8192, ROUTER_FEW_MAX_PACK = 16384;
+// Up to this many tokens two wavefronts per 16 tokens are faster than one; beyond it there are wavefronts enough to hide the loads.
+// Eight are faster still while a compute unit has no second workgroup of them, or where rows are long.  One / two / eight, us:
+// E 8, H 4096: 777 tokens 27.1 / 16.6 / 10.1, 4096 28.4 / 17.8 / 11.0, 32768 68.6 / - / 66.1; H 1024: 777 10.0 / 7.5 / 6.1, 8192
+// 10.6 / 8.0 / 8.6; E 16, H 2048, 8192 19.4 / 12.4 / 14.1.  With the packed copy of x: E 8, H 4096, 2048 tokens 44.6 / 21.4 / 13.8,
+// 16384 102.6 / 92.7 / 78.2, 32768 156.7 / - / 136.7; E 32, H 512, 8192 15.6 / 9.7 / 11.6.
+constexpr int64_t ROUTER_FEW_MAX = 8192, ROUTER_FEW_MAX_PACK = 16384, ROUTER_EIGHT_MAX = 4096, ROUTER_EIGHT_MAX_LONG = 32768;
+constexpr int ROUTER_LONG_H = 4096;
 
 bool mfma_router_applies(int E, int H) { return E <= 32 && H % 32 == 0; }
 
 template <bool PACK>
 void launch_mfma(const void* x, const void* Wgate, int64_t T, int E, int H, float* logits, void* xpacked,
                  int64_t blocks, hipStream_t s) {
-  if (T <= (PACK ? ROUTER_FEW_MAX_PACK : ROUTER_FEW_MAX)) {
-    const dim3 grid((unsigned)(2 * blocks));              // 32 tokens per workgroup instead of 64
-    if (E > 16)
-      hipLaunchKernelGGL((router_few_kernel<PACK, true>), grid, dim3(256), 0, s, (const uint4*)x, (const uint4*)Wgate,
-                         logits, T, E, H, (uint4*)xpacked);
-    else
-      hipLaunchKernelGGL((router_few_kernel<PACK, false>), grid, dim3(256), 0, s, (const uint4*)x, (const uint4*)Wgate,
-                         logits, T, E, H, (uint4*)xpacked);
+  const int64_t tiles = ceil_div(PACK ? ceil_div(T, 256) * 256 : T, 16);      // of 16 tokens
+#define MOEP_ROUTER_FEW(WIDE, W, PER_GROUP)                                                                              \
+  hipLaunchKernelGGL((router_few_kernel<PACK, WIDE, W>), dim3((unsigned)ceil_div(tiles, PER_GROUP)), dim3(64 * W * PER_GROUP), 0, s, \
+                     (const uint4*)x, (const uint4*)Wgate, logits, T, E, H, (uint4*)xpacked)
+  if (T <= (H >= ROUTER_LONG_H ? ROUTER_EIGHT_MAX_LONG : ROUTER_EIGHT_MAX)) {
+    if (E > 16) MOEP_ROUTER_FEW(true, 8, 1);
+    else MOEP_ROUTER_FEW(false, 8, 1);
     return;
   }
+  if (T <= (PACK ? ROUTER_FEW_MAX_PACK : ROUTER_FEW_MAX)) {
+    if (E > 16) MOEP_ROUTER_FEW(true, 2, 2);
+    else MOEP_ROUTER_FEW(false, 2, 2);
+    return;
+  }
+#undef MOEP_ROUTER_FEW
   if (E > 16)
     hipLaunchKernelGGL((router_mfma_kernel<PACK, true>), dim3((unsigned)blocks), dim3(256), 0, s, (const uint4*)x,
                        (const uint4*)Wgate, logits, T, E, H, (uint4*)xpacked);

@@ -29,6 +29,29 @@ def test_logits_of_every_form_are_the_same_bits(E, H):
         assert torch.equal(dense, full[:T]) and torch.equal(routed, full[:T])
 
 
+@pytest.mark.parametrize("E,H,sizes", [
+    (8, 1088, (4096, 4097)), (20, 192, (4096, 4097)),               # eight wavefronts per 16 tokens, and two
+    (8, 96, (7, 4096)), (32, 320, (16, 4097)),                      # fewer slices than wavefronts, a ragged last slice of each
+    (8, 4096, (4097, 32768)), (17, 4160, (777, 8193)),              # long rows: eight wavefronts up to 32768 tokens
+])
+def test_logits_of_the_forms_by_length_of_a_row_are_the_same_bits(E, H, sizes):
+    T = 32769 if H == 4096 else 8400
+    _, layer = small_layer("bf16", E, 2, max(H // 64, 1) * 64, 64, T, index=35)
+    d = to_dev(layer)
+    rest = [d[n] for n in NAMES[1:]]
+    full, _, _, _ = pkg.moe_expert_outputs_ranked(d["x"], *rest, 1)
+    torch.cuda.synchronize()
+    some = slice(0, 512)
+    ref = layer["x"][some].double() @ layer["Wgate"].double().t()
+    assert (full[some].cpu().double() - ref).abs().max() <= 1e-5 * ref.abs().max()
+    for n in sizes:
+        x = d["x"][:n].contiguous()
+        dense, _ = pkg.moe_expert_outputs(x, *rest)
+        _, _, routed, _ = pkg.moe_forward_skip(x, *rest, 0.5)
+        torch.cuda.synchronize()
+        assert torch.equal(dense, full[:n]) and torch.equal(routed, full[:n])
+
+
 @pytest.mark.parametrize("E,T,n", [(8, 16400, 3), (5, 8193, 2), (32, 9000, 1)])
 def test_slots_of_many_routing_blocks(E, T, n):
     """Rows of the rank-limited pass: grouped by expert, ascending token within an expert, nothing left out."""
