@@ -4,15 +4,16 @@
 //
 // Bound by the fp32 matrix rate (157 TFLOP/s nominal; 109 reached at 6000 tokens) where there are tiles for the chip, by the
 // serial walk over K where there are not.  A workgroup of 256 threads owns 64 rows x 128 accumulator columns (gate/up: 64
-// columns of either branch; few tiles: 32 x 128, then 32 x 64) and walks K in slabs of 32 through two LDS buffers: the next
-// slab is in flight in registers while the current one is multiplied, one barrier per slab (two slabs in flight: 3 %
-// slower).  The tiles are small because the layers are: a dense pass takes as many experts per launch as its scratch room
+// columns of either branch; few tiles: 32 x 128, then 32 x 64) and walks K in slabs of 32 through a ring of LDS stages that
+// direct loads fill one or two slabs ahead, one barrier per slab.  Against a slab in registers and two buffers, all experts, E 8,
+// H 512, F 1024: T = 64 164 -> 145 us, 400 226 -> 208, 1501 449 -> 441, 4000 976 -> 960; E 4, H 1024, F 3584, T = 400 514 -> 466.  The tiles are small
+// because the layers are: a dense pass takes as many experts per launch as its scratch room
 // allows for the same reason.
 // A row of a slab is 128 bytes in LDS, its 16-byte chunk c at position c ^ (row & 7), so that the fragment reads (16 rows
 // apart 128 bytes) are free of bank conflicts.  A lane reads 4 consecutive k as one 16-byte word; element j of it feeds
 // MFMA j, for both operands alike, so the four MFMAs of 16 k-values sum k = j, 4 + j, 8 + j, 12 + j.
 // Measured, all experts, E 8, H 512, F 1024, against the plain-FMA kernel with 64 x 64 tiles that this replaces: T = 64
-// 1356 -> 164 us, 1501 1369 -> 454, 6000 2284 -> 1376; E 4, H 64, F 128, T = 512: 109 -> 36 us.
+// 1356 -> 145 us, 1501 1369 -> 439, 6000 2284 -> 1376; E 4, H 64, F 128, T = 512: 109 -> 36 us.
 // A row's sum depends on K only, so a token's outputs do not depend on the batch or on the tile.
 #include "common.h"
 
@@ -34,14 +35,16 @@ struct FArgs {
   int64_t a_expert_stride, c_expert_stride;
   int N, K;
   bool c_by_word;                                          // C or C_rest is not 16-byte aligned: stored float by float
+  bool by_register;                                        // the weights are not 16-byte aligned
 };
 
-template <int EPI, int TM, int TB>    // TM = rows, TB = accumulator columns per tile
+template <int EPI, int TM, int TB, int AHEAD>    // TM = rows, TB = accumulator columns per tile; AHEAD = slabs in flight
 __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
   constexpr int RT = TM / 32, CT = TB / 32;                // 16-row and 16-column tiles of a wavefront = rows staged per thread
-  constexpr int SLAB = (TM + TB) * TK;                     // floats of one LDS buffer
+  constexpr int SLAB = (TM + TB) * TK;                     // floats of one LDS stage
+  constexpr int LOADS = (TM + TB) / 32;                    // 1 KB loads of a wavefront per slab
   constexpr int TN = EPI == EPI_SWIGLU ? TB / 2 : TB;      // output columns
-  __shared__ __attribute__((aligned(16))) float lds[2][SLAB];
+  __shared__ __attribute__((aligned(16))) float lds[AHEAD + 1][SLAB];
 
   // blockIdx.x walks TM-row sub-tiles; in grouped mode GEMM_BM / TM of them share one 256-row map entry.
   int64_t row0, row_end;
@@ -65,16 +68,15 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
 
-  // staging: a thread brings chunk (tid & 7) of rows tid / 8 + 32 i of A (i < TM / 32) and of B (i < TB / 32); rows beyond the last
-  // one repeat it (their products are not stored), chunks beyond K are zero
-  const int sr = tid >> 3, sc = tid & 7;
-  const float* ap[RT];
-  const float* bp[CT];
+  // staging: a load brings 8 rows, lane l the chunk that belongs at position l % 8 of row l / 8; wavefront w the rows 8 w .. + 7 of
+  // every 32 of A, then of B.  Rows beyond the last one repeat it (their products are not stored).
+  const int sr = tid >> 3, sc = (tid & 7) ^ (sr & 7);
+  const float* src[LOADS];
 #pragma unroll
   for (int i = 0; i < RT; ++i) {
     int64_t r = row0 + sr + 32 * i;
     if (r >= row_end) r = row_end - 1;
-    ap[i] = A + (p.a_rows ? (int64_t)p.a_rows[r] : r) * p.lda + sc * 4;
+    src[i] = A + (p.a_rows ? (int64_t)p.a_rows[r] : r) * p.lda + sc * 4;
   }
 #pragma unroll
   for (int i = 0; i < CT; ++i) {
@@ -82,22 +84,16 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
     const float* base = EPI == EPI_SWIGLU && br >= TN ? B1 : B0;
     int n = n0 + (EPI == EPI_SWIGLU ? br % TN : br);
     if (n >= p.N) n = p.N - 1;
-    bp[i] = base + (int64_t)n * p.K + sc * 4;
+    src[RT + i] = base + (int64_t)n * p.K + sc * 4;
   }
-  const int spos = sr * TK + ((sc ^ (sr & 7)) << 2);       // (rows 32 apart keep the position)
-  f32x4 ga[RT], gb[CT];
-  auto fetch = [&](int k0) {
-    const bool in = k0 + sc * 4 < p.K;                     // K is a multiple of 4
+  typedef __attribute__((address_space(3))) char lds_char;
+  lds_char* const lds3 = (lds_char*)&lds[0][0] + __builtin_amdgcn_readfirstlane(wave) * 1024;
+  const int slabs = p.by_register ? 0 : p.K / TK;          // whole ones
+  auto fetch = [&](int stage, int slab) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i) ga[i] = in ? *(const f32x4*)(ap[i] + k0) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < CT; ++i) gb[i] = in ? *(const f32x4*)(bp[i] + k0) : f32x4{0.f, 0.f, 0.f, 0.f};
-  };
-  auto put = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < RT; ++i) *(f32x4*)(&lds[buf][spos + 32 * i * TK]) = ga[i];
-#pragma unroll
-    for (int i = 0; i < CT; ++i) *(f32x4*)(&lds[buf][TM * TK + spos + 32 * i * TK]) = gb[i];
+    for (int i = 0; i < LOADS; ++i)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[i] + slab * TK),
+                                       (__attribute__((address_space(3))) void*)(lds3 + stage * (SLAB * 4) + i * 4096), 16, 0, 0);
   };
 
   const int frow = lane & 15, fg = lane >> 4;
@@ -107,13 +103,7 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
 #pragma unroll
     for (int j = 0; j < CT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const int slabs = (p.K + TK - 1) / TK;
-  fetch(0);
-  put(0);
-  __syncthreads();
-  for (int s = 0; s < slabs; ++s) {
-    if (s + 1 < slabs) fetch((s + 1) * TK);
-    const float* const buf = lds[s & 1];
+  auto multiply = [&](const float* buf) {
 #pragma unroll
     for (int h = 0; h < TK / 16; ++h) {
       const int pos = ((4 * h + fg) ^ (frow & 7)) << 2;    // (fragment rows are 16 apart: the same position in all)
@@ -133,8 +123,46 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
           for (int j = 0; j < CT; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][e], fa[i][e], acc[i][j], 0, 0, 0);
     }
-    if (s + 1 < slabs) put((s + 1) & 1);                   // (that buffer was last read before the previous barrier)
+  };
+  // Slab s + AHEAD goes into the stage of slab s - 1, which every wavefront has read when it meets the others in front of slab s.
+  // Past the last whole slab a wavefront re-reads that one (in bounds, into a stage nobody reads again), so that the loads in
+  // flight are the same in every step.
+  if (slabs > 0) {
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) fetch(s, s < slabs ? s : slabs - 1);
+    int stage = 0, next = AHEAD;
+    for (int s = 0; s < slabs; ++s) {
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int FLYING = (AHEAD - 1) * LOADS;          // of the slabs after this one
+      __builtin_amdgcn_s_waitcnt(0x0070 | (FLYING & 15) | ((FLYING >> 4) << 14));
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(next, s + AHEAD < slabs ? s + AHEAD : slabs - 1);
+      multiply(lds[stage]);
+      stage = stage == AHEAD ? 0 : stage + 1;
+      next = next == AHEAD ? 0 : next + 1;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0070);                    // the re-reads target this workgroup's LDS
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // A last slab that is not whole (K is a multiple of 4: chunks beyond it are zero), and every slab of weights that are not
+  // 16-byte aligned, goes through registers.
+  f32x4 held[LOADS];
+  auto hold = [&](int slab) {
+    const bool in = slab * TK + sc * 4 < p.K;
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) held[i] = in ? *(const f32x4*)(src[i] + slab * TK) : f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  if (slabs * TK < p.K) hold(slabs);
+  for (int s = slabs; s * TK < p.K; ++s) {
     __syncthreads();
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) *(f32x4*)(&lds[0][tid * 4 + i * 1024]) = held[i];
+    __syncthreads();
+    if ((s + 1) * TK < p.K) hold(s + 1);
+    multiply(lds[0]);
   }
 
   // Register v of lane l of tile (i, j): row 16 i + l % 16 of the wavefront's TM / 2, weight row 4 (l / 16) + v of tile j.
@@ -170,6 +198,10 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
 constexpr int64_t SMALL_TILES_BELOW = 512;
 // (the same line for half the width again: T 64 of that layer 241 -> 164 us, 400 270 -> 227, 1501 470 -> 454; at 256 tiles 464)
 constexpr int64_t NARROW_TILES_BELOW = 512;
+// From three 64-row tiles per compute unit on, one slab in flight and a third workgroup on the compute unit are worth more than
+// a second slab (E 8, H 256, F 512, top-2, T 8000 185 -> 175 us); with fewer the second slab is (E 16, H 1024, F 512, top-2, T 1501
+// 223 -> 172).
+constexpr int64_t MANY_TILES = 768;
 
 }  // namespace
 
@@ -187,6 +219,7 @@ int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name) {
   f.N = g.N; f.K = g.K;
   const bool several = g.experts > 1;      // (the *_rest operands are of no use otherwise)
   if (((uintptr_t)g.A | (several ? (uintptr_t)g.A_rest : 0)) & 15) return fail(MOEP_EUNSUPPORTED, "%s: A must be 16-byte aligned", name);
+  f.by_register = (((uintptr_t)g.B0 | (uintptr_t)g.B1) & 15) != 0;
   f.c_by_word = (((uintptr_t)g.C | (several ? (uintptr_t)g.C_rest : 0)) & 15) != 0;
   if (g.experts < 1 || g.experts > 65535 || (g.tile_expert && g.experts != 1)) return fail(MOEP_EINVAL, "%s: bad batch count %d", name, g.experts);
   auto m_tiles = [&](int tm) { return g.tile_expert ? g.max_m_tiles * (GEMM_BM / tm) : ceil_div(g.M, tm); };
@@ -194,20 +227,25 @@ int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name) {
   // 64 x 128 accumulators per tile, 32 x 128 where those are few, 32 x 64 where these are
   const int tm = m_tiles(64) * n_tiles(128) * g.experts < SMALL_TILES_BELOW ? 32 : 64;
   const int tb = tm == 32 && m_tiles(32) * n_tiles(128) * g.experts < NARROW_TILES_BELOW ? 64 : 128;
+  // (rows of a routed launch are spread over the map's tiles: counted as if they filled them)
+  const bool many = ceil_div(g.M, 64) * n_tiles(128) * g.experts >= MANY_TILES;
   if (m_tiles(tm) > 2147483647LL || n_tiles(tb) > 65535) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
   dim3 grid((unsigned)m_tiles(tm), (unsigned)n_tiles(tb), (unsigned)g.experts);
   Timed t(name, s);
+#define MOEP_F32_LAUNCH(EPI, TM, TB, AHEAD) hipLaunchKernelGGL((gemm_f32_kernel<EPI, TM, TB, AHEAD>), grid, dim3(THREADS), 0, s, f)
 #define MOEP_F32_CASE(EPI)                                                                              \
   case EPI:                                                                                             \
-    if (tb == 64) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 32, 64>), grid, dim3(THREADS), 0, s, f);       \
-    else if (tm == 32) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 32, 128>), grid, dim3(THREADS), 0, s, f); \
-    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 64, 128>), grid, dim3(THREADS), 0, s, f);               \
+    if (tb == 64) MOEP_F32_LAUNCH(EPI, 32, 64, 2);                                                      \
+    else if (tm == 32) MOEP_F32_LAUNCH(EPI, 32, 128, 2);                                                \
+    else if (many) MOEP_F32_LAUNCH(EPI, 64, 128, 1);                                                    \
+    else MOEP_F32_LAUNCH(EPI, 64, 128, 2);                                                              \
     break;
   switch (g.epilogue) {
     MOEP_F32_CASE(EPI_STORE) MOEP_F32_CASE(EPI_SWIGLU) MOEP_F32_CASE(EPI_ROWSCALE_F32)
     default: return fail(MOEP_EINVAL, "%s: unknown epilogue %d", name, g.epilogue);
   }
 #undef MOEP_F32_CASE
+#undef MOEP_F32_LAUNCH
   MOEP_HIP(hipGetLastError());
   return MOEP_OK;
 }

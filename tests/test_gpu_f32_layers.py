@@ -84,3 +84,31 @@ def test_fp32_expert_outputs_at_four_byte_alignment(E, H, F, T, offset):
     pkg.moe_expert_outputs_ranked(*ws, 2, out=(*[torch.empty_like(v) for v in ranked[:3]], part))
     torch.cuda.synchronize()
     assert torch.equal(part, ranked[3])
+
+
+@pytest.mark.parametrize("E,H,F,T", [
+    (8, 192, 128, 4000),    # 64 x 128 tiles, two slabs in flight
+    (8, 96, 100, 700),      # three slabs; three and a partly filled one
+    (4, 32, 28, 50),        # one slab, and less than one
+])
+def test_fp32_weights_of_any_alignment_give_the_same_bits(E, H, F, T):
+    """Direct loads take 16-byte aligned weights; weights that begin 4 bytes further are staged through registers."""
+    _, layer = small_layer("f32", E, 2, H, F, T, index=36)
+    d = to_dev(layer)
+
+    def shifted(w):
+        room = torch.empty(w.numel() + 1, dtype=w.dtype, device=w.device)
+        room[1:] = w.reshape(-1)
+        return room[1:].view(w.shape)
+
+    ws = [d[n] for n in NAMES]
+    odd = [d["x"], d["Wgate"], *[shifted(d[n]) for n in NAMES[2:]]]
+    assert all(w.data_ptr() % 16 == 4 for w in odd[2:])
+    _, Y = pkg.moe_expert_outputs(*ws)
+    _, Y_odd = pkg.moe_expert_outputs(*odd)
+    out, _, _, _ = pkg.moe_forward_skip(*ws, 0.5)
+    out_odd, _, _, _ = pkg.moe_forward_skip(*odd, 0.5)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, Y_odd) and torch.equal(out, out_odd)
+    _, ref = oracle.expert_outputs(*[wl.to_f64(layer[n]) for n in NAMES])
+    assert np.abs(wl.to_f64(Y) - ref).max() <= 1e-5 * np.abs(ref).max()
