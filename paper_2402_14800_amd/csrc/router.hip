@@ -37,6 +37,8 @@ struct Chunk<false> {
   }
 };
 
+__device__ __forceinline__ float pick(bool first, float a, float b) { return first ? a : b; }   // (of two values, not of two places)
+
 template <bool BF16, int EMAX>
 __global__ __launch_bounds__(256) void router_kernel(const void* __restrict__ x,
                                                      const void* __restrict__ Wgate,
@@ -64,29 +66,48 @@ __global__ __launch_bounds__(256) void router_kernel(const void* __restrict__ x,
         const int64_t t = t0 + i < T ? t0 + i : T - 1;
         C::load((const char*)x + t * row_bytes, c, xv[i]);
       }
+      // (experts beyond the last one repeat it, their sums are not stored: without a branch per expert the loads overlap)
 #pragma unroll
       for (int e = 0; e < EMAX; ++e) {
-        if (e < E) {
-          float wv[C::N];
-          C::load((const char*)Wgate + e * row_bytes, c, wv);
+        float wv[C::N];
+        C::load((const char*)Wgate + (e < E ? e : E - 1) * row_bytes, c, wv);
 #pragma unroll
-          for (int i = 0; i < TOK; ++i)
+        for (int i = 0; i < TOK; ++i)
 #pragma unroll
-            for (int j = 0; j < C::N; ++j) acc[i][e] = fmaf(xv[i][j], wv[j], acc[i][e]);
-        }
+          for (int j = 0; j < C::N; ++j) acc[i][e] = fmaf(xv[i][j], wv[j], acc[i][e]);
       }
     }
+    // Sums over the lanes, 32, 16, ..., 1 apart.  A lane keeps half of its values at each distance and gives the others away, so
+    // that TOK x EMAX of them take about as many exchanges, where a butterfly per value took six for each.  With the branches
+    // per expert gone as well: all experts of a layer, E 8, H 512, F 1024, 1501 tokens 439 -> 431 us, E 16, H 1024, F 512, 64 tokens
+    // 153 -> 137.
+    float v[TOK * EMAX];
 #pragma unroll
     for (int i = 0; i < TOK; ++i)
 #pragma unroll
-      for (int e = 0; e < EMAX; ++e) {
-        if (e < E) {
-          float v = acc[i][e];
+      for (int e = 0; e < EMAX; ++e) v[i * EMAX + e] = acc[i][e];
+    int first = 0;                                       // of the lane's values
+    constexpr int N = TOK * EMAX, HALVINGS = N >= 64 ? 6 : N >= 32 ? 5 : 4;
+    static_assert(N >= 16 && (N & (N - 1)) == 0, "values that halve");
 #pragma unroll
-          for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-          if (lane == 0 && t0 + i < T) logits[(t0 + i) * E + e] = v;
-        }
+    for (int h = 0; h < HALVINGS; ++h) {
+      const int n = N >> (h + 1), off = 32 >> h;
+      const bool upper = (lane & off) != 0;
+#pragma unroll
+      for (int i = 0; i < n; ++i) {
+        const float a = v[i], b = v[n + i];
+        v[i] = pick(upper, b, a) + __shfl_xor(pick(upper, a, b), off, 64);
       }
+      first += upper ? n : 0;
+    }
+    constexpr int LEFT = TOK * EMAX > 64 ? TOK * EMAX / 64 : 1;
+#pragma unroll
+    for (int off = 32 >> HALVINGS; off >= 1; off >>= 1) v[0] += __shfl_xor(v[0], off, 64);
+#pragma unroll
+    for (int i = 0; i < LEFT; ++i) {
+      const int token = (first + i) / EMAX, e = (first + i) % EMAX;
+      if (e < E && t0 + token < T) logits[(t0 + token) * E + e] = v[i];
+    }
   }
 }
 
