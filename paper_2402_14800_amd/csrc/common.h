@@ -126,6 +126,8 @@ constexpr int TILE_ORDER_HEADER = 4, TILE_ORDER_HALF = 0, TILE_ORDER_ROW_GROUPS 
 
 int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name);
 
+constexpr double STREAM_BYTES = 192e6;   // weights of a launch from which they are streamed past the caches
+
 // ---- bf16 GEMM on packed operands (dense expert pass) ---------------------------------
 // Operands are re-laid out once into 16 KB blocks of 256 rows x 32 k-values (the layout is described in
 // gemm_bf16_packed.hip); EPI_SWIGLU writes its result as a packed A operand with K = N.
@@ -152,6 +154,7 @@ struct PackedGemmArgs {
   // Dense batched mode: `experts` GEMMs of the same shape in one launch; expert e reads A + e a_expert_bytes
   // (0: every expert reads the same A), B + e packed_b_bytes(..), and writes C + e c_expert_bytes.
   int experts = 1;
+  int busy_experts = 1;          // grouped: experts that are expected to have rows
   int64_t a_expert_bytes = 0, c_expert_bytes = 0;
   // EPI_ROWSCALE_F32, optional: rows r with row_dest[r] >= 0 are not written to C but, rounded to bf16 and
   // unscaled (their scale is 1), to row row_dest[r] of `direct_out` (leading dimension ldc): the slots of

@@ -167,6 +167,7 @@ struct KArgs {
   int nsl;                // K / 32
   int m_tiles, n_tiles;   // dense; n_tiles: of the width the launch walks
   int half_width, row_groups;
+  bool stream;            // the weights are far more than the caches hold
   // grouped mode (rows partitioned into per-expert segments, tile t = rows tile_row0[t] .. of expert
   // tile_expert[t]; A and a packed C are indexed by TILE, a row-major C by row)
   const int32_t* tile_expert; const int32_t* tile_row0; const int32_t* seg_end; const int32_t* tiles_in_use;
@@ -191,7 +192,8 @@ __device__ unsigned long long g_round_count[8 * 8];
 
 // NG: accumulator tiles of a wavefront along N: 8, or 4 for tiles of half the width.  MG: along M: 8, or 6 or 4 for launches
 // none of whose tiles has more than 192 or 128 rows (the rows beyond are neither fetched nor multiplied).
-template <int EPI, bool GROUPED, bool BROW, int NG, int MG>
+// STREAM: the weights' loads carry the non-temporal hint.
+template <int EPI, bool GROUPED, bool BROW, int NG, int MG, bool STREAM>
 __device__ __forceinline__ void gemm_body() {
   // (the kernel's arguments, through a pointer the compiler cannot see through: it would load what all bodies use before it
   // picks one, and hold it in scalar registers that the loops need; they start the kernel-argument segment, being the only
@@ -309,17 +311,17 @@ __device__ __forceinline__ void gemm_body() {
   // loads over the step).  On packed operands, one address register pair each, plain loads are 1 % faster.
   typedef __attribute__((address_space(3))) void* lds_t;
   typedef const __attribute__((address_space(1))) void* gptr_t;
-#define MOEP_BUFFER_LOAD(base, lane_offset, offset, dst, imm)                                   \
+#define MOEP_BUFFER_LOAD(base, lane_offset, offset, dst, imm, hint)                             \
   __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)(base), 0, -1, 0x00027000), \
-      (lds_t)(lds3 + (dst)), 16, lane_offset, offset, imm, 0);
+      (lds_t)(lds3 + (dst)), 16, lane_offset, offset, imm, hint);
 #define MOEP_LOAD_A(q)                                                                          \
   if constexpr (!BROW) __builtin_amdgcn_global_load_lds((gptr_t)ga, (lds_t)(lds3 + st_ld + wave_u * (MG * 512)), 16, (q) * 1024, 0); \
-  else MOEP_BUFFER_LOAD(a_ld, lane_off, 0, st_ld + wave_u * (MG * 512), (q) * 1024)
+  else MOEP_BUFFER_LOAD(a_ld, lane_off, 0, st_ld + wave_u * (MG * 512), (q) * 1024, 0)
 #define MOEP_LOAD_B(q, unit)                                                                    \
-  if constexpr (!BROW) __builtin_amdgcn_global_load_lds((gptr_t)gb, (lds_t)(lds3 + RING + st_ld + wave_u * (NG * 512)), 16, (q) * 1024, 0); \
+  if constexpr (!BROW) __builtin_amdgcn_global_load_lds((gptr_t)gb, (lds_t)(lds3 + RING + st_ld + wave_u * (NG * 512)), 16, (q) * 1024, STREAM ? 2 : 0); \
   else MOEP_BUFFER_LOAD(b_ld + ((unit) ? (EPI == EPI_SWIGLU ? b1_branch : (int64_t)b1_rows) : 0),  \
                         (q) & 1 ? brow_odd : brow_even, (16 * ((q) & 1) + 4 * ((q) >> 1)) * pitch, \
-                        RING + st_ld + wave_u * (NG * 512) + (q) * 1024, 0)
+                        RING + st_ld + wave_u * (NG * 512) + (q) * 1024, 0, STREAM ? 2 : 0)
   // After a slice has been issued: next slice, next stage (branch-free, so that it can be scheduled into
   // the shadow of the MFMAs).  Past the end of the workgroup's stream the loader stays on its last slice:
   // the re-reads are in bounds and land in stages nobody reads again, every step issues the same loads and
@@ -669,6 +671,10 @@ __device__ __forceinline__ void gemm_body() {
 // skipping forward, Mixtral shape, median of three processes each way: T = 300 (75 rows per expert) 712 -> 598, 450 719 -> 600,
 // 777 737 -> 659; dense pass of 128 tokens 700 -> 581, of 192 707 -> 631.  They are bodies of their own: with one
 // accumulator array and a loop per height the register allocator spilled some 400 registers around the loops.
+// A launch of tiles of up to 128 rows reads every expert's weights once (an expert has one tile): where they are far more than
+// the caches hold, they come with the non-temporal hint.  Without / with, us per call, no token skipped: Mixtral shape, T = 200
+// 570 / 552 (packed 576 / 537), 400 586 / 577 (588 / 565); E 16, H 2048, F 5632, T = 300 257 / 249; dense, 64 tokens, Mixtral shape
+// 557 / 537.  Taller tiles gain nothing (T = 777 720 / 718).
 // A launch with so few tiles that compute units would stand idle walks tiles of half the width instead, 256 x 128
 // accumulator columns (64 outputs in SwiGLU mode), bits unchanged.  Half-width tiles cost well over half the time of full
 // ones (the same rows of A per step), so they only pay while they still fit one round (half_width_pays).  Grouped launches
@@ -681,9 +687,10 @@ void gemm_packed_kernel(KArgs p) {
   const bool half = GROUPED ? p.tile_order[TILE_ORDER_HALF] != 0 : p.half_width != 0;
   const uint32_t mg = GROUPED ? p.tile_order[TILE_ORDER_ROW_GROUPS] : (uint32_t)p.row_groups;
 #define MOEP_BODY(NG)                                                                           \
-  if (mg > 6) gemm_body<EPI, GROUPED, BROW, NG, 8>();                                          \
-  else if (mg > 4) gemm_body<EPI, GROUPED, BROW, NG, 6>();                                     \
-  else gemm_body<EPI, GROUPED, BROW, NG, 4>();
+  if (mg > 6) gemm_body<EPI, GROUPED, BROW, NG, 8, false>();                                   \
+  else if (mg > 4) gemm_body<EPI, GROUPED, BROW, NG, 6, false>();                              \
+  else if (p.stream) gemm_body<EPI, GROUPED, BROW, NG, 4, true>();                             \
+  else gemm_body<EPI, GROUPED, BROW, NG, 4, false>();
   if (full) { MOEP_BODY(8) }
   if (GROUPED && full && half) __builtin_amdgcn_s_barrier();   // (the ring begins anew: all have read what it held)
   if (half) { MOEP_BODY(4) }
@@ -835,6 +842,7 @@ int launch_gemm_bf16_packed(const PackedGemmArgs& g, hipStream_t s, const char* 
   if (m_tiles * n_tiles * g.experts >= ((int64_t)1 << 31)) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
   k.m_tiles = (int)m_tiles; k.n_tiles = (int)n_tiles; k.half_width = half ? 1 : 0;
   k.row_groups = gemm_row_groups(g.M);
+  k.stream = (double)g.N * g.K * 2.0 * (g.epilogue == EPI_SWIGLU ? 2.0 : 1.0) * (grouped ? g.busy_experts : g.experts) > STREAM_BYTES;
   Timed t(name, s);
 #define MOEP_GEMM_CASE(EPI, GROUPED) \
   return g.b_row_major ? launch<EPI, GROUPED, true>(k, s) : launch<EPI, GROUPED, false>(k, s)

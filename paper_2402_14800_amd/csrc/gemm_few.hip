@@ -43,7 +43,6 @@ constexpr int DEEP_WAVES = 4;                    // wavefronts per compute unit 
 // Wavefronts of a workgroup.  Four with the small ring: they read neighbouring column groups in step (16 tokens, packed: the
 // gate/up launch 290 us, 316 with workgroups of one).  One with the deep ring, so that few of them spread over the chip.
 constexpr int waves_of(int ring) { return ring == DEEP_RING ? 1 : 4; }
-constexpr double STREAM_BYTES = 192e6;   // weights of a launch from which they are streamed
 
 struct FewArgs {
   const char* W0; const char* W1;     // row-major: W0 [N,K] (gate), W1 (up); packed: W0 = blocked copy
