@@ -158,21 +158,21 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 
 def _dev(*tensors: torch.Tensor) -> torch.device:
-    d = tensors[0].device
+    index = tensors[0].get_device()                      # (an int, -1 on the host: device objects cost 0.2 us each)
     for t in tensors:
-        if t.device != d or t.device.type != "cuda":
+        if t.get_device() != index or not t.is_cuda:
             raise ValueError("all tensors must live on the same GPU")
         if not t.is_contiguous():
             raise ValueError("tensors must be contiguous (row-major)")
-    return d
+    return tensors[0].device
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()           # (every such parameter is declared c_void_p, which takes an int)
 
 
 def _stream(dev: torch.device):
-    return c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(dev.index)   # (a Stream object of torch.cuda.current_stream takes 2 us)
 
 
 def _workspace(nbytes: int, dev: torch.device, ws: Optional[torch.Tensor]) -> torch.Tensor:
@@ -315,12 +315,8 @@ def prune_enumerate_multi(logits, Y, k: int, rs, workspace=None, count_unaffecte
     ws = _workspace(need, dev, workspace)
     _check(_lib.prune_enumerate_multi(_ptr(logits), _ptr(Y), T, E, H, dt, k, len(rs), arr, _ptr(loss), _ptr(argmin),
                                       _ptr(amask), _ptr(unaffected), _ptr(ws), ws.numel(), _stream(dev)))
-    out, off = [], 0
-    for i, n in enumerate(ns):
-        out.append((loss[off:off + n], argmin[i:i + 1], amask[i:i + 1],
-                    unaffected[i:i + 1] if unaffected is not None else None))
-        off += n
-    return out
+    none = (None,) * len(rs)
+    return list(zip(loss.split(ns), argmin.split(1), amask.split(1), none if unaffected is None else unaffected.split(1)))
 
 
 def moe_expert_outputs_ranked(x, Wgate, W1, W3, W2, n_rank: int, workspace=None, out=None):
