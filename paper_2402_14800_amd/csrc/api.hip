@@ -636,8 +636,10 @@ static int forward_pruned_skip(const void* x, const void* Wgate, const void* W1,
   char* w = (char*)ws;
 
   float* logits = logits_out ? logits_out : (float*)(w + p.off_logits);
-  if (int st = launch_router(x, Wgate, T, E, H, dt, logits, s)) return st;
-  if (int st = launch_skip_routing(p, logits, kept_mask, beta, skip_mask, top2_out, w, s)) return st;
+  const bool together = routing_computes_logits(p, x, Wgate);
+  if (!together)
+    if (int st = launch_router(x, Wgate, T, E, H, dt, logits, s)) return st;
+  if (int st = launch_skip_routing(p, logits, kept_mask, beta, skip_mask, top2_out, w, s, together ? x : nullptr, Wgate)) return st;
 
   // bf16: the down projection writes the output of every token routed to a single expert itself
   void* direct = dt == MOEP_BF16 ? out : nullptr;
@@ -717,8 +719,11 @@ int moe_forward_skip_topk(const void* x, const void* Wgate, const void* W1, cons
   hipStream_t s = (hipStream_t)hip_stream;
   char* w = (char*)ws;
   float* logits = logits_out ? logits_out : (float*)(w + p.off_logits);
-  if (int st = launch_router(x, Wgate, T, E, H, dt, logits, s)) return st;
-  if (int st = launch_skip_topk_routing(p, logits, kept_mask, beta, n_used, topk_out, w, s)) return st;
+  const bool together = routing_computes_logits(p, x, Wgate);
+  if (!together)
+    if (int st = launch_router(x, Wgate, T, E, H, dt, logits, s)) return st;
+  if (int st = launch_skip_topk_routing(p, logits, kept_mask, beta, n_used, topk_out, w, s, nullptr, together ? x : nullptr, Wgate))
+    return st;
   void* direct = dt == MOEP_BF16 ? out : nullptr;
   if (int st = run_routed_ffn(p, x, W1, W3, W2, dt, w, s, nullptr, nullptr, direct)) return st;
   return launch_skip_topk_combine(p, dt, out, w, s, direct != nullptr);
@@ -784,12 +789,15 @@ int moe_expert_outputs_ranked(const void* x, const void* Wgate, const void* W1, 
   if (int st = check_ws(ws, ws_bytes, p.total, who)) return st;
   hipStream_t s = (hipStream_t)hip_stream;
   char* w = (char*)ws;
-  if (int st = launch_router(x, Wgate, T, E, H, dt, logits, s)) return st;
+  const bool together = routing_computes_logits(p, x, Wgate);
+  if (!together)
+    if (int st = launch_router(x, Wgate, T, E, H, dt, logits, s)) return st;
   const uint32_t all = E < 32 ? (1u << E) - 1u : 0xffffffffu;
   // beta = 0 keeps all n_rank experts of every token; the [T, n_rank] region of the workspace that would
   // hold the expert ids (they go to ranked_experts instead) takes the per-token counts.
   int32_t* n_used = (int32_t*)(w + p.off_pos) + (int64_t)n_rank * T;
-  if (int st = launch_skip_topk_routing(p, logits, all, 0.0f, n_used, ranked_experts, w, s, slot_of)) return st;
+  if (int st = launch_skip_topk_routing(p, logits, all, 0.0f, n_used, ranked_experts, w, s, slot_of, together ? x : nullptr, Wgate))
+    return st;
   return run_routed_ffn(p, x, W1, W3, W2, dt, w, s, Yr);
 }
 

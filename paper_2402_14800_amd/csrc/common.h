@@ -290,14 +290,17 @@ struct SkipPlan {
 };
 // kept_experts: experts that tokens can be routed to (decides the path, not the size of the workspace)
 int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_experts, SkipPlan* p, bool with_slot_out = true);
+// Whether the routing of a handful of tokens computes their logits as well, in the same launch: it is then given x and Wgate
+// (both NULL otherwise) and writes `logits`.
+bool routing_computes_logits(const SkipPlan& p, const void* x, const void* Wgate);
 int launch_skip_routing(const SkipPlan& p, const float* logits, uint32_t kept_mask, float beta, uint8_t* skip_mask,
-                        int32_t* top2_out, char* ws, hipStream_t s);
+                        int32_t* top2_out, char* ws, hipStream_t s, const void* x = nullptr, const void* Wgate = nullptr);
 // `singles_done`: tokens routed to a single expert already have their output (written by the down projection)
 int launch_skip_combine(const SkipPlan& p, moep_dtype dt, const uint8_t* skip_mask, void* out,
                         char* ws, hipStream_t s, bool singles_done);
 int launch_skip_topk_routing(const SkipPlan& p, const float* logits, uint32_t kept_mask, float beta,
                              int32_t* n_used, int32_t* topk_out, char* ws, hipStream_t s,
-                             int32_t* pos_out = nullptr);
+                             int32_t* pos_out = nullptr, const void* x = nullptr, const void* Wgate = nullptr);
 int launch_skip_topk_combine(const SkipPlan& p, moep_dtype dt, void* out, char* ws, hipStream_t s, bool singles_done);
 
 // ---- beta calibration -----------------------------------------------------------------

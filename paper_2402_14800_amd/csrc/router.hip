@@ -7,6 +7,7 @@
 // order for a token depends on nothing but H, so the same token gives the same bits in any batch
 // -- moe_expert_outputs and moe_forward_skip rely on that.
 #include "common.h"
+#include "router_few.h"
 
 namespace moep {
 namespace {
@@ -118,14 +119,6 @@ __global__ __launch_bounds__(256) void router_kernel(const void* __restrict__ x,
 // hidden units 8 (l / 16) .. + 7 of a slice; register v of lane l of the result is token 4 (l / 16) + v,
 // expert l % 16.  A token's sum depends on its own row and H only.  (Two tiles per wavefront sharing the
 // Wgate fragments, and 1 KB row-wise loads staged through LDS, both measured slower.)
-typedef __attribute__((ext_vector_type(8))) __bf16 r_bf16x8;
-typedef __attribute__((ext_vector_type(4))) float r_f32x4;
-// The sums of the slices 0, 8, ..., of 1, 9, ..., up to 7, 15, ... added: the order of every kernel here.
-template <class F>
-__device__ __forceinline__ r_f32x4 sum_of_eight(F part) {
-  return ((part(0) + part(1)) + (part(2) + part(3))) + ((part(4) + part(5)) + (part(6) + part(7)));
-}
-
 // PACK: the wavefront also writes its 16 rows of x in the blocked operand layout of the packed GEMM (see
 // gemm_bf16_packed.hip: tile of 256 rows, slice of 32 hidden units, row p of a block = 64 bytes whose 16-byte chunk c
 // sits at position c ^ ((p >> 2) & 3)) -- the registers it feeds the MFMA with are exactly one row group of a block,
@@ -184,77 +177,11 @@ __global__ __launch_bounds__(256) void router_mfma_kernel(const uint4* __restric
   }
 }
 
-// The same for few tokens, where a wavefront's serial walk over H is all there is (27 us for 777 tokens of H = 4096, 11 for one):
-// W = 2 or 8 wavefronts share 16 tokens, wavefront w takes the slices w, w + W, ..., each with 32 or 16 of them in flight, and the
-// eight sums (acc[] above) are added at the end -- the sums of the kernel above, bit for bit.
 template <bool PACK, bool WIDE, int W>
 __global__ __launch_bounds__(W == 8 ? 512 : 256) void router_few_kernel(const uint4* __restrict__ x, const uint4* __restrict__ Wgate,
                                                                         float* __restrict__ logits, int64_t T, int E, int H,
                                                                         uint4* __restrict__ xpacked) {
-  constexpr int B = W == 8 || WIDE ? 8 : 16;              // slices per batch, two batches in registers
-  constexpr int SUMS = 8 / W, TILES = W == 8 ? 1 : 2, PARTS = WIDE ? 2 : 1;
-  __shared__ r_f32x4 part[TILES][8][PARTS][64];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int tile = wave / W, w = wave % W;
-  const int64_t t0 = ((int64_t)blockIdx.x * TILES + tile) * 16;
-  const bool active = t0 < (PACK ? (T + 255) / 256 * 256 : T);
-  const int row = lane & 15, kg = lane >> 4;
-  const int chunks = H / 8;
-  const int64_t t = t0 + row < T ? t0 + row : T - 1;
-  const uint4* xp = x + t * chunks + kg + w * 4;
-  const int p_row = (int)((t0 + row) & 255);
-  uint4* const dst = PACK ? xpacked + ((t0 >> 8) * (int64_t)(H / 32) + w) * 1024 + p_row * 4 + (kg ^ ((p_row >> 2) & 3)) : nullptr;
-  const bool w_valid = row < E, w2_valid = WIDE && 16 + row < E;
-  const uint4* wp = Wgate + (int64_t)(w_valid ? row : 0) * chunks + kg + w * 4;
-  const uint4* wp2 = Wgate + (int64_t)(w2_valid ? 16 + row : 0) * chunks + kg + w * 4;
-  const int n = (H / 32 - w + W - 1) / W;                 // slices w, w + W, ...: the i-th belongs to sum w + W (i % SUMS)
-  r_f32x4 acc[SUMS], acc2[SUMS];
-#pragma unroll
-  for (int i = 0; i < SUMS; ++i) acc[i] = acc2[i] = r_f32x4{0.f, 0.f, 0.f, 0.f};
-  uint4 xv[2][B], wv[2][B], wv2[2][WIDE ? B : 1];
-  auto fetch = [&](int set, int i0) {
-#pragma unroll
-    for (int i = 0; i < B; ++i) {
-      const bool in = i0 + i < n;
-      xv[set][i] = in ? xp[(int64_t)(i0 + i) * (4 * W)] : make_uint4(0, 0, 0, 0);
-      wv[set][i] = (in && w_valid) ? wp[(int64_t)(i0 + i) * (4 * W)] : make_uint4(0, 0, 0, 0);
-      if (WIDE) wv2[set][i] = (in && w2_valid) ? wp2[(int64_t)(i0 + i) * (4 * W)] : make_uint4(0, 0, 0, 0);
-    }
-  };
-  auto use = [&](int set, int i0) {
-#pragma unroll
-    for (int i = 0; i < B; ++i) {
-      if (PACK && i0 + i < n) dst[(int64_t)(i0 + i) * (1024 * W)] = xv[set][i];
-      acc[i % SUMS] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[set][i]),
-                                                              __builtin_bit_cast(r_bf16x8, wv[set][i]), acc[i % SUMS], 0, 0, 0);
-      if (WIDE)
-        acc2[i % SUMS] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r_bf16x8, xv[set][i]),
-                                                                 __builtin_bit_cast(r_bf16x8, wv2[set][i]), acc2[i % SUMS], 0, 0, 0);
-    }
-  };
-  if (active) {
-    fetch(0, 0);
-    for (int i0 = 0; i0 < n; i0 += 2 * B) {
-      fetch(1, i0 + B);
-      use(0, i0);
-      fetch(0, i0 + 2 * B);
-      use(1, i0 + B);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < SUMS; ++i) {
-    part[tile][w + W * i][0][lane] = acc[i];
-    if (WIDE) part[tile][w + W * i][PARTS - 1][lane] = acc2[i];
-  }
-  __syncthreads();
-  if (w >= PARTS || !active) return;                      // a wavefront per 16 experts adds them
-  const r_f32x4 sum = sum_of_eight([&](int i) { return part[tile][i][w][lane]; });
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int64_t tt = t0 + 4 * kg + v;
-    if (tt < T && 16 * w + row < E) logits[tt * E + 16 * w + row] = sum[v];
-  }
+  router_few<PACK, WIDE, W>(x, Wgate, logits, T, E, H, xpacked);
 }
 
 // Up to this many tokens two wavefronts per 16 tokens are faster than one; beyond it there are wavefronts enough to hide the loads.
@@ -264,8 +191,6 @@ __global__ __launch_bounds__(W == 8 ? 512 : 256) void router_few_kernel(const ui
 // 16384 102.6 / 92.7 / 78.2, 32768 156.7 / - / 136.7; E 32, H 512, 8192 15.6 / 9.7 / 11.6.
 constexpr int64_t ROUTER_FEW_MAX = 8192, ROUTER_FEW_MAX_PACK = 16384, ROUTER_EIGHT_MAX = 4096, ROUTER_EIGHT_MAX_LONG = 32768;
 constexpr int ROUTER_LONG_H = 4096;
-
-bool mfma_router_applies(int E, int H) { return E <= 32 && H % 32 == 0; }
 
 template <bool PACK>
 void launch_mfma(const void* x, const void* Wgate, int64_t T, int E, int H, float* logits, void* xpacked,

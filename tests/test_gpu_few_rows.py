@@ -385,3 +385,27 @@ def test_dispatch_gives_every_token_its_experts(E, H, F, T):
     want = lg.masked_fill(~torch.tensor([bool(kept >> e & 1) for e in range(E)], device=lg.device), float("-inf"))
     assert torch.equal(torch.argsort(want, dim=1, descending=True, stable=True)[:, :2].to(torch.int32), top)
     assert torch.equal(torch.sort(slot_of.reshape(-1)).values, torch.arange(3 * T, dtype=torch.int32, device=lg.device))
+
+
+@pytest.mark.parametrize("E,H,T,k", [(8, 64, 1, 2), (8, 1088, 16, 2), (17, 128, 15, 2), (32, 4160, 16, 2), (16, 192, 7, 1), (20, 320, 16, 4),
+                                     (16, 64, 16, 5)])
+def test_routing_with_the_router_in_one_launch_gives_the_same_bits(E, H, T, k):
+    """Up to 16 tokens and 4 experts each are routed by the launch that computes their logits: everything as in a batch of 20."""
+    _, layer = small_layer("bf16", E, k, H, 64, 20, index=37)
+    d = to_dev(layer)
+    rest = [d[n] for n in NAMES[1:]]
+    x = d["x"][:T].contiguous()
+    all_ = pkg.moe_forward_skip_topk(d["x"], *rest, k, 0.1)
+    some = pkg.moe_forward_skip_topk(x, *rest, k, 0.1)
+    two_all = pkg.moe_forward_skip(d["x"], *rest, 0.6)
+    two = pkg.moe_forward_skip(x, *rest, 0.6, want_logits=False, want_top2=False)
+    lg, experts, slot, Yr = pkg.moe_expert_outputs_ranked(x, *rest, k)
+    _, Y = pkg.moe_expert_outputs(x, *rest)
+    torch.cuda.synchronize()
+    for a, b in zip(all_, some):
+        assert torch.equal(a[:T], b)
+    assert torch.equal(bits(two_all[0][:T].contiguous()), bits(two[0])) and torch.equal(two_all[1][:T], two[1])
+    assert torch.equal(lg, some[2]) and torch.equal(experts, some[3])
+    rows = Yr[slot.reshape(-1).long()].reshape(T, k, H)
+    want = Y.permute(1, 0, 2)[torch.arange(T, device=Y.device)[:, None], experts.long()]
+    assert torch.equal(bits(rows.contiguous()), bits(want.contiguous()))
