@@ -7,7 +7,7 @@
 // A wavefront takes 64 tokens at a time.  Each lane ranks its token's logits; one ballot per expert then gives the set of
 // tokens that selected it, and lane p adds popcount(set_i & set_j) to the pairs (i, j) it owns: E ballots and a few
 // look-ups per 64 tokens.  (Counting pairs with LDS atomics, k^2 per token into E^2 counters, took 14 to 19 us however few
-// the tokens.)  Up to ONE_MAX tokens one workgroup does everything, the kept set included, in one launch instead of three.
+// the tokens.)  Up to some hundred tokens (one_max) one workgroup does everything, the kept set included, in one launch instead of three.
 // Measured, before and after: E 8, k 2: 512 tokens 21 -> 4 us, 16384 22 -> 8 us, 262144 43 -> 28 us; E 32, 2048 78 -> 25.
 #include "common.h"
 
@@ -15,9 +15,9 @@ namespace moep {
 namespace {
 
 constexpr int SB_THREADS = 256, ONE_THREADS = 1024;
-// Most tokens of the single-workgroup form: one per thread (E 8: 512 tokens 4 us against 7 in three launches; 2048
-// tokens would take 13).
-constexpr int64_t ONE_MAX = 1024;
+// Most tokens of the single-workgroup form.  One launch / three, us: E 8, 1500 tokens 7.5 / 11.2, 2048 8.7 / 11.3, 4001 12.1 / 11.3;
+// E 16, 1024 13.8 / 15, 2048 20.2 / 15.4; E 32, 512 28 / 29, 1024 37.6 / 29.
+constexpr int64_t one_max(int emax) { return emax <= 8 ? 2048 : emax <= 16 ? 1024 : 512; }
 
 __global__ __launch_bounds__(SB_THREADS) void stats_zero_kernel(unsigned long long* count, unsigned long long* co, int E) {
   for (int i = threadIdx.x; i < E * E; i += SB_THREADS) co[i] = 0;
@@ -63,12 +63,21 @@ __global__ __launch_bounds__(ONE ? ONE_THREADS : SB_THREADS) void stats_kernel(
   }
   __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * THREADS;
-  for (int64_t t0 = (int64_t)blockIdx.x * THREADS + wave * 64; t0 < T; t0 += stride) {
+  float next[EMAX];                          // (the next tokens' logits are on their way while these are counted)
+  auto fetch = [&](int64_t t0) {
+    const int64_t t = t0 + lane < T ? t0 + lane : T - 1;
+    load_logits<EMAX>(logits, t, E, vec, next);
+  };
+  int64_t t0 = (int64_t)blockIdx.x * THREADS + wave * 64;
+  if (t0 < T) fetch(t0);
+  for (; t0 < T; t0 += stride) {
     const int64_t t = t0 + lane;
     uint32_t mask = 0;                       // expert e is in the top-k iff fewer than k experts come before it
+    float v[EMAX];
+#pragma unroll
+    for (int e = 0; e < EMAX; ++e) v[e] = next[e];
+    if (t0 + stride < T) fetch(t0 + stride);
     if (t < T) {
-      float v[EMAX];
-      load_logits<EMAX>(logits, t, E, vec, v);
 #pragma unroll
       for (int e = 0; e < EMAX; ++e) {
         int before = 0;
@@ -123,7 +132,7 @@ template <int EMAX>
 void launch(const float* logits, int64_t T, int E, int k, int r, unsigned long long* count, unsigned long long* co,
             uint32_t* mask, hipStream_t s) {
   const bool vec = logits_vec(logits, E);
-  if (T <= ONE_MAX) {
+  if (T <= one_max(EMAX)) {
     hipLaunchKernelGGL((stats_kernel<EMAX, true>), dim3(1), dim3(ONE_THREADS), 0, s, logits, T, E, vec, k, r, count, co, mask);
     return;
   }

@@ -72,3 +72,14 @@ def test_selection_statistics_at_every_form(T, E, k, offset, rounding):
     assert np.array_equal(count.cpu().numpy(), ref_count) and np.array_equal(co.cpu().numpy(), ref_co)
     order = sorted(range(E), key=lambda e: (-int(ref_count[e]), e))
     assert (int(mask.item()) & 0xFFFFFFFF) == sum(1 << e for e in order[:r])
+
+
+@pytest.mark.parametrize("T,E,k,rounding", [(2047, 8, 2, None), (2048, 5, 3, 2.0), (2049, 8, 2, None), (512, 32, 2, None), (513, 17, 4, 4.0)])
+def test_selection_statistics_around_the_one_workgroup_limit(T, E, k, rounding):
+    lg, dev = logits_on_gpu(T, E, 91 + T, 0, rounding)
+    count, co, mask = pkg.expert_selection_stats(dev, k, max(1, E // 2))
+    ref_count, ref_co = oracle.expert_selection_stats(lg, k)
+    torch.cuda.synchronize()
+    assert np.array_equal(count.cpu().numpy(), ref_count) and np.array_equal(co.cpu().numpy(), ref_co)
+    best = np.argsort(-ref_count, kind="stable")[:max(1, E // 2)]
+    assert int(mask.item()) & 0xFFFFFFFF == sum(1 << int(e) for e in best)
