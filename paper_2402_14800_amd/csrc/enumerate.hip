@@ -1732,39 +1732,42 @@ int launch_enumerate_from_gram(const EnumJob& job, const float* logits, const vo
                               job.argmin, job.argmin_mask, unaffected, p.T > 0, s);
 }
 
-// Partial sums that one workgroup reduces as fast as three launches follow each other (28 + 70 subsets, 2048 tokens: 15 us
-// for both against 26).
-constexpr int64_t REDUCE_ONE_MAX = 32768;
+// Partial sums of one r that one workgroup reduces as fast as two launches follow each other, one of them over the whole chip.
+// One / two, us: 70 subsets, 5500 tokens (12040 sums) 13.5 / -, 7000 16.1 / 10.2, 8192 18.2 / 10.0; 28 subsets, 16384 tokens (14336)
+// 12.5 / 9.7; 120 subsets, 4001 tokens 13.4 / 11.2.
+constexpr int64_t REDUCE_ONE_MAX = 12288;
 
-// `cleared`: the counters are 0 already.
-static int reduce_argmin(ReduceSet set, int E, bool cleared, hipStream_t s) {
-  int64_t all = 0, most = 0;
-  for (int i = 0; i < set.n; ++i) {
-    ReduceJob& j = set.job[i];
-    if (!j.partial_cnt) j.unaffected = nullptr;            // counted elsewhere
-    all = j.n_tiles * j.n_sub > all ? j.n_tiles * j.n_sub : all;
-    most = j.n_sub > most ? j.n_sub : most;
-  }
+// `cleared`: the counters are 0 already.  How a job is reduced depends on that job alone, so that an r gives the same bits by
+// itself and among others; jobs that are reduced alike share the launches.
+static int reduce_argmin(const ReduceSet& set, int E, bool cleared, hipStream_t s) {
   Timed t("loss_reduce_argmin", s);
-  if (all <= REDUCE_ONE_MAX && most <= REDUCE_ONE_MAX) {
-    for (int i = 0; i < set.n; ++i)
-      for (set.job[i].S = 1; set.job[i].S < set.job[i].n_sub && set.job[i].S < 1024;) set.job[i].S <<= 1;
-    hipLaunchKernelGGL(reduce_one_kernel, dim3(set.n), dim3(1024), 0, s, set, E);
+  for (int subs : {0, 1, 32}) {                            // in one workgroup; by reduce_kernel<1>, <32>
+    ReduceSet part = {};
+    uint32_t blocks = 0;
+    for (int i = 0; i < set.n; ++i) {
+      ReduceJob j = set.job[i];
+      const bool one = j.n_tiles * j.n_sub <= REDUCE_ONE_MAX && j.n_sub <= REDUCE_ONE_MAX;
+      if (subs != (one ? 0 : j.n_sub >= 1024 ? 32 : 1)) continue;
+      if (!j.partial_cnt) j.unaffected = nullptr;          // counted elsewhere
+      if (one) {
+        for (j.S = 1; j.S < (int)j.n_sub && j.S < 1024;) j.S <<= 1;
+      } else {
+        if (j.unaffected && !cleared) hipLaunchKernelGGL(zero_i64_kernel, dim3(1), dim3(1), 0, s, j.unaffected);
+        j.first_block = blocks;
+        blocks += (uint32_t)ceil_div(j.n_sub, subs);
+      }
+      part.job[part.n++] = j;
+    }
+    if (part.n == 0) continue;
+    if (subs == 0) {
+      hipLaunchKernelGGL(reduce_one_kernel, dim3(part.n), dim3(1024), 0, s, part, E);
+    } else {
+      if (subs == 32) hipLaunchKernelGGL(reduce_kernel<32>, dim3(blocks), dim3(256), 0, s, part);
+      else hipLaunchKernelGGL(reduce_kernel<1>, dim3(blocks), dim3(256), 0, s, part);
+      hipLaunchKernelGGL(argmin_kernel, dim3(part.n), dim3(1024), 0, s, part, E);
+    }
     MOEP_HIP(hipGetLastError());
-    return MOEP_OK;
   }
-  const int subs = most >= 1024 ? 32 : 1;
-  uint32_t blocks = 0;
-  for (int i = 0; i < set.n; ++i) {
-    ReduceJob& j = set.job[i];
-    if (j.unaffected && !cleared) hipLaunchKernelGGL(zero_i64_kernel, dim3(1), dim3(1), 0, s, j.unaffected);
-    j.first_block = blocks;
-    blocks += (uint32_t)ceil_div(j.n_sub, subs);
-  }
-  if (subs == 32) hipLaunchKernelGGL(reduce_kernel<32>, dim3(blocks), dim3(256), 0, s, set);
-  else hipLaunchKernelGGL(reduce_kernel<1>, dim3(blocks), dim3(256), 0, s, set);
-  hipLaunchKernelGGL(argmin_kernel, dim3(set.n), dim3(1024), 0, s, set, E);
-  MOEP_HIP(hipGetLastError());
   return MOEP_OK;
 }
 

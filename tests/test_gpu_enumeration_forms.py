@@ -109,3 +109,23 @@ def test_scoring_with_tables_in_lds(E, k, r, T, spread):
     assert (int(amask.item()) & 0xFFFFFFFF) == int(masks[int(amin.item())])
     import math
     assert int(unaff.item()) == T * math.comb(E - k, r - k)
+
+
+@pytest.mark.parametrize("E,k,rs,T", [
+    (8, 2, (6, 4), 9001),        # 28 subsets in one workgroup, 70 over the chip
+    (8, 2, (4, 6, 7, 1), 5600),  # four r, the most that share a launch
+    (8, 2, (4, 6, 7, 1, 5), 700),  # five: through Gram matrices in memory
+    (16, 4, (12, 15), 1100),     # tables for one r, records of the same pass for the other
+    (5, 2, (3,), 1),
+    (12, 3, (6, 11), 77),
+])
+def test_several_r_give_the_bits_of_each_alone(E, k, rs, T):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(7 * T + E)
+    logits = torch.randn((T, E), generator=gen, device="cuda:0")
+    Y = torch.randn((E, T, 192), generator=gen, device="cuda:0").to(torch.bfloat16)
+    parts = pkg.prune_enumerate_multi(logits, Y, k, list(rs))
+    for r, part in zip(rs, parts):
+        alone = pkg.prune_enumerate(logits, Y, k, r)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(part, alone)), r
