@@ -9,10 +9,10 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 r_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float r_f32x4;
-// The sums of the slices 0, 8, ..., of 1, 9, ..., up to 7, 15, ... added: the order of every kernel here.
+// The sums of the slices 0, 8, ..., of 1, 9, ..., up to 7, 15, ..., added four, two and one apart: the order of every kernel here.
 template <class F>
 __device__ __forceinline__ r_f32x4 sum_of_eight(F part) {
-  return ((part(0) + part(1)) + (part(2) + part(3))) + ((part(4) + part(5)) + (part(6) + part(7)));
+  return ((part(0) + part(4)) + (part(2) + part(6))) + ((part(1) + part(5)) + (part(3) + part(7)));
 }
 
 // The same for few tokens, where a wavefront's serial walk over H is all there is (27 us for 777 tokens of H = 4096, 11 for one):
