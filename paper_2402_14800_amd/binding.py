@@ -315,8 +315,12 @@ def prune_enumerate_multi(logits, Y, k: int, rs, workspace=None, count_unaffecte
     ws = _workspace(need, dev, workspace)
     _check(_lib.prune_enumerate_multi(_ptr(logits), _ptr(Y), T, E, H, dt, k, len(rs), arr, _ptr(loss), _ptr(argmin),
                                       _ptr(amask), _ptr(unaffected), _ptr(ws), ws.numel(), _stream(dev)))
-    none = (None,) * len(rs)
-    return list(zip(loss.split(ns), argmin.split(1), amask.split(1), none if unaffected is None else unaffected.split(1)))
+    out, off = [], 0
+    for i, n in enumerate(ns):                           # (slices: autograd lets a caller write into them, unlike the views of split)
+        out.append((loss[off:off + n], argmin[i:i + 1], amask[i:i + 1],
+                    unaffected[i:i + 1] if unaffected is not None else None))
+        off += n
+    return out
 
 
 def moe_expert_outputs_ranked(x, Wgate, W1, W3, W2, n_rank: int, workspace=None, out=None):

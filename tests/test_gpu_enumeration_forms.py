@@ -129,3 +129,12 @@ def test_several_r_give_the_bits_of_each_alone(E, k, rs, T):
         alone = pkg.prune_enumerate(logits, Y, k, r)
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(part, alone)), r
+
+
+def test_a_loss_of_several_r_can_be_written_under_autograd():
+    logits = torch.randn((64, 8), device="cuda:0")
+    Y = torch.randn((8, 64, 192), device="cuda:0").to(torch.bfloat16)
+    weight = torch.ones((), device="cuda:0", requires_grad=True)
+    loss = pkg.prune_enumerate_multi(logits, Y, 2, [6, 4])[0][0]
+    loss.mul_(weight)                                    # (a view of a multi-output operation would refuse this)
+    assert loss.requires_grad
