@@ -8,6 +8,7 @@
 
 #include "enum_plan.h"
 #include "moeprune.h"
+#include "skip_plan.h"
 #include "tile_plan.h"
 
 namespace moep {
@@ -126,8 +127,6 @@ constexpr int TILE_ORDER_HEADER = 4, TILE_ORDER_HALF = 0, TILE_ORDER_ROW_GROUPS 
 
 int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name);
 
-constexpr double STREAM_BYTES = 192e6;   // weights of a launch from which they are streamed past the caches
-
 // ---- bf16 GEMM on packed operands (dense expert pass) ---------------------------------
 // Operands are re-laid out once into 16 KB blocks of 256 rows x 32 k-values (the layout is described in
 // gemm_bf16_packed.hip); EPI_SWIGLU writes its result as a packed A operand with K = N.
@@ -154,7 +153,7 @@ struct PackedGemmArgs {
   // Dense batched mode: `experts` GEMMs of the same shape in one launch; expert e reads A + e a_expert_bytes
   // (0: every expert reads the same A), B + e packed_b_bytes(..), and writes C + e c_expert_bytes.
   int experts = 1;
-  int busy_experts = 1;          // grouped: experts that are expected to have rows
+  bool stream = false;           // grouped: the weights that can be read are far more than the caches hold (routed_weights_stream)
   int64_t a_expert_bytes = 0, c_expert_bytes = 0;
   // EPI_ROWSCALE_F32, optional: rows r with row_dest[r] >= 0 are not written to C but, rounded to bf16 and
   // unscaled (their scale is 1), to row row_dest[r] of `direct_out` (leading dimension ldc): the slots of
@@ -277,19 +276,6 @@ int launch_enumerate_direct(const DirectPlan& p, const float* logits, const void
                             int32_t* argmin, uint32_t* argmin_mask, int64_t* unaffected, char* ws, hipStream_t s);
 
 // ---- skipping ---------------------------------------------------------------------
-struct SkipPlan {
-  int64_t T; int E, H, F;
-  int ks;                // slots per token (2 for the top-2 rule, k for the generalised rule)
-  int64_t max_slots;     // ks T
-  bool few;              // bf16, few rows per expert: gemm_few.hip, no operand is re-laid out
-  int tile_rows;         // rows per tile of the map
-  int64_t max_tiles;     // upper bound on M tiles over all experts
-  size_t off_logits, off_slot_token, off_slot_scale, off_slot_dest, off_pos, off_counts, off_seg_end,
-         off_tile_expert, off_tile_row0, off_order_up, off_order_down, off_h, off_xp, off_w13, off_w2, off_slot_out, total;
-  bool packed;           // bf16: packed-operand GEMMs (tile order tables are built)
-};
-// kept_experts: experts that tokens can be routed to (decides the path, not the size of the workspace)
-int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_experts, SkipPlan* p, bool with_slot_out = true);
 // Whether the routing of a handful of tokens computes their logits as well, in the same launch: it is then given x and Wgate
 // (both NULL otherwise) and writes `logits`.
 bool routing_computes_logits(const SkipPlan& p, const void* x, const void* Wgate);

@@ -842,7 +842,7 @@ int launch_gemm_bf16_packed(const PackedGemmArgs& g, hipStream_t s, const char* 
   if (m_tiles * n_tiles * g.experts >= ((int64_t)1 << 31)) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
   k.m_tiles = (int)m_tiles; k.n_tiles = (int)n_tiles; k.half_width = half ? 1 : 0;
   k.row_groups = gemm_row_groups(g.M);
-  k.stream = (double)g.N * g.K * 2.0 * (g.epilogue == EPI_SWIGLU ? 2.0 : 1.0) * (grouped ? g.busy_experts : g.experts) > STREAM_BYTES;
+  k.stream = grouped ? g.stream : streams_weights(g.N, g.K, g.epilogue == EPI_SWIGLU, g.experts);
   Timed t(name, s);
 #define MOEP_GEMM_CASE(EPI, GROUPED) \
   return g.b_row_major ? launch<EPI, GROUPED, true>(k, s) : launch<EPI, GROUPED, false>(k, s)

@@ -557,7 +557,7 @@ __global__ __launch_bounds__(512) void route_dispatch_kernel(const uint4* __rest
 
 int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_experts, SkipPlan* p, bool with_slot_out) {
   if ((int64_t)ks * T >= ((int64_t)1 << 31)) return fail(MOEP_EUNSUPPORTED, "moe_forward_skip: T too large");
-  p->T = T; p->E = E; p->H = H; p->F = F; p->ks = ks;
+  p->T = T; p->E = E; p->H = H; p->F = F; p->ks = ks; p->kept_experts = kept_experts;
   p->max_slots = (int64_t)ks * T;
   p->few = dt == MOEP_BF16 && few_rows(T, ks, kept_experts, 3.0 * H * F * 2);
   p->tile_rows = p->few ? FEW_ROWS : GEMM_BM;

@@ -1,0 +1,35 @@
+// The plan of a routed forward.  Host arithmetic only, without HIP, so that a program built on the CPU can check it.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include "moeprune.h"
+#include "tile_plan.h"
+
+namespace moep {
+
+struct SkipPlan {
+  int64_t T; int E, H, F;
+  int ks;                // slots per token (2 for the top-2 rule, k for the generalised rule)
+  int kept_experts;      // experts that tokens can be routed to
+  int64_t max_slots;     // ks T
+  bool few;              // bf16, few rows per expert: gemm_few.hip, no operand is re-laid out
+  int tile_rows;         // rows per tile of the map
+  int64_t max_tiles;     // upper bound on M tiles over all experts
+  size_t off_logits, off_slot_token, off_slot_scale, off_slot_dest, off_pos, off_counts, off_seg_end,
+         off_tile_expert, off_tile_row0, off_order_up, off_order_down, off_h, off_xp, off_w13, off_w2, off_slot_out, total;
+  bool packed;           // bf16: packed-operand GEMMs (tile order tables are built)
+};
+// kept_experts decides the path, not the size of the workspace
+int plan_skip(int64_t T, int E, int H, int F, moep_dtype dt, int ks, int kept_experts, SkipPlan* p, bool with_slot_out = true);
+
+// Whether the 256-row GEMM's gate/up or down launch of a routed forward loads its weights past the caches: no expert that was
+// pruned away is read, however many the layer has.  us per call, all the layer's experts counted / the kept ones: 3 of 16 experts,
+// H 2048, F 5632, 127 tokens 132 / 89, 4 of them (184 MB of gate/up) 137 / 126; 2 of 8, H 2048, F 8192, 85 tokens 137 / 95; 4 of 32,
+// H 2048, F 2816, 120 tokens 90 / 68.
+inline bool routed_weights_stream(const SkipPlan& p, bool gate_up) {
+  return gate_up ? streams_weights(p.F, p.H, true, p.kept_experts) : streams_weights(p.H, p.F, false, p.kept_experts);
+}
+
+}  // namespace moep

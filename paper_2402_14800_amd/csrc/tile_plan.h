@@ -24,6 +24,12 @@ constexpr int64_t tail_tiles(int64_t tiles, int n_full, int n_half, int k, int r
   return tiles > 256 && n_half > n_full && k >= TAIL_MIN_K && row_groups > 4 && half_width_pays(tiles & 255) ? tiles & 255 : 0;
 }
 
+// Weights of a launch from which they are loaded past the caches.  `experts`: the ones that can have rows.
+constexpr double STREAM_BYTES = 192e6;
+constexpr bool streams_weights(int N, int K, bool gate_up, int experts) {
+  return (double)N * K * 2.0 * (gate_up ? 2.0 : 1.0) * experts > STREAM_BYTES;
+}
+
 // Rows per tile of a routed launch: 256, or SHORT_TILE_ROWS where the call's two launches are shorter with that.  What they
 // cost is the rounds of 256 tiles (compute units) that they take, each as many steps as its K is deep and the epilogue: about
 // 4 steps of 32 for the SwiGLU one, 24 for the row-scaled one, whose loads wait for each other.  A 192-row tile costs 13/16 of a

@@ -9,6 +9,7 @@
 
 #include "enum_plan.h"
 #include "moeprune.h"
+#include "skip_plan.h"
 #include "tile_plan.h"
 
 static int failures = 0;
@@ -123,6 +124,18 @@ int main() {
     EXPECT(pays(128, 8640, 33, 48) && pays(512, 9408, 16, 18));              // more, short of what the shorter steps save
     // a third round, or a second, of a few steps and a whole epilogue
     EXPECT(!pays(3136, 128, 32, 45) && !pays(1664, 64, 32, 54) && !pays(1984, 128, 32, 40) && !pays(1920, 64, 64, 79));
+  }
+
+  // ---- weights of a routed call that are loaded past the caches: of the kept experts, not of the layer (gate/up 738 MB, 184 MB of
+  // four experts, 92 MB of two; down half of that)
+  {
+    auto streams = [](int kept, bool gate_up) {
+      moep::SkipPlan q;
+      EXPECT(moep::plan_skip(42 * kept, 16, 2048, 5632, MOEP_BF16, 2, kept, &q) == MOEP_OK && !q.few && q.kept_experts == kept);
+      return moep::routed_weights_stream(q, gate_up);
+    };
+    EXPECT(streams(16, true) && streams(5, true) && !streams(4, true) && !streams(2, true));
+    EXPECT(streams(16, false) && streams(9, false) && !streams(8, false) && !streams(2, false));
   }
 
   // ---- argument errors: every call must come back with a status and a message, having launched nothing
