@@ -247,7 +247,6 @@ struct EnumJob {
   EnumPlan plan;
   float* loss; int32_t* argmin; uint32_t* argmin_mask; int64_t* unaffected;   // unaffected may be NULL
 };
-constexpr int RECORD_SETS = 4;                             // most jobs that share a launch
 // Every job on the same logits and Y, up to RECORD_SETS of them; ws_bytes: the largest of their plans' totals.
 int launch_enumerate(const EnumJob* jobs, int n, const float* logits, const void* Y, moep_dtype dt, char* ws, size_t ws_bytes,
                      hipStream_t s, const RankedSource* ranked = nullptr);

@@ -108,9 +108,10 @@ __device__ __forceinline__ uint4 load_streaming(const uint4* p) {
 // pair of experts, which re-read every row E times.
 //
 // Records: for up to RECORD_SETS values of r the wavefront goes on to write its tokens' records itself, from the 16 x 16 products
-// in its LDS, and the Gram matrices never go to memory (recs.n = 0: they do, for the prep kernel).  The pass waits for memory
-// with 128 KB in flight on every compute unit, which covers the extra work; E 16, H 2048, 65536 tokens, two r: this
-// kernel 702 -> 706 us and the 35 + 24 us of prep_kernel gone, E 8, H 4096 716 -> 729 and 11 + 8 gone.
+// in its LDS, and the Gram matrices never go to memory (!RECORDS: they do, for the prep kernel).  With long rows the pass waits
+// for memory with 128 KB in flight on every compute unit, which covers the extra work; E 16, H 2048, 65536 tokens, two r: this
+// kernel 702 -> 706 us and the 35 + 24 us of prep_kernel gone, E 8, H 4096 716 -> 729 and 11 + 8 gone.  Long batches of short rows
+// have nothing to cover it (records_pay in enum_plan.h).
 struct RecordArgs {
   const float* logits;
   int n, k;
@@ -122,7 +123,7 @@ __device__ __forceinline__ void wavefront_sync() {         // LDS written by oth
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <bool F32, int EPAD, bool RANKED, bool STREAM>
+template <bool F32, int EPAD, bool RANKED, bool STREAM, bool RECORDS>
 __global__ __launch_bounds__(256) void gram_kernel(const uint4* __restrict__ Y,
                                                         const int32_t* __restrict__ slot_of,
                                                         const int32_t* __restrict__ experts,
@@ -134,9 +135,9 @@ __global__ __launch_bounds__(256) void gram_kernel(const uint4* __restrict__ Y,
   const int wave = threadIdx.x >> 6;
   const int64_t tile = (int64_t)blockIdx.x * 4 + wave;
   const int64_t t0 = tile * TPT;
-  if (blockIdx.x == 0 && threadIdx.x < RECORD_SETS && (int)threadIdx.x < recs.n && recs.set[threadIdx.x].clear)
+  if (RECORDS && blockIdx.x == 0 && threadIdx.x < RECORD_SETS && (int)threadIdx.x < recs.n && recs.set[threadIdx.x].clear)
     *recs.set[threadIdx.x].clear = 0ull;
-  if (recs.n == 0 && t0 >= T) return;
+  if (!RECORDS && t0 >= T) return;
   // Records: what they need beside the products is made while the first rows are on their way: per token (lane lt of token tq),
   // by rank, exp, logit, full-layer weight and row of the products, per 4 ranks the experts, and a word that stays 0; per set the
   // place of each word's value in those (or its row and column of the triangle).
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(256) void gram_kernel(const uint4* __restrict__ Y,
   __shared__ uint16_t s_word[RECORD_SETS][rec_size(EPAD)];
   constexpr int AT_L = 16, AT_A = 32, AT_ROW = 48, AT_ORDER = 64, AT_ZERO = 68, TRIANGLE = 0x8000;
   const int tq = lane / LPT, lt = lane % LPT;
-  const bool some = recs.n > 0 && t0 + tq < T;
+  const bool some = RECORDS && t0 + tq < T;
   const float logit = some && lt < E ? recs.logits[(t0 + tq) * E + lt] : 0.f;
   const int expert = RANKED && some && lt < n ? experts[(t0 + tq) * n + lt] : 0;
   uint4* st = stage[wave];
@@ -170,7 +171,7 @@ __global__ __launch_bounds__(256) void gram_kernel(const uint4* __restrict__ Y,
     v[j] = !(rvalid[j] && (kb) * 64 + lane < chunks) ? make_uint4(0, 0, 0, 0)                    \
            : STREAM ? load_streaming(&rowp[j][(kb) * 64]) : rowp[j][(kb) * 64];
   MOEP_GRAM_FETCH(0)
-  if (recs.n > 0) {
+  if constexpr (RECORDS) {
     uint32_t* const tok = s_token[wave][tq];
     float* const lg = (float*)st + tq * 64;                // (the stage is not in use yet)
     int* const rank_of = (int*)lg + 16;
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(256) void gram_kernel(const uint4* __restrict__ Y,
 #undef MOEP_GRAM_FETCH
   // Accumulator layout of the 16x16 tile: register v of lane l = row 4 (l / 16) + v, column l % 16.
   const int col = lane & 15;
-  if (recs.n > 0) {
+  if constexpr (RECORDS) {
     float* const g = (float*)st;                           // the products, in the place of the stage
     wavefront_sync();
 #pragma unroll
@@ -1542,26 +1543,50 @@ static void launch_score(const EnumPlan& p, const float* rec, float* partial, ui
 #undef MOEP_SCORE
 }
 
+bool records_by_gram_pass(const EnumPlan* const* plans, int n, int n_rank, bool f32, size_t ws_bytes, RecordPlan* out) {
+  const EnumPlan& p0 = *plans[0];
+  if (p0.E > 16 || p0.T == 0 || n > RECORD_SETS) return false;
+  int weights = 0;
+  for (int i = 0; i < n; ++i) weights += record_weight(plans[i]->n_act);
+  if (!records_pay(p0.T, n_rank ? n_rank : p0.E, p0.H, f32, n_rank != 0, weights)) return false;
+  size_t off = 0;
+  auto take = [&](size_t bytes) { const size_t o = off; off += align256(bytes); return o; };
+  for (int i = 0; i < n; ++i) {
+    const EnumPlan& p = *plans[i];
+    const size_t sums = (size_t)p.n_tok_tiles * p.n_sub * sizeof(float);
+    out->rec[i] = take((size_t)p.T * p.rec_floats * sizeof(float));
+    out->partial[i] = take(sums);
+    out->cnt[i] = take(p.fused_threads ? 0 : sums);
+  }
+  return off <= ws_bytes;
+}
+
 // Whether the Gram kernel can write the records itself: up to 16 experts, rows of whole 16-byte chunks.
 static bool gram_writes_records(const EnumPlan& p, const void* Y, moep_dtype dt) {
   return p.E <= 16 && (dt == MOEP_BF16 || (p.H % 4 == 0 && ((uintptr_t)Y & 15) == 0));
 }
 
-// G: where the Gram matrices go; recs.n > 0: records instead.
+// G: where the Gram matrices go; recs.n > 0: records instead (the kernels that read word by word and those of more than 16 experts
+// write Gram matrices only).
 static int launch_gram(const EnumPlan& p, const void* Y, moep_dtype dt, float* G, const RecordArgs& recs,
                        const RankedSource* ranked, hipStream_t s) {
   Timed t("gram", s);
   const unsigned per_tok_blocks = (unsigned)ceil_div(p.T, 4);
   // streaming loads for a Y beyond half a GB
   const bool stream = (double)p.T * (ranked ? ranked->n_rank : p.E) * p.H * 2.0 >= 512.0 * 1024 * 1024;
-#define MOEP_GRAM_LAUNCH(EPAD, RANKED, GRID, ...)                                                                  \
-  do {                                                                                                             \
-    if (dt != MOEP_BF16)                                                                                           \
-      hipLaunchKernelGGL((gram_kernel<true, EPAD, RANKED, false>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__, recs); \
-    else if (stream)                                                                                               \
-      hipLaunchKernelGGL((gram_kernel<false, EPAD, RANKED, true>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__, recs); \
-    else                                                                                                           \
-      hipLaunchKernelGGL((gram_kernel<false, EPAD, RANKED, false>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__, recs); \
+#define MOEP_GRAM_FORM(EPAD, RANKED, RECORDS, GRID, ...)                                                                  \
+  do {                                                                                                                   \
+    if (dt != MOEP_BF16)                                                                                                 \
+      hipLaunchKernelGGL((gram_kernel<true, EPAD, RANKED, false, RECORDS>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__, recs); \
+    else if (stream)                                                                                                     \
+      hipLaunchKernelGGL((gram_kernel<false, EPAD, RANKED, true, RECORDS>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__, recs); \
+    else                                                                                                                 \
+      hipLaunchKernelGGL((gram_kernel<false, EPAD, RANKED, false, RECORDS>), dim3(GRID), dim3(256), 0, s, __VA_ARGS__, recs); \
+  } while (0)
+#define MOEP_GRAM_LAUNCH(EPAD, RANKED, GRID, ...)                                                                         \
+  do {                                                                                                                   \
+    if (recs.n > 0) MOEP_GRAM_FORM(EPAD, RANKED, true, GRID, __VA_ARGS__);                                               \
+    else MOEP_GRAM_FORM(EPAD, RANKED, false, GRID, __VA_ARGS__);                                                         \
   } while (0)
   // fp32 rows that are not whole 16-byte chunks go through the kernels that read word by word
   const bool by_word = dt != MOEP_BF16 && (p.H % 4 || ((uintptr_t)Y & 15));
@@ -1593,6 +1618,7 @@ static int launch_gram(const EnumPlan& p, const void* Y, moep_dtype dt, float* G
     hipLaunchKernelGGL(gram_f32_32_kernel, dim3((unsigned)ceil_div(p.T, 2)), dim3(128), 0, s, (const uint4*)Y, G, p.T, p.E, p.H);
   }
 #undef MOEP_GRAM_LAUNCH
+#undef MOEP_GRAM_FORM
   MOEP_HIP(hipGetLastError());
   return MOEP_OK;
 }
@@ -1782,20 +1808,12 @@ int launch_reduce_argmin(const float* partial, const uint32_t* pcnt, int64_t n_t
 
 int launch_enumerate(const EnumJob* jobs, int n, const float* logits, const void* Y, moep_dtype dt, char* ws, size_t ws_bytes,
                      hipStream_t s, const RankedSource* ranked) {
-  // The Gram pass does not depend on r.  Where the records of every r, their partial sums and counts fit the workspace (which
-  // has room for Gram matrices), it writes the records itself.
-  size_t off = 0, at_rec[RECORD_SETS], at_partial[RECORD_SETS], at_cnt[RECORD_SETS];
-  auto take = [&](size_t bytes) { const size_t o = off; off += align256(bytes); return o; };
+  const EnumPlan* plans[RECORD_SETS];
+  for (int i = 0; i < n; ++i) plans[i] = &jobs[i].plan;
   const EnumPlan& p0 = jobs[0].plan;
-  bool direct = p0.T > 0 && gram_writes_records(p0, Y, dt);
-  for (int i = 0; direct && i < n; ++i) {
-    const EnumPlan& p = jobs[i].plan;
-    const size_t sums = (size_t)p.n_tok_tiles * p.n_sub * sizeof(float);
-    at_rec[i] = take((size_t)p.T * p.rec_floats * sizeof(float));
-    at_partial[i] = take(sums);
-    at_cnt[i] = take(p.fused_threads ? 0 : sums);
-  }
-  if (!direct || off > ws_bytes) {
+  RecordPlan at;
+  if (!gram_writes_records(p0, Y, dt) ||
+      !records_by_gram_pass(plans, n, ranked ? ranked->n_rank : 0, dt != MOEP_BF16, ws_bytes, &at)) {
     for (int i = 0; i < n; ++i)
       if (int st = launch_enumerate_from_gram(jobs[i], logits, Y, dt, ws, s, ranked, i > 0)) return st;
     return MOEP_OK;
@@ -1809,13 +1827,13 @@ int launch_enumerate(const EnumJob* jobs, int n, const float* logits, const void
   for (int i = 0; i < n; ++i) {
     const EnumJob& j = jobs[i];
     const EnumPlan& p = j.plan;
-    recs.set[i] = {(float*)(ws + at_rec[i]), (unsigned long long*)j.unaffected, capacity_for(p.n_act), p.n_act, p.rec_floats};
-    set.job[i] = {(const float*)(ws + at_partial[i]), p.fused_threads ? nullptr : (const uint32_t*)(ws + at_cnt[i]), p.n_tok_tiles,
+    recs.set[i] = {(float*)(ws + at.rec[i]), (unsigned long long*)j.unaffected, capacity_for(p.n_act), p.n_act, p.rec_floats};
+    set.job[i] = {(const float*)(ws + at.partial[i]), p.fused_threads ? nullptr : (const uint32_t*)(ws + at.cnt[i]), p.n_tok_tiles,
                   (uint32_t)p.n_sub, 0, 0, p.r, j.loss, (unsigned long long*)j.unaffected, j.argmin, j.argmin_mask};
   }
   if (int st = launch_gram(p0, Y, dt, nullptr, recs, ranked, s)) return st;
   for (int i = 0; i < n; ++i)
-    if (int st = launch_scores(jobs[i].plan, recs.set[i].rec, (float*)(ws + at_partial[i]), (uint32_t*)(ws + at_cnt[i]), ws,
+    if (int st = launch_scores(jobs[i].plan, recs.set[i].rec, (float*)(ws + at.partial[i]), (uint32_t*)(ws + at.cnt[i]), ws,
                                jobs[i].unaffected, s)) return st;
   return reduce_argmin(set, p0.E, true, s);
 }

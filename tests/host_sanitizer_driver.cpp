@@ -114,6 +114,45 @@ int main() {
         }
       }
 
+  // ---- records written by the Gram pass: few tokens or long rows, and only where those of every r fit beside their sums
+  {
+    auto records = [](int64_t T, int E, int H, int k, std::vector<int> rs, moep_dtype dt = MOEP_BF16, int n_rank = 0) {
+      std::vector<moep::EnumPlan> q(rs.size());
+      std::vector<const moep::EnumPlan*> at;
+      for (size_t i = 0; i < rs.size(); ++i) {
+        EXPECT(moep::plan_enumerate(T, E, H, k, rs[i], &q[i]) == MOEP_OK);
+        at.push_back(&q[i]);
+      }
+      const size_t room = prune_enumerate_multi_workspace(T, E, H, k, (int)rs.size(), rs.data(), dt);
+      moep::RecordPlan r;
+      if (!moep::records_by_gram_pass(at.data(), (int)rs.size(), n_rank, dt == MOEP_F32, room, &r)) return false;
+      size_t end = 0;                                // nothing overlaps, everything lies in the workspace
+      for (size_t i = 0; i < rs.size(); ++i) {
+        const size_t sums = (size_t)q[i].n_tok_tiles * q[i].n_sub * 4;
+        EXPECT(r.rec[i] >= end && r.rec[i] % 256 == 0);
+        EXPECT(r.partial[i] >= r.rec[i] + (size_t)T * q[i].rec_floats * 4 && r.partial[i] % 256 == 0);
+        EXPECT(r.cnt[i] >= r.partial[i] + sums && r.cnt[i] % 256 == 0);
+        end = r.cnt[i] + (q[i].fused_threads ? 0 : sums);
+        EXPECT(end <= room);
+      }
+      return true;
+    };
+    EXPECT(records(4608, 16, 64, 2, {14}) && !records(4609, 16, 64, 2, {14}));                   // a tile per token, 4 active ranks
+    EXPECT(records(6912, 16, 64, 4, {12}) && !records(6913, 16, 64, 4, {12}));                   // 8
+    EXPECT(records(9216, 16, 64, 8, {15}) && !records(9217, 16, 64, 8, {15}));                   // 9
+    EXPECT(records(11520, 16, 64, 2, {14, 12}) && !records(11521, 16, 64, 2, {14, 12}));         // 4 and 6
+    EXPECT(records(9216, 8, 64, 2, {7}) && !records(9217, 8, 64, 2, {7}));                       // two tokens to a tile
+    EXPECT(records(18432, 4, 64, 2, {2}) && !records(18433, 4, 64, 2, {2}));                     // four
+    EXPECT(records(65536, 16, 1024, 2, {14}) && !records(65536, 16, 960, 2, {14}));              // rows long enough
+    EXPECT(records(65536, 8, 1024, 2, {6, 4}, MOEP_F32) && !records(65536, 8, 960, 2, {6, 4}, MOEP_F32));
+    EXPECT(!records(32000, 9, 2048, 2, {6}, MOEP_F32) && records(32000, 9, 2048, 2, {6}));       // seven rows of padding
+    EXPECT(records(18432, 16, 64, 4, {12}, MOEP_BF16, 8) && !records(18433, 16, 64, 4, {12}, MOEP_BF16, 8));   // 8 ranked rows per token
+    EXPECT(records(40000, 16, 512, 4, {12}, MOEP_BF16, 8) && !records(40000, 16, 448, 4, {12}, MOEP_BF16, 8));
+    EXPECT(records(700, 8, 192, 2, {5, 6, 7}) && records(700, 8, 192, 1, {5, 6, 7, 8}));         // three and four r that fit
+    EXPECT(!records(5600, 8, 192, 2, {4, 6, 7, 1}) && !records(700, 8, 192, 2, {4, 6, 7, 1}));   // four that do not
+    EXPECT(!records(700, 8, 192, 1, {5, 6, 7, 8, 7}) && !records(100, 17, 64, 2, {16}) && !records(0, 8, 64, 2, {6}));
+  }
+
   // ---- tiles of a routed call: shorter ones where they make it shorter (us of whole calls, 256 / 192 rows, at tile_plan.h)
   {
     auto pays = [](int H, int F, int tall, int shortened) {

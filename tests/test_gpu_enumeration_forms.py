@@ -13,8 +13,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("E,k,r,T,H,dtype", [
-    (8, 2, 4, 14976, 64, "bf16"),      # 468 tiles x 70 subsets: the last size of the one-workgroup reduction
-    (8, 2, 4, 14977, 64, "bf16"),      # one token more: reduced by a workgroup per subset
+    (8, 2, 4, 14976, 64, "bf16"),      # 468 tiles x 70 subsets, through Gram matrices in memory
+    (8, 2, 4, 14977, 64, "bf16"),      # a last tile of one token
+    (8, 2, 4, 5600, 64, "bf16"),       # 175 tiles x 70 subsets: the last size of the one-workgroup reduction
+    (8, 2, 4, 5601, 64, "bf16"),       # one token more: reduced by a workgroup per subset
+    (16, 2, 14, 4608, 64, "bf16"),     # the most tokens of short rows whose records the Gram kernel writes
+    (16, 2, 14, 4609, 64, "bf16"),     # one more: through Gram matrices in memory
     (8, 2, 4, 33, 64, "bf16"),         # a tile of one token: strands without work
     (4, 2, 2, 7, 64, "f32"),           # fewer tokens than strands
     (1, 1, 1, 40, 64, "bf16"),         # one expert, one subset
@@ -113,8 +117,11 @@ def test_scoring_with_tables_in_lds(E, k, r, T, spread):
 
 @pytest.mark.parametrize("E,k,rs,T", [
     (8, 2, (6, 4), 9001),        # 28 subsets in one workgroup, 70 over the chip
-    (8, 2, (4, 6, 7, 1), 5600),  # four r, the most that share a launch
-    (8, 2, (4, 6, 7, 1, 5), 700),  # five: through Gram matrices in memory
+    (8, 2, (5, 6, 7), 700),      # three r and four r whose records are written in one pass
+    (8, 1, (5, 6, 7, 8), 700),
+    (8, 2, (4, 6, 7, 1), 5600),  # four whose records do not fit the workspace: through Gram matrices in memory
+    (8, 2, (4, 6, 7, 1, 5), 700),  # five: the same
+    (16, 2, (14, 12), 8000),     # written in one pass for both, through Gram matrices for each alone
     (16, 4, (12, 15), 1100),     # tables for one r, records of the same pass for the other
     (5, 2, (3,), 1),
     (12, 3, (6, 11), 77),
@@ -125,10 +132,16 @@ def test_several_r_give_the_bits_of_each_alone(E, k, rs, T):
     logits = torch.randn((T, E), generator=gen, device="cuda:0")
     Y = torch.randn((E, T, 192), generator=gen, device="cuda:0").to(torch.bfloat16)
     parts = pkg.prune_enumerate_multi(logits, Y, k, list(rs))
+    some = T <= 700                                      # (the oracle takes a second for each r)
+    l64, y64 = wl.to_f64(logits), wl.to_f64(Y) if some else None
     for r, part in zip(rs, parts):
         alone = pkg.prune_enumerate(logits, Y, k, r)
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(part, alone)), r
+        if some:
+            ref = oracle.prune_enumerate_gram_form(l64, y64, k, r)[0]
+            got = part[0].cpu().numpy().astype(np.float64)
+            assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6 * np.abs(ref).max())
 
 
 def test_a_loss_of_several_r_can_be_written_under_autograd():
