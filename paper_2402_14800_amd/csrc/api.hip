@@ -581,6 +581,7 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
   up.seg_end = (const int32_t*)(w + p.off_seg_end);
   up.max_m_tiles = p.max_tiles;
   up.tiles_in_use = up.tile_expert + p.max_tiles;
+  up.busy_experts = p.kept_experts;
   if (int st = launch_gemm_f32(up, s, "gemm_gate_up_swiglu_routed")) return st;
 
   GemmArgs down;                    // slot_out[slot] = weight(slot) * h[slot] W2[e]^T, fp32
@@ -593,6 +594,7 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
   down.tile_expert = up.tile_expert; down.tile_row0 = up.tile_row0; down.seg_end = up.seg_end;
   down.max_m_tiles = p.max_tiles;
   down.tiles_in_use = up.tiles_in_use;
+  down.busy_experts = up.busy_experts;
   return launch_gemm_f32(down, s, "gemm_down_routed");
 }
 

@@ -109,6 +109,7 @@ struct GemmArgs {
   void* C_rest = nullptr;
   int64_t a_expert_stride = 0, c_expert_stride = 0;
   int64_t max_m_tiles = 0;              // grouped: number of entries in tile_expert/tile_row0
+  int busy_experts = 1;                 // grouped: experts that can have rows
   const int32_t* tiles_in_use = nullptr; // grouped, optional: device count of leading entries that hold work
 };
 

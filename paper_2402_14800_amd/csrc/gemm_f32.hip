@@ -5,15 +5,15 @@
 // Bound by the fp32 matrix rate (157 TFLOP/s nominal; 109 reached at 6000 tokens) where there are tiles for the chip, by the
 // serial walk over K where there are not.  A workgroup of 256 threads owns 64 rows x 128 accumulator columns (gate/up: 64
 // columns of either branch; few tiles: 32 x 128, then 32 x 64) and walks K in slabs of 32 through a ring of LDS stages that
-// direct loads fill one or two slabs ahead, one barrier per slab.  Against a slab in registers and two buffers, all experts, E 8,
-// H 512, F 1024: T = 64 164 -> 145 us, 400 226 -> 208, 1501 449 -> 441, 4000 976 -> 960; E 4, H 1024, F 3584, T = 400 514 -> 466.  The tiles are small
-// because the layers are: a dense pass takes as many experts per launch as its scratch room
-// allows for the same reason.
+// direct loads fill one or two slabs ahead, one barrier per slab (how many: f32_slabs_ahead in tile_plan.h).  Against a slab in
+// registers and two buffers, all experts, E 8, H 512, F 1024: T = 64 164 -> 145 us, 400 226 -> 208, 1501 453 -> 434, 4000 973 ->
+// 936, 6000 1379 -> 1369; E 4, H 1024, F 3584, T = 400 514 -> 466.  The tiles are small because the layers are: a dense pass takes as
+// many experts per launch as its scratch room allows for the same reason.
 // A row of a slab is 128 bytes in LDS, its 16-byte chunk c at position c ^ (row & 7), so that the fragment reads (16 rows
 // apart 128 bytes) are free of bank conflicts.  A lane reads 4 consecutive k as one 16-byte word; element j of it feeds
 // MFMA j, for both operands alike, so the four MFMAs of 16 k-values sum k = j, 4 + j, 8 + j, 12 + j.
 // Measured, all experts, E 8, H 512, F 1024, against the plain-FMA kernel with 64 x 64 tiles that this replaces: T = 64
-// 1356 -> 145 us, 1501 1369 -> 439, 6000 2284 -> 1376; E 4, H 64, F 128, T = 512: 109 -> 36 us.
+// 1356 -> 145 us, 1501 1369 -> 434, 6000 2284 -> 1369; E 4, H 64, F 128, T = 512: 109 -> 36 us.
 // A row's sum depends on K only, so a token's outputs do not depend on the batch or on the tile.
 #include "common.h"
 
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
     __builtin_amdgcn_sched_barrier(0);
   }
   // A last slab that is not whole (K is a multiple of 4: chunks beyond it are zero), and every slab of weights that are not
-  // 16-byte aligned, goes through registers.
+  // 16-byte aligned, goes through registers, into two of the stages in turn.
   f32x4 held[LOADS];
   auto hold = [&](int slab) {
     const bool in = slab * TK + sc * 4 < p.K;
@@ -157,12 +157,12 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
   };
   if (slabs * TK < p.K) hold(slabs);
   for (int s = slabs; s * TK < p.K; ++s) {
-    __syncthreads();
+    float* const buf = lds[(s - slabs) & 1];               // (last read before the previous barrier)
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) *(f32x4*)(&lds[0][tid * 4 + i * 1024]) = held[i];
+    for (int i = 0; i < LOADS; ++i) *(f32x4*)(buf + tid * 4 + i * 1024) = held[i];
     __syncthreads();
     if ((s + 1) * TK < p.K) hold(s + 1);
-    multiply(lds[0]);
+    multiply(buf);
   }
 
   // Register v of lane l of tile (i, j): row 16 i + l % 16 of the wavefront's TM / 2, weight row 4 (l / 16) + v of tile j.
@@ -198,10 +198,6 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
 constexpr int64_t SMALL_TILES_BELOW = 512;
 // (the same line for half the width again: T 64 of that layer 241 -> 164 us, 400 270 -> 227, 1501 470 -> 454; at 256 tiles 464)
 constexpr int64_t NARROW_TILES_BELOW = 512;
-// From three 64-row tiles per compute unit on, one slab in flight and a third workgroup on the compute unit are worth more than
-// a second slab (E 8, H 256, F 512, top-2, T 8000 185 -> 175 us); with fewer the second slab is (E 16, H 1024, F 512, top-2, T 1501
-// 223 -> 172).
-constexpr int64_t MANY_TILES = 768;
 
 }  // namespace
 
@@ -227,8 +223,9 @@ int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name) {
   // 64 x 128 accumulators per tile, 32 x 128 where those are few, 32 x 64 where these are
   const int tm = m_tiles(64) * n_tiles(128) * g.experts < SMALL_TILES_BELOW ? 32 : 64;
   const int tb = tm == 32 && m_tiles(32) * n_tiles(128) * g.experts < NARROW_TILES_BELOW ? 64 : 128;
-  // (rows of a routed launch are spread over the map's tiles: counted as if they filled them)
-  const bool many = ceil_div(g.M, 64) * n_tiles(128) * g.experts >= MANY_TILES;
+  // (weights that are not 16-byte aligned use two stages only: as many workgroups per compute unit as there can be)
+  const int64_t tiles = (g.tile_expert ? routed_row_tiles(g.M, g.busy_experts, tm) : ceil_div(g.M, tm)) * n_tiles(tb) * g.experts;
+  const int ahead = f.by_register && tiles > 512 ? 1 : f32_slabs_ahead(tiles, 2, tm == 64 ? 3 : 4);
   if (m_tiles(tm) > 2147483647LL || n_tiles(tb) > 65535) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
   dim3 grid((unsigned)m_tiles(tm), (unsigned)n_tiles(tb), (unsigned)g.experts);
   Timed t(name, s);
@@ -236,8 +233,9 @@ int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name) {
 #define MOEP_F32_CASE(EPI)                                                                              \
   case EPI:                                                                                             \
     if (tb == 64) MOEP_F32_LAUNCH(EPI, 32, 64, 2);                                                      \
+    else if (tm == 32 && ahead == 1) MOEP_F32_LAUNCH(EPI, 32, 128, 1);                                  \
     else if (tm == 32) MOEP_F32_LAUNCH(EPI, 32, 128, 2);                                                \
-    else if (many) MOEP_F32_LAUNCH(EPI, 64, 128, 1);                                                    \
+    else if (ahead == 1) MOEP_F32_LAUNCH(EPI, 64, 128, 1);                                              \
     else MOEP_F32_LAUNCH(EPI, 64, 128, 2);                                                              \
     break;
   switch (g.epilogue) {

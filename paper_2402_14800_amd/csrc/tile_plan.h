@@ -55,4 +55,15 @@ constexpr bool short_tiles_pay(const Shorten& s, int64_t tall, int64_t shortened
   return 13 * routed_cost(s, shortened) < 16 * routed_cost(s, tall);
 }
 
+// Slabs of K that the fp32 expert GEMM fetches ahead.  Two keep `of_two` workgroups of its tile on a compute unit, one lets
+// `of_one` of them fit: one where that saves a round of `tiles` on 256 compute units.  us per call, two / one.  64 x 128 tiles (2, 3):
+// skipping forward, E 16, H 1024, F 512, T = 2000 (564 in either launch) 254 / 213; E 4, H 512, F 512, T = 2700 (690) 139 / 125, T =
+// 3300 (840: two rounds both ways) 142 / 166, T = 4000 (1016) 143 / 156.  32 x 128 tiles (2, 4): all experts, E 4, H 1024, F 2048, T =
+// 3000 (752) 1401 / 1338; E 8, H 512, F 1024, T = 1500, skipping forward (392) 144 / 163.
+constexpr int f32_slabs_ahead(int64_t tiles, int of_two, int of_one) {
+  return (tiles + 256 * of_two - 1) / (256 * of_two) > (tiles + 256 * of_one - 1) / (256 * of_one) ? 1 : 2;
+}
+// Row tiles of a routed launch, expected: every expert's last one is half full.
+constexpr int64_t routed_row_tiles(int64_t rows, int experts, int tile_rows) { return (rows + (int64_t)experts * (tile_rows / 2)) / tile_rows; }
+
 }  // namespace moep

@@ -177,6 +177,17 @@ int main() {
     EXPECT(streams(16, false) && streams(9, false) && !streams(8, false) && !streams(2, false));
   }
 
+  // ---- slabs ahead in the fp32 GEMM: one where a third (64-row tiles) or a third and fourth workgroup per compute unit saves a round
+  {
+    auto tall = [](int64_t tiles) { return moep::f32_slabs_ahead(tiles, 2, 3); };
+    auto low = [](int64_t tiles) { return moep::f32_slabs_ahead(tiles, 2, 4); };
+    EXPECT(tall(1) == 2 && tall(512) == 2 && tall(513) == 1 && tall(768) == 1 && tall(769) == 2 && tall(1024) == 2 && tall(1025) == 1);
+    for (int64_t tiles : {1500, 1536, 1537, 2048, 4000, 100000}) EXPECT(tall(tiles) == 1);
+    EXPECT(low(512) == 2 && low(513) == 1 && low(1024) == 1);
+    EXPECT(moep::routed_row_tiles(4000, 4, 64) == 64 && moep::routed_row_tiles(4000, 8, 64) == 66 && moep::routed_row_tiles(3000, 8, 32) == 97);
+    EXPECT(moep::routed_row_tiles(1, 1, 64) == 0 && moep::routed_row_tiles((int64_t)1 << 31, 32, 32) == ((int64_t)1 << 26) + 16);
+  }
+
   // ---- argument errors: every call must come back with a status and a message, having launched nothing
   void* p = (void*)(uintptr_t)(1 << 20);          // never dereferenced on the host
   float* fp = (float*)p;

@@ -87,7 +87,8 @@ def test_fp32_expert_outputs_at_four_byte_alignment(E, H, F, T, offset):
 
 
 @pytest.mark.parametrize("E,H,F,T", [
-    (8, 192, 128, 4000),    # 64 x 128 tiles, two slabs in flight
+    (8, 192, 128, 4000),    # 64 x 128 tiles, one slab in flight
+    (8, 192, 128, 5500),    # two
     (8, 96, 100, 700),      # three slabs; three and a partly filled one
     (4, 32, 28, 50),        # one slab, and less than one
 ])
