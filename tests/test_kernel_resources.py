@@ -1,8 +1,8 @@
 """What the compiler made of the GEMM kernel: all 256 accumulator registers of a wavefront in the AGPR half of
 its register file, one wavefront per SIMD, and nothing spilled to scratch memory in any instantiation (a spill
 inside the K loop costs far more than the few registers it saves; outside it, it still means the loop's
-register budget was exceeded somewhere); the order of the loads that the hand-counted waits of this kernel and of the few-rows
-GEMM rely on; and the registers of the table scorers, whose launches are planned by residency.  Compiles the device code; no
+register budget was exceeded somewhere); the order of the loads that the hand-counted waits of this kernel, of the few-rows
+GEMM and of the fp32 GEMM rely on; and the registers of the table scorers, whose launches are planned by residency.  Compiles the device code; no
 GPU needed."""
 import re
 
@@ -173,3 +173,48 @@ def test_few_rows_gemm_does_not_spill():
     for name, u in usage.items():
         assert u["ScratchSize"] == 0 and u["VGPRs Spill"] == 0 and u["SGPRs Spill"] == 0, (name, u)
         assert u["Occupancy"] >= (1 if "Li40960E" in name else 2), (name, u)      # as many wavefronts as the rings leave room for
+
+
+def test_fp32_gemm_waits_for_the_loads_it_means():
+    """A wavefront of gemm_f32_kernel waits until all but the loads of the newest AHEAD - 1 slabs have landed.  That is right only if
+    a slab is exactly (TM + TB) / 32 loads into the ring, AHEAD slabs of them in front of the loop and one in every step of it, after
+    the barrier, and nothing else of that kind: a load merged, dropped or moved by the compiler would be a silent race.  Past the
+    loop everything has landed before the ring is used again."""
+    text = build.device_assembly("gemm_f32.hip").splitlines()
+    starts = [i for i, line in enumerate(text) if re.match(r"_ZN\S*gemm_f32_kernel\S*:", line)]
+    assert len(starts) == 15                     # 3 epilogues; 64 x 128 and 32 x 128 with one and two slabs ahead, 32 x 64 with two
+    for start in starts:
+        tm, tb, ahead = map(int, re.search(r"kernelILi\d+ELi(\d+)ELi(\d+)ELi(\d+)E", text[start]).groups())
+        kernel = text[start:next(i for i in range(start, len(text)) if ".Lfunc_end" in text[i])]
+        loads = (tm + tb) // 32
+        header = next(i for i, line in enumerate(kernel) if "Inner Loop Header" in line)
+        label = re.match(r"(\.LBB\d+_\d+):", kernel[header]).group(1)
+        end = next(i for i in range(header + 1, len(kernel)) if re.match(r"\s+s_c?branch\S*\s+" + re.escape(label) + r"\b", kernel[i]))
+
+        def ops(lines):
+            found = []
+            for line in lines:
+                op = line.split()[0] if line.split() else ""
+                if op.startswith(("global_", "flat_", "buffer_", "scratch_")):
+                    found.append("ring" if op == "global_load_lds_dwordx4" else op)
+                elif op == "s_barrier":
+                    found.append(op)
+                elif op == "s_waitcnt" and (m := re.search(r"vmcnt\((\d+)\)", line)):
+                    found.append(int(m.group(1)))
+            return found
+
+        before, loop, after = ops(kernel[:header]), ops(kernel[header:end]), ops(kernel[end:])
+        assert loop == [(ahead - 1) * loads, "s_barrier"] + loads * ["ring"], (text[start], loop)
+        assert before[-ahead * loads:] == ahead * loads * ["ring"] and before.count("ring") == ahead * loads, (text[start], before)
+        assert after[:2] == [0, "s_barrier"] and "ring" not in after, (text[start], after)
+        assert sum("v_mfma_f32_16x16x4_f32" in line for line in kernel[header:end]) == 8 * (tm // 32) * (tb // 32), text[start]
+
+
+def test_fp32_gemm_does_not_spill():
+    usage = {n: u for n, u in build.kernel_resource_usage("gemm_f32.hip").items() if "gemm_f32_kernel" in n}
+    assert len(usage) == 15
+    for name, u in usage.items():
+        tm, tb, ahead = map(int, re.search(r"kernelILi\d+ELi(\d+)ELi(\d+)ELi(\d+)E", name).groups())
+        assert u["ScratchSize"] == 0 and u["VGPRs Spill"] == 0 and u["SGPRs Spill"] == 0, (name, u)
+        # the workgroups per compute unit that f32_slabs_ahead counts on
+        assert u["Occupancy"] >= {(64, 2): 2, (64, 1): 3, (32, 2): 2 if tb == 128 else 4, (32, 1): 4}[tm, ahead], (name, u)
