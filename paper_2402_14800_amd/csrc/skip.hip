@@ -28,16 +28,6 @@ namespace moep {
 namespace {
 
 constexpr int RB = 256;     // tokens per routing block
-// Most tokens that the one-workgroup dispatch takes, one thread each, and most entries of the tile orders: there it is shorter
-// than the two kernels it stands for.  In two / in one, us: Mixtral shape (E 8, H 4096, F 14336), top-2, T = 300 12.2 / 10.6,
-// 777 13.0 / 11.2, 1000 13.0 / 12.1; top-4, 500 14.0 / 13.4, 600 14.2 / 15.0; E 32, H 384, F 4096, top-2, 500 14.3 / 13.5,
-// 600 15.2 / 19.6, top-4, 200 18.1 / 14.7, 400 18.8 / 22.8; 3072 entries, 1000 tokens 14.7 / 18.2.  Routing, slots, the map of
-// tiles and their order in launches of their own took 19 to 27 us from 513 tokens on.
-constexpr int DISPATCH_ONE_MAX = 1024, DISPATCH_ONE_ORDER_MAX = 2048;
-static int dispatch_one_tokens(int E, int slots) {
-  const int most = 2 * DISPATCH_ONE_MAX / slots;
-  return (most > DISPATCH_ONE_MAX ? DISPATCH_ONE_MAX : most < 256 ? 256 : most) >> (E > 16 ? 1 : 0);
-}
 // Most routing blocks whose counts every workgroup of the place kernel adds up for itself (E 8: 8 KB of counts each).
 constexpr int64_t PLACE_MAX_BLOCKS = 256;
 
@@ -518,7 +508,16 @@ __device__ __forceinline__ void dispatch_one(const Dispatch& d) {
     lay_out_segments(t, E, run, seg, lay, true);
   }
   __syncthreads();
-  write_tile_map(lay, E, seg, tile_row0, t, blockDim.x);
+  // the map of tiles, an expert's by its thread (with a look-up per tile, as in the place kernel, this launch takes 0.2 to 0.5 us more)
+  if (t < E)
+    for (int i = lay.first_tile[t]; i < lay.first_tile[t + 1]; ++i) {
+      seg.tile_expert[i] = t;
+      tile_row0[i] = lay.begin[t] + (i - lay.first_tile[t]) * lay.rows_of_tile;
+    }
+  for (int i = lay.first_tile[E] + t; i < seg.max_tiles; i += blockDim.x) {
+    seg.tile_expert[i] = -1;
+    tile_row0[i] = 0;
+  }
   if (up.order) {
     write_order(lay, E, up, t, blockDim.x);
     write_order(lay, E, down, t, blockDim.x);

@@ -32,4 +32,16 @@ inline bool routed_weights_stream(const SkipPlan& p, bool gate_up) {
   return gate_up ? streams_weights(p.F, p.H, true, p.kept_experts) : streams_weights(p.H, p.F, false, p.kept_experts);
 }
 
+// Most tokens that the one-workgroup dispatch takes, one thread each, and most entries of the tile orders: there it is shorter
+// than the two kernels it stands for.  In two / in one, us: Mixtral shape (E 8, H 4096, F 14336), top-2, T = 300 12.2 / 10.6,
+// 777 13.0 / 11.2, 1000 13.0 / 12.1; top-4, 500 14.0 / 13.4, 600 14.2 / 15.0; E 32, H 384, F 4096, top-2, 500 14.3 / 13.5,
+// 600 15.2 / 19.6, top-4, 200 18.1 / 14.7, 400 18.8 / 22.8; 3072 entries, 1000 tokens 14.7 / 18.2.  Up to 256 tokens it is shorter for
+// every k: calls with H = F = 64, E 24, k 8, T = 129 37.3 / 33.9, E 32, k 16, T = 180 4 to 7 us less, k 6, T = 257 the same.
+// Routing, slots, the map of tiles and their order in launches of their own took 19 to 27 us from 513 tokens on.
+constexpr int DISPATCH_ONE_MAX = 1024, DISPATCH_ONE_ORDER_MAX = 2048, DISPATCH_ONE_ALWAYS = 256;
+constexpr int dispatch_one_tokens(int E, int slots) {
+  const int by_slots = 2 * DISPATCH_ONE_MAX / slots, most = (by_slots < DISPATCH_ONE_MAX ? by_slots : DISPATCH_ONE_MAX) >> (E > 16 ? 1 : 0);
+  return most > DISPATCH_ONE_ALWAYS ? most : DISPATCH_ONE_ALWAYS;
+}
+
 }  // namespace moep

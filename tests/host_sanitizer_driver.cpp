@@ -188,6 +188,15 @@ int main() {
     EXPECT(moep::routed_row_tiles(1, 1, 64) == 0 && moep::routed_row_tiles((int64_t)1 << 31, 32, 32) == ((int64_t)1 << 26) + 16);
   }
 
+  // ---- tokens dispatched by one workgroup: a thread each, 256 at least
+  for (int E = 2; E <= 32; ++E)
+    for (int k = 1; k <= 16; ++k) {
+      const int most = moep::dispatch_one_tokens(E, k);
+      EXPECT(most >= 256 && most <= moep::DISPATCH_ONE_MAX && (k == 1 || most <= moep::dispatch_one_tokens(E, k - 1)));
+    }
+  EXPECT(moep::dispatch_one_tokens(8, 2) == 1024 && moep::dispatch_one_tokens(16, 4) == 512 && moep::dispatch_one_tokens(32, 2) == 512);
+  EXPECT(moep::dispatch_one_tokens(24, 6) == 256 && moep::dispatch_one_tokens(32, 16) == 256 && moep::dispatch_one_tokens(16, 16) == 256);
+
   // ---- argument errors: every call must come back with a status and a message, having launched nothing
   void* p = (void*)(uintptr_t)(1 << 20);          // never dereferenced on the host
   float* fp = (float*)p;

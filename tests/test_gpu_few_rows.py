@@ -387,6 +387,19 @@ def test_dispatch_gives_every_token_its_experts(E, H, F, T):
     assert torch.equal(torch.sort(slot_of.reshape(-1)).values, torch.arange(3 * T, dtype=torch.int32, device=lg.device))
 
 
+@pytest.mark.parametrize("E,k", [(24, 8), (32, 16), (8, 8)])
+def test_dispatch_of_many_slots_gives_every_token_its_experts(E, k):
+    """256 tokens, the most that one workgroup dispatches with so many slots, and 257: every token as in a smaller batch."""
+    _, layer = small_layer("bf16", E, k, 64, 64, 257, index=38)
+    d = to_dev(layer)
+    rest = [d[n] for n in NAMES[1:]]
+    out, used, _, experts = pkg.moe_forward_skip_topk(d["x"], *rest, k, 0.1)
+    for t0, t1 in ((0, 256), (1, 257), (100, 229)):
+        o, u, _, e = pkg.moe_forward_skip_topk(d["x"][t0:t1].contiguous(), *rest, k, 0.1)
+        torch.cuda.synchronize()
+        assert torch.equal(u, used[t0:t1]) and torch.equal(e, experts[t0:t1]) and torch.equal(bits(o), bits(out[t0:t1].contiguous()))
+
+
 @pytest.mark.parametrize("E,H,T,k", [(8, 64, 1, 2), (8, 1088, 16, 2), (17, 128, 15, 2), (32, 4160, 16, 2), (16, 192, 7, 1), (20, 320, 16, 4),
                                      (16, 64, 16, 5)])
 def test_routing_with_the_router_in_one_launch_gives_the_same_bits(E, H, T, k):
