@@ -171,8 +171,12 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()           # (every such parameter is declared c_void_p, which takes an int)
 
 
+# The current stream's handle; a Stream object of torch.cuda.current_stream takes 2 us, and is what a torch without the other has.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
 def _stream(dev: torch.device):
-    return torch._C._cuda_getCurrentRawStream(dev.index)   # (a Stream object of torch.cuda.current_stream takes 2 us)
+    return _raw_stream(dev.index)
 
 
 def _workspace(nbytes: int, dev: torch.device, ws: Optional[torch.Tensor]) -> torch.Tensor:

@@ -1,12 +1,14 @@
 """Host-side logic of the C-ABI library: loads, exports, subset indexing, argument checks.
 No kernel is launched here."""
 import ctypes
+import importlib.util
 import itertools
 import math
 import os
 import re
 
 import pytest
+import torch
 
 import paper_2402_14800_amd as pkg
 from paper_2402_14800_amd import binding
@@ -250,3 +252,16 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True,
                        timeout=120)
     assert r.returncode == 2 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_stream_handle_without_the_private_query(monkeypatch):
+    """The binding asks torch for the raw stream where it can, for a Stream object where it has to: the same handle."""
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: Stream if device == 3 else None)
+    spec = importlib.util.spec_from_file_location("paper_2402_14800_amd._binding_again", binding.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    assert again._stream(torch.device("cuda", 3)) == 0x1234
