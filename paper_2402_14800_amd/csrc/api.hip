@@ -551,7 +551,7 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
     up.A = w + p.off_xp; up.B = w13; up.C = w + p.off_h;
     up.b_row_major = in_place; up.B1 = in_place ? W3 : nullptr;
     up.M = p.max_slots; up.N = F; up.K = H; up.epilogue = EPI_SWIGLU;
-    up.tile_expert = tile_expert; up.tile_row0 = tile_row0; up.seg_end = seg_end; up.tiles_in_use = tiles_in_use;
+    up.tile_expert = tile_expert; up.tile_row0 = tile_row0; up.seg_end = seg_end;
     up.max_m_tiles = p.max_tiles;
     up.stream = routed_weights_stream(p, true);
     up.tile_order = (const uint32_t*)(w + p.off_order_up);

@@ -146,7 +146,6 @@ struct PackedGemmArgs {
   const int32_t* tile_expert = nullptr;
   const int32_t* tile_row0 = nullptr;
   const int32_t* seg_end = nullptr;
-  const int32_t* tiles_in_use = nullptr;
   int64_t max_m_tiles = 0;
   // Grouped mode: the order in which the launch walks its tiles: TILE_ORDER_HEADER words, then entry i = (M tile << 12) |
   // N tile (see write_order in skip.hip).

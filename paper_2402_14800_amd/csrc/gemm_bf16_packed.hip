@@ -170,7 +170,7 @@ struct KArgs {
   bool stream;            // the weights are far more than the caches hold
   // grouped mode (rows partitioned into per-expert segments, tile t = rows tile_row0[t] .. of expert
   // tile_expert[t]; A and a packed C are indexed by TILE, a row-major C by row)
-  const int32_t* tile_expert; const int32_t* tile_row0; const int32_t* seg_end; const int32_t* tiles_in_use;
+  const int32_t* tile_expert; const int32_t* tile_row0; const int32_t* seg_end;
   int64_t b_expert_bytes;
   const float* row_scale;
   // dense batched mode: `experts` independent GEMMs of the same shape in one launch, tile ids expert-major;
@@ -209,8 +209,8 @@ __device__ __forceinline__ void gemm_body() {
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int wm = wave_u >> 1, wn = wave_u & 1;
   const int nsl = p.nsl;
-  // Grouped launches are sized for the largest possible tile map; only its leading entries hold work.
-  // Grouped: full-width tiles come first in the order, half-width ones after them.
+  // Grouped launches are sized for the largest possible tile map; the order says how many tiles there are: full-width ones first,
+  // half-width ones after them.
   const uint32_t m_tiles = (uint32_t)p.m_tiles, n_tiles = (uint32_t)p.n_tiles;
   const uint32_t per_expert = m_tiles * n_tiles;
   const uint32_t nblk = GROUPED ? p.tile_order[NG == 8 ? TILE_ORDER_FULL : TILE_ORDER_HALF] : per_expert * (uint32_t)p.experts;
@@ -810,13 +810,13 @@ int launch_gemm_bf16_packed(const PackedGemmArgs& g, hipStream_t s, const char* 
     return fail(MOEP_EUNSUPPORTED, "%s: operands must be 16-byte aligned", name);
   if (g.epilogue != EPI_SWIGLU && (g.ldc % 8 || g.ldc < g.N)) return fail(MOEP_EINVAL, "%s: bad leading dimension", name);
   const bool grouped = g.tile_expert != nullptr;
-  if (grouped && (!g.tile_row0 || !g.seg_end || !g.tiles_in_use || !g.tile_order || g.max_m_tiles <= 0))
+  if (grouped && (!g.tile_row0 || !g.seg_end || !g.tile_order || g.max_m_tiles <= 0))
     return fail(MOEP_EINVAL, "%s: incomplete tile map", name);
   if (g.epilogue == EPI_ROWSCALE_F32 && !g.row_scale) return fail(MOEP_EINVAL, "%s: row_scale is NULL", name);
   KArgs k = {};
   k.A = (const char*)g.A; k.B = (const char*)g.B; k.C = g.C;
   k.M = g.M; k.ldc = g.ldc; k.N = g.N; k.nsl = g.K / 32;
-  k.tile_expert = g.tile_expert; k.tile_row0 = g.tile_row0; k.seg_end = g.seg_end; k.tiles_in_use = g.tiles_in_use;
+  k.tile_expert = g.tile_expert; k.tile_row0 = g.tile_row0; k.seg_end = g.seg_end;
   if (g.b_row_major) {
     if (g.N % 64 || ((uintptr_t)g.B1 & 15) || (g.epilogue == EPI_SWIGLU && !g.B1))
       return fail(MOEP_EUNSUPPORTED, "%s: row-major weights need N=%d to be a multiple of 64 and 16-byte alignment", name, g.N);

@@ -3,7 +3,7 @@
 // Bandwidth-bound: x is read once, Wgate (E x H) stays in L1/L2.  bf16 goes through
 // router_mfma_kernel below; fp32 storage (and bf16 with H not a multiple of 32) through this kernel: a wavefront takes four
 // tokens at a time; lane l owns the h-chunks l, l + 64, ... of every row (16 bytes each), keeps
-// 4 x E partial sums and a butterfly of shuffles adds them across the lanes.  The summation
+// 4 x E partial sums, which are added across the lanes by halving (below).  The summation
 // order for a token depends on nothing but H, so the same token gives the same bits in any batch
 // -- moe_expert_outputs and moe_forward_skip rely on that.
 #include "common.h"
@@ -185,10 +185,13 @@ __global__ __launch_bounds__(W == 8 ? 512 : 256) void router_few_kernel(const ui
 }
 
 // Up to this many tokens two wavefronts per 16 tokens are faster than one; beyond it there are wavefronts enough to hide the loads.
-// Eight are faster still while a compute unit has no second workgroup of them, or where rows are long.  One / two / eight, us:
-// E 8, H 4096: 777 tokens 27.1 / 16.6 / 10.1, 4096 28.4 / 17.8 / 11.0, 32768 68.6 / - / 66.1; H 1024: 777 10.0 / 7.5 / 6.1, 8192
-// 10.6 / 8.0 / 8.6; E 16, H 2048, 8192 19.4 / 12.4 / 14.1.  With the packed copy of x: E 8, H 4096, 2048 tokens 44.6 / 21.4 / 13.8,
-// 16384 102.6 / 92.7 / 78.2, 32768 156.7 / - / 136.7; E 32, H 512, 8192 15.6 / 9.7 / 11.6.
+// Eight are faster still while a compute unit has no second workgroup of them, or where rows are long.  One / two / eight, us.
+// E 8: H 1024, 4096 tokens 10.5 / 8.0 / 6.2, 8192 10.5 / 8.1 / 8.6; H 2048, 4096 16.2 / 10.7 / 7.8, 8192 17.2 / 11.6 / 12.4; H 3072,
+// 4096 21.6 / 14.0 / 8.9, 8192 23.3 / 17.2 / 16.4, 16384 27.7 / 30.3 / 29.4; H 4096, 4096 28.2 / 17.6 / 11.2, 8192 30.1 / 26.6 / 23.0,
+// 32768 69.2 / 79.7 / 66.1, 49152 99.4 / 112 / 95.3; H 6144, 32768 106 / 108 / 104, 49152 146 / 156 / 152.  E 32: H 2048, 8192 27.0 /
+// 16.9 / 17.5; H 4096, 8192 49.2 / 33.1 / 29.9, 32768 101 / 105 / 103.  With the packed copy of x, E 8: H 1024, 8192 15.5 / 12.2 / 10.6; H 4096,
+// 4096 70.4 / 27.0 / 21.0, 16384 99.1 / 94.5 / 78.6, 32768 158 / 142 / 137.  (That copy leaves room: H 4096, 49152 tokens 214 / 189 / 172,
+// H 2048, 24576 71.8 / 59.5 / 58.1, with one wavefront now.)
 constexpr int64_t ROUTER_FEW_MAX = 8192, ROUTER_FEW_MAX_PACK = 16384, ROUTER_EIGHT_MAX = 4096, ROUTER_EIGHT_MAX_LONG = 32768;
 constexpr int ROUTER_LONG_H = 4096;
 

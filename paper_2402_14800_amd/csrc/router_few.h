@@ -15,9 +15,9 @@ __device__ __forceinline__ r_f32x4 sum_of_eight(F part) {
   return ((part(0) + part(4)) + (part(2) + part(6))) + ((part(1) + part(5)) + (part(3) + part(7)));
 }
 
-// The same for few tokens, where a wavefront's serial walk over H is all there is (27 us for 777 tokens of H = 4096, 11 for one):
-// W = 2 or 8 wavefronts share 16 tokens, wavefront w takes the slices w, w + W, ..., each with 32 or 16 of them in flight, and the
-// eight sums (acc[] above) are added at the end -- the sums of the kernel above, bit for bit.
+// router_mfma_kernel (router.hip) for few tokens, where a wavefront's serial walk over H is all there is (27 us for 777 tokens of H =
+// 4096, 11 for one): W = 2 or 8 wavefronts share 16 tokens, wavefront w takes the slices w, w + W, ..., each with 32 or 16 of them in
+// flight, and the eight sums are added at the end -- the sums of that kernel, bit for bit.
 // The workgroup has 64 W wavefront lanes per 16 tokens: 512 threads and 16 tokens (W = 8) or 256 and 32.
 template <bool PACK, bool WIDE, int W>
 __device__ __forceinline__ void router_few(const uint4* __restrict__ x, const uint4* __restrict__ Wgate, float* __restrict__ logits,

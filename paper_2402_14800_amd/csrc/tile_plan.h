@@ -16,9 +16,9 @@ constexpr bool half_width_pays(int64_t tiles) { return tiles <= 128; }
 // that half of the compute units would otherwise sit out.  us per call, without / with: E 16, H 2304, F 2368, T = 3133
 // (2.4 rounds) 339 / 315; E 8, H 1920, F 7168, top-4, T = 2240 778 / 723; E 8, H 4096, F 14336, T = 969 899 / 882.  Below
 // TAIL_MIN_K what a tile saves goes into the second ring's fill (E 4, H 576, F 4032, top-4, T = 544 92 / 97; E 8, H 896, F 1984,
-// T = 2427 109 / 111).  Not with tiles of up to 128 rows (row_groups 4), whose
-// steps are the load of the weights: E 8, H 4096, F 14336, T = 262 581 / 606, E 16, H 2048, F 5632, T = 900 275 / 286.  n_full, n_half: tiles of either width along N; the launch's table has room for n_half per M tile, which
-// is enough for both kinds where n_half > n_full.
+// T = 2427 109 / 111).  Not with tiles of up to 128 rows (row_groups 4), whose steps are the load of the weights: E 8, H 4096,
+// F 14336, T = 262 581 / 606, E 16, H 2048, F 5632, T = 900 275 / 286.  n_full, n_half: tiles of either width along N; the launch's
+// table has room for n_half per M tile, which is enough for both kinds where n_half > n_full.
 constexpr int TAIL_MIN_K = 1024;
 constexpr int64_t tail_tiles(int64_t tiles, int n_full, int n_half, int k, int row_groups) {
   return tiles > 256 && n_half > n_full && k >= TAIL_MIN_K && row_groups > 4 && half_width_pays(tiles & 255) ? tiles & 255 : 0;
@@ -32,16 +32,17 @@ constexpr bool streams_weights(int N, int K, bool gate_up, int experts) {
 
 // Rows per tile of a routed launch: 256, or SHORT_TILE_ROWS where the call's two launches are shorter with that.  What they
 // cost is the rounds of 256 tiles (compute units) that they take, each as many steps as its K is deep and the epilogue: about
-// 4 steps of 32 for the SwiGLU one, 24 for the row-scaled one, whose loads wait for each other.  A 192-row tile costs 13/16 of a
-// 256-row one (6/8 of the products, but the same weights), and a launch of half-width tiles, which fits one round, 10/16 of a
-// round.  256 / 192 rows, us per call: Mixtral shape, T = 1500 (about 281 rows per expert, two tiles either way) 1081 / 938,
-// T = 3000 1687 / 1586, T = 2000 (375 rows: two or three tiles) 1116 / 1323; E 8, H 1024, F 3584, T = 1500 131 / 111,
-// T = 6000 261 / 247; E 16, H 2048, F 5632, top-4, T = 1200 497 / 438, T = 1500 (a 257th tile in the down projection)
-// 515 / 563; E 32, H 512, F 1472, T = 8192 159 / 150.  The epilogues matter where K is a few hundred (E 32, H 3136, F 128,
-// T = 3006, three rounds of 4 steps for two: 148 / 166; E 32, H 1664, F 64, top-4, T = 1591 101 / 107).  Of 138 random shapes
-// (H 64 to 4096, F 64 to 12800, 150 to 900 rows per expert) that the depths alone would cut, into another number of rounds, the
-// epilogues leave 15 whole: six 3 to 8 % faster so, one 8 % slower, the rest within 2 %.  The other 123 gain 5.5 % on average;
-// five of them lose 4 to 10 % (the worst E 4, H 1088, F 8128, T = 412 135 / 148, twice as many tiles of half the width).
+// 4 steps of 32 for the SwiGLU one, 24 for the row-scaled one.  A 192-row tile costs 13/16 of a 256-row one (6/8 of the products,
+// but the same weights), and a launch of half-width tiles, which fits one round, 10/16 of a round.  256 / 192 rows, us per call, no
+// token skipped: E 16, H 2048, F 5632, top-4, T = 1200 492 / 435, T = 1500 (a 257th tile in the down projection) 495 / 527; E 8, H 1024,
+// F 3584, T = 1500 126 / 120; Mixtral shape, T = 2000 1368 / 1339, T = 777 with some expert beyond 192 rows 762 / 875.  The epilogues
+// matter where K is a few hundred (E 32, H 3136, F 128, T = 3006, three rounds of 4 steps for two: 122 / 141; E 32, H 1664, F 64, top-4,
+// T = 1591 85 / 88).
+// The price counts whole rounds: neither a last round in half tiles (above) nor the row-scaled epilogue's loads, which have come
+// together since the 24 steps were fitted, are in it.  Where they would turn the choice, both heights were timed: Mixtral shape, T = 900
+// 755 / 944, E 4, H 1408, F 4096, top-4, T = 4647 598 / 598, E 32, H 2176, F 960, top-4, T = 4206 372 / 338: the present price takes
+// the shorter one of each.  It is wrong where twice as many tiles of half the width are dearer than it has them (E 4, H 1088, F 8128,
+// T = 412 133 / 143).
 struct Shorten { int n_up = 0, n_down = 0, k_up = 0, k_down = 0; };   // full-width N tiles of the launches; n_up = 0: tiles as given
 constexpr int SHORT_TILE_ROWS = 192;
 constexpr int EPILOGUE_UP = 4 * 32, EPILOGUE_DOWN = 24 * 32;          // in units of K

@@ -165,6 +165,22 @@ int main() {
     EXPECT(!pays(3136, 128, 32, 45) && !pays(1664, 64, 32, 54) && !pays(1984, 128, 32, 40) && !pays(1920, 64, 64, 79));
   }
 
+  // ---- a last round of up to 128 tiles in half the width: from two rounds on, K deep enough, more than 128 rows, and a table that holds both
+  {
+    auto tail = [](int64_t tiles, int k = 1024, int row_groups = 8, int n_half = 16) { return moep::tail_tiles(tiles, 8, n_half, k, row_groups); };
+    EXPECT(tail(1) == 0 && tail(128) == 0 && tail(256) == 0 && tail(257) == 1 && tail(384) == 128 && tail(385) == 0 && tail(511) == 0);
+    EXPECT(tail(512) == 0 && tail(513) == 1 && tail(640) == 128 && tail(641) == 0);
+    EXPECT(tail(300, 1023) == 0 && tail(300, 1024) == 44 && tail(300, 1024, 6) == 44 && tail(300, 1024, 4) == 0);
+    EXPECT(tail(300, 1024, 8, 8) == 0 && tail(300, 1024, 8, 15) == 44);
+    for (int n_full = 1; n_full <= 200; ++n_full)
+      for (int n_half : {2 * n_full - 1, 2 * n_full})
+        for (int64_t m_tiles = 1; m_tiles <= 600; ++m_tiles) {
+          const int64_t tiles = m_tiles * n_full, t = moep::tail_tiles(tiles, n_full, n_half, 4096, 8);
+          EXPECT(t >= 0 && t <= 128 && tiles + t <= m_tiles * n_half);
+          if (t) EXPECT((tiles - t) % 256 == 0 && tiles - t >= 256);
+        }
+  }
+
   // ---- weights of a routed call that are loaded past the caches: of the kept experts, not of the layer (gate/up 738 MB, 184 MB of
   // four experts, 92 MB of two; down half of that)
   {
