@@ -146,7 +146,10 @@ int main() {
     EXPECT(records(65536, 16, 1024, 2, {14}) && !records(65536, 16, 960, 2, {14}));              // rows long enough
     EXPECT(records(65536, 8, 1024, 2, {6, 4}, MOEP_F32) && !records(65536, 8, 960, 2, {6, 4}, MOEP_F32));
     EXPECT(!records(32000, 9, 2048, 2, {6}, MOEP_F32) && records(32000, 9, 2048, 2, {6}));       // seven rows of padding
-    EXPECT(records(18432, 16, 64, 4, {12}, MOEP_BF16, 8) && !records(18433, 16, 64, 4, {12}, MOEP_BF16, 8));   // 8 ranked rows per token
+    EXPECT(records(15360, 16, 64, 4, {12}, MOEP_BF16, 8) && !records(15361, 16, 64, 4, {12}, MOEP_BF16, 8));   // 8 ranked rows per token
+    EXPECT(records(12288, 4, 64, 2, {2}, MOEP_BF16, 4) && !records(12289, 4, 64, 2, {2}, MOEP_BF16, 4));       // 4
+    EXPECT(records(10752, 16, 64, 4, {12}, MOEP_BF16, 9) && !records(10753, 16, 64, 4, {12}, MOEP_BF16, 9));   // 9
+    EXPECT(!records(65536, 2, 4096, 1, {1}, MOEP_BF16, 2) && records(65536, 3, 704, 2, {2}, MOEP_BF16, 3));    // 2 and 3: padding
     EXPECT(records(40000, 16, 512, 4, {12}, MOEP_BF16, 8) && !records(40000, 16, 448, 4, {12}, MOEP_BF16, 8));
     EXPECT(records(700, 8, 192, 2, {5, 6, 7}) && records(700, 8, 192, 1, {5, 6, 7, 8}));         // three and four r that fit
     EXPECT(!records(5600, 8, 192, 2, {4, 6, 7, 1}) && !records(700, 8, 192, 2, {4, 6, 7, 1}));   // four that do not
