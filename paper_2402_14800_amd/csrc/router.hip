@@ -190,10 +190,11 @@ __global__ __launch_bounds__(W == 8 ? 512 : 256) void router_few_kernel(const ui
 // 4096 21.6 / 14.0 / 8.9, 8192 23.3 / 17.2 / 16.4, 16384 27.7 / 30.3 / 29.4; H 4096, 4096 28.2 / 17.6 / 11.2, 8192 30.1 / 26.6 / 23.0,
 // 32768 69.2 / 79.7 / 66.1, 49152 99.4 / 112 / 95.3; H 6144, 32768 106 / 108 / 104, 49152 146 / 156 / 152.  E 32: H 2048, 8192 27.0 /
 // 16.9 / 17.5; H 4096, 8192 49.2 / 33.1 / 29.9, 32768 101 / 105 / 103.  With the packed copy of x, E 8: H 1024, 8192 15.5 / 12.2 / 10.6; H 4096,
-// 4096 70.4 / 27.0 / 21.0, 16384 99.1 / 94.5 / 78.6, 32768 158 / 142 / 137.  (That copy leaves room: H 4096, 49152 tokens 214 / 189 / 172,
-// H 2048, 24576 71.8 / 59.5 / 58.1, with one wavefront now.)
+// 4096 70.4 / 27.0 / 21.0, 16384 99.1 / 94.5 / 78.6, 32768 158 / 142 / 137.  Short rows
+// with it: H 64, 12000 tokens 6.7 / 10.4 / 9.2, H 256 8.8 / 11.5 / 10.6, H 384 10.7 / 12.6 / 11.8, H 512, 16384 11.1 / 11.8 / 12.9.
+// (It leaves room: H 4096, 49152 tokens 214 / 189 / 172, H 2048, 24576 71.8 / 59.5 / 58.1, with one wavefront now.)
 constexpr int64_t ROUTER_FEW_MAX = 8192, ROUTER_FEW_MAX_PACK = 16384, ROUTER_EIGHT_MAX = 4096, ROUTER_EIGHT_MAX_LONG = 32768;
-constexpr int ROUTER_LONG_H = 4096;
+constexpr int ROUTER_LONG_H = 4096, ROUTER_SHORT_H = 512;
 
 template <bool PACK>
 void launch_mfma(const void* x, const void* Wgate, int64_t T, int E, int H, float* logits, void* xpacked,
@@ -207,7 +208,7 @@ void launch_mfma(const void* x, const void* Wgate, int64_t T, int E, int H, floa
     else MOEP_ROUTER_FEW(false, 8, 1);
     return;
   }
-  if (T <= (PACK ? ROUTER_FEW_MAX_PACK : ROUTER_FEW_MAX)) {
+  if (T <= (PACK && H >= ROUTER_SHORT_H ? ROUTER_FEW_MAX_PACK : ROUTER_FEW_MAX)) {
     if (E > 16) MOEP_ROUTER_FEW(true, 2, 2);
     else MOEP_ROUTER_FEW(false, 2, 2);
     return;
