@@ -581,7 +581,7 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
   up.seg_end = (const int32_t*)(w + p.off_seg_end);
   up.max_m_tiles = p.max_tiles;
   up.tiles_in_use = up.tile_expert + p.max_tiles;
-  up.busy_experts = p.kept_experts;
+  up.busy_experts = p.kept_experts; up.rows_unknown = p.may_skip;
   if (int st = launch_gemm_f32(up, s, "gemm_gate_up_swiglu_routed")) return st;
 
   GemmArgs down;                    // slot_out[slot] = weight(slot) * h[slot] W2[e]^T, fp32
@@ -594,7 +594,7 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
   down.tile_expert = up.tile_expert; down.tile_row0 = up.tile_row0; down.seg_end = up.seg_end;
   down.max_m_tiles = p.max_tiles;
   down.tiles_in_use = up.tiles_in_use;
-  down.busy_experts = up.busy_experts;
+  down.busy_experts = up.busy_experts; down.rows_unknown = up.rows_unknown;
   return launch_gemm_f32(down, s, "gemm_down_routed");
 }
 
@@ -634,6 +634,7 @@ static int forward_pruned_skip(const void* x, const void* Wgate, const void* W1,
   if (!x || !out || !skip_mask) return fail(MOEP_EINVAL, "%s: NULL x, out or skip_mask", who);
   SkipPlan p;
   if (int st = plan_skip(T, E, H, F, dt, 2, __builtin_popcount(kept_mask), &p)) return st;
+  p.may_skip = beta > 0;
   if (int st = check_ws(ws, ws_bytes, p.total, who)) return st;
   hipStream_t s = (hipStream_t)hip_stream;
   char* w = (char*)ws;
@@ -718,6 +719,7 @@ int moe_forward_skip_topk(const void* x, const void* Wgate, const void* W1, cons
   if (!x || !out || !n_used) return fail(MOEP_EINVAL, "%s: NULL x, out or n_used", who);
   SkipPlan p;
   if (int st = plan_skip(T, E, H, F, dt, k, __builtin_popcount(kept_mask), &p)) return st;
+  p.may_skip = beta > 0 && k > 1;
   if (int st = check_ws(ws, ws_bytes, p.total, who)) return st;
   hipStream_t s = (hipStream_t)hip_stream;
   char* w = (char*)ws;

@@ -109,7 +109,8 @@ struct GemmArgs {
   void* C_rest = nullptr;
   int64_t a_expert_stride = 0, c_expert_stride = 0;
   int64_t max_m_tiles = 0;              // grouped: number of entries in tile_expert/tile_row0
-  int busy_experts = 1;                 // grouped: experts that can have rows
+  int busy_experts = 1;                 // grouped: experts that can have rows,
+  bool rows_unknown = false;            //   and whether a threshold can leave them much fewer than M
   const int32_t* tiles_in_use = nullptr; // grouped, optional: device count of leading entries that hold work
 };
 

@@ -36,6 +36,7 @@ struct FArgs {
   int N, K;
   bool c_by_word;                                          // C or C_rest is not 16-byte aligned: stored float by float
   bool by_register;                                        // the weights are not 16-byte aligned
+  bool columns_first;                                      // blockIdx.x walks the column tiles, y the row tiles
 };
 
 template <int EPI, int TM, int TB, int AHEAD>    // TM = rows, TB = accumulator columns per tile; AHEAD = slabs in flight
@@ -46,25 +47,26 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
   constexpr int TN = EPI == EPI_SWIGLU ? TB / 2 : TB;      // output columns
   __shared__ __attribute__((aligned(16))) float lds[AHEAD + 1][SLAB];
 
-  // blockIdx.x walks TM-row sub-tiles; in grouped mode GEMM_BM / TM of them share one 256-row map entry.
+  // A row tile is a TM-row sub-tile; in grouped mode GEMM_BM / TM of them share one 256-row map entry.
+  const unsigned row_tile = p.columns_first ? blockIdx.y : blockIdx.x, column_tile = p.columns_first ? blockIdx.x : blockIdx.y;
   int64_t row0, row_end;
   int64_t expert = blockIdx.z;
   if (p.tile_expert) {
-    const int t = blockIdx.x / (GEMM_BM / TM);
+    const int t = row_tile / (GEMM_BM / TM);
     expert = p.tile_expert[t];
     if (expert < 0) return;
-    row0 = (int64_t)p.tile_row0[t] + (blockIdx.x % (GEMM_BM / TM)) * TM;
+    row0 = (int64_t)p.tile_row0[t] + (row_tile % (GEMM_BM / TM)) * TM;
     row_end = p.seg_end[expert];
     if (row0 >= row_end) return;
   } else {
-    row0 = (int64_t)blockIdx.x * TM;
+    row0 = (int64_t)row_tile * TM;
     row_end = p.M;
   }
   const float* const A = blockIdx.z && p.A_rest ? p.A_rest + (blockIdx.z - 1) * p.a_expert_stride : p.A;
   float* const C = blockIdx.z ? p.C_rest + (blockIdx.z - 1) * p.c_expert_stride : p.C;
   const float* const B0 = p.B0 + expert * p.b_expert_stride;
   const float* const B1 = EPI == EPI_SWIGLU ? p.B1 + expert * p.b_expert_stride : nullptr;
-  const int n0 = blockIdx.y * TN;
+  const int n0 = column_tile * TN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
 
@@ -223,11 +225,15 @@ int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name) {
   // 64 x 128 accumulators per tile, 32 x 128 where those are few, 32 x 64 where these are
   const int tm = m_tiles(64) * n_tiles(128) * g.experts < SMALL_TILES_BELOW ? 32 : 64;
   const int tb = tm == 32 && m_tiles(32) * n_tiles(128) * g.experts < NARROW_TILES_BELOW ? 64 : 128;
-  // (weights that are not 16-byte aligned use two stages only: as many workgroups per compute unit as there can be)
+  // (weights that are not 16-byte aligned use two stages only: as many workgroups per compute unit as there can be; so it is with
+  // rows that a threshold leaves, whose number is known on the device only: 150 routed layers of 200 to 8000 tokens with one, against a
+  // slab in registers, geometric mean and worst: one ahead 0.75, 1.00, two 0.77, 1.13, by a share of rows guessed from it 0.75, 1.03)
   const int64_t tiles = (g.tile_expert ? routed_row_tiles(g.M, g.busy_experts, tm) : ceil_div(g.M, tm)) * n_tiles(tb) * g.experts;
-  const int ahead = f.by_register && tiles > 512 ? 1 : f32_slabs_ahead(tiles, 2, tm == 64 ? 3 : 4);
-  if (m_tiles(tm) > 2147483647LL || n_tiles(tb) > 65535) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
+  const int ahead = (f.by_register && tiles > 512) || g.rows_unknown ? 1 : f32_slabs_ahead(tiles, 2, tm == 64 ? 3 : 4);
+  if (m_tiles(tm) > 2147483647LL || n_tiles(tb) > GRID_Y_MAX) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
   dim3 grid((unsigned)m_tiles(tm), (unsigned)n_tiles(tb), (unsigned)g.experts);
+  f.columns_first = f32_columns_first(g.tile_expert != nullptr, m_tiles(tm));
+  if (f.columns_first) grid = dim3((unsigned)n_tiles(tb), (unsigned)m_tiles(tm), 1);
   Timed t(name, s);
 #define MOEP_F32_LAUNCH(EPI, TM, TB, AHEAD) hipLaunchKernelGGL((gemm_f32_kernel<EPI, TM, TB, AHEAD>), grid, dim3(THREADS), 0, s, f)
 #define MOEP_F32_CASE(EPI)                                                                              \

@@ -14,6 +14,7 @@ struct SkipPlan {
   int ks;                // slots per token (2 for the top-2 rule, k for the generalised rule)
   int kept_experts;      // experts that tokens can be routed to
   int64_t max_slots;     // ks T
+  bool may_skip = false; // a threshold above zero: any part of them can be left
   bool few;              // bf16, few rows per expert: gemm_few.hip, no operand is re-laid out
   int tile_rows;         // rows per tile of the map
   int64_t max_tiles;     // upper bound on M tiles over all experts

@@ -204,6 +204,7 @@ int main() {
     for (int64_t tiles : {1500, 1536, 1537, 2048, 4000, 100000}) EXPECT(tall(tiles) == 1);
     EXPECT(low(512) == 2 && low(513) == 1 && low(1024) == 1);
     EXPECT(moep::routed_row_tiles(4000, 4, 64) == 64 && moep::routed_row_tiles(4000, 8, 64) == 66 && moep::routed_row_tiles(3000, 8, 32) == 97);
+    EXPECT(moep::f32_columns_first(true, 1) && moep::f32_columns_first(true, 65535) && !moep::f32_columns_first(true, 65536) && !moep::f32_columns_first(false, 8));
     EXPECT(moep::routed_row_tiles(1, 1, 64) == 0 && moep::routed_row_tiles((int64_t)1 << 31, 32, 32) == ((int64_t)1 << 26) + 16);
   }
 
