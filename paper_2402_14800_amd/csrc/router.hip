@@ -81,7 +81,9 @@ __global__ __launch_bounds__(256) void router_kernel(const void* __restrict__ x,
     // Sums over the lanes, 32, 16, ..., 1 apart.  A lane keeps half of its values at each distance and gives the others away, so
     // that TOK x EMAX of them take about as many exchanges, where a butterfly per value took six for each.  With the branches
     // per expert gone as well: all experts of a layer, E 8, H 512, F 1024, 1501 tokens 439 -> 431 us, E 16, H 1024, F 512, 64 tokens
-    // 153 -> 137.
+    // 153 -> 137.  All EMAX columns are multiplied, so the forms are a factor of two apart: this kernel, fp32, H 2048,
+    // us, with the branches / by 8 columns / by 4: E 2, 64 tokens 8.2 / 9.1 / 7.2, 12000 19.2 / 22.6 / 19.4; E 3, 12000 22.6 / 24.5 / 20.9;
+    // E 17 by 32 columns, 12000 130 / 111.
     float v[TOK * EMAX];
 #pragma unroll
     for (int i = 0; i < TOK; ++i)
@@ -234,7 +236,8 @@ int launch_t(const void* x, const void* Wgate, int64_t T, int E, int H, float* l
   }
   const int64_t groups = ceil_div(T, TOK);
   const unsigned blocks = (unsigned)(ceil_div(groups, 4) < 16384 ? ceil_div(groups, 4) : 16384);
-  if (E <= 8) hipLaunchKernelGGL((router_kernel<BF16, 8>), dim3(blocks), dim3(256), 0, s, x, Wgate, logits, T, E, H);
+  if (E <= 4) hipLaunchKernelGGL((router_kernel<BF16, 4>), dim3(blocks), dim3(256), 0, s, x, Wgate, logits, T, E, H);
+  else if (E <= 8) hipLaunchKernelGGL((router_kernel<BF16, 8>), dim3(blocks), dim3(256), 0, s, x, Wgate, logits, T, E, H);
   else if (E <= 16) hipLaunchKernelGGL((router_kernel<BF16, 16>), dim3(blocks), dim3(256), 0, s, x, Wgate, logits, T, E, H);
   else hipLaunchKernelGGL((router_kernel<BF16, 32>), dim3(blocks), dim3(256), 0, s, x, Wgate, logits, T, E, H);
   MOEP_HIP(hipGetLastError());

@@ -52,6 +52,21 @@ def test_logits_of_the_forms_by_length_of_a_row_are_the_same_bits(E, H, sizes):
         assert torch.equal(dense, full[:n]) and torch.equal(routed, full[:n])
 
 
+@pytest.mark.parametrize("E", [2, 4, 5])
+@pytest.mark.parametrize("H,T", [(4, 3), (516, 65), (2048, 1025)])
+def test_fp32_logits_of_few_experts_are_those_among_more(E, H, T):
+    """Up to 4, 8 and 16 experts are forms of their own: an expert's logit is the same bits in each, and near its sum in 64 bits
+    (H products and at most H additions, each off by 2^-24 of the sum of magnitudes)."""
+    _, layer = small_layer("f32", 16, 2, H, 64, T, index=39)
+    d = to_dev(layer)
+    full, _ = pkg.moe_expert_outputs(*[d[n] for n in NAMES])
+    few, _ = pkg.moe_expert_outputs(d["x"], *[d[n][:E].contiguous() for n in NAMES[1:]])
+    torch.cuda.synchronize()
+    assert torch.equal(few, full[:, :E].contiguous())
+    x, w = layer["x"].double(), layer["Wgate"][:E].double()
+    assert bool(((few.cpu().double() - x @ w.t()).abs() <= 2 * H * 2.0 ** -24 * (x.abs() @ w.abs().t())).all())
+
+
 @pytest.mark.parametrize("E,T,n", [(8, 16400, 3), (5, 8193, 2), (32, 9000, 1)])
 def test_slots_of_many_routing_blocks(E, T, n):
     """Rows of the rank-limited pass: grouped by expert, ascending token within an expert, nothing left out."""
