@@ -48,6 +48,14 @@ __global__ __launch_bounds__(ONE ? ONE_THREADS : SB_THREADS) void stats_kernel(
   __shared__ unsigned int tab[EMAX][EMAX];
   __shared__ unsigned long long totals[EMAX];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t stride = (int64_t)gridDim.x * THREADS;
+  float next[EMAX];                          // (the first tokens' logits are on their way during the set-up, the next ones' while these are counted)
+  auto fetch = [&](int64_t t0) {
+    const int64_t t = t0 + lane < T ? t0 + lane : T - 1;
+    load_logits<EMAX>(logits, t, E, vec, next);
+  };
+  int64_t t0 = (int64_t)blockIdx.x * THREADS + wave * 64;
+  if (t0 < T) fetch(t0);
   for (int i = threadIdx.x; i < EMAX * EMAX; i += THREADS) (&tab[0][0])[i] = 0;
   // lane p owns pairs p, p + 64, ... of the upper triangle (i <= j), row by row
   int pi[OWN], pj[OWN];
@@ -62,14 +70,6 @@ __global__ __launch_bounds__(ONE ? ONE_THREADS : SB_THREADS) void stats_kernel(
     n[o] = 0;
   }
   __syncthreads();
-  const int64_t stride = (int64_t)gridDim.x * THREADS;
-  float next[EMAX];                          // (the next tokens' logits are on their way while these are counted)
-  auto fetch = [&](int64_t t0) {
-    const int64_t t = t0 + lane < T ? t0 + lane : T - 1;
-    load_logits<EMAX>(logits, t, E, vec, next);
-  };
-  int64_t t0 = (int64_t)blockIdx.x * THREADS + wave * 64;
-  if (t0 < T) fetch(t0);
   for (; t0 < T; t0 += stride) {
     const int64_t t = t0 + lane;
     uint32_t mask = 0;                       // expert e is in the top-k iff fewer than k experts come before it
