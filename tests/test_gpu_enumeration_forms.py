@@ -1,6 +1,8 @@
 """The enumeration's reduction on both sides of its one-workgroup form, scoring tiles dealt to strands of wavefronts, and
 the record capacities of the routing prep, against the fp64 oracle (losses: fp32 sums within a tile of 32 tokens and up to
 a few hundred fp32 operations per term, 1e-5 relative covers both)."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -151,3 +153,15 @@ def test_a_loss_of_several_r_can_be_written_under_autograd():
     loss = pkg.prune_enumerate_multi(logits, Y, 2, [6, 4])[0][0]
     loss.mul_(weight)                                    # (a view of a multi-output operation would refuse this)
     assert loss.requires_grad
+
+
+@pytest.mark.parametrize("k,r", [(2, 4), (3, 4), (2, 2)])
+def test_unaffected_pairs_are_counted_with_ties_as_without(k, r):
+    """Equal logits are ranked by index, so every token leaves C(E - k, r - k) subsets without change, ties or not."""
+    E, T = 6, 200
+    logits, Y = wl.make_enumeration_inputs(E, T, 64, "bf16", seed=9, device="cuda:0")
+    logits[::7, 2] = logits[::7, 0]
+    logits[1::7] = 0.5
+    unaffected = pkg.prune_enumerate(logits, Y, k, r)[3]
+    torch.cuda.synchronize()
+    assert unaffected.item() == T * math.comb(E - k, r - k)
