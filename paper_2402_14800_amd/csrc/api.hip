@@ -576,11 +576,7 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
   up.C = w + p.off_h; up.ldc = F;
   up.M = p.max_slots; up.N = F; up.K = H;
   up.epilogue = EPI_SWIGLU;
-  up.tile_expert = (const int32_t*)(w + p.off_tile_expert);
-  up.tile_row0 = (const int32_t*)(w + p.off_tile_row0);
-  up.seg_end = (const int32_t*)(w + p.off_seg_end);
-  up.max_m_tiles = p.max_tiles;
-  up.tiles_in_use = up.tile_expert + p.max_tiles;
+  up.seg_end = (const int32_t*)(w + p.off_seg_end); up.segments = p.E;
   up.busy_experts = p.kept_experts; up.rows_unknown = p.may_skip;
   if (int st = launch_gemm_f32(up, s, "gemm_gate_up_swiglu_routed")) return st;
 
@@ -591,9 +587,7 @@ static int run_routed_ffn(const SkipPlan& p, const void* x, const void* W1, cons
   down.M = p.max_slots; down.N = H; down.K = F;
   down.epilogue = plain_out ? EPI_STORE : EPI_ROWSCALE_F32;
   down.row_scale = plain_out ? nullptr : (const float*)(w + p.off_slot_scale);
-  down.tile_expert = up.tile_expert; down.tile_row0 = up.tile_row0; down.seg_end = up.seg_end;
-  down.max_m_tiles = p.max_tiles;
-  down.tiles_in_use = up.tiles_in_use;
+  down.seg_end = up.seg_end; down.segments = up.segments;
   down.busy_experts = up.busy_experts; down.rows_unknown = up.rows_unknown;
   return launch_gemm_f32(down, s, "gemm_down_routed");
 }

@@ -95,12 +95,9 @@ struct GemmArgs {
   int N = 0, K = 0;
   int epilogue = EPI_STORE;
   const float* row_scale = nullptr;
-  // Grouped mode (rows partitioned into per-expert segments): tile t of the M
-  // dimension covers rows [tile_row0[t], min(tile_row0[t] + BM, seg_end[tile_expert[t]]))
-  // and multiplies with expert tile_expert[t]'s weights; tile_expert[t] < 0 = no work.
-  const int32_t* tile_expert = nullptr;
-  const int32_t* tile_row0 = nullptr;
-  const int32_t* seg_end = nullptr;     // [E] end row (exclusive) of each expert's segment
+  // Grouped mode: rows seg_end[e - 1] (0) .. seg_end[e] - 1 are multiplied with expert e's weights, e < segments (0: dense).
+  const int32_t* seg_end = nullptr;
+  int segments = 0;
   int64_t b_expert_stride = 0;          // elements between consecutive experts' weights
   // Dense batched mode: `experts` GEMMs of the same shape in one launch.  Expert 0 reads A and writes C; expert e > 0
   // reads A_rest + (e - 1) a_expert_stride (A_rest NULL: A as well) and writes C_rest + (e - 1) c_expert_stride (elements).
@@ -108,13 +105,11 @@ struct GemmArgs {
   const void* A_rest = nullptr;
   void* C_rest = nullptr;
   int64_t a_expert_stride = 0, c_expert_stride = 0;
-  int64_t max_m_tiles = 0;              // grouped: number of entries in tile_expert/tile_row0
   int busy_experts = 1;                 // grouped: experts that can have rows,
   bool rows_unknown = false;            //   and whether a threshold can leave them much fewer than M
-  const int32_t* tiles_in_use = nullptr; // grouped, optional: device count of leading entries that hold work
 };
 
-constexpr int GEMM_BM = 256;   // rows per tile of either GEMM implementation's grouped map
+constexpr int GEMM_BM = 256;   // rows per tile of the grouped map
 // bf16 packed GEMM: M tiles per group of tiles that an XCD works through together, and output columns per tile,
 // for the gate/up (SwiGLU) and the down projection (measured: the long-K down projection prefers 4 x 8 tiles per XCD)
 constexpr int GEMM_GROUP_M_SWIGLU = 8, GEMM_GROUP_M_STORE = 4;

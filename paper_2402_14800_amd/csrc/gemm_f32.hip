@@ -29,7 +29,7 @@ struct FArgs {
   const int32_t* a_rows;
   float* C;
   const float* row_scale;
-  const int32_t* tile_expert; const int32_t* tile_row0; const int32_t* seg_end;
+  const int32_t* seg_end; int segments;                    // routed: the experts' segment ends; segments 0: dense
   int64_t M, lda, ldc, b_expert_stride;
   const float* A_rest; float* C_rest;                      // dense, blockIdx.z = expert: experts 1, 2, ...
   int64_t a_expert_stride, c_expert_stride;
@@ -47,17 +47,31 @@ __global__ __launch_bounds__(THREADS) void gemm_f32_kernel(FArgs p) {
   constexpr int TN = EPI == EPI_SWIGLU ? TB / 2 : TB;      // output columns
   __shared__ __attribute__((aligned(16))) float lds[AHEAD + 1][SLAB];
 
-  // A row tile is a TM-row sub-tile; in grouped mode GEMM_BM / TM of them share one 256-row map entry.
   const unsigned row_tile = p.columns_first ? blockIdx.y : blockIdx.x, column_tile = p.columns_first ? blockIdx.x : blockIdx.y;
   int64_t row0, row_end;
   int64_t expert = blockIdx.z;
-  if (p.tile_expert) {
-    const int t = row_tile / (GEMM_BM / TM);
-    expert = p.tile_expert[t];
-    if (expert < 0) return;
-    row0 = (int64_t)p.tile_row0[t] + (row_tile % (GEMM_BM / TM)) * TM;
-    row_end = p.seg_end[expert];
-    if (row0 >= row_end) return;
+  if (p.segments) {
+    // The experts' tiles of TM rows one after the other, lane e holding expert e's, so that the row tiles without rows are the last ones
+    // of the grid.  Workgroups are dealt to the compute units in turn, whichever of them return at once: from a map of 256-row tiles,
+    // whose first TM-row part always has rows and whose last often has none, the first parts met on the same compute units and some of
+    // these had a round more.  us per call, nothing skipped, from the map / so: E 16, H 1024, F 512, T = 2000 215 / 213, 2500 288 / 217,
+    // 2750 337 / 218; E 4, H 1472, F 1908, T = 244 201 / 128; launches of 10 us are up to 0.5 us longer (E 8, H 156, F 96, top-3,
+    // T = 2594 42.1 / 43.4).
+    const int l = threadIdx.x & 63;
+    const int end = l < p.segments ? p.seg_end[l] : 0;
+    const int begin = __builtin_amdgcn_update_dpp(0, end, 0x138, 0xf, 0xf, true);            // the lane before (lane 0: 0)
+    const int tiles = l < p.segments ? (int)(((unsigned)(end - begin) + TM - 1) / TM) : 0;
+    int through = tiles;                                   // tiles of the experts up to this lane's: sums over 16 lanes,
+    through += __builtin_amdgcn_update_dpp(0, through, 0x111, 0xf, 0xf, true);
+    through += __builtin_amdgcn_update_dpp(0, through, 0x112, 0xf, 0xf, true);
+    through += __builtin_amdgcn_update_dpp(0, through, 0x114, 0xf, 0xf, true);
+    through += __builtin_amdgcn_update_dpp(0, through, 0x118, 0xf, 0xf, true);
+    through += __builtin_amdgcn_update_dpp(0, through, 0x142, 0x2, 0xf, false);              // and the first 16 to the second
+    const int e = __popcll(__ballot(l < p.segments && through <= (int)row_tile));
+    if (e >= p.segments) return;
+    expert = e;
+    row_end = __builtin_amdgcn_readlane(end, e);
+    row0 = __builtin_amdgcn_readlane(begin, e) + (int64_t)((int)row_tile - __builtin_amdgcn_readlane(through - tiles, e)) * TM;
   } else {
     row0 = (int64_t)row_tile * TM;
     row_end = p.M;
@@ -210,7 +224,7 @@ int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name) {
   FArgs f = {};
   f.A = (const float*)g.A; f.B0 = (const float*)g.B0; f.B1 = (const float*)g.B1;
   f.a_rows = g.a_rows; f.C = (float*)g.C; f.row_scale = g.row_scale;
-  f.tile_expert = g.tile_expert; f.tile_row0 = g.tile_row0; f.seg_end = g.seg_end;
+  f.seg_end = g.seg_end; f.segments = g.segments;
   f.M = g.M; f.lda = g.lda; f.ldc = g.ldc; f.b_expert_stride = g.b_expert_stride;
   f.A_rest = (const float*)g.A_rest; f.C_rest = (float*)g.C_rest;
   f.a_expert_stride = g.a_expert_stride; f.c_expert_stride = g.c_expert_stride;
@@ -219,21 +233,24 @@ int launch_gemm_f32(const GemmArgs& g, hipStream_t s, const char* name) {
   if (((uintptr_t)g.A | (several ? (uintptr_t)g.A_rest : 0)) & 15) return fail(MOEP_EUNSUPPORTED, "%s: A must be 16-byte aligned", name);
   f.by_register = (((uintptr_t)g.B0 | (uintptr_t)g.B1) & 15) != 0;
   f.c_by_word = (((uintptr_t)g.C | (several ? (uintptr_t)g.C_rest : 0)) & 15) != 0;
-  if (g.experts < 1 || g.experts > 65535 || (g.tile_expert && g.experts != 1)) return fail(MOEP_EINVAL, "%s: bad batch count %d", name, g.experts);
-  auto m_tiles = [&](int tm) { return g.tile_expert ? g.max_m_tiles * (GEMM_BM / tm) : ceil_div(g.M, tm); };
+  if (g.experts < 1 || g.experts > 65535 || (g.segments && g.experts != 1)) return fail(MOEP_EINVAL, "%s: bad batch count %d", name, g.experts);
+  if (g.segments < 0 || g.segments > 32 || (g.segments && (!g.seg_end || g.M >= ((int64_t)1 << 31)))) return fail(MOEP_EINVAL, "%s: bad segments", name);
+  // row tiles: for the choice between the forms, of a routed launch those of a map of 256-row tiles; and how many there can be
+  auto m_tiles = [&](int tm) { return g.segments ? (ceil_div(g.M, GEMM_BM) + g.segments) * (GEMM_BM / tm) : ceil_div(g.M, tm); };
   auto n_tiles = [&](int tb) { return ceil_div(g.N, g.epilogue == EPI_SWIGLU ? tb / 2 : tb); };
   // 64 x 128 accumulators per tile, 32 x 128 where those are few, 32 x 64 where these are
   const int tm = m_tiles(64) * n_tiles(128) * g.experts < SMALL_TILES_BELOW ? 32 : 64;
   const int tb = tm == 32 && m_tiles(32) * n_tiles(128) * g.experts < NARROW_TILES_BELOW ? 64 : 128;
   // (weights that are not 16-byte aligned use two stages only: as many workgroups per compute unit as there can be; so it is with
-  // rows that a threshold leaves, whose number is known on the device only: 150 routed layers of 200 to 8000 tokens with one, against a
-  // slab in registers, geometric mean and worst: one ahead 0.75, 1.00, two 0.77, 1.13, by a share of rows guessed from it 0.75, 1.03)
-  const int64_t tiles = (g.tile_expert ? routed_row_tiles(g.M, g.busy_experts, tm) : ceil_div(g.M, tm)) * n_tiles(tb) * g.experts;
+  // rows that a threshold leaves, whose number is known on the device only: 70 routed layers of 200 to 8000 tokens with one, against
+  // row tiles from the map, geometric mean and worst: one ahead 0.80, 1.01, two 0.80, 1.01, by the rule for all rows 0.80, 1.06)
+  const int64_t tiles = (g.segments ? routed_row_tiles(g.M, g.busy_experts, tm) : ceil_div(g.M, tm)) * n_tiles(tb) * g.experts;
   const int ahead = (f.by_register && tiles > 512) || g.rows_unknown ? 1 : f32_slabs_ahead(tiles, 2, tm == 64 ? 3 : 4);
-  if (m_tiles(tm) > 2147483647LL || n_tiles(tb) > GRID_Y_MAX) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
-  dim3 grid((unsigned)m_tiles(tm), (unsigned)n_tiles(tb), (unsigned)g.experts);
-  f.columns_first = f32_columns_first(g.tile_expert != nullptr, m_tiles(tm));
-  if (f.columns_first) grid = dim3((unsigned)n_tiles(tb), (unsigned)m_tiles(tm), 1);
+  const int64_t row_tiles = ceil_div(g.M, tm) + g.segments;
+  if (row_tiles > 2147483647LL || n_tiles(tb) > GRID_Y_MAX) return fail(MOEP_EUNSUPPORTED, "%s: too many tiles", name);
+  dim3 grid((unsigned)row_tiles, (unsigned)n_tiles(tb), (unsigned)g.experts);
+  f.columns_first = f32_columns_first(g.segments > 0, row_tiles);
+  if (f.columns_first) grid = dim3((unsigned)n_tiles(tb), (unsigned)row_tiles, 1);
   Timed t(name, s);
 #define MOEP_F32_LAUNCH(EPI, TM, TB, AHEAD) hipLaunchKernelGGL((gemm_f32_kernel<EPI, TM, TB, AHEAD>), grid, dim3(THREADS), 0, s, f)
 #define MOEP_F32_CASE(EPI)                                                                              \

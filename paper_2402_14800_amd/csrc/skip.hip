@@ -6,7 +6,7 @@
 //            a0 = 1 / (1 + rho), a1 = rho / (1 + rho), rho = exp(delta); a0 = 1 when skipped.
 //            Also counts, per block of 256 tokens, the rows each expert receives.
 //   place    turns the counts into each (block, expert)'s first slot and each expert's segment end, and writes the map from
-//            M tiles (256 or 192 rows, or 64) to (expert, first row) that the grouped GEMMs walk (entry [max_tiles] of the
+//            M tiles (256 or 192 rows, or 64) to (expert, first row) that the grouped bf16 GEMMs walk (entry [max_tiles] of the
 //            expert list holds the number of tiles in use), for the 256-row GEMM the order in which they walk it, the slot -> token and
 //            slot -> weight lists and the token -> slot positions.  Within an expert's segment the rows are in ascending
 //            token order, so the result is reproducible.
@@ -104,7 +104,7 @@ __device__ __forceinline__ void lay_out_segments(int lane, int E, int count, con
   }
   if (lane == E) {
     if (publish) {
-      s.tile_expert[s.max_tiles] = tile_end;     // number of tiles in use, read by the packing of x and by the few-rows and fp32 GEMMs
+      s.tile_expert[s.max_tiles] = tile_end;     // number of tiles in use, read by the packing of x and by the few-rows GEMM
       s.seg_end[2 * E + 1] = tile_rows;
     }
     out.rows_of_tile = tile_rows;

@@ -58,18 +58,18 @@ constexpr bool short_tiles_pay(const Shorten& s, int64_t tall, int64_t shortened
 
 // Slabs of K that the fp32 expert GEMM fetches ahead.  Two keep `of_two` workgroups of its tile on a compute unit, one lets
 // `of_one` of them fit: one where that saves a round of `tiles` on 256 compute units.  us per call, two / one.  64 x 128 tiles (2, 3):
-// skipping forward, nothing skipped, E 16, H 1024, F 512, T = 2000 (560 in either launch) 251 / 211; E 4, H 512, F 512, T = 2700 (688)
-// 139 / 117, T = 3300 (840: two rounds both ways) 142 / 145, T = 4000 (1016) 144 / 155.  32 x 128 tiles (2, 4): the same, E 8, H 1024,
-// F 256, up, T = 2000 (516) 134 / 124, T = 2700 (688) 150 / 128.  The routed counts are expected ones: with a little more of them than
-// one round holds the choice is wrong (E 16, H 1024, F 512, T = 2700, 736 expected, 265 / 313).
+// skipping forward, nothing skipped, E 16, H 1024, F 512, T = 2000 (560 in either launch) 216 / 213, T = 2750 (752) 244 / 218; E 4, H 512,
+// F 512, T = 3000 (766) 140 / 119, T = 3300 (840: two rounds both ways) 145 / 147, T = 4000 (1016) 145 / 157.  32 x 128 tiles (2, 4): the
+// same, E 8, H 1024, F 256, up, T = 2000 (516) 107 / 105, T = 2700 (688) 139 / 129.  The routed counts are expected ones, and where either
+// takes several rounds the rule can be wrong by a few per cent (E 8, H 512, F 1024, T = 2400 187 / 196).
 constexpr int f32_slabs_ahead(int64_t tiles, int of_two, int of_one) {
   return (tiles + 256 * of_two - 1) / (256 * of_two) > (tiles + 256 * of_one - 1) / (256 * of_one) ? 1 : 2;
 }
-// Whether the column tiles of an fp32 launch are the fastest in the grid.  A routed launch has row tiles without rows (the map's bound,
-// each expert's last 256), and with the row tiles fastest its workgroups that have work are dealt to few compute units, several to one
-// while others stay idle.  us per launch, row / column tiles fastest, threshold 0.6: E 4, H 864, F 768, top-4, T = 653, up 121 / 97, down
-// 67 / 51; E 8, H 388, F 1792, top-6, T = 1657, down 124 / 73.  Dense launches have no such tiles: 91 passes of all experts by columns
-// took 1.00 of the time, the worst 1.08.
+// Whether the column tiles of an fp32 launch are the fastest in the grid.  A routed launch has row tiles without rows, the last ones,
+// and with the row tiles fastest they come once per column tile: the workgroups that have work are dealt to the compute units unevenly.
+// us per call, row / column tiles fastest, threshold 0.6: E 4, H 864, F 768, top-4, T = 653 135 / 82; E 8, H 388, F 1792, top-6, T = 1657
+// 248 / 190; nothing skipped: E 8, H 1024, F 256, T = 2000 126 / 105; E 4, H 180, F 324, T = 956 38 / 39.  Dense launches have no such
+// tiles: 91 passes of all experts by columns took 1.00 of the time, the worst 1.08.
 constexpr int64_t GRID_Y_MAX = 65535;
 constexpr bool f32_columns_first(bool routed, int64_t row_tiles) { return routed && row_tiles <= GRID_Y_MAX; }
 // Row tiles of a routed launch, expected: every expert's last one is half full.

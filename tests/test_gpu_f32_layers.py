@@ -113,3 +113,28 @@ def test_fp32_weights_of_any_alignment_give_the_same_bits(E, H, F, T):
     assert torch.equal(Y, Y_odd) and torch.equal(out, out_odd)
     _, ref = oracle.expert_outputs(*[wl.to_f64(layer[n]) for n in NAMES])
     assert np.abs(wl.to_f64(Y) - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("E,H,F,T,kept", [
+    (32, 64, 68, 300, 0x80000001),      # rows for the first and the last expert only
+    (32, 36, 132, 2600, 0xffffffff),    # 32-row tiles
+    (17, 64, 64, 9001, 0x1a005),        # 64-row tiles, experts without rows on both sides of the 16th
+    (16, 128, 192, 700, 0x8001),
+    (2, 64, 64, 65, 0x3),
+])
+def test_fp32_row_tiles_of_each_experts_segment(E, H, F, T, kept):
+    """Every routed row is multiplied with its own expert's weights, whichever experts have rows: the outputs are the Eq. 2 sums of
+    the dense pass (the same products; three fp32 roundings and expf besides, within the bound above)."""
+    _, layer = small_layer("f32", E, 2, H, F, T, index=40)
+    d = to_dev(layer)
+    ws = [d[n] for n in NAMES]
+    lg, Y = pkg.moe_expert_outputs(*ws)
+    out, skip, lg_f, top2 = pkg.moe_forward_pruned_skip(*ws, kept, 0.0)
+    torch.cuda.synchronize()
+    assert torch.equal(lg, lg_f) and not skip.any()
+    t = torch.arange(T, device=Y.device)
+    e0, e1 = top2[:, 0].long(), top2[:, 1].long()
+    assert set(top2.unique().tolist()) <= {e for e in range(E) if kept >> e & 1}
+    rho = (lg[t, e1].double() - lg[t, e0].double()).exp()[:, None]
+    ref = (Y[e0, t].double() + rho * Y[e1, t].double()) / (1 + rho)
+    assert (out.double() - ref).abs().max() <= 1e-5 * ref.abs().max()
