@@ -138,7 +138,8 @@ struct PackedGemmArgs {
   int N = 0, K = 0;
   int epilogue = EPI_STORE;
   const float* row_scale = nullptr;
-  // Grouped mode: the same tile map as GemmArgs; A (and a packed C) hold one 256-row block per TILE.
+  // Grouped mode: M tile t covers rows tile_row0[t] .. of expert tile_expert[t] (< 0: no work), up to its segment's end; A (and a
+  // packed C) hold one 256-row block per TILE.
   const int32_t* tile_expert = nullptr;
   const int32_t* tile_row0 = nullptr;
   const int32_t* seg_end = nullptr;
@@ -208,7 +209,7 @@ struct FewGemmArgs {
   int64_t max_rows = 0;          // dense: rows; grouped: most rows an expert can have
   int64_t busy_tiles = 1;        // tiles that are expected to hold rows (choose the load ring and the cache policy)
   int experts = 1;               // dense
-  // grouped: the tile map of GemmArgs with FEW_ROWS rows per tile
+  // grouped: the tile map of PackedGemmArgs with FEW_ROWS rows per tile
   const int32_t* tile_expert = nullptr;
   const int32_t* tile_row0 = nullptr;
   const int32_t* seg_end = nullptr;

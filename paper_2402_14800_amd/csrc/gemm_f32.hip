@@ -1,6 +1,6 @@
 // fp32 GEMM (storage type MOEP_F32): C = epilogue(A B^T) on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: fp32
-// operands, fp32 accumulate).  Serves layers kept in fp32; the layout of arguments, epilogues and the grouped tile map
-// (256-row M tiles) are those of the bf16 kernel.
+// operands, fp32 accumulate).  Serves layers kept in fp32; the layout of arguments and the epilogues are those of the
+// bf16 kernel.
 //
 // Bound by the fp32 matrix rate (157 TFLOP/s nominal; 109 reached at 6000 tokens) where there are tiles for the chip, by the
 // serial walk over K where there are not.  A workgroup of 256 threads owns 64 rows x 128 accumulator columns (gate/up: 64
